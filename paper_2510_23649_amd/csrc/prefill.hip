@@ -1,600 +1,981 @@
 // p1 -- prefill factorisation (Alg. 1; Sec. 4.1 "Prefill": the four update rules; App. A.1).
 //
-// Every update of Alg. 1 is made of two kinds of products with one long dimension (l):
-//   "reduce"  X^T Y and X^T X   (r x d and r x r, sums over the l rows)   X = A_Q or A_K
-//   "apply"   X = Y M           (l x r, row by row)                      Y = Q or K, M d x r
-// and r x r solves in between.  Per row of Y (256 bytes in bf16) the products cost
-// 2 r (2 d + r) flops: about 50 flop per byte at r = 32, above what the chip's fp32 rate can
-// do per byte of HBM traffic.  This is the one dense contraction of the method, and it runs
-// on the matrix cores in fp32 (v_mfma_f32_32x32x2_f32; App. B.1 keeps these updates in fp32).
+// With X = Y M (Y = Q or K of a head, M the d x r operand of an update), the sums that the next
+// update needs are  X^T Y = M^T (Y^T Y)  and  X^T X = M^T (Y^T Y) M:  once the d x d matrix
+// G = Y^T Y of a head is known, every round but for its last products is r x d algebra.  So Q
+// and K are read twice, whatever the number of rounds:
 //
-// prefill_pass_kernel<R, BF16, APPLY, REDUCE>: one workgroup (4 wavefronts) walks a chunk of
-// 2048 rows in tiles of 128.  The tile of Y is read with coalesced 16-byte loads (the next
-// tile's loads are issued before the current tile's MFMAs) and kept in LDS as it is (bf16 pairs
-// are widened when an operand is read) with an odd row stride in dwords, so that both operand
-// shapes the MFMAs need (a column pair of 32 rows, a row pair of 32 columns) are conflict-free
-// LDS reads; with bf16 inputs a workgroup needs 66 KB of LDS at r = 32 and two of them share
-// a CU, one running MFMAs while the other moves its tile.
-//   APPLY : wavefront w computes rows 32w..32w+31 of X = Y M (64 MFMAs per 32 x 32 block),
-//           writes them to HBM and into LDS;
-//   REDUCE: wavefront w accumulates the 32-column block w of X^T Y over the tile's 128 rows
-//           (64 MFMAs per block) and its quarter of the rows of X^T X; the accumulators stay
-//           in registers across the chunk and leave as one partial per chunk.
-// Fusing the two means Y is read once per update of A and X is never read back.
-// prefill_sum_kernel adds the chunk partials (fixed order); the three solve kernels do the
-// r x r work: a Cholesky factorisation inside one wavefront, then one thread per column of
-// the r x d right-hand side.
-#include "lrqk_device.h"
+//   1. prefill_reduce_kernel   G = Y^T Y,  S = A0^T Y,  H = A0^T A0  of every head (A0 = the
+//                              initial A_Q, A_K), one partial per chunk of rows
+//   2. prefill_sum_kernel      adds the chunk partials in order, in fp64
+//   3. n_iter times            B_K = H_K^-1 S_K, M_K, and S_K, H_K of A_K = K M_K
+//      (prefill_round_k)       and, in other workgroups, B_Q = H_Q^-1 S_Q;
+//      (prefill_round_q)       M_Q, and S_Q, H_Q of A_Q = Q M_Q unless it is the last round
+//   4. prefill_apply_kernel    A_K = K M_K, A_Q = Q M_Q
+//
+// (With a pass over Q and K in every update, X^T Y and X^T X from the fp32 matrix cores and the
+// solves in fp32, the whole took 2.35 ms at 32 + 8 heads, l = 131072, r = 32, bf16, two rounds;
+// now 0.91 ms.)
+//
+// Precision.  The long products run on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16) with
+// every fp32 operand split into three bf16 terms (x = x0 + x1 + x2 exactly: 3 x 8 bits of
+// significand) and the products x_i y_j with i + j <= 2, fp32 accumulation; what is left out is
+// below 2^-26 of a product.  bf16 rows are one term.  The r x d algebra is fp64.  Distance from the
+// factors computed in 64 bits, |.|_2, worst of the four: 9e-6 (with fp32 throughout 2.2e-4) at l = 131072,
+// r = 32; 1.9e-5 (1.8e-4) at l = 4096, r = 16; 9e-6 (1.6e-4) at l = 30011, r = 64.
+#include <type_traits>
+
 #include "lrqk_internal.h"
-#include "lrqk_linalg.h"
 
 namespace lrqk {
 namespace {
 
-using namespace linalg;
-
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-constexpr int kPfThreads = 256;
-constexpr int kPfTile = 128;          // rows per tile: 32 per wavefront
-constexpr int kPfTilesPerChunk = 16;  // 2048 rows per workgroup
-constexpr int kLDY = kD + 1;          // LDS row stride of the Y tile (odd: conflict-free)
-
-__device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) {
-  // D(32x32) = A(32x2) B(2x32) + C; lane = i + 32 k supplies A[i][k] and B[k][i];
-  // register v of lane l holds D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32]
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+// D(32x32) = A(32x16) B(16x32) + C; lane i + 32 h supplies A[i][8h .. 8h+7] and B[8h .. 8h+7][i];
+// register v of lane l holds D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32]
+__device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 __device__ __forceinline__ int mfma_row(int v, int lane) {
   return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
 }
+// D(16x16) = A(16x4) B(4x16) + C; lane i + 16 h supplies A[i][h] and B[h][i]; register v of
+// lane l holds D[4 v + l / 16][l % 16]
+__device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// x0, x1 as three bf16 pairs (packed in dwords) that add up to them exactly
+__device__ __forceinline__ void split3(float x0, float x1, uint32_t (&s)[3]) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const f32x2 x = {x0, x1};
+    s[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+    x0 -= __uint_as_float(s[i] << 16);
+    x1 -= __uint_as_float(s[i] & 0xffff0000u);
+  }
+}
+
+constexpr int kPfThreads = 256;
 
 template <int R>
 struct PfShape {
   static constexpr int RB = (R + 31) / 32;  // 32-wide blocks of the rank dimension
   static constexpr int RP = 32 * RB;        // rank padded to the MFMA block
-  static constexpr int LDX = RP + 1;
-  static constexpr int P = R * (kD + R);    // floats of one partial: X^T Y then X^T X
-  // dwords per LDS row of the Y tile: fp32 values, or bf16 pairs as they come from memory;
-  // odd in both cases, so that 32 consecutive rows fall on 32 different banks
-  static constexpr int ldy(bool bf16) { return bf16 ? kD / 2 + 1 : kD + 1; }
-  static constexpr size_t lds_floats(bool bf16, bool apply) {
-    return (size_t)kPfTile * ldy(bf16) + (size_t)kPfTile * LDX + (apply ? (size_t)kD * RP : 0);
-  }
+  // 32 x 32 blocks of a chunk's partial, each as 16 registers x 64 lanes: 10 of G (the upper
+  // ones), 4 RB of S, HB of H, 4 of the second-order diagonal terms of G (fp32 rows)
+  static constexpr int HB = RB == 1 ? 4 : 8;
+  static constexpr int SB0 = 10, HB0 = 10 + 4 * RB, GB0 = HB0 + HB, PB = GB0 + 4;
+  static constexpr size_t mpack_units = (size_t)3 * RB * 8 * 64;  // 16-byte units of M per head
 };
 
-template <int R, bool BF16, bool APPLY, bool REDUCE>
-__global__ __launch_bounds__(kPfThreads) void prefill_pass_kernel(
-    const void* __restrict__ Y,   // [heads][l][d]
-    float* X,                     // [heads][xrows][R]  read (!APPLY) or written (APPLY)
-    const float* __restrict__ M,  // [heads][d][RP]     (APPLY)
-    float* __restrict__ part,     // [heads][nchunk][P] (REDUCE)
-    int l, int xrows, int nchunk) {
+// ------------------------------------------------------------------------------------------
+// Reduce.  A workgroup (8 wavefronts) walks a chunk of rows in tiles.  A tile of Y is 256 bytes
+// a row and plane (bf16 rows: one plane, fp32 rows: the three terms) in LDS, a tile of A0 three
+// planes; the next tile's global loads are issued before the current tile's products.  The
+// products contract over the rows while the rows are what is contiguous in memory:
+// ds_read_b64_tr_b16 delivers four rows of a column to a lane, two of them make an operand.
+// A row is four units of 64 bytes (32 columns); unit u of row i is kept at u ^ (i % 4), so that
+// the four rows a transposing read takes together lie in different banks.
+// Wavefront c < 4 owns the blocks (c, c), (c, c + 1) of G (indices modulo 4); wavefront 4 + c
+// column block c of S and, c < 2, block (c, c + 2) of G.  With A0 = a0 + a1 + a2,
+// H = D + U + U^T, D = a0^T a0 + a1^T a1, U = a0^T a1 + a0^T a2: r <= 32: wavefront 6 does D, 7 U;
+// r = 64: wavefronts 4, 5 the diagonal blocks of U, 6, 7 those of D and block (0, 1) of H.
+// a1^T a1 has accumulators of its own: its diagonal is a sum of squares 2^-18 the size of the
+// main term's, and each addend would round away against that sum (H 2e-6 too small after 11000
+// rows).  The same for the diagonal blocks of G with fp32 rows.
+// Bound by HBM: 2.0 GB in 0.40 ms = 5.0 TB/s at 32 + 8 heads, l = 131072, r = 32 (a large copy:
+// 5.1 TB/s); a SIMD needs 7 MFMAs of 32 cycles per 16 rows.  256 registers a wavefront hold one
+// workgroup on a CU: the LDS takes two tiles.
+constexpr int kRedThreads = 512;
+constexpr int kFlushRows = 512;
+template <int R, int NS>
+struct PfReduce {
+  static constexpr int TR = NS > 1 ? 64 : R > 32 ? 96 : 128;  // rows per tile
+  static constexpr int kYPlane = TR * 256;                    // bytes
+  static constexpr int kAPlane = TR * 2 * PfShape<R>::RP;
+  static constexpr int kTile = NS * kYPlane + 3 * kAPlane;
+  static constexpr size_t lds_bytes = 2 * (size_t)kTile;      // two tiles in turn
+  static constexpr int kFlushTiles = kFlushRows / TR;
+};
+
+// Orders LDS traffic only: loads from memory stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+template <int R, int NS>
+__global__ __launch_bounds__(kRedThreads, 2) void prefill_reduce_kernel(
+    const void* __restrict__ Q, const void* __restrict__ K, const float* __restrict__ A_Q,
+    const float* __restrict__ A_K, float* __restrict__ part, int BHq, int l, int lk, int nchunk,
+    int tiles_per_chunk) {
   using S = PfShape<R>;
-  constexpr int RB = S::RB, RP = S::RP, LDX = S::LDX;
-  constexpr int ROW16 = kD * (BF16 ? 2 : 4) / 16;          // 16-byte pieces per row of Y
-  constexpr int NPRE = kPfTile * ROW16 / kPfThreads;       // pieces per thread and tile
-  extern __shared__ __align__(16) float pf_lds[];
-  constexpr int YW = S::ldy(BF16);
-  uint32_t* const Yw = reinterpret_cast<uint32_t*>(pf_lds);  // the Y tile, [kPfTile][YW] dwords
-  float* const Xs = pf_lds + kPfTile * YW;
-  float* const Ms = Xs + kPfTile * LDX;
-  static_assert(kPfTile * (YW + LDX) >= 4 * RP * RP, "room for the final sum of X^T X");
-  // element (row, col) of the Y tile as fp32
-  auto y_at = [&](int row, int col) -> float {
-    if (BF16) {
-      const uint32_t wd = Yw[row * YW + (col >> 1)];
-      return __uint_as_float((col & 1) ? (wd & 0xffff0000u) : (wd << 16));
-    }
-    return __uint_as_float(Yw[row * YW + col]);
-  };
+  using T = PfReduce<R, NS>;
+  constexpr int RB = S::RB, TR = T::TR;
+  constexpr int ROW16 = NS == 1 ? 16 : 32;      // 16-byte pieces per row of Y
+  constexpr int NY = TR * ROW16 / kRedThreads;  // ... per thread and tile
+  constexpr int NA4 = TR * R / 4;               // 16-byte pieces of a tile of A0
+  constexpr int NA = (NA4 + kRedThreads - 1) / kRedThreads;
+  extern __shared__ __align__(16) unsigned char pf_lds[];
+  unsigned char* Yl = pf_lds;  // this tile's
+  unsigned char* Al = pf_lds + NS * T::kYPlane;
 
-  const int head = blockIdx.y, chunk = blockIdx.x;
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int mi = lane & 31, mk = lane >> 5;
+  const int bh = blockIdx.x / nchunk, chunk = blockIdx.x - bh * nchunk;  // Q heads, then K heads
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int cb = w & 3;        // column block
+  const bool sums = w >= 4;    // S and what shares its wavefronts, or G
+  const bool isq = bh < BHq;
+  const size_t head = isq ? bh : bh - BHq;
   const uint4* __restrict__ Yh =
-      reinterpret_cast<const uint4*>(static_cast<const char*>(Y) +
-                                     (size_t)head * (size_t)l * (kD * (BF16 ? 2 : 4)));
-  float* Xh = X + (size_t)head * (size_t)xrows * R;
-  const int row_begin = chunk * kPfTile * kPfTilesPerChunk;
-  const int row_end = min(l, row_begin + kPfTile * kPfTilesPerChunk);
+      static_cast<const uint4*>(isq ? Q : K) + head * (size_t)l * ROW16;
+  const float* __restrict__ Ah = isq ? A_Q + head * (size_t)l * R : A_K + head * (size_t)lk * R;
+  const int row_begin = chunk * TR * tiles_per_chunk;
+  const int row_end = min(l, row_begin + TR * tiles_per_chunk);
 
-  // padding columns of X (rank up to the MFMA block) stay zero for the whole kernel
-  if (RP > R)
-    for (int i = t; i < kPfTile * (RP - R); i += kPfThreads)
-      Xs[(i / (RP - R)) * LDX + R + i % (RP - R)] = 0.0f;
-  if (APPLY) {
-    const float* Mh = M + (size_t)head * kD * RP;
-    for (int i = t; i < kD * RP; i += kPfThreads) Ms[i] = Mh[i];
+  if (S::RP > R) {  // padding columns of A0 stay zero
+    for (int i = t; i < 2 * T::kTile / 16; i += kRedThreads)
+      reinterpret_cast<uint4*>(pf_lds)[i] = make_uint4(0u, 0u, 0u, 0u);
+    lds_barrier();
   }
 
-  f32x16 accXY[RB], accXY1[RB], accXX[RB * RB];
-#pragma unroll
-  for (int i = 0; i < RB; ++i)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) accXY[i][v] = accXY1[i][v] = 0.0f;
-#pragma unroll
-  for (int i = 0; i < RB * RB; ++i)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) accXX[i][v] = 0.0f;
-
-  uint4 pre[NPRE];
+  // (addresses past the end are clamped and the values zeroed later: a load in a branch of its
+  // own would be waited for before the next is issued)
+  uint4 py[NY];
+  float4 pa[NA];
   auto prefetch = [&](int row0) {
 #pragma unroll
-    for (int j = 0; j < NPRE; ++j) {
-      const int q = t + kPfThreads * j;
-      const int row = row0 + q / ROW16;
-      pre[j] = row < row_end ? Yh[(size_t)row * ROW16 + q % ROW16] : make_uint4(0u, 0u, 0u, 0u);
+    for (int j = 0; j < NY; ++j) {
+      const int q = t + kRedThreads * j, row = min(row0 + q / ROW16, row_end - 1);
+      py[j] = Yh[(size_t)row * ROW16 + q % ROW16];
+    }
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+      const int q = t + kRedThreads * j, row = min(row0 + q / (R / 4), row_end - 1);
+      pa[j] = reinterpret_cast<const float4*>(Ah + (size_t)row * R)[q % (R / 4)];
     }
   };
   prefetch(row_begin);
 
-  for (int row0 = row_begin; row0 < row_end; row0 += kPfTile) {
-    __syncthreads();  // the previous tile's LDS reads are done
-#pragma unroll
-    for (int j = 0; j < NPRE; ++j) {
-      const int q = t + kPfThreads * j;
-      const int rr = q / ROW16, c = q % ROW16;
-      uint32_t* dst = Yw + rr * YW + 4 * c;  // bf16: 8 values in 4 dwords; fp32: 4 values
-      dst[0] = pre[j].x;
-      dst[1] = pre[j].y;
-      dst[2] = pre[j].z;
-      dst[3] = pre[j].w;
-    }
-    if (!APPLY) {
-      // X tile from HBM: 128 consecutive rows of R floats are one contiguous span
-      for (int i = t; i < kPfTile * R / 4; i += kPfThreads) {
-        const int rr = (4 * i) / R, cc = (4 * i) % R;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (row0 + rr < row_end)
-          v = reinterpret_cast<const float4*>(Xh + (size_t)row0 * R)[i];
-        Xs[rr * LDX + cc + 0] = v.x; Xs[rr * LDX + cc + 1] = v.y;
-        Xs[rr * LDX + cc + 2] = v.z; Xs[rr * LDX + cc + 3] = v.w;
-      }
-    }
-    if (row0 + kPfTile < row_end) prefetch(row0 + kPfTile);
-    __syncthreads();
+  // transposing reads: this lane's row within 4, its 8 bytes of a 64-byte unit, its row of 16
+  const int rl = (lane & 15) >> 2, off = 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+  const int row_l = 8 * (lane >> 5) + rl;
+  auto tr_pair = [&](const unsigned char* p, int step) {  // p: first four rows; step: four rows
+    union { s16x4 h[2]; bf16x8 v; } o;
+    o.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+    o.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + step));
+    return o.v;
+  };
+  auto y_op = [&](int plane, int ks, int c) {
+    return tr_pair(Yl + plane * T::kYPlane + (ks * 16 + row_l) * 256 + ((c ^ rl) << 6) + off,
+                   4 * 256);
+  };
+  auto a_op = [&](int plane, int ks, int rb) {
+    const int unit = RB == 1 ? 0 : (rb ^ (rl >> 1)) << 6;
+    return tr_pair(Al + plane * T::kAPlane + (ks * 16 + row_l) * (2 * S::RP) + unit + off,
+                   4 * 2 * S::RP);
+  };
 
-    if (APPLY) {
-      // rows 32w .. 32w+31 of X = Y M
+  // One barrier per tile: a wavefront that stores a tile while others still read the one before
+  // writes the other half of the LDS.  The whole walk is compiled once for each role of a
+  // wavefront (0: G; 1, 2, 3: S with what column blocks 0 and 1, 2, 3 add to it): with the roles
+  // as branches around the products the accumulators were copied at every step (0.76 ms instead
+  // of 0.40 ms at l = 131072, r = 32, 32 + 8 heads).  Every role passes the same barriers.
+  auto walk = [&](auto role) {
+    constexpr int ROLE = decltype(role)::value;
+    // G wavefronts: (cb, cb), (cb, cb + 1), second-order part of (cb, cb); the others: S, then
+    // (cb, cb + 2) of G or parts of H.  acc2: see flush
+    constexpr int NACC = RB + 1 + RB;
+    f32x16 acc[NACC], acc2[RB + 1];
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        // two accumulators, so that consecutive MFMAs do not wait for each other's result
-        f32x16 acc, acc1;
+    for (int v = 0; v < 16; ++v) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = acc1[v] = 0.0f;
-#pragma unroll 4
-        for (int kk = 0; kk < kD; kk += 4) {
-          acc = mfma32(y_at(32 * w + mi, kk + mk), Ms[(kk + mk) * RP + 32 * rb + mi], acc);
-          acc1 = mfma32(y_at(32 * w + mi, kk + 2 + mk), Ms[(kk + 2 + mk) * RP + 32 * rb + mi],
-                        acc1);
-        }
+      for (int i = 0; i < NACC; ++i) acc[i][v] = 0.0f;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] += acc1[v];
+      for (int i = 0; i <= RB; ++i) acc2[i][v] = 0.0f;
+    }
+    // What the accumulators hold goes to second ones every kFlushRows rows: rounding errors follow
+    // the size of the sum they are made in, and the second round's factors amplify those of S and G
+    // (without: A_Q twice as far off at l = 131072).
+    auto flush = [&]() {
+#pragma unroll
+      for (int i = 0; i <= RB; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const int i = 32 * w + mfma_row(v, lane), j = 32 * rb + mi;
-          if (j < R) {
-            Xs[i * LDX + j] = acc[v];
-            if (row0 + i < row_end) Xh[(size_t)(row0 + i) * R + j] = acc[v];
+          acc2[i][v] += acc[i][v];
+          acc[i][v] = 0.0f;
+        }
+    };
+
+    int tile = 0;
+    for (int row0 = row_begin; row0 < row_end; row0 += TR, ++tile) {
+      Yl = pf_lds + (tile & 1) * T::kTile;
+      Al = Yl + NS * T::kYPlane;
+#pragma unroll
+      for (int j = 0; j < NY; ++j) {
+        const int q = t + kRedThreads * j, row = q / ROW16, c = q % ROW16;
+        if (row0 + row >= row_end) py[j] = make_uint4(0u, 0u, 0u, 0u);
+        if (NS == 1) {
+          *reinterpret_cast<uint4*>(Yl + row * 256 + (((c >> 2) ^ (row & 3)) << 6) + 16 * (c & 3)) =
+              py[j];
+        } else {
+          uint32_t lo[3], hi[3];
+          split3(__uint_as_float(py[j].x), __uint_as_float(py[j].y), lo);
+          split3(__uint_as_float(py[j].z), __uint_as_float(py[j].w), hi);
+#pragma unroll
+          for (int p = 0; p < NS; ++p)
+            *reinterpret_cast<uint2*>(Yl + p * T::kYPlane + row * 256 +
+                                      (((c >> 3) ^ (row & 3)) << 6) + 8 * (c & 7)) =
+                make_uint2(lo[p], hi[p]);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < NA; ++j) {
+        const int q = t + kRedThreads * j, row = q / (R / 4), c = q % (R / 4);
+        if (NA4 % kRedThreads == 0 || q < NA4) {
+          if (row0 + row >= row_end) pa[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+          uint32_t lo[3], hi[3];
+          split3(pa[j].x, pa[j].y, lo);
+          split3(pa[j].z, pa[j].w, hi);
+          const int unit = RB == 1 ? 0 : ((c >> 3) ^ ((row >> 1) & 1)) << 6;
+#pragma unroll
+          for (int p = 0; p < 3; ++p)
+            *reinterpret_cast<uint2*>(Al + p * T::kAPlane + row * (2 * S::RP) + unit + 8 * (c & 7)) =
+                make_uint2(lo[p], hi[p]);
+        }
+      }
+      if (row0 + TR < row_end) prefetch(row0 + TR);
+      if (tile % T::kFlushTiles == 0) flush();
+      lds_barrier();
+
+#pragma unroll 2
+      for (int ks = 0; ks < TR / 16; ++ks) {
+        bf16x8 y0[NS];
+#pragma unroll
+        for (int p = 0; p < NS; ++p) y0[p] = y_op(p, ks, cb);
+        if constexpr (ROLE == 0) {
+          bf16x8 y1[NS];
+#pragma unroll
+          for (int p = 0; p < NS; ++p) y1[p] = y_op(p, ks, (cb + 1) & 3);
+#pragma unroll
+          for (int i = 0; i < NS; ++i)
+#pragma unroll
+            for (int j = 0; i + j < 3 && j < NS; ++j) {
+              if (i == 1 && j == 1)
+                acc[2] = mfma_bf16(y0[i], y0[j], acc[2]);
+              else
+                acc[0] = mfma_bf16(y0[i], y0[j], acc[0]);
+              acc[1] = mfma_bf16(y0[i], y1[j], acc[1]);
+            }
+        } else {
+          bf16x8 a[RB][3];
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) a[rb][p] = a_op(p, ks, rb);
+#pragma unroll
+          for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; i + j < 3 && j < NS; ++j)
+#pragma unroll
+              for (int rb = 0; rb < RB; ++rb) acc[rb] = mfma_bf16(a[rb][i], y0[j], acc[rb]);
+          f32x16& e0 = acc[RB];
+          f32x16& e1 = acc[RB + 1];
+          f32x16& e2 = acc[NACC - 1];
+          if constexpr (ROLE == 1) {
+            bf16x8 y2[NS];
+#pragma unroll
+            for (int p = 0; p < NS; ++p) y2[p] = y_op(p, ks, cb + 2);
+#pragma unroll
+            for (int i = 0; i < NS; ++i)
+#pragma unroll
+              for (int j = 0; i + j < 3 && j < NS; ++j) e0 = mfma_bf16(y0[i], y2[j], e0);
+            if constexpr (RB > 1) {  // U of diagonal block cb
+              const bf16x8 b0 = a_op(0, ks, cb);
+              e1 = mfma_bf16(b0, a_op(1, ks, cb), e1);
+              e1 = mfma_bf16(b0, a_op(2, ks, cb), e1);
+            }
+          } else if constexpr (ROLE == 2) {
+            e0 = mfma_bf16(a[0][0], a[0][0], e0);
+            e2 = mfma_bf16(a[0][1], a[0][1], e2);
+            if constexpr (RB > 1) e1 = mfma_bf16(a[0][0], a[RB - 1][0], e1);
+          } else if constexpr (RB == 1) {
+            e0 = mfma_bf16(a[0][0], a[0][1], e0);
+            e1 = mfma_bf16(a[0][0], a[0][2], e1);
+          } else {
+            constexpr int B1 = RB - 1;
+            e1 = mfma_bf16(a[0][0], a[B1][1], e1);
+            e0 = mfma_bf16(a[B1][0], a[B1][0], e0);
+            e1 = mfma_bf16(a[0][1], a[B1][0], e1);
+            e2 = mfma_bf16(a[B1][1], a[B1][1], e2);
+            e1 = mfma_bf16(a[0][0], a[B1][2], e1);
+            e1 = mfma_bf16(a[0][2], a[B1][0], e1);
+            e1 = mfma_bf16(a[0][1], a[B1][1], e1);
           }
         }
       }
-      if (REDUCE) __syncthreads();
     }
 
-    if (REDUCE) {
-      // block w of the d columns of X^T Y over all 128 rows of the tile (two accumulator sets,
-      // row pairs alternate between them), and this wavefront's quarter of the rows of X^T X,
-      // interleaved with it: consecutive MFMAs never wait for each other's result
-      auto xy_step = [&](int kk) {
-        const float b0 = y_at(kk + mk, 32 * w + mi), b1 = y_at(kk + 2 + mk, 32 * w + mi);
+    flush();
+    float* out = part + (size_t)blockIdx.x * (S::PB * 1024) + lane;
+    auto put = [&](int block, const f32x16& x) {
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          accXY[rb] = mfma32(Xs[(kk + mk) * LDX + 32 * rb + mi], b0, accXY[rb]);
-          accXY1[rb] = mfma32(Xs[(kk + 2 + mk) * LDX + 32 * rb + mi], b1, accXY1[rb]);
-        }
-      };
-#pragma unroll 2
-      for (int kk = 0; kk < 32; kk += 4) {
-        xy_step(kk);
+      for (int v = 0; v < 16; ++v) out[block * 1024 + v * 64] = x[v];
+    };
+    if constexpr (ROLE == 0) {
+      put(cb, acc2[0]);
+      put(4 + cb, acc2[1]);
+      if constexpr (NS > 1) put(S::GB0 + cb, RB == 1 ? acc[NACC - 1] : acc2[RB]);
+    } else {
 #pragma unroll
-        for (int h = 0; h < 4; h += 2) {
-          float a[RB];
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb)
-            a[rb] = Xs[(32 * w + kk + h + mk) * LDX + 32 * rb + mi];
-#pragma unroll
-          for (int r1 = 0; r1 < RB; ++r1)
-#pragma unroll
-            for (int r2 = 0; r2 < RB; ++r2)
-              accXX[r1 * RB + r2] = mfma32(a[r1], a[r2], accXX[r1 * RB + r2]);
-        }
-      }
-#pragma unroll 4
-      for (int kk = 32; kk < kPfTile; kk += 4) xy_step(kk);
+      for (int rb = 0; rb < RB; ++rb) put(S::SB0 + 4 * rb + cb, acc2[rb]);
+      put(cb < 2 ? 8 + cb : S::HB0 + cb - 2, acc2[RB]);
+      if constexpr (RB > 1) put(S::HB0 + 2 + cb, acc[RB + 1]);
+      if (cb >= 2) put(S::GB0 - 4 + cb, acc[NACC - 1]);
     }
-  }
-
-  if (REDUCE) {
-    float* out = part + ((size_t)head * nchunk + chunk) * S::P;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int i = 32 * rb + mfma_row(v, lane);
-        if (i < R) out[(size_t)i * kD + 32 * w + mi] = accXY[rb][v] + accXY1[rb][v];
-      }
-    // X^T X: add the four wavefronts' parts through LDS (the Y tile's space)
-    __syncthreads();
-    float* red = pf_lds;  // [4][RP * RP], over the tiles' space
-#pragma unroll
-    for (int r1 = 0; r1 < RB; ++r1)
-#pragma unroll
-      for (int r2 = 0; r2 < RB; ++r2)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          red[w * RP * RP + (32 * r1 + mfma_row(v, lane)) * RP + 32 * r2 + mi] =
-              accXX[r1 * RB + r2][v];
-    __syncthreads();
-    for (int e = t; e < R * R; e += kPfThreads) {
-      const int i = e / R, c = e % R;
-      out[(size_t)R * kD + e] = (red[0 * RP * RP + i * RP + c] + red[1 * RP * RP + i * RP + c]) +
-                                (red[2 * RP * RP + i * RP + c] + red[3 * RP * RP + i * RP + c]);
-    }
-  }
+  };
+  if (!sums)
+    walk(std::integral_constant<int, 0>{});
+  else if (cb < 2)
+    walk(std::integral_constant<int, 1>{});
+  else if (cb == 2)
+    walk(std::integral_constant<int, 2>{});
+  else
+    walk(std::integral_constant<int, 3>{});
 }
 
-// sum[head][e] = sum over chunks of part[head][chunk][e], chunks in order
+// Place of element (i, j) of a 32 x 32 block among its 16 x 64 accumulator values.
+__device__ __forceinline__ int acc_index(int i, int j) {
+  return (4 * (i >> 3) + (i & 3)) * 64 + 32 * ((i >> 2) & 1) + j;
+}
+
+// The chunk partials of a head added in chunk order, in fp64: G [d][d], S [r][d], H [r][r].
+template <int R, int NS>
 __global__ __launch_bounds__(256) void prefill_sum_kernel(const float* __restrict__ part,
-                                                          float* __restrict__ sum, int nchunk,
-                                                          int P) {
-  const int head = blockIdx.y;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= P) return;
-  const float* p = part + (size_t)head * nchunk * P + e;
-  float acc = 0.0f;
-  int c = 0;
-  for (; c + 8 <= nchunk; c += 8) {
-    float v[8];
+                                                          double* __restrict__ G,
+                                                          double* __restrict__ Sm,
+                                                          double* __restrict__ H, int nchunk) {
+  using S = PfShape<R>;
+  constexpr int kBlocks = (S::HB0 * 1024 + R * R + 255) / 256;  // workgroups per head
+  const size_t head = blockIdx.x / kBlocks;
+  const int e = blockIdx.x % kBlocks * 256 + threadIdx.x;
+  const float* __restrict__ p = part + head * nchunk * (size_t)(S::PB * 1024);
+  auto total = [&](int at) {
+    double acc = 0.0;
+    const float* q = p + at;
+    int c = 0;
+    for (; c + 8 <= nchunk; c += 8) {
+      float v[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = p[(size_t)(c + j) * P];
+      for (int j = 0; j < 8; ++j) v[j] = q[(size_t)(c + j) * (S::PB * 1024)];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc += v[j];
+      for (int j = 0; j < 8; ++j) acc += (double)v[j];
+    }
+    for (; c < nchunk; ++c) acc += (double)q[(size_t)c * (S::PB * 1024)];
+    return acc;
+  };
+  if (e < S::HB0 * 1024) {
+    const int block = e >> 10, v = (e >> 6) & 15, lane = e & 63;
+    const int row = mfma_row(v, lane), col = lane & 31;
+    if (block < S::SB0) {
+      const int bi = block & 3, bj = (bi + (block >> 2)) & 3;
+      double x = total(e);
+      if (NS > 1 && block < 4) x += total(e + S::GB0 * 1024);
+      double* Gh = G + head * kD * kD;
+      Gh[(32 * bi + row) * kD + 32 * bj + col] = x;
+      if (bi != bj) Gh[(32 * bj + col) * kD + 32 * bi + row] = x;
+    } else {
+      const int i = 32 * ((block - S::SB0) >> 2) + row, j = 32 * ((block - S::SB0) & 3) + col;
+      if (i < R) Sm[(head * R + i) * kD + j] = total(e);
+    }
+    return;
   }
-  for (; c < nchunk; ++c) acc += p[(size_t)c * P];
-  sum[(size_t)head * P + e] = acc;
+  const int h = e - S::HB0 * 1024;
+  if (h >= R * R) return;
+  int i = h / R, j = h % R;
+  double x = 0.0;
+  auto add = [&](int block, int i, int j) { x += total((S::HB0 + block) * 1024 + acc_index(i, j)); };
+  if (S::RB == 1) {
+    add(0, i, j);  // D, U, second-order parts of D and U
+    add(2, i, j);
+    for (int block = 1; block < 4; block += 2) {
+      add(block, i, j);
+      add(block, j, i);
+    }
+  } else if (i / 32 == j / 32) {
+    const int d = i / 32;  // D, U, second-order part of D
+    i &= 31;
+    j &= 31;
+    add(d, i, j);
+    add(6 + d, i, j);
+    add(2 + d, i, j);
+    add(2 + d, j, i);
+  } else {
+    const int lo = i < j ? i : j, hi = i < j ? j : i;
+    add(4, lo, hi - 32);
+    add(5, lo, hi - 32);
+  }
+  H[head * R * R + h] = x;
 }
 
 // ------------------------------------------------------------------------------------------
-// LDS row stride of an r x r system: four consecutive elements of a row are one 16-byte read.
-template <int R>
-constexpr int kLDS = R + 4;
+// The r x d algebra of one head in fp64, by a workgroup of 8 wavefronts.
+constexpr int kAlgThreads = 512;
+constexpr int kLdx = kD + 2;  // LDS row stride: 16 rows x 2 columns fall on 32 different bank pairs
 
-// Solves S Xs = Ys in place for a symmetric positive definite S (r x r, LDS, row stride
-// kLDS<R> = R + 4 floats so that four consecutive elements of a row are one 16-byte read;
-// destroyed) and an r x d right-hand side (LDS, row stride kLDY).  The first wavefront
-// factorises S (lane = row) and leaves L and 1 / diag(L) in LDS; then thread j < d owns
-// column j and runs the two triangular solves in 4 x 4 blocks: the block of the factor is
-// read as broadcasts (four 16-byte reads), four elements of the column come from LDS, sixteen
-// multiply-adds follow.  Called by all threads of a 256-thread workgroup.
 template <int R>
-__device__ void spd_solve_columns(float* Ssh, float* dinv_sh, float* Ysh) {
-  constexpr int LDS_ = kLDS<R>;
-  static_assert(R % 4 == 0, "4 x 4 blocks");
-  const int t = threadIdx.x;
-  __syncthreads();
-  if (t < 64) {
-    float m[R];
-    const int li = t < R ? t : 0;
-#pragma unroll
-    for (int c = 0; c < R; ++c) m[c] = Ssh[li * LDS_ + c];
-    const float dinv = chol_factor<R>(m, t);
-    if (t < R) {
-#pragma unroll
-      for (int c = 0; c < R; ++c) Ssh[t * LDS_ + c] = m[c];  // L[t][c] for c <= t
-      dinv_sh[t] = dinv;
-    }
-  }
-  __syncthreads();
-  if (t < kD) {
-    float* const y = Ysh + t;  // this thread's column, element i at y[i * kLDY]
-    auto lrow = [&](int row, int col) {
-      return *reinterpret_cast<const float4*>(&Ssh[row * LDS_ + col]);
-    };
-    // L z = y
+struct PfAlg {
+  static constexpr int RT = (R + 15) / 16;  // 16 x 16 tiles: RT x RT of the system,
+  static constexpr int NT = RT + kD / 16;   // RT x 8 of the right-hand sides
+  static constexpr int WPR = 8 / RT;        // wavefronts per tile row
+  static constexpr int TPW = (NT + WPR - 1) / WPR;  // tiles of a wavefront: columns c, c + WPR, ...
+  static constexpr int kX = 16 * RT * kLdx;         // doubles of an r x d matrix in LDS
+  static constexpr int kP = NT * 64, kC = 16 * RT * 4;  // pivot rows, pivot columns
+  static constexpr size_t lds_bytes = ((size_t)2 * kX + 2 * (kP + kC)) * sizeof(double);
+};
+
+// [A | Y] -> [I | A^-1 Y] by Gauss-Jordan elimination with 4 x 4 pivot blocks, A symmetric
+// positive definite (no pivoting needed).  A step takes the pivot block D, its rows P and columns
+// C through LDS (two copies in turn: one barrier a step) and adds N P to every tile, N = -C D^-1
+// and D^-1 - I for the pivot rows themselves: a rank-4 update, one MFMA per tile, whose operand
+// P is the register that the pivot rows' owners hold.
+template <int R>
+__device__ __forceinline__ void solve_tiles(f64x4 (&d)[PfAlg<R>::TPW], double* Pl, double* Cl,
+                                            int w, int lane) {
+  using Z = PfAlg<R>;
+  const int tr = w / Z::WPR, tc0 = w % Z::WPR;
+  const int i = 16 * tr + (lane & 15), k = lane >> 4;
 #pragma unroll 1
-    for (int I = 0; I < R; I += 4) {
-      float a0 = y[(I + 0) * kLDY], a1 = y[(I + 1) * kLDY], a2 = y[(I + 2) * kLDY],
-            a3 = y[(I + 3) * kLDY];
-#pragma unroll 2
-      for (int C = 0; C < I; C += 4) {
-        const float z0 = y[(C + 0) * kLDY], z1 = y[(C + 1) * kLDY], z2 = y[(C + 2) * kLDY],
-                    z3 = y[(C + 3) * kLDY];
-        const float4 l0 = lrow(I + 0, C), l1 = lrow(I + 1, C), l2 = lrow(I + 2, C),
-                     l3 = lrow(I + 3, C);
-        a0 = __builtin_fmaf(-l0.w, z3, __builtin_fmaf(-l0.z, z2, __builtin_fmaf(-l0.y, z1, __builtin_fmaf(-l0.x, z0, a0))));
-        a1 = __builtin_fmaf(-l1.w, z3, __builtin_fmaf(-l1.z, z2, __builtin_fmaf(-l1.y, z1, __builtin_fmaf(-l1.x, z0, a1))));
-        a2 = __builtin_fmaf(-l2.w, z3, __builtin_fmaf(-l2.z, z2, __builtin_fmaf(-l2.y, z1, __builtin_fmaf(-l2.x, z0, a2))));
-        a3 = __builtin_fmaf(-l3.w, z3, __builtin_fmaf(-l3.z, z2, __builtin_fmaf(-l3.y, z1, __builtin_fmaf(-l3.x, z0, a3))));
+  for (int pt = 0; pt < (R + 15) / 16; ++pt) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int p0 = 16 * pt + 4 * q;  // first pivot
+      if (p0 >= R) break;
+      double* const P = Pl + (q & 1) * Z::kP;
+      double* const C = Cl + (q & 1) * Z::kC;
+#pragma unroll
+      for (int u = 0; u < Z::TPW; ++u) {
+        const int tc = tc0 + Z::WPR * u;
+        if (tr == pt && tc < Z::NT) P[tc * 64 + lane] = d[u][q];
+        if (tc == pt && ((lane & 15) >> 2) == q) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) C[(16 * tr + 4 * v + k) * 4 + (lane & 3)] = d[u][v];
+        }
       }
-      const float4 l1 = lrow(I + 1, I), l2 = lrow(I + 2, I), l3 = lrow(I + 3, I);
-      a0 *= dinv_sh[I];
-      a1 = __builtin_fmaf(-l1.x, a0, a1) * dinv_sh[I + 1];
-      a2 = __builtin_fmaf(-l2.y, a1, __builtin_fmaf(-l2.x, a0, a2)) * dinv_sh[I + 2];
-      a3 = __builtin_fmaf(-l3.z, a2, __builtin_fmaf(-l3.y, a1, __builtin_fmaf(-l3.x, a0, a3))) *
-           dinv_sh[I + 3];
-      y[(I + 0) * kLDY] = a0; y[(I + 1) * kLDY] = a1;
-      y[(I + 2) * kLDY] = a2; y[(I + 3) * kLDY] = a3;
-    }
-    // L^T x = z: the block of L^T for rows I.. and columns C.. is rows C.. of L at columns I..
-#pragma unroll 1
-    for (int I = R - 4; I >= 0; I -= 4) {
-      float a0 = y[(I + 0) * kLDY], a1 = y[(I + 1) * kLDY], a2 = y[(I + 2) * kLDY],
-            a3 = y[(I + 3) * kLDY];
-#pragma unroll 2
-      for (int C = I + 4; C < R; C += 4) {
-        const float x0 = y[(C + 0) * kLDY], x1 = y[(C + 1) * kLDY], x2 = y[(C + 2) * kLDY],
-                    x3 = y[(C + 3) * kLDY];
-        const float4 l0 = lrow(C + 0, I), l1 = lrow(C + 1, I), l2 = lrow(C + 2, I),
-                     l3 = lrow(C + 3, I);
-        a0 = __builtin_fmaf(-l3.x, x3, __builtin_fmaf(-l2.x, x2, __builtin_fmaf(-l1.x, x1, __builtin_fmaf(-l0.x, x0, a0))));
-        a1 = __builtin_fmaf(-l3.y, x3, __builtin_fmaf(-l2.y, x2, __builtin_fmaf(-l1.y, x1, __builtin_fmaf(-l0.y, x0, a1))));
-        a2 = __builtin_fmaf(-l3.z, x3, __builtin_fmaf(-l2.z, x2, __builtin_fmaf(-l1.z, x1, __builtin_fmaf(-l0.z, x0, a2))));
-        a3 = __builtin_fmaf(-l3.w, x3, __builtin_fmaf(-l2.w, x2, __builtin_fmaf(-l1.w, x1, __builtin_fmaf(-l0.w, x0, a3))));
+      __syncthreads();
+      const double* D = C + p0 * 4;
+      const double d00 = D[0], d01 = D[1], d02 = D[2], d03 = D[3], d11 = D[5], d12 = D[6],
+                   d13 = D[7], d22 = D[10], d23 = D[11], d33 = D[15];
+      // D = [E F; F^T L] in 2 x 2 blocks, W = E^-1 F, T = (L - F^T W)^-1
+      const double ie = 1.0 / (d00 * d11 - d01 * d01);
+      const double e00 = d11 * ie, e01 = -d01 * ie, e11 = d00 * ie;
+      const double w00 = e00 * d02 + e01 * d12, w01 = e00 * d03 + e01 * d13;
+      const double w10 = e01 * d02 + e11 * d12, w11 = e01 * d03 + e11 * d13;
+      const double l00 = d22 - (d02 * w00 + d12 * w10), l01 = d23 - (d02 * w01 + d12 * w11);
+      const double l11 = d33 - (d03 * w01 + d13 * w11);
+      const double il = 1.0 / (l00 * l11 - l01 * l01);
+      const double t00 = l11 * il, t01 = -l01 * il, t11 = l00 * il;
+      const double u00 = w00 * t00 + w01 * t01, u01 = w00 * t01 + w01 * t11;  // W T
+      const double u10 = w10 * t00 + w11 * t01, u11 = w10 * t01 + w11 * t11;
+      // column k of D^-1 = [E^-1 + W T W^T, -W T; -T W^T, T].  (Every entry is computed before the
+      // selection: with the arithmetic inside the branches of a chain of ifs on k, this compiler
+      // gave the lanes of the last branch an unset register.)
+      const double f00 = e00 + (u00 * w00 + u01 * w01), f01 = e01 + (u00 * w10 + u01 * w11);
+      const double f11 = e11 + (u10 * w10 + u11 * w11);
+      const bool odd = k & 1, low = k < 2;
+      const double x0 = low ? (odd ? f01 : f00) : -(odd ? u01 : u00);
+      const double x1 = low ? (odd ? f11 : f01) : -(odd ? u11 : u10);
+      const double x2 = low ? -(odd ? u10 : u00) : (odd ? t01 : t00);
+      const double x3 = low ? -(odd ? u11 : u01) : (odd ? t11 : t01);
+      const double* c = C + i * 4;
+      double n = -(c[0] * x0 + c[1] * x1 + (c[2] * x2 + c[3] * x3));
+      const int m = i - p0;
+      if (m >= 0 && m < 4) n = (m == 0 ? x0 : m == 1 ? x1 : m == 2 ? x2 : x3) - (m == k ? 1.0 : 0.0);
+#pragma unroll
+      for (int u = 0; u < Z::TPW; ++u) {
+        const int tc = tc0 + Z::WPR * u;
+        if (tc >= pt && tc < Z::NT) d[u] = mfma_f64(n, P[tc * 64 + lane], d[u]);
       }
-      const float4 l1 = lrow(I + 1, I), l2 = lrow(I + 2, I), l3 = lrow(I + 3, I);
-      a3 *= dinv_sh[I + 3];
-      a2 = __builtin_fmaf(-l3.z, a3, a2) * dinv_sh[I + 2];
-      a1 = __builtin_fmaf(-l3.y, a3, __builtin_fmaf(-l2.y, a2, a1)) * dinv_sh[I + 1];
-      a0 = __builtin_fmaf(-l3.x, a3, __builtin_fmaf(-l2.x, a2, __builtin_fmaf(-l1.x, a1, a0))) *
-           dinv_sh[I];
-      y[(I + 0) * kLDY] = a0; y[(I + 1) * kLDY] = a1;
-      y[(I + 2) * kLDY] = a2; y[(I + 3) * kLDY] = a3;
     }
   }
   __syncthreads();
 }
 
-// S1a, one workgroup per head (the B*Hq query heads, then the B*Hkv KV heads): from the sums
-// (A^T Y | A^T A) of the head,  B = (A^T A)^-1 A^T Y.
+// The tiles of [A | Y] of this wavefront: a(i, j) and y(i, j) give the elements (i < r).
+template <int R, typename FA, typename FY>
+__device__ __forceinline__ void load_tiles(f64x4 (&d)[PfAlg<R>::TPW], int w, int lane, FA a, FY y) {
+  using Z = PfAlg<R>;
+  const int tr = w / Z::WPR, tc0 = w % Z::WPR;
+#pragma unroll
+  for (int u = 0; u < Z::TPW; ++u) {
+    const int tc = tc0 + Z::WPR * u;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 16 * tr + 4 * v + (lane >> 4), j = 16 * tc + (lane & 15);
+      double x = 0.0;
+      if (tc < Z::RT)
+        x = (i < R && j < R) ? a(i, j) : (i == j ? 1.0 : 0.0);
+      else if (tc < Z::NT)
+        x = i < R ? y(i, j - 16 * Z::RT) : 0.0;
+      d[u][v] = x;
+    }
+  }
+}
+
+// The solution part of the tiles: put(i, j, value) for i < r, j < d.
+template <int R, typename F>
+__device__ __forceinline__ void store_solution(const f64x4 (&d)[PfAlg<R>::TPW], int w, int lane,
+                                               F put) {
+  using Z = PfAlg<R>;
+  const int tr = w / Z::WPR, tc0 = w % Z::WPR;
+#pragma unroll
+  for (int u = 0; u < Z::TPW; ++u) {
+    const int tc = tc0 + Z::WPR * u;
+    if (tc < Z::RT || tc >= Z::NT) continue;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 16 * tr + 4 * v + (lane >> 4);
+      if (i < R) put(i, 16 * (tc - Z::RT) + (lane & 15), d[u][v]);
+    }
+  }
+}
+
+// System tiles += lam X X^T, X [r][d] in LDS (rows up to the tile size are zero).
 template <int R>
-__global__ __launch_bounds__(256) void prefill_solve_b_kernel(const float* __restrict__ sum_q,
-                                                              const float* __restrict__ sum_k,
-                                                              float* __restrict__ B_Q,
-                                                              float* __restrict__ B_K, int BHq) {
-  using S = PfShape<R>;
-  constexpr int LDS_ = kLDS<R>;
-  extern __shared__ __align__(16) float pf_lds[];
-  float* const Ysh = pf_lds;              // [R][kLDY]
-  float* const Ssh = Ysh + R * kLDY;      // [R][R + 4]
-  float* const dinv_sh = Ssh + R * LDS_;  // [R]
-  const int t = threadIdx.x;
-  const bool iskv = (int)blockIdx.x >= BHq;
-  const size_t head = iskv ? blockIdx.x - BHq : blockIdx.x;
-  const float* sm = (iskv ? sum_k : sum_q) + head * S::P;
-  // (unrolled: the loads of several trips are in flight together)
+__device__ __forceinline__ void add_gram(f64x4 (&d)[PfAlg<R>::TPW], const double* X, double lam,
+                                         int w, int lane) {
+  using Z = PfAlg<R>;
+  const int tr = w / Z::WPR, tc0 = w % Z::WPR;
+#pragma unroll
+  for (int u = 0; u < Z::TPW; ++u) {
+    const int tc = tc0 + Z::WPR * u;
+    if (tc >= Z::RT) continue;
+    const double* xa = X + (16 * tr + (lane & 15)) * kLdx + (lane >> 4);
+    const double* xb = X + (16 * tc + (lane & 15)) * kLdx + (lane >> 4);
 #pragma unroll 8
-  for (int e = t; e < R * kD; e += 256) Ysh[(e / kD) * kLDY + e % kD] = sm[e];
+    for (int s = 0; s < kD; s += 4) d[u] = mfma_f64(lam * xa[s], xb[s], d[u]);
+  }
+}
+
+// S = X G and H = S X^T for X [r][d] in LDS and G [d][d] in memory; Ys [r][d]: LDS scratch.
+template <int R>
+__device__ __forceinline__ void sums_of(const double* X, double* Ys, const double* __restrict__ G,
+                                        double* __restrict__ Sm, double* __restrict__ H, int w,
+                                        int lane) {
+  using Z = PfAlg<R>;
+  const int c16 = lane & 15, k = lane >> 4;
+  f64x4 acc[Z::RT];
+#pragma unroll
+  for (int tr = 0; tr < Z::RT; ++tr) acc[tr] = f64x4{0.0, 0.0, 0.0, 0.0};
+  const double* g = G + k * kD + 16 * w + c16;  // wavefront w: columns 16 w .. 16 w + 15
+#pragma unroll 1
+  for (int s0 = 0; s0 < kD; s0 += 64) {
+    double b[16];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) b[s] = g[(s0 + 4 * s) * kD];
+#pragma unroll
+    for (int s = 0; s < 16; ++s)
+#pragma unroll
+      for (int tr = 0; tr < Z::RT; ++tr)
+        acc[tr] = mfma_f64(X[(16 * tr + c16) * kLdx + s0 + 4 * s + k], b[s], acc[tr]);
+  }
+#pragma unroll
+  for (int tr = 0; tr < Z::RT; ++tr)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 16 * tr + 4 * v + k, j = 16 * w + c16;
+      Ys[i * kLdx + j] = acc[tr][v];
+      if (i < R) Sm[i * kD + j] = acc[tr][v];
+    }
+  __syncthreads();
+  for (int tile = w; tile < Z::RT * Z::RT; tile += 8) {
+    const int tr = tile / Z::RT, tc = tile % Z::RT;
+    const double* ya = Ys + (16 * tr + c16) * kLdx + k;
+    const double* xb = X + (16 * tc + c16) * kLdx + k;
+    f64x4 h = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+    for (int s = 0; s < kD; s += 4) h = mfma_f64(ya[s], xb[s], h);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 16 * tr + 4 * v + k, j = 16 * tc + c16;
+      if (i < R && j < R) H[i * R + j] = h[v];
+    }
+  }
+}
+
+// M (its transpose [r][d] in LDS) as the apply kernel's operands: unit (term, rank block, k step,
+// lane) holds M[16 step + 8 (lane / 32) ..][32 block + lane % 32], one of three bf16 terms.
+template <int R>
+__device__ __forceinline__ void pack_operand(const double* Xt, uint4* __restrict__ pack, int t) {
+  constexpr int RB = PfShape<R>::RB;
+  for (int e = t; e < RB * 8 * 64; e += kAlgThreads) {
+    const int rank = 32 * (e >> 9) + (e & 31), k0 = 16 * ((e >> 6) & 7) + 8 * ((e >> 5) & 1);
+    uint32_t s[4][3];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      split3(rank < R ? (float)Xt[rank * kLdx + k0 + 2 * j] : 0.0f,
+             rank < R ? (float)Xt[rank * kLdx + k0 + 2 * j + 1] : 0.0f, s[j]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      pack[p * (RB * 512) + e] = make_uint4(s[0][p], s[1][p], s[2][p], s[3][p]);
+  }
+}
+
+struct PfState {
+  const double* G;  // [BHq + BHkv][d][d]
+  double* S;        // [BHq + BHkv][r][d]
+  double* H;        // [BHq + BHkv][r][r]
+  double* BQ;       // [BHq][r][d]
+  uint4* M;         // [BHq + BHkv] packed operands
+  float* B_Q;       // results
+  float* B_K;
+  int Hq, Hkv, BHq, BHkv;
+  double lam_pQ, lam_pK;
+  bool last;  // last round: M is needed, the sums of the new A_Q are not
+};
+
+// First half of a round.  Workgroups [0, B Hkv), a KV head each:
+//   B_K = H_K^-1 S_K,
+//   M_K = (sum_g S_Q,g^T + lambda_pK B_K^T)(sum_g H_Q,g + lambda_pK B_K B_K^T)^-1,
+//   S_K, H_K of A_K = K M_K.
+// The others, a query head each: B_Q = H_Q^-1 S_Q (the next launch reads it).
+template <int R>
+__global__ __launch_bounds__(kAlgThreads) void prefill_round_k_kernel(const PfState a) {
+  using Z = PfAlg<R>;
+  extern __shared__ __align__(16) double pf_alg[];
+  double* const X = pf_alg;
+  double* const Ys = X + Z::kX;
+  double* const Pl = Ys + Z::kX;
+  double* const Cl = Pl + 2 * Z::kP;
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const bool iskv = (int)blockIdx.x < a.BHkv;
+  const size_t own = iskv ? a.BHq + blockIdx.x : blockIdx.x - a.BHkv;  // row of S, H, G
+  f64x4 d[Z::TPW];
+  {
+    const double* H = a.H + own * R * R;
+    const double* S = a.S + own * R * kD;
+    load_tiles<R>(d, w, lane, [&](int i, int j) { return H[i * R + j]; },
+                  [&](int i, int j) { return S[i * kD + j]; });
+  }
+  solve_tiles<R>(d, Pl, Cl, w, lane);
+  if (!iskv) {
+    double* BQ = a.BQ + own * R * kD;
+    float* B_Q = a.B_Q + own * R * kD;
+    store_solution<R>(d, w, lane, [&](int i, int j, double x) {
+      BQ[i * kD + j] = x;
+      if (a.last) B_Q[i * kD + j] = (float)x;
+    });
+    return;
+  }
+  const int bkv = blockIdx.x, b = bkv / a.Hkv, kvh = bkv - b * a.Hkv, G = a.Hq / a.Hkv;
+  if (16 * Z::RT > R)
+    for (int e = t; e < (16 * Z::RT - R) * kLdx; e += kAlgThreads) X[R * kLdx + e] = 0.0;
+  {
+    float* B_K = a.B_K + (size_t)bkv * R * kD;
+    store_solution<R>(d, w, lane, [&](int i, int j, double x) {
+      X[i * kLdx + j] = x;
+      if (a.last) B_K[i * kD + j] = (float)x;
+    });
+  }
+  __syncthreads();
+  {
+    const size_t q0 = (size_t)b * a.Hq + (size_t)kvh * G;
+    const double* H = a.H + q0 * R * R;
+    const double* S = a.S + q0 * R * kD;
+    load_tiles<R>(d, w, lane,
+                  [&](int i, int j) { return H[i * R + j]; },
+                  [&](int i, int j) { return __builtin_fma(a.lam_pK, X[i * kLdx + j], S[i * kD + j]); });
+    for (int g = 1; g < G; ++g) {
+      f64x4 more[Z::TPW];
+      load_tiles<R>(more, w, lane, [&](int i, int j) { return H[(size_t)g * R * R + i * R + j]; },
+                    [&](int i, int j) { return S[(size_t)g * R * kD + i * kD + j]; });
+#pragma unroll
+      for (int u = 0; u < Z::TPW; ++u) d[u] += more[u];
+    }
+    // (padding rows of the system came in as G times the identity: any multiple will do)
+    add_gram<R>(d, X, a.lam_pK, w, lane);
+  }
+  __syncthreads();  // X has been read
+  solve_tiles<R>(d, Pl, Cl, w, lane);
+  store_solution<R>(d, w, lane, [&](int i, int j, double x) { X[i * kLdx + j] = x; });
+  __syncthreads();
+  if (a.last) pack_operand<R>(X, a.M + own * PfShape<R>::mpack_units, t);
+  sums_of<R>(X, Ys, a.G + own * kD * kD, a.S + own * R * kD, a.H + own * R * R, w, lane);
+}
+
+// Second half, a query head per workgroup: with the sums of the new A_K,
+//   M_Q = (S_K^T + lambda_pQ B_Q^T)(H_K + lambda_pQ B_Q B_Q^T)^-1,  and S_Q, H_Q of A_Q = Q M_Q.
+template <int R>
+__global__ __launch_bounds__(kAlgThreads) void prefill_round_q_kernel(const PfState a) {
+  using Z = PfAlg<R>;
+  extern __shared__ __align__(16) double pf_alg[];
+  double* const X = pf_alg;
+  double* const Ys = X + Z::kX;
+  double* const Pl = Ys + Z::kX;
+  double* const Cl = Pl + 2 * Z::kP;
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int bh = blockIdx.x, b = bh / a.Hq, kvh = (bh - b * a.Hq) / (a.Hq / a.Hkv);
+  const size_t kv = a.BHq + (size_t)b * a.Hkv + kvh;
+  const double* BQ = a.BQ + (size_t)bh * R * kD;
 #pragma unroll 4
-  for (int e = t; e < R * R; e += 256) Ssh[(e / R) * LDS_ + e % R] = sm[R * kD + e];
-  spd_solve_columns<R>(Ssh, dinv_sh, Ysh);
-  float* Bout = (iskv ? B_K : B_Q) + head * R * kD;
-  for (int e = t; e < R * kD; e += 256) Bout[e] = Ysh[(e / kD) * kLDY + e % kD];
-}
-
-// S1b, one workgroup per (batch, KV head):
-//   M_K = (sum_g Q_g^T A_Q,g + lambda_pK B_K^T)(sum_g A_Q,g^T A_Q,g + lambda_pK B_K B_K^T)^-1,
-// the d x r operand of the A_K update, written as [d][RP] (padding columns zero).
-template <int R>
-__global__ __launch_bounds__(256) void prefill_solve_mk_kernel(const float* __restrict__ sum_q,
-                                                               const float* __restrict__ B_K,
-                                                               float* __restrict__ Mk, int Hq,
-                                                               int Hkv, float lam_pK) {
-  using S = PfShape<R>;
-  constexpr int LDS_ = kLDS<R>, RP = S::RP;
-  extern __shared__ __align__(16) float pf_lds[];
-  float* const Wsh = pf_lds;              // [R][kLDY]  W^T
-  float* const Bsh = Wsh + R * kLDY;      // [R][kLDY]  B_K
-  float* const Ssh = Bsh + R * kLDY;      // [R][R + 4]
-  float* const dinv_sh = Ssh + R * LDS_;  // [R]
-  const int bkv = blockIdx.x, t = threadIdx.x;
-  const int b = bkv / Hkv, kvh = bkv - b * Hkv, G = Hq / Hkv;
-  const float* sq = sum_q + ((size_t)b * Hq + (size_t)kvh * G) * S::P;  // the group's G heads
-  const float* Bk = B_K + (size_t)bkv * R * kD;
-  // The group's sums are added head by head with the element loops innermost and unrolled, so
-  // that the loads of one head are all in flight together (G is not a compile-time constant).
-  constexpr int kT1 = R * kD / 256, kT2 = (R * R + 255) / 256;
-  float w[kT1], gs[kT2];
-#pragma unroll
-  for (int u = 0; u < kT1; ++u) {
-    const int e = t + 256 * u;
-    const float bk = Bk[e];
-    Bsh[(e / kD) * kLDY + e % kD] = bk;
-    w[u] = lam_pK * bk;
-  }
-#pragma unroll
-  for (int u = 0; u < kT2; ++u) gs[u] = 0.0f;
-  for (int g = 0; g < G; ++g) {
-    const float* sg = sq + (size_t)g * S::P;
-#pragma unroll
-    for (int u = 0; u < kT1; ++u) w[u] += sg[t + 256 * u];
-#pragma unroll
-    for (int u = 0; u < kT2; ++u)
-      if (t + 256 * u < R * R) gs[u] += sg[R * kD + t + 256 * u];
-  }
-#pragma unroll
-  for (int u = 0; u < kT1; ++u) {
-    const int e = t + 256 * u;
-    Wsh[(e / kD) * kLDY + e % kD] = w[u];
+  for (int e = t; e < 16 * Z::RT * kD; e += kAlgThreads)
+    X[(e / kD) * kLdx + e % kD] = e < R * kD ? BQ[e] : 0.0;
+  f64x4 d[Z::TPW];
+  {
+    const double* H = a.H + kv * R * R;
+    const double* S = a.S + kv * R * kD;
+    load_tiles<R>(d, w, lane, [&](int i, int j) { return H[i * R + j]; },
+                  [&](int i, int j) { return __builtin_fma(a.lam_pQ, BQ[i * kD + j], S[i * kD + j]); });
   }
   __syncthreads();
+  add_gram<R>(d, X, a.lam_pQ, w, lane);
+  __syncthreads();  // X has been read
+  solve_tiles<R>(d, Pl, Cl, w, lane);
+  store_solution<R>(d, w, lane, [&](int i, int j, double x) { X[i * kLdx + j] = x; });
+  __syncthreads();
+  if (a.last)
+    pack_operand<R>(X, a.M + (size_t)bh * PfShape<R>::mpack_units, t);
+  else
+    sums_of<R>(X, Ys, a.G + (size_t)bh * kD * kD, a.S + (size_t)bh * R * kD,
+               a.H + (size_t)bh * R * R, w, lane);
+}
+
+// ------------------------------------------------------------------------------------------
+// Apply: X = Y M, a wavefront per 32 rows.  The rows pass through 8 KB of LDS of the wavefront's
+// own (256 bytes a row: bf16 rows at once, fp32 rows in two halves), from coalesced loads to
+// "lane = row"; 16-byte piece c of row i is kept at c ^ (i % 16), so that 16 rows' reads of one
+// piece lie in different banks.  The next rows' loads are in flight during the products.  M is
+// the same for a whole head: in registers at r <= 32 (96 of them), in LDS at r = 64.
+// Bound by HBM (Y in, X out): 2.0 GB in 0.39 ms at 32 + 8 heads, l = 131072, r = 32.
+template <int R>
+constexpr size_t apply_lds_bytes() {
+  return 4 * 8192 + (R > 32 ? PfShape<R>::mpack_units * 16 : 0);
+}
+
+template <int R, int NS>
+__global__ __launch_bounds__(kPfThreads, 2) void prefill_apply_kernel(
+    const void* __restrict__ Q, const void* __restrict__ K, const uint4* __restrict__ M,
+    float* __restrict__ A_Q, float* __restrict__ A_K, int BHq, int l, int lk, int units,
+    int blocks_per_head) {
+  using S = PfShape<R>;
+  constexpr int RB = S::RB;
+  constexpr int ROW16 = NS == 1 ? 16 : 32;
+  constexpr int NPH = ROW16 / 16;            // 256-byte phases of a row
+  constexpr int STEPS = 8 / NPH;             // k steps of 16 per phase
+  extern __shared__ __align__(16) unsigned char pf_lds[];
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  u32x4* const Yl = reinterpret_cast<u32x4*>(pf_lds) + w * 512;
+  u32x4* const Ml = reinterpret_cast<u32x4*>(pf_lds) + 4 * 512;
+  const int bh = blockIdx.x / blocks_per_head, block = blockIdx.x - bh * blocks_per_head;
+  const bool isq = bh < BHq;
+  const size_t head = isq ? bh : bh - BHq;
+  const u32x4* __restrict__ Yh = static_cast<const u32x4*>(isq ? Q : K) + head * (size_t)l * ROW16;
+  float* __restrict__ Xh = isq ? A_Q + head * (size_t)l * R : A_K + head * (size_t)lk * R;
+  const u32x4* __restrict__ Mh = reinterpret_cast<const u32x4*>(M) + bh * S::mpack_units;
+
+  u32x4 mreg[RB == 1 ? 24 : 1];
+  if (RB == 1) {
 #pragma unroll
-  for (int u = 0; u < kT2; ++u) {
-    const int e = t + 256 * u;
-    if (e < R * R) {
-      const int i = e / R, c = e % R;
-      float bb = 0.0f;
-#pragma unroll 16
-      for (int j = 0; j < kD; ++j) bb = __builtin_fmaf(Bsh[i * kLDY + j], Bsh[c * kLDY + j], bb);
-      Ssh[i * LDS_ + c] = __builtin_fmaf(lam_pK, bb, gs[u]);
+    for (int i = 0; i < 24; ++i) mreg[RB == 1 ? i : 0] = Mh[i * 64 + lane];
+  } else {
+    for (int i = t; i < (int)S::mpack_units; i += kPfThreads) Ml[i] = Mh[i];
+    __syncthreads();
+  }
+  auto m_op = [&](int p, int rb, int step) {
+    const u32x4 u = RB == 1 ? mreg[RB == 1 ? p * 8 + step : 0] : Ml[((p * RB + rb) * 8 + step) * 64 + lane];
+    return __builtin_bit_cast(bf16x8, u);
+  };
+
+  const int first = (block * 4 + w) * units * 32;
+  const int last = min(l, first + units * 32);
+  u32x4 pre[8];
+  auto prefetch = [&](int row0, int ph) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int row = min(row0 + 4 * j + (lane >> 4), last - 1);  // (results past the end are dropped)
+      pre[j] = Yh[(size_t)row * ROW16 + 16 * ph + (lane & 15)];
+    }
+  };
+  if (first >= last) return;  // (no barrier follows)
+  prefetch(first, 0);
+  const int i = lane & 31, kh = lane >> 5;
+  for (int row0 = first; row0 < last; row0 += 32) {
+    f32x16 acc[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[rb][v] = 0.0f;
+#pragma unroll
+    for (int ph = 0; ph < NPH; ++ph) {
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int row = 4 * j + (lane >> 4);
+        Yl[row * 16 + ((lane & 15) ^ (row & 15))] = pre[j];
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (ph + 1 < NPH)
+        prefetch(row0, ph + 1);
+      else if (row0 + 32 < last)
+        prefetch(row0 + 32, 0);
+#pragma unroll
+      for (int st = 0; st < STEPS; ++st) {
+        const int step = ph * STEPS + st;
+        bf16x8 y[NS];
+        if (NS == 1) {
+          y[0] = __builtin_bit_cast(bf16x8, Yl[i * 16 + ((2 * st + kh) ^ (i & 15))]);
+        } else {
+          uint32_t s[4][3];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const u32x4 u = Yl[i * 16 + ((4 * st + 2 * kh + h) ^ (i & 15))];
+            split3(__uint_as_float(u.x), __uint_as_float(u.y), s[2 * h]);
+            split3(__uint_as_float(u.z), __uint_as_float(u.w), s[2 * h + 1]);
+          }
+#pragma unroll
+          for (int p = 0; p < NS; ++p)
+            y[p] = __builtin_bit_cast(bf16x8, (u32x4{s[0][p], s[1][p], s[2][p], s[3][p]}));
+        }
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            const bf16x8 m = m_op(j, rb, step);
+#pragma unroll
+            for (int p = 0; p < NS && p + j < 3; ++p) acc[rb] = mfma_bf16(y[p], m, acc[rb]);
+          }
+      }
+    }
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      const int j = 32 * rb + i;
+      if (j < R) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int row = row0 + mfma_row(v, lane);
+          if (row < last) Xh[(size_t)row * R + j] = acc[rb][v];
+        }
+      }
     }
   }
-  spd_solve_columns<R>(Ssh, dinv_sh, Wsh);  // M_K^T = S^-1 W^T
-  float* Mo = Mk + (size_t)bkv * kD * RP;
-  for (int e = t; e < kD * RP; e += 256) {
-    const int j = e / RP, i = e % RP;
-    Mo[e] = i < R ? Wsh[i * kLDY + j] : 0.0f;
-  }
 }
 
-// S2, one workgroup per (batch, query head): with the sums of the new A_K,
-//   M_Q = (K^T A_K + lambda_pQ B_Q^T)(A_K^T A_K + lambda_pQ B_Q B_Q^T)^-1,  written as [d][RP].
-template <int R>
-__global__ __launch_bounds__(256) void prefill_solve_q_kernel(const float* __restrict__ sum_k,
-                                                              const float* __restrict__ B_Q,
-                                                              float* __restrict__ Mq, int Hq,
-                                                              int Hkv, float lam_pQ) {
-  using S = PfShape<R>;
-  constexpr int LDS_ = kLDS<R>, RP = S::RP;
-  extern __shared__ __align__(16) float pf_lds[];
-  float* const Ysh = pf_lds;              // [R][kLDY]
-  float* const Bsh = Ysh + R * kLDY;      // [R][kLDY]
-  float* const Ssh = Bsh + R * kLDY;      // [R][R + 4]
-  float* const dinv_sh = Ssh + R * LDS_;  // [R]
-  const int bh = blockIdx.x, t = threadIdx.x;
-  const int b = bh / Hq, h = bh - b * Hq, kvh = h / (Hq / Hkv);
-  const float* sm = sum_k + ((size_t)b * Hkv + kvh) * S::P;
-  const float* Bq = B_Q + (size_t)bh * R * kD;
-#pragma unroll 8
-  for (int e = t; e < R * kD; e += 256) {
-    const float bq = Bq[e];
-    Bsh[(e / kD) * kLDY + e % kD] = bq;
-    Ysh[(e / kD) * kLDY + e % kD] = __builtin_fmaf(lam_pQ, bq, sm[e]);
+// ------------------------------------------------------------------------------------------
+// Chunks of rows per head: the fewest workgroup rounds (one workgroup per CU) times the tiles
+// of a workgroup, a partial costing about as much as two tiles.  At most kPfSlots partials
+// unless there are more heads than that.
+constexpr int kPfSlots = 1024;
+int reduce_chunks(int heads, int l, int TR) {
+  const int tiles = ceil_div(l, TR);
+  const int most = heads >= kPfSlots ? 1 : min(tiles, kPfSlots / heads);
+  int best = 1;
+  long best_cost = 0;
+  for (int n = 1; n <= most; ++n) {
+    const int per = ceil_div(tiles, n);
+    const long cost = (long)ceil_div(heads * ceil_div(tiles, per), 256) * (per + 2);
+    if (n == 1 || cost < best_cost) {
+      best = n;
+      best_cost = cost;
+    }
   }
-  __syncthreads();
-  for (int e = t; e < R * R; e += 256) {
-    const int i = e / R, c = e % R;
-    float acc = 0.0f;
-#pragma unroll 16
-    for (int j = 0; j < kD; ++j) acc = __builtin_fmaf(Bsh[i * kLDY + j], Bsh[c * kLDY + j], acc);
-    Ssh[i * LDS_ + c] = __builtin_fmaf(lam_pQ, acc, sm[R * kD + e]);
-  }
-  spd_solve_columns<R>(Ssh, dinv_sh, Ysh);
-  float* Mo = Mq + (size_t)bh * kD * RP;
-  for (int e = t; e < kD * RP; e += 256) {
-    const int j = e / RP, i = e % RP;
-    Mo[e] = i < R ? Ysh[i * kLDY + j] : 0.0f;
-  }
-}
-
-// Kernels that use more than 64 KB of dynamic LDS have to opt in (once per kernel).
-template <typename K>
-hipError_t allow_lds(K kernel, size_t bytes) {
-  static bool done = false;  // one flag per kernel type
-  if (bytes <= 64 * 1024 || done) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  if (e == hipSuccess) done = true;
-  return e;
-}
-template <int R>
-constexpr size_t solve_lds_bytes() {
-  return ((size_t)2 * R * kLDY + (size_t)R * kLDS<R> + R) * sizeof(float);
-}
-
-template <int R, bool BF16, bool APPLY, bool REDUCE>
-hipError_t launch_pass(const void* Y, float* X, const float* M, float* part, int heads, int l,
-                       int xrows, int nchunk, hipStream_t st) {
-  const size_t lds = PfShape<R>::lds_floats(BF16, APPLY) * sizeof(float);
-  auto kernel = prefill_pass_kernel<R, BF16, APPLY, REDUCE>;
-  const hipError_t e = allow_lds(kernel, lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, dim3(nchunk, heads), dim3(kPfThreads), lds, st, Y, X, M, part, l,
-                     xrows, nchunk);
-  return hipGetLastError();
+  return best;
 }
 
 struct PrefillWs {
-  float *part_q, *part_k, *sum_q, *sum_k, *Mq, *Mk;
-  size_t floats;
+  float* part;
+  double *G, *S, *H, *BQ;
+  uint4* M;
+  size_t bytes;
 };
 template <int R>
-PrefillWs carve_prefill(float* base, const lrqk_shape& s) {
+PrefillWs carve_prefill(void* base, const lrqk_shape& s) {
   using S = PfShape<R>;
-  const size_t BHq = (size_t)s.B * s.Hq, BHkv = (size_t)s.B * s.Hkv;
-  const size_t nchunk = (size_t)ceil_div(s.l, kPfTile * kPfTilesPerChunk);
+  const size_t BHq = (size_t)s.B * s.Hq, heads = BHq + (size_t)s.B * s.Hkv;
+  // room for the partials of any shape that is no larger than this one
+  const size_t tiles = (size_t)ceil_div(s.l, 64);
+  const size_t most = heads > kPfSlots ? heads : (size_t)kPfSlots;
+  const size_t parts = heads * tiles < most ? heads * tiles : most;
   PrefillWs w;
   size_t off = 0;
   auto take = [&](size_t n) {
-    float* p = base ? base + off : nullptr;
-    off += (n + 63) / 64 * 64;
-    return p;
+    char* p = base ? static_cast<char*>(base) + off : nullptr;
+    off += round_up(n, 256);
+    return static_cast<void*>(p);
   };
-  w.part_q = take(BHq * nchunk * S::P);
-  w.part_k = take(BHkv * nchunk * S::P);
-  w.sum_q = take(BHq * S::P);
-  w.sum_k = take(BHkv * S::P);
-  w.Mq = take(BHq * kD * S::RP);
-  w.Mk = take(BHkv * kD * S::RP);
-  w.floats = off;
+  w.part = static_cast<float*>(take(parts * S::PB * 1024 * sizeof(float)));
+  w.G = static_cast<double*>(take(heads * kD * kD * sizeof(double)));
+  w.S = static_cast<double*>(take(heads * R * kD * sizeof(double)));
+  w.H = static_cast<double*>(take(heads * R * R * sizeof(double)));
+  w.BQ = static_cast<double*>(take(BHq * R * kD * sizeof(double)));
+  w.M = static_cast<uint4*>(take(heads * S::mpack_units * sizeof(uint4)));
+  w.bytes = off;
   return w;
 }
 
-template <int R, bool BF16>
+// A kernel's dynamic-LDS ceiling is raised once per device and instantiation.
+template <int R, int NS>
+struct PfKernels {
+  static hipError_t allow() {
+    static std::atomic<uint64_t> reduce{0}, rk{0}, rq{0}, apply{0};
+    hipError_t e = raise_dynamic_lds_once(prefill_reduce_kernel<R, NS>, PfReduce<R, NS>::lds_bytes, reduce);
+    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_round_k_kernel<R>, PfAlg<R>::lds_bytes, rk);
+    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_round_q_kernel<R>, PfAlg<R>::lds_bytes, rq);
+    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_apply_kernel<R, NS>, apply_lds_bytes<R>(), apply);
+    return e;
+  }
+};
+
+template <int R, int NS>
 hipError_t run_prefill(const lrqk_shape& s, const void* Q, const void* K, float* A_Q, float* A_K,
-                       float* B_Q, float* B_K, float lam_pQ, float lam_pK, int n_iter, float* ws,
+                       float* B_Q, float* B_K, float lam_pQ, float lam_pK, int n_iter, void* ws,
                        hipStream_t st) {
   using S = PfShape<R>;
   const PrefillWs w = carve_prefill<R>(ws, s);
-  const int BHq = s.B * s.Hq, BHkv = s.B * s.Hkv, l = s.l, lk = row_cap(s);
-  const int nchunk = ceil_div(l, kPfTile * kPfTilesPerChunk);
-  const dim3 sum_grid_q(ceil_div(S::P, 256), BHq), sum_grid_k(ceil_div(S::P, 256), BHkv);
-  hipError_t e;
-#define PF_TRY(x)                  \
-  do {                             \
-    e = (x);                       \
-    if (e != hipSuccess) return e; \
-  } while (0)
-  // sums of the initial factors
-  PF_TRY((launch_pass<R, BF16, false, true>(Q, A_Q, nullptr, w.part_q, BHq, l, l, nchunk, st)));
-  PF_TRY((launch_pass<R, BF16, false, true>(K, A_K, nullptr, w.part_k, BHkv, l, lk, nchunk, st)));
-  hipLaunchKernelGGL(prefill_sum_kernel, sum_grid_q, dim3(256), 0, st, w.part_q, w.sum_q, nchunk,
-                     S::P);
-  hipLaunchKernelGGL(prefill_sum_kernel, sum_grid_k, dim3(256), 0, st, w.part_k, w.sum_k, nchunk,
-                     S::P);
+  const int BHq = s.B * s.Hq, BHkv = s.B * s.Hkv, heads = BHq + BHkv, l = s.l, lk = row_cap(s);
+  hipError_t e = PfKernels<R, NS>::allow();
+  if (e != hipSuccess) return e;
+  constexpr int TR = PfReduce<R, NS>::TR;
+  const int per_chunk = ceil_div(ceil_div(l, TR), reduce_chunks(heads, l, TR));
+  const int nchunk = ceil_div(ceil_div(l, TR), per_chunk);
+  hipLaunchKernelGGL((prefill_reduce_kernel<R, NS>), dim3(nchunk * heads), dim3(kRedThreads),
+                     (PfReduce<R, NS>::lds_bytes), st, Q, K, A_Q, A_K, w.part, BHq, l, lk, nchunk,
+                     per_chunk);
+  hipLaunchKernelGGL((prefill_sum_kernel<R, NS>), dim3(ceil_div(S::HB0 * 1024 + R * R, 256) * heads),
+                     dim3(256), 0, st, w.part, w.G, w.S, w.H, nchunk);
+  PfState a;
+  a.G = w.G; a.S = w.S; a.H = w.H; a.BQ = w.BQ; a.M = w.M; a.B_Q = B_Q; a.B_K = B_K;
+  a.Hq = s.Hq; a.Hkv = s.Hkv; a.BHq = BHq; a.BHkv = BHkv; a.lam_pQ = lam_pQ; a.lam_pK = lam_pK;
   for (int it = 0; it < n_iter; ++it) {
-    PF_TRY(allow_lds(prefill_solve_b_kernel<R>, solve_lds_bytes<R>()));
-    PF_TRY(allow_lds(prefill_solve_mk_kernel<R>, solve_lds_bytes<R>()));
-    PF_TRY(allow_lds(prefill_solve_q_kernel<R>, solve_lds_bytes<R>()));
-    hipLaunchKernelGGL((prefill_solve_b_kernel<R>), dim3(BHq + BHkv), dim3(256),
-                       solve_lds_bytes<R>(), st, w.sum_q, w.sum_k, B_Q, B_K, BHq);
-    hipLaunchKernelGGL((prefill_solve_mk_kernel<R>), dim3(BHkv), dim3(256), solve_lds_bytes<R>(),
-                       st, w.sum_q, B_K, w.Mk, s.Hq, s.Hkv, lam_pK);
-    PF_TRY((launch_pass<R, BF16, true, true>(K, A_K, w.Mk, w.part_k, BHkv, l, lk, nchunk, st)));
-    hipLaunchKernelGGL(prefill_sum_kernel, sum_grid_k, dim3(256), 0, st, w.part_k, w.sum_k,
-                       nchunk, S::P);
-    hipLaunchKernelGGL((prefill_solve_q_kernel<R>), dim3(BHq), dim3(256), solve_lds_bytes<R>(),
-                       st, w.sum_k, B_Q, w.Mq, s.Hq, s.Hkv, lam_pQ);
-    if (it + 1 < n_iter) {
-      PF_TRY((launch_pass<R, BF16, true, true>(Q, A_Q, w.Mq, w.part_q, BHq, l, l, nchunk, st)));
-      hipLaunchKernelGGL(prefill_sum_kernel, sum_grid_q, dim3(256), 0, st, w.part_q, w.sum_q,
-                         nchunk, S::P);
-    } else {  // nothing reads the sums of the final A_Q
-      PF_TRY((launch_pass<R, BF16, true, false>(Q, A_Q, w.Mq, nullptr, BHq, l, l, nchunk, st)));
-    }
+    a.last = it + 1 == n_iter;
+    hipLaunchKernelGGL((prefill_round_k_kernel<R>), dim3(heads), dim3(kAlgThreads),
+                       PfAlg<R>::lds_bytes, st, a);
+    hipLaunchKernelGGL((prefill_round_q_kernel<R>), dim3(BHq), dim3(kAlgThreads),
+                       PfAlg<R>::lds_bytes, st, a);
   }
-#undef PF_TRY
+  // 32-row units per wavefront: enough workgroups to fill the chip a few times over
+  const int row_units = ceil_div(l, 32);
+  int units = 1;
+  while (units < 16 && (long)ceil_div(row_units, 8 * units) * heads >= 2048) units *= 2;
+  const int blocks = ceil_div(row_units, 4 * units);
+  hipLaunchKernelGGL((prefill_apply_kernel<R, NS>), dim3(blocks * heads), dim3(kPfThreads),
+                     apply_lds_bytes<R>(), st, Q, K, w.M, A_Q, A_K, BHq, l, lk, units, blocks);
   return hipGetLastError();
 }
 
 template <int R>
 hipError_t run_prefill_dtype(const lrqk_shape& s, const void* Q, const void* K, float* A_Q,
                              float* A_K, float* B_Q, float* B_K, float lam_pQ, float lam_pK,
-                             int n_iter, float* ws, hipStream_t st) {
+                             int n_iter, void* ws, hipStream_t st) {
   return s.kv_dtype == LRQK_KV_BF16
-             ? run_prefill<R, true>(s, Q, K, A_Q, A_K, B_Q, B_K, lam_pQ, lam_pK, n_iter, ws, st)
-             : run_prefill<R, false>(s, Q, K, A_Q, A_K, B_Q, B_K, lam_pQ, lam_pK, n_iter, ws, st);
+             ? run_prefill<R, 1>(s, Q, K, A_Q, A_K, B_Q, B_K, lam_pQ, lam_pK, n_iter, ws, st)
+             : run_prefill<R, 3>(s, Q, K, A_Q, A_K, B_Q, B_K, lam_pQ, lam_pK, n_iter, ws, st);
 }
 
 }  // namespace
@@ -604,15 +985,13 @@ bool prefill_supported(const lrqk_shape& s) {
 }
 
 size_t prefill_ws_bytes(const lrqk_shape& s) {
-  size_t f = 0;
   switch (s.r) {
-    case 8: f = carve_prefill<8>(nullptr, s).floats; break;
-    case 16: f = carve_prefill<16>(nullptr, s).floats; break;
-    case 32: f = carve_prefill<32>(nullptr, s).floats; break;
-    case 64: f = carve_prefill<64>(nullptr, s).floats; break;
+    case 8: return carve_prefill<8>(nullptr, s).bytes;
+    case 16: return carve_prefill<16>(nullptr, s).bytes;
+    case 32: return carve_prefill<32>(nullptr, s).bytes;
+    case 64: return carve_prefill<64>(nullptr, s).bytes;
     default: return 0;
   }
-  return round_up(f * sizeof(float), 256);
 }
 
 hipError_t launch_prefill(const lrqk_shape& s, const void* Q, const void* K, float* A_Q,

@@ -169,3 +169,17 @@ def test_product_never_touches_the_oracle():
             if f.endswith((".py", ".c", ".h")):
                 text = open(os.path.join(dirpath, f)).read()
                 assert "paper_2510_23649_amd" not in text and "lrqk.h" not in text
+
+
+@pytest.mark.parametrize("r", [8, 16, 32, 64])
+def test_prefill_workspace_grows_with_the_shape(lib, r):
+    """A workspace sized for a larger shape serves every smaller one."""
+    def need(B, l):
+        return lib.lrqk_workspace_bytes(lib.Shape.make(B=B, Hq=28, Hkv=4, l=l, r=r, k=16, w=0,
+                                                   C_slots=16), lib.LRQK_WS_PREFILL)
+    for B in (1, 3, 8, 40):
+        sizes = [need(B, l) for l in (100, 128, 1000, 4097, 20000, 65536, 131072)]
+        assert sizes == sorted(sizes) and sizes[0] > 0
+    for l in (100, 5000, 131072):
+        sizes = [need(B, l) for B in (1, 2, 3, 8, 32, 40)]
+        assert sizes == sorted(sizes)

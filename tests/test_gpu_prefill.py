@@ -179,6 +179,22 @@ def test_prefill_at_128k():
     run_prefill_case(pf_cfg(Hq=4, Hkv=1, l=131072, r=32))
 
 
+@pytest.mark.parametrize("r,l,kv_dtype", [
+    (64, 96, "bf16"), (64, 97, "bf16"), (64, 1055, "bf16"),     # tiles of 96 rows
+    (32, 127, "bf16"), (32, 129, "bf16"), (8, 1153, "bf16"),    # 128 rows, accumulators moved on at 512
+    (64, 127, "f32"), (64, 577, "f32"), (16, 65, "f32"), (8, 1025, "f32")])   # 64 rows
+def test_prefill_tile_edges(r, l, kv_dtype):
+    """Around the tile heights of the reduction (one per rank and row type), the rows after which
+    its accumulators are moved on, and the 32-row units of the last product."""
+    say(f"prefill r={r} l={l} {kv_dtype}")
+    run_prefill_case(pf_cfg(r=r, l=l, kv_dtype=kv_dtype, k=32, C=32))
+
+
+def test_prefill_eight_heads_a_group_and_many_chunks():
+    say("prefill G=8, 1 KV head, fp32 rows, l = 20011")
+    run_prefill_case(pf_cfg(Hq=8, Hkv=1, l=20011, r=16, kv_dtype="f32"))
+
+
 def test_prefill_rejects_bad_arguments():
     t = torch.zeros(1 << 16, device=DEV)
     shp = L.Shape.make(B=1, Hq=2, Hkv=1, l=512, r=12, k=16, w=0, C_slots=16)
