@@ -25,13 +25,15 @@
 // r = 32; 1.9e-5 (1.8e-4) at l = 4096, r = 16; 9e-6 (1.6e-4) at l = 30011, r = 64.
 #include <type_traits>
 
+#include "lrqk_alg64.h"
 #include "lrqk_internal.h"
 
 namespace lrqk {
 namespace {
 
+using namespace alg64;
+
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -47,12 +49,6 @@ __device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 c) {
 __device__ __forceinline__ int mfma_row(int v, int lane) {
   return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
 }
-// D(16x16) = A(16x4) B(4x16) + C; lane i + 16 h supplies A[i][h] and B[h][i]; register v of
-// lane l holds D[4 v + l / 16][l % 16]
-__device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
 // x0, x1 as three bf16 pairs (packed in dwords) that add up to them exactly
 __device__ __forceinline__ void split3(float x0, float x1, uint32_t (&s)[3]) {
 #pragma unroll
@@ -106,11 +102,6 @@ struct PfReduce {
   static constexpr size_t lds_bytes = 2 * (size_t)kTile;      // two tiles in turn
   static constexpr int kFlushTiles = kFlushRows / TR;
 };
-
-// Orders LDS traffic only: loads from memory stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
 
 template <int R, int NS>
 __global__ __launch_bounds__(kRedThreads, 2) void prefill_reduce_kernel(
@@ -370,15 +361,13 @@ __global__ __launch_bounds__(256) void prefill_sum_kernel(const float* __restric
   auto total = [&](int at) {
     double acc = 0.0;
     const float* q = p + at;
-    int c = 0;
-    for (; c + 8 <= nchunk; c += 8) {
+    for (int c0 = 0; c0 < nchunk; c0 += 8) {  // (eight loads in flight, those past the end unused)
       float v[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = q[(size_t)(c + j) * (S::PB * 1024)];
+      for (int j = 0; j < 8; ++j) v[j] = q[(size_t)min(c0 + j, nchunk - 1) * (S::PB * 1024)];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc += (double)v[j];
+      for (int j = 0; j < 8; ++j) acc += c0 + j < nchunk ? (double)v[j] : 0.0;
     }
-    for (; c < nchunk; ++c) acc += (double)q[(size_t)c * (S::PB * 1024)];
     return acc;
   };
   if (e < S::HB0 * 1024) {
@@ -469,35 +458,8 @@ __device__ __forceinline__ void solve_tiles(f64x4 (&d)[PfAlg<R>::TPW], double* P
           for (int v = 0; v < 4; ++v) C[(16 * tr + 4 * v + k) * 4 + (lane & 3)] = d[u][v];
         }
       }
-      __syncthreads();
-      const double* D = C + p0 * 4;
-      const double d00 = D[0], d01 = D[1], d02 = D[2], d03 = D[3], d11 = D[5], d12 = D[6],
-                   d13 = D[7], d22 = D[10], d23 = D[11], d33 = D[15];
-      // D = [E F; F^T L] in 2 x 2 blocks, W = E^-1 F, T = (L - F^T W)^-1
-      const double ie = 1.0 / (d00 * d11 - d01 * d01);
-      const double e00 = d11 * ie, e01 = -d01 * ie, e11 = d00 * ie;
-      const double w00 = e00 * d02 + e01 * d12, w01 = e00 * d03 + e01 * d13;
-      const double w10 = e01 * d02 + e11 * d12, w11 = e01 * d03 + e11 * d13;
-      const double l00 = d22 - (d02 * w00 + d12 * w10), l01 = d23 - (d02 * w01 + d12 * w11);
-      const double l11 = d33 - (d03 * w01 + d13 * w11);
-      const double il = 1.0 / (l00 * l11 - l01 * l01);
-      const double t00 = l11 * il, t01 = -l01 * il, t11 = l00 * il;
-      const double u00 = w00 * t00 + w01 * t01, u01 = w00 * t01 + w01 * t11;  // W T
-      const double u10 = w10 * t00 + w11 * t01, u11 = w10 * t01 + w11 * t11;
-      // column k of D^-1 = [E^-1 + W T W^T, -W T; -T W^T, T].  (Every entry is computed before the
-      // selection: with the arithmetic inside the branches of a chain of ifs on k, this compiler
-      // gave the lanes of the last branch an unset register.)
-      const double f00 = e00 + (u00 * w00 + u01 * w01), f01 = e01 + (u00 * w10 + u01 * w11);
-      const double f11 = e11 + (u10 * w10 + u11 * w11);
-      const bool odd = k & 1, low = k < 2;
-      const double x0 = low ? (odd ? f01 : f00) : -(odd ? u01 : u00);
-      const double x1 = low ? (odd ? f11 : f01) : -(odd ? u11 : u10);
-      const double x2 = low ? -(odd ? u10 : u00) : (odd ? t01 : t00);
-      const double x3 = low ? -(odd ? u11 : u01) : (odd ? t11 : t01);
-      const double* c = C + i * 4;
-      double n = -(c[0] * x0 + c[1] * x1 + (c[2] * x2 + c[3] * x3));
-      const int m = i - p0;
-      if (m >= 0 && m < 4) n = (m == 0 ? x0 : m == 1 ? x1 : m == 2 ? x2 : x3) - (m == k ? 1.0 : 0.0);
+      lds_barrier();
+      const double n = pivot_factor(C, p0, i, k);
 #pragma unroll
       for (int u = 0; u < Z::TPW; ++u) {
         const int tc = tc0 + Z::WPR * u;
@@ -505,27 +467,69 @@ __device__ __forceinline__ void solve_tiles(f64x4 (&d)[PfAlg<R>::TPW], double* P
       }
     }
   }
-  __syncthreads();
+  lds_barrier();
 }
 
-// The tiles of [A | Y] of this wavefront: a(i, j) and y(i, j) give the elements (i < r).
-template <int R, typename FA, typename FY>
-__device__ __forceinline__ void load_tiles(f64x4 (&d)[PfAlg<R>::TPW], int w, int lane, FA a, FY y) {
+// The tiles of [H | S] of this wavefront, H [r][r] and S [r][d] in memory, added up over `n`
+// matrices that follow each other.  Every load is issued before the first is waited for: rows and
+// tiles that do not exist read ones that do.
+template <int R>
+__device__ __forceinline__ void load_tiles(f64x4 (&d)[PfAlg<R>::TPW], int w, int lane,
+                                           const double* __restrict__ H,
+                                           const double* __restrict__ S, int n) {
+  using Z = PfAlg<R>;
+  const int tr = w / Z::WPR, tc0 = w % Z::WPR;
+  const double* p[Z::TPW];
+  int row_stride[Z::TPW], stride[Z::TPW];
+#pragma unroll
+  for (int u = 0; u < Z::TPW; ++u) {
+    const int tc = min(tc0 + Z::WPR * u, Z::NT - 1);
+    const bool sys = tc < Z::RT;
+    const int j = 16 * tc + (lane & 15);
+    row_stride[u] = sys ? R : kD;
+    stride[u] = sys ? R * R : R * kD;
+    p[u] = sys ? H + min(j, R - 1) : S + (j - 16 * Z::RT);
+    d[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+  }
+#pragma unroll 2
+  for (int g = 0; g < n; ++g) {
+    double x[Z::TPW][4];
+#pragma unroll
+    for (int u = 0; u < Z::TPW; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        x[u][v] = p[u][(size_t)g * stride[u] +
+                       min(16 * tr + 4 * v + (lane >> 4), R - 1) * row_stride[u]];
+#pragma unroll
+    for (int u = 0; u < Z::TPW; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) d[u][v] += x[u][v];
+  }
+  if (R % 16 != 0) {  // the padding of a system is the identity, that of its right-hand sides zero
+#pragma unroll
+    for (int u = 0; u < Z::TPW; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int tc = tc0 + Z::WPR * u, i = 16 * tr + 4 * v + (lane >> 4), j = 16 * tc + (lane & 15);
+        if (i >= R || (tc < Z::RT && j >= R)) d[u][v] = (tc < Z::RT && i == j) ? 1.0 : 0.0;
+      }
+  }
+}
+
+// Right-hand-side tiles += lam X, X [r][d] in LDS.
+template <int R>
+__device__ __forceinline__ void add_rhs(f64x4 (&d)[PfAlg<R>::TPW], const double* X, double lam,
+                                        int w, int lane) {
   using Z = PfAlg<R>;
   const int tr = w / Z::WPR, tc0 = w % Z::WPR;
 #pragma unroll
   for (int u = 0; u < Z::TPW; ++u) {
     const int tc = tc0 + Z::WPR * u;
+    if (tc < Z::RT || tc >= Z::NT) continue;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = 16 * tr + 4 * v + (lane >> 4), j = 16 * tc + (lane & 15);
-      double x = 0.0;
-      if (tc < Z::RT)
-        x = (i < R && j < R) ? a(i, j) : (i == j ? 1.0 : 0.0);
-      else if (tc < Z::NT)
-        x = i < R ? y(i, j - 16 * Z::RT) : 0.0;
-      d[u][v] = x;
-    }
+    for (int v = 0; v < 4; ++v)
+      d[u][v] = __builtin_fma(lam, X[(16 * tr + 4 * v + (lane >> 4)) * kLdx + 16 * (tc - Z::RT) +
+                                     (lane & 15)], d[u][v]);
   }
 }
 
@@ -564,9 +568,17 @@ __device__ __forceinline__ void add_gram(f64x4 (&d)[PfAlg<R>::TPW], const double
   }
 }
 
-// S = X G and H = S X^T for X [r][d] in LDS and G [d][d] in memory; Ys [r][d]: LDS scratch.
+// This wavefront's operands of X G, G [d][d] in memory: columns 16 w .. 16 w + 15.
+__device__ __forceinline__ void load_gram(double (&g)[32], const double* __restrict__ G, int w,
+                                          int lane) {
+  const double* p = G + (lane >> 4) * kD + 16 * w + (lane & 15);
+#pragma unroll
+  for (int s = 0; s < 32; ++s) g[s] = p[4 * s * kD];
+}
+
+// S = X G and H = S X^T for X [r][d] in LDS; Ys [r][d]: LDS scratch.
 template <int R>
-__device__ __forceinline__ void sums_of(const double* X, double* Ys, const double* __restrict__ G,
+__device__ __forceinline__ void sums_of(const double* X, double* Ys, const double (&g)[32],
                                         double* __restrict__ Sm, double* __restrict__ H, int w,
                                         int lane) {
   using Z = PfAlg<R>;
@@ -574,18 +586,11 @@ __device__ __forceinline__ void sums_of(const double* X, double* Ys, const doubl
   f64x4 acc[Z::RT];
 #pragma unroll
   for (int tr = 0; tr < Z::RT; ++tr) acc[tr] = f64x4{0.0, 0.0, 0.0, 0.0};
-  const double* g = G + k * kD + 16 * w + c16;  // wavefront w: columns 16 w .. 16 w + 15
-#pragma unroll 1
-  for (int s0 = 0; s0 < kD; s0 += 64) {
-    double b[16];
 #pragma unroll
-    for (int s = 0; s < 16; ++s) b[s] = g[(s0 + 4 * s) * kD];
+  for (int s = 0; s < 32; ++s)
 #pragma unroll
-    for (int s = 0; s < 16; ++s)
-#pragma unroll
-      for (int tr = 0; tr < Z::RT; ++tr)
-        acc[tr] = mfma_f64(X[(16 * tr + c16) * kLdx + s0 + 4 * s + k], b[s], acc[tr]);
-  }
+    for (int tr = 0; tr < Z::RT; ++tr)
+      acc[tr] = mfma_f64(X[(16 * tr + c16) * kLdx + 4 * s + k], g[s], acc[tr]);
 #pragma unroll
   for (int tr = 0; tr < Z::RT; ++tr)
 #pragma unroll
@@ -594,7 +599,7 @@ __device__ __forceinline__ void sums_of(const double* X, double* Ys, const doubl
       Ys[i * kLdx + j] = acc[tr][v];
       if (i < R) Sm[i * kD + j] = acc[tr][v];
     }
-  __syncthreads();
+  lds_barrier();
   for (int tile = w; tile < Z::RT * Z::RT; tile += 8) {
     const int tr = tile / Z::RT, tc = tile % Z::RT;
     const double* ya = Ys + (16 * tr + c16) * kLdx + k;
@@ -658,12 +663,7 @@ __global__ __launch_bounds__(kAlgThreads) void prefill_round_k_kernel(const PfSt
   const bool iskv = (int)blockIdx.x < a.BHkv;
   const size_t own = iskv ? a.BHq + blockIdx.x : blockIdx.x - a.BHkv;  // row of S, H, G
   f64x4 d[Z::TPW];
-  {
-    const double* H = a.H + own * R * R;
-    const double* S = a.S + own * R * kD;
-    load_tiles<R>(d, w, lane, [&](int i, int j) { return H[i * R + j]; },
-                  [&](int i, int j) { return S[i * kD + j]; });
-  }
+  load_tiles<R>(d, w, lane, a.H + own * R * R, a.S + own * R * kD, 1);
   solve_tiles<R>(d, Pl, Cl, w, lane);
   if (!iskv) {
     double* BQ = a.BQ + own * R * kD;
@@ -675,6 +675,7 @@ __global__ __launch_bounds__(kAlgThreads) void prefill_round_k_kernel(const PfSt
     return;
   }
   const int bkv = blockIdx.x, b = bkv / a.Hkv, kvh = bkv - b * a.Hkv, G = a.Hq / a.Hkv;
+  const size_t q0 = (size_t)b * a.Hq + (size_t)kvh * G;  // the group's query heads
   if (16 * Z::RT > R)
     for (int e = t; e < (16 * Z::RT - R) * kLdx; e += kAlgThreads) X[R * kLdx + e] = 0.0;
   {
@@ -684,30 +685,19 @@ __global__ __launch_bounds__(kAlgThreads) void prefill_round_k_kernel(const PfSt
       if (a.last) B_K[i * kD + j] = (float)x;
     });
   }
-  __syncthreads();
-  {
-    const size_t q0 = (size_t)b * a.Hq + (size_t)kvh * G;
-    const double* H = a.H + q0 * R * R;
-    const double* S = a.S + q0 * R * kD;
-    load_tiles<R>(d, w, lane,
-                  [&](int i, int j) { return H[i * R + j]; },
-                  [&](int i, int j) { return __builtin_fma(a.lam_pK, X[i * kLdx + j], S[i * kD + j]); });
-    for (int g = 1; g < G; ++g) {
-      f64x4 more[Z::TPW];
-      load_tiles<R>(more, w, lane, [&](int i, int j) { return H[(size_t)g * R * R + i * R + j]; },
-                    [&](int i, int j) { return S[(size_t)g * R * kD + i * kD + j]; });
-#pragma unroll
-      for (int u = 0; u < Z::TPW; ++u) d[u] += more[u];
-    }
-    // (padding rows of the system came in as G times the identity: any multiple will do)
-    add_gram<R>(d, X, a.lam_pK, w, lane);
-  }
-  __syncthreads();  // X has been read
+  lds_barrier();
+  // (the padding of the system comes in as the identity, to which padding of X adds nothing)
+  load_tiles<R>(d, w, lane, a.H + q0 * R * R, a.S + q0 * R * kD, G);
+  double gram[32];  // on its way during the second solve
+  load_gram(gram, a.G + own * kD * kD, w, lane);
+  add_rhs<R>(d, X, a.lam_pK, w, lane);
+  add_gram<R>(d, X, a.lam_pK, w, lane);
+  lds_barrier();  // X has been read
   solve_tiles<R>(d, Pl, Cl, w, lane);
   store_solution<R>(d, w, lane, [&](int i, int j, double x) { X[i * kLdx + j] = x; });
-  __syncthreads();
+  lds_barrier();
   if (a.last) pack_operand<R>(X, a.M + own * PfShape<R>::mpack_units, t);
-  sums_of<R>(X, Ys, a.G + own * kD * kD, a.S + own * R * kD, a.H + own * R * R, w, lane);
+  sums_of<R>(X, Ys, gram, a.S + own * R * kD, a.H + own * R * R, w, lane);
 }
 
 // Second half, a query head per workgroup: with the sums of the new A_K,
@@ -724,26 +714,25 @@ __global__ __launch_bounds__(kAlgThreads) void prefill_round_q_kernel(const PfSt
   const int bh = blockIdx.x, b = bh / a.Hq, kvh = (bh - b * a.Hq) / (a.Hq / a.Hkv);
   const size_t kv = a.BHq + (size_t)b * a.Hkv + kvh;
   const double* BQ = a.BQ + (size_t)bh * R * kD;
-#pragma unroll 4
-  for (int e = t; e < 16 * Z::RT * kD; e += kAlgThreads)
-    X[(e / kD) * kLdx + e % kD] = e < R * kD ? BQ[e] : 0.0;
   f64x4 d[Z::TPW];
-  {
-    const double* H = a.H + kv * R * R;
-    const double* S = a.S + kv * R * kD;
-    load_tiles<R>(d, w, lane, [&](int i, int j) { return H[i * R + j]; },
-                  [&](int i, int j) { return __builtin_fma(a.lam_pQ, BQ[i * kD + j], S[i * kD + j]); });
-  }
-  __syncthreads();
+  load_tiles<R>(d, w, lane, a.H + kv * R * R, a.S + kv * R * kD, 1);
+#pragma unroll 8
+  for (int e = t; e < R * kD; e += kAlgThreads) X[(e / kD) * kLdx + e % kD] = BQ[e];
+  if (16 * Z::RT > R)
+    for (int e = t; e < (16 * Z::RT - R) * kLdx; e += kAlgThreads) X[R * kLdx + e] = 0.0;
+  double gram[32];
+  if (!a.last) load_gram(gram, a.G + (size_t)bh * kD * kD, w, lane);
+  lds_barrier();
+  add_rhs<R>(d, X, a.lam_pQ, w, lane);
   add_gram<R>(d, X, a.lam_pQ, w, lane);
-  __syncthreads();  // X has been read
+  lds_barrier();  // X has been read
   solve_tiles<R>(d, Pl, Cl, w, lane);
   store_solution<R>(d, w, lane, [&](int i, int j, double x) { X[i * kLdx + j] = x; });
-  __syncthreads();
+  lds_barrier();
   if (a.last)
     pack_operand<R>(X, a.M + (size_t)bh * PfShape<R>::mpack_units, t);
   else
-    sums_of<R>(X, Ys, a.G + (size_t)bh * kD * kD, a.S + (size_t)bh * R * kD,
+    sums_of<R>(X, Ys, gram, a.S + (size_t)bh * R * kD,
                a.H + (size_t)bh * R * R, w, lane);
 }
 
@@ -869,7 +858,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_apply_kernel(
 
 // ------------------------------------------------------------------------------------------
 // Chunks of rows per head: the fewest workgroup rounds (one workgroup per CU) times the tiles
-// of a workgroup, a partial costing about as much as two tiles.  At most kPfSlots partials
+// of a workgroup, a partial costing about as much as four tiles.  At most kPfSlots partials
 // unless there are more heads than that.
 constexpr int kPfSlots = 1024;
 int reduce_chunks(int heads, int l, int TR) {
@@ -879,7 +868,7 @@ int reduce_chunks(int heads, int l, int TR) {
   long best_cost = 0;
   for (int n = 1; n <= most; ++n) {
     const int per = ceil_div(tiles, n);
-    const long cost = (long)ceil_div(heads * ceil_div(tiles, per), 256) * (per + 2);
+    const long cost = (long)ceil_div(heads * ceil_div(tiles, per), 256) * (per + 4);
     if (n == 1 || cost < best_cost) {
       best = n;
       best_cost = cost;
