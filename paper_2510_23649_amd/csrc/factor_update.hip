@@ -2,48 +2,34 @@
 // two gradient steps; Sec. 4.2 update rules for q_hat_t, k_hat_t, B_Q, B_K; App. A.2 optimal
 // step lengths).
 //
-// Two launches.
+// Three launches.
 //
-//  1. factor_gram_kernel: everything that is a sum over many rows.  For a list of rows a_i
-//     (r floats each) with weights u_i it produces  S = sum_i a_i^T a_i  (r x r)  and
-//     g = sum_i u_i a_i  (r).  Three kinds of jobs share the code:
-//       * Omega of a query head (the k rows selected at the previous step, read from their
-//         cache slots, and the w lite rows): a_i = row of A_K, u_i = q . K_i.  This gives
-//         A_Om^T A_Om and q K_Om^T A_Om.  The row list of a head is cut into chunks of at most
-//         144 rows, one workgroup each, so that batch-1 steps still use hundreds of CUs; K rows
-//         are read by 16 lanes each exactly as the attention kernel reads them;
-//       * B_Q of a query head, read column-wise: a_i = column i of B_Q, u_i = q_i, which
-//         gives B_Q B_Q^T and q B_Q^T;
-//       * B_K of a KV head with u = k_t: B_K B_K^T and k B_K^T.
-//     The chunk's rows are staged in LDS, then every thread owns r*r/256 entries of S and
-//     adds the rows' outer products to them; partial sums per chunk go to the
-//     workspace and are added up, in chunk order, by the second kernel: no atomics, the
-//     result does not depend on scheduling.
+//  1. factor_gram_kernel: the sums over the rows of Omega of a query head (the k rows selected at
+//     the previous step, read from their cache slots, and the w lite rows):  S = sum_i a_i^T a_i
+//     (r x r) and g = sum_i u_i a_i (r), a_i = row of A_K, u_i = q . K_i.  The row list of a head is
+//     cut into chunks of at most 144 rows, one workgroup each, so that batch-1 steps still use
+//     hundreds of CUs; K rows are read by 16 lanes each exactly as the attention kernel reads
+//     them.  Partial sums per chunk go to the workspace: no atomics, the result does not depend
+//     on scheduling.
+//  2. factor_inverse_kernel: P^-1 and N^-1 (what changes between rounds is a low-rank correction
+//     of these two), a workgroup per matrix.
+//  3. factor_rounds_kernel: the n_iter rounds and the line-search gradient steps on B_Q and B_K in
+//     place, a workgroup per (batch, KV head).
+// us at k = 2048, w = 64, 32 + 8 heads, r = 32: 8 + 10 + 13; at 8 x (28 + 4) heads, k = 1024, r = 64:
+// 38 + 28 + 31.  (Factorising in fp32 with a row per lane, P once and the k_hat system in every
+// round, all in one wavefront per head, launches 2 and 3 took 30 and 114 us.)  What is left is
+// latency: the loads at the start of each launch, a chain of r / 4 elimination steps (0.5 us each
+// at r = 32, 0.8 us at r = 64).
 //
-//  2. factor_solve_kernel: one workgroup per (batch, KV head), one wavefront per query
-//     head of the group.  The r x r systems (r <= 64) are solved inside a wavefront: lane i
-//     holds row i of the matrix in registers, a right-looking Cholesky factorisation takes
-//     column j from lane registers with v_readlane (all register indices are compile-time
-//     constants), the two triangular solves follow the same pattern, with one transpose of
-//     the factor through LDS in between.  Only what changes between rounds is factorised
-//     again: M_rq = P + lambda_d1 k_hat^T k_hat differs from the fixed
-//     P = B_Q B_Q^T + lambda_d2 A_Om^T A_Om by a rank-one term, so P is factorised once and
-//     each q_hat costs one pair of triangular solves (Sherman-Morrison); the k_hat system
-//     changes by a rank-G term and is factorised anew each round.  The alternating updates
-//     of q_hat (per query head) and k_hat (per KV head, summed over the group's heads)
-//     exchange q_hat through LDS; every wavefront solves the k_hat system redundantly, which
-//     is cheaper than a second exchange.  The same kernel then applies the two rank-one
-//     gradient steps to B_Q and B_K in place.
-//
-// All arithmetic is fp32 (App. B.1 runs these updates in fp32).
+// Sums over rows are fp32 (App. B.1 runs these updates in fp32), the rest fp64.
+#include "lrqk_alg64.h"
 #include "lrqk_device.h"
 #include "lrqk_internal.h"
-#include "lrqk_linalg.h"
 
 namespace lrqk {
 namespace {
 
-using namespace linalg;
+using namespace alg64;
 
 constexpr int kGramThreads = 256;
 constexpr int kGramBatch = 144;  // rows staged in LDS at a time (a multiple of 16)
@@ -59,12 +45,6 @@ __device__ __forceinline__ float row16_sum(float v) {
   v += fu_dpp<0x122>(v);  // row_ror:2
   v += fu_dpp<0x121>(v);  // row_ror:1
   return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-  v = row16_sum(v);
-  // the four 16-lane rows of the wavefront
-  const float a = __shfl(v, 0), b = __shfl(v, 16), c = __shfl(v, 32), e = __shfl(v, 48);
-  return (a + b) + (c + e);
 }
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
   return __uint_as_float((uint32_t)h << 16);
@@ -157,12 +137,7 @@ struct GramArgs {
   const int32_t* sel_idx_prev;   // [B,Hq,k]
   const int32_t* sel_slot_prev;  // [B,Hq,k]
   const float* q;                // [B,Hq,d]
-  const void* k_new;             // [B,Hkv,d]
-  const float* B_Q;              // [B,Hq,r,d]
-  const float* B_K;              // [B,Hkv,r,d]
   float* gram_om;                // [B*Hq][nchunk][r*r + r]
-  float* gram_q;                 // [B*Hq][r*r + r]
-  float* gram_k;                 // [B*Hkv][r*r + r]
   int Hq, Hkv, l, l_rows, k, w, C, nchunk, chunk_rows;
 };
 
@@ -183,17 +158,14 @@ __global__ __launch_bounds__(kGramThreads) void factor_gram_kernel(GramArgs a) {
   const int G = a.Hq / a.Hkv;
   const int kvh = h / G;
   const int bkv = b * a.Hkv + kvh;
-  if (job == a.nchunk + 1 && h != kvh * G) return;  // the B_K job runs once per KV head
 
   f32x16 sacc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) sacc[v] = 0.0f;
   float gpart = 0.0f;
 
-  float* out;
-  if (job < a.nchunk) {
-    // ---- a chunk of the rows of Omega --------------------------------------------------
-    out = a.gram_om + ((size_t)bh * a.nchunk + job) * (kEntries + R);
+  float* out = a.gram_om + ((size_t)bh * a.nchunk + job) * (kEntries + R);
+  {
     const int n_om = a.k + a.w;
     const int i_begin = job * a.chunk_rows;
     const int i_end = min(n_om, i_begin + a.chunk_rows);
@@ -271,41 +243,6 @@ __global__ __launch_bounds__(kGramThreads) void factor_gram_kernel(GramArgs a) {
       __syncthreads();
       gram_accumulate<R>(a_s, u_s, sacc, gpart, t);
     }
-  } else {
-    // ---- B_Q of this query head, or B_K of this KV head, read column by column ------------
-    const bool isq = job == a.nchunk;
-    out = isq ? a.gram_q + (size_t)bh * (kEntries + R) : a.gram_k + (size_t)bkv * (kEntries + R);
-    const float* __restrict__ Bm =
-        isq ? a.B_Q + (size_t)bh * R * kD : a.B_K + (size_t)bkv * R * kD;
-    for (int i0 = 0; i0 < kD; i0 += kGramBatch) {
-      __syncthreads();
-      if (t < kGramBatch) {
-        const int i = i0 + t;
-        float u = 0.0f;
-        if (i < kD)
-          u = isq ? a.q[(size_t)bh * kD + i]
-                  : kv_load<BF16>(static_cast<const char*>(a.k_new) + (size_t)bkv * ROWB, i);
-        u_s[t] = u;
-      }
-      // every load is issued before the first is waited for (addresses clamped, the values
-      // past the end zeroed)
-      constexpr int kBPieces = (kGramBatch * R + kGramThreads - 1) / kGramThreads;
-      float bv[kBPieces];
-#pragma unroll
-      for (int u = 0; u < kBPieces; ++u) {
-        const int idx = t + u * kGramThreads;
-        const int c = min(idx / kGramBatch, R - 1), ii = idx % kGramBatch;
-        bv[u] = Bm[(size_t)c * kD + min(i0 + ii, kD - 1)];
-        if (i0 + ii >= kD) bv[u] = 0.0f;
-      }
-#pragma unroll
-      for (int u = 0; u < kBPieces; ++u) {
-        const int idx = t + u * kGramThreads;
-        if (idx < kGramBatch * R) a_s[idx % kGramBatch * LDA + idx / kGramBatch] = bv[u];
-      }
-      __syncthreads();
-      gram_accumulate<R>(a_s, u_s, sacc, gpart, t);
-    }
   }
   // Register v of lane l of an accumulator holds element [8 (v / 4) + 4 (l / 32) + v % 4][l % 32]
   // of its block.
@@ -346,224 +283,397 @@ __global__ __launch_bounds__(kGramThreads) void factor_gram_kernel(GramArgs a) {
 
 struct SolveArgs {
   const float* gram_om;  // [B*Hq][nchunk][r*r + r]
-  const float* gram_q;   // [B*Hq][r*r + r]
-  const float* gram_k;   // [B*Hkv][r*r + r]
+  double* inv;           // [B*Hq + B*Hkv][r*r + r]: P^-1 and c of a query head, N^-1 and nb of a KV head
   const float* q;        // [B,Hq,d]
   const void* k_new;     // [B,Hkv,d]
   float* B_Q;            // [B,Hq,r,d]   updated in place
   float* B_K;            // [B,Hkv,r,d]  updated in place
   float* q_hat;          // [B,Hq,r]
   float* k_hat;          // [B,Hkv,r]
-  int Hq, Hkv, nchunk, n_iter;
+  int Hq, Hkv, BHq, nchunk, n_iter;
   float lam1, lam2;
 };
 
-// One exact line-search gradient step on 1/2 |x_hat B - x|^2 (App. A.2), by one wavefront:
-//   resid = x_hat B - x,  grad = x_hat^T resid,  eta = <resid, x_hat grad> / |x_hat grad|^2,
-//   B <- B - eta grad.  Lane i (< R) holds x_hat_i; x(j) returns element j of the target.
-template <int R, typename XF>
-__device__ __forceinline__ void line_search_step(float xh, float* __restrict__ Bm, XF x, int lane) {
-  const float xhz = lane < R ? xh : 0.0f;
-  const float nrm2 = wave_sum(xhz * xhz);
-  // this lane's two columns of the residual
-  float e0 = -x(lane), e1 = -x(lane + 64);
+// ---- 2. the inverses --------------------------------------------------------------------------
+// One workgroup of 8 wavefronts per matrix, all in fp64:
+//   query head:  P = B_Q B_Q^T + lambda_d2 A_Om^T A_Om,  c = q B_Q^T + lambda_d2 q K_Om^T A_Om
+//   KV head:     N = B_K B_K^T,                          nb = k B_K^T
+// The chunk partials of launch 1 are added in chunk order.  The matrix lies in 16 x 16 tiles in
+// the wavefronts' registers and is inverted in place by Gauss-Jordan elimination with 4 x 4 pivot
+// blocks, one MFMA per tile and step (lrqk_alg64.h).  Latency bound: r / 4 steps, each an exchange
+// through LDS, two reciprocals and the MFMAs.
+constexpr int kInvThreads = 512;
+constexpr int kLdb = kD + 2;  // LDS row stride: 16 rows x 2 columns fall on 32 different bank pairs
+template <int R>
+struct InvShape {
+  static constexpr int RT = (R + 15) / 16;                    // RT x RT tiles
+  static constexpr int TPW = RT * RT > 8 ? RT * RT / 8 : 1;   // tiles of a wavefront, one tile row
+  static constexpr int kX = 16 * RT * kLdb, kP = RT * 64, kC = 16 * RT * 4;
+  static constexpr size_t lds_bytes = ((size_t)kX + kD + 2 * (kP + kC)) * sizeof(double);
+};
+
+template <int R, bool BF16>
+__global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a) {
+  using Z = InvShape<R>;
+  constexpr int kEntries = R * R;
+  constexpr size_t ROWB = kD * (BF16 ? 2 : 4);
+  extern __shared__ __align__(16) double inv_lds[];
+  double* const X = inv_lds;            // [16 RT][kLdb]  B
+  double* const xs = X + Z::kX;         // [d]  q or k
+  double* const Pl = xs + kD;
+  double* const Cl = Pl + 2 * Z::kP;
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int m = blockIdx.x;
+  const bool isq = m < a.BHq;
+  const size_t head = isq ? m : m - a.BHq;
+  const float* __restrict__ Bm = (isq ? a.B_Q : a.B_K) + head * R * kD;
+  const float* __restrict__ part = a.gram_om + head * a.nchunk * (size_t)(kEntries + R);
+  const int tr = w * Z::TPW / Z::RT, tc0 = w * Z::TPW % Z::RT;
+  const bool own = tr < Z::RT;          // (r <= 32: the other wavefronts own no tile)
+  const int k = lane >> 4, c16 = lane & 15;
+
+  constexpr int NB4 = R * kD / 4, NB = (NB4 + kInvThreads - 1) / kInvThreads;
+  float4 bv[NB];
 #pragma unroll
-  for (int i = 0; i < R; ++i) {
-    const float xi = lane_value(xh, i);
-    e0 = __builtin_fmaf(xi, Bm[(size_t)i * kD + lane], e0);
-    e1 = __builtin_fmaf(xi, Bm[(size_t)i * kD + lane + 64], e1);
+  for (int j = 0; j < NB; ++j)
+    bv[j] = reinterpret_cast<const float4*>(Bm)[min(t + kInvThreads * j, NB4 - 1)];
+  double xv = 0.0;
+  if (t < kD)
+    xv = isq ? a.q[head * kD + t]
+             : kv_load<BF16>(static_cast<const char*>(a.k_new) + head * ROWB, t);
+  f64x4 d[Z::TPW];
+#pragma unroll
+  for (int u = 0; u < Z::TPW; ++u) d[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+  if (isq && own) {
+    constexpr int SB = 16 / Z::TPW;  // chunks whose loads are in flight together
+    for (int s0 = 0; s0 < a.nchunk; s0 += SB) {
+      float x[SB][Z::TPW][4];
+#pragma unroll
+      for (int sc = 0; sc < SB; ++sc)
+#pragma unroll
+        for (int u = 0; u < Z::TPW; ++u)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            x[sc][u][v] = part[(size_t)min(s0 + sc, a.nchunk - 1) * (kEntries + R) +
+                               min(16 * tr + 4 * v + k, R - 1) * R + min(16 * (tc0 + u) + c16, R - 1)];
+#pragma unroll
+      for (int sc = 0; sc < SB; ++sc)
+#pragma unroll
+        for (int u = 0; u < Z::TPW; ++u)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) d[u][v] += s0 + sc < a.nchunk ? (double)x[sc][u][v] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < Z::TPW; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) d[u][v] *= (double)a.lam2;
   }
-  // x_hat grad = |x_hat|^2 resid
-  const float v0 = nrm2 * e0, v1 = nrm2 * e1;
-  const float num = wave_sum(e0 * v0 + e1 * v1);
-  const float den = wave_sum(v0 * v0 + v1 * v1);
-  const float eta = den > 0.0f ? num / den : 0.0f;
+  if (t < kD) xs[t] = xv;
+  if (16 * Z::RT > R)
+    for (int e = t; e < (16 * Z::RT - R) * kLdb; e += kInvThreads) X[R * kLdb + e] = 0.0;
 #pragma unroll
-  for (int i = 0; i < R; ++i) {
-    const float s = eta * lane_value(xh, i);
-    Bm[(size_t)i * kD + lane] = __builtin_fmaf(-s, e0, Bm[(size_t)i * kD + lane]);
-    Bm[(size_t)i * kD + lane + 64] = __builtin_fmaf(-s, e1, Bm[(size_t)i * kD + lane + 64]);
+  for (int j = 0; j < NB; ++j) {
+    const int e = 4 * (t + kInvThreads * j);
+    if (e < R * kD) {
+      double* x = X + e / kD * kLdb + e % kD;
+      x[0] = bv[j].x; x[1] = bv[j].y; x[2] = bv[j].z; x[3] = bv[j].w;
+    }
+  }
+  lds_barrier();
+  // c (or nb): 8 lanes a row
+  double* const out = a.inv + (size_t)m * (kEntries + R);
+  {
+    const int row = t >> 3, part8 = t & 7;
+    double c = 0.0;
+    if (row < R) {
+      const double* x = X + row * kLdb + part8;
+#pragma unroll
+      for (int j = 0; j < kD; j += 8) c = __builtin_fma(x[j], xs[j + part8], c);
+      if (isq)
+        for (int s = part8; s < a.nchunk; s += 8)
+          c = __builtin_fma((double)a.lam2, (double)part[(size_t)s * (kEntries + R) + kEntries + row], c);
+    }
+    c += dpp_f64<0xB1>(c);   // quad_perm [1,0,3,2]
+    c += dpp_f64<0x4E>(c);   // quad_perm [2,3,0,1]
+    c += dpp_f64<0x141>(c);  // row_half_mirror
+    if (row < R && part8 == 0) out[kEntries + row] = c;
+  }
+  // += B B^T
+  if (own) {
+#pragma unroll
+    for (int u = 0; u < Z::TPW; ++u) {
+      const double* xa = X + (16 * tr + c16) * kLdb + k;
+      const double* xb = X + (16 * (tc0 + u) + c16) * kLdb + k;
+#pragma unroll 8
+      for (int s = 0; s < kD; s += 4) d[u] = mfma_f64(xa[s], xb[s], d[u]);
+      if (R % 16 != 0) {  // the padding is the identity
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int i = 16 * tr + 4 * v + k, j = 16 * (tc0 + u) + c16;
+          if (i >= R || j >= R) d[u][v] = i == j ? 1.0 : 0.0;
+        }
+      }
+    }
+  }
+  // in-place inversion: a step's pivot columns start again as columns of the identity
+#pragma unroll 1
+  for (int pt = 0; pt < Z::RT; ++pt) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int p0 = 16 * pt + 4 * q;
+      if (p0 >= R) break;
+      double* const P = Pl + (q & 1) * Z::kP;  // two copies in turn: one barrier a step
+      double* const C = Cl + (q & 1) * Z::kC;
+      if (own) {
+#pragma unroll
+        for (int u = 0; u < Z::TPW; ++u) {
+          const int tc = tc0 + u;
+          const bool pivot_col = tc == pt && (c16 >> 2) == q;
+          const double unit = k == (lane & 3) ? 1.0 : 0.0;
+          if (tr == pt) P[tc * 64 + lane] = pivot_col ? unit : d[u][q];
+          if (tc == pt) {
+            if (pivot_col) {
+#pragma unroll
+              for (int v = 0; v < 4; ++v) C[(16 * tr + 4 * v + k) * 4 + (lane & 3)] = d[u][v];
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              d[u][v] = pivot_col ? ((tr == pt && v == q) ? unit : 0.0) : d[u][v];
+          }
+        }
+      }
+      lds_barrier();
+      if (own) {
+        const double n = pivot_factor(C, p0, 16 * tr + c16, k);
+#pragma unroll
+        for (int u = 0; u < Z::TPW; ++u) d[u] = mfma_f64(n, P[(tc0 + u) * 64 + lane], d[u]);
+      }
+    }
+  }
+  if (own) {
+#pragma unroll
+    for (int u = 0; u < Z::TPW; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = 16 * tr + 4 * v + k, j = 16 * (tc0 + u) + c16;
+        if (i < R && j < R) out[i * R + j] = d[u][v];
+      }
   }
 }
 
-template <int R, bool BF16>
-__global__ __launch_bounds__(kMaxG * 64) void factor_solve_kernel(SolveArgs a) {
-  constexpr int kEntries = R * R;
-  constexpr size_t ROWB = kD * (BF16 ? 2 : 4);
-  extern __shared__ __align__(16) float lds[];
-  const int G = a.Hq / a.Hkv;
-  constexpr int NLD = R + 4;  // padded row of the LDS copy of N
-  // [G][R*(R+1)] transpose space | [R][NLD] N = B_K B_K^T | [G][R] q_hat exchange | [G] q.k
-  float* const lt = lds + (size_t)(threadIdx.x >> 6) * R * (R + 1);
-  float* const n_s = lds + ((size_t)G * R * (R + 1) + 3) / 4 * 4;
-  float* const qhat_s = n_s + R * NLD;
-  float* const qk_s = qhat_s + G * R;
+// ---- 3. the rounds ------------------------------------------------------------------------------
+// One workgroup per (batch, KV head), wavefront g < G per query head of the group; lane i holds
+// element i of a vector.  With P^-1 and N^-1 at hand a round is products of an r x r matrix with a
+// vector (the vector's elements as LDS broadcasts, the matrix symmetric: lane i reads column i):
+//   q_hat = m_lq M_rq^-1, M_rq = P + lambda_d1 k_hat^T k_hat a rank-one change of P:
+//     z = k_hat P^-1,  v = m_lq P^-1 = y0 + lambda_d1 (q.k) z  (y0 = c P^-1),
+//     q_hat = v - z * lambda_d1 (k_hat . v) / (1 + lambda_d1 (k_hat . z))
+//   k_hat = rhs M^-1, M = N + lambda_d1 Q^T Q (Q: the group's q_hat as rows) a rank-G change of N:
+//     W = Q N^-1,  u = rhs N^-1 = nb N^-1 + lambda_d1 sum_g (q_g.k) w_g,
+//     k_hat = u - lambda_d1 s W  with  (I + lambda_d1 W Q^T) s = Q u,
+//   a G x G system that every wavefront solves for itself, lane 8 a + b holding element (a, b).
+// fp64 throughout, so that the corrections lose nothing.
+// Then one gradient step on 1/2 |x_hat B - x|^2 for every B_Q of the group and B_K (App. A.2): with
+// e = x_hat B - x the gradient is x_hat^T e and x_hat times it |x_hat|^2 e, so the step length
+// <e, |x_hat|^2 e> / | |x_hat|^2 e |^2 is 1 / |x_hat|^2 and a column of B needs nothing from the
+// others: a thread per column.  (e = 0 or x_hat = 0: B stays.)
+constexpr int kRoundThreads = kMaxG * 64;
+template <int R>
+struct RoundShape {
+  static constexpr int LDV = R + 2;  // LDS row stride of the exchanged vectors: 8 rows, 8 bank groups
+  static constexpr size_t lds_bytes =
+      ((size_t)R * R + 3 * kMaxG * LDV + kMaxG + kMaxG + 1) * sizeof(double);
+};
 
-  const int bkv = blockIdx.x;
-  const int b = bkv / a.Hkv, kvh = bkv - b * a.Hkv;
-  const int g = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int bh = b * a.Hq + kvh * G + g;
+template <int R, bool BF16>
+__global__ __launch_bounds__(kRoundThreads) void factor_rounds_kernel(SolveArgs a) {
+  using Z = RoundShape<R>;
+  constexpr int kEntries = R * R, LDV = Z::LDV;
+  constexpr size_t ROWB = kD * (BF16 ? 2 : 4);
+  extern __shared__ __align__(16) double rnd_lds[];
+  double* const n_s = rnd_lds;                  // [r][r]  N^-1
+  double* const qh_s = n_s + kEntries;          // [8][LDV]  q_hat of the group
+  double* const wv_s = qh_s + kMaxG * LDV;      // [8][LDV]  q_hat N^-1
+  double* const vec_s = wv_s + kMaxG * LDV;     // [8][LDV]  one vector per wavefront
+  double* const qk_s = vec_s + kMaxG * LDV;     // [8]
+  double* const inv_norm_s = qk_s + kMaxG;      // [9]  1 / |x_hat|^2 of the group's q_hat, of k_hat
+  const int t = threadIdx.x, lane = t & 63, g = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int G = a.Hq / a.Hkv;
+  const int bkv = blockIdx.x, b = bkv / a.Hkv, kvh = bkv - b * a.Hkv;
+  const bool act = g < G;
+  const int bh = b * a.Hq + kvh * G + (act ? g : 0);
   const bool row = lane < R;
   const int li = row ? lane : 0;  // keeps the loads of idle lanes in bounds
+  const double* __restrict__ inv_q = a.inv + (size_t)bh * (kEntries + R);
+  const double* __restrict__ inv_k = a.inv + (size_t)(a.BHq + bkv) * (kEntries + R);
   const float* qp = a.q + (size_t)bh * kD;
   const char* kp = static_cast<const char*>(a.k_new) + (size_t)bkv * ROWB;
-  const float qk_part = qp[lane] * kv_load<BF16>(kp, lane) +
-                        qp[lane + 64] * kv_load<BF16>(kp, lane + 64);
-  // P = B_Q B_Q^T + lambda_d2 A_Om^T A_Om,  cvec = q B_Q^T + lambda_d2 q K_Om^T A_Om;
-  // N = B_K B_K^T,  nb = k B_K^T.  The chunk partials are added in chunk order.  They are
-  // read with consecutive lanes on consecutive 16-byte pieces and turned into "lane = row"
-  // through LDS.
-  float p[R], pt[R], m[R];
-  float cvec, nb;
+
+  double pinv[R];
+#pragma unroll
+  for (int c = 0; c < R; ++c) pinv[c] = inv_q[c * R + li];
+  const double cvec = inv_q[kEntries + li], nb = inv_k[kEntries + li];
+  for (int e = t; e < kEntries / 2; e += kRoundThreads)
+    reinterpret_cast<double2*>(n_s)[e] = reinterpret_cast<const double2*>(inv_k)[e];
+  for (int e = t; e < 2 * kMaxG * LDV; e += kRoundThreads) qh_s[e] = 0.0;  // and wv_s
+  const double qk = wave_sum_f64((double)qp[lane] * kv_load<BF16>(kp, lane) +
+                                 (double)qp[lane + 64] * kv_load<BF16>(kp, lane + 64));
+  if (lane == 0) qk_s[g] = act ? qk : 0.0;
+  double* const vec = vec_s + g * LDV;
+  const double lam1 = a.lam1;
+  // x M of the vector x that lane i holds element i of
+  auto put = [&](double x) {
+    __builtin_amdgcn_wave_barrier();
+    if (row) vec[lane] = x;
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto times_pinv = [&](double x) {
+    put(x);
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int c = 0; c < R; c += 2) {
+      const double2 v = *reinterpret_cast<const double2*>(vec + c);
+      s0 = __builtin_fma(pinv[c], v.x, s0);
+      s1 = __builtin_fma(pinv[c + 1], v.y, s1);
+    }
+    return row ? s0 + s1 : 0.0;
+  };
+  auto times_ninv = [&](double x) {
+    put(x);
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll 16
+    for (int c = 0; c < R; c += 2) {
+      const double2 v = *reinterpret_cast<const double2*>(vec + c);
+      s0 = __builtin_fma(n_s[c * R + li], v.x, s0);
+      s1 = __builtin_fma(n_s[(c + 1) * R + li], v.y, s1);
+    }
+    return row ? s0 + s1 : 0.0;
+  };
+  const double y0 = times_pinv(cvec);
+  __syncthreads();  // n_s, qk_s; qh_s and wv_s are zero
+  // k0 = nb N^-1, also the initial guess (lambda_d1 = 0): every wavefront an eighth of the sum
   {
-    constexpr int U = (kEntries / 4 + 63) / 64;  // 16-byte pieces of an r x r matrix per lane
-    const float* gq = a.gram_q + (size_t)bh * (kEntries + R);
-    const float* gk = a.gram_k + (size_t)bkv * (kEntries + R);
-    constexpr bool kHoist = U <= 4;  // large r: too many registers to hold them that long
-    float4 acc[U], vq[U], vk[U];
+    put(nb);
+    double s0 = 0.0;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      acc[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      const int e4 = lane + 64 * u;  // issued first: these loads overlap the first round below
-      const bool on = kHoist && e4 < kEntries / 4;
-      vq[u] = on ? reinterpret_cast<const float4*>(gq)[e4] : acc[u];
-      vk[u] = (on && g == 0) ? reinterpret_cast<const float4*>(gk)[e4] : acc[u];
-    }
-    const float cq = gq[kEntries + li];
-    nb = gk[kEntries + li];
-    float gsum = 0.0f;
-    // chunks whose loads are in flight together (the partials were written by the previous
-    // kernel and come from memory, so each round of loads costs a full memory latency)
-    constexpr int SB = U >= 16 ? 2 : (U >= 4 ? 8 : 16);
-    const float* go0 = a.gram_om + (size_t)bh * a.nchunk * (kEntries + R);
-    for (int s0 = 0; s0 < a.nchunk; s0 += SB) {
-      float4 v[SB][U];
-      float gv[SB];
-#pragma unroll
-      for (int j = 0; j < SB; ++j) {
-        const bool on = s0 + j < a.nchunk;
-        const float* go = go0 + (size_t)(on ? s0 + j : s0) * (kEntries + R);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int e4 = lane + 64 * u;
-          v[j][u] = (on && e4 < kEntries / 4) ? reinterpret_cast<const float4*>(go)[e4]
-                                              : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        gv[j] = on ? go[kEntries + li] : 0.0f;
-      }
-#pragma unroll
-      for (int j = 0; j < SB; ++j) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          acc[u].x += v[j][u].x; acc[u].y += v[j][u].y;
-          acc[u].z += v[j][u].z; acc[u].w += v[j][u].w;
-        }
-        gsum += gv[j];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int e4 = lane + 64 * u;
-      if (e4 < kEntries / 4) {
-        if (!kHoist) {
-          vq[u] = reinterpret_cast<const float4*>(gq)[e4];
-          if (g == 0) vk[u] = reinterpret_cast<const float4*>(gk)[e4];
-        }
-        const int e = 4 * e4, rr = e / R, cc = e % R;
-        lt[rr * (R + 1) + cc + 0] = __builtin_fmaf(a.lam2, acc[u].x, vq[u].x);
-        lt[rr * (R + 1) + cc + 1] = __builtin_fmaf(a.lam2, acc[u].y, vq[u].y);
-        lt[rr * (R + 1) + cc + 2] = __builtin_fmaf(a.lam2, acc[u].z, vq[u].z);
-        lt[rr * (R + 1) + cc + 3] = __builtin_fmaf(a.lam2, acc[u].w, vq[u].w);
-        if (g == 0) *reinterpret_cast<float4*>(&n_s[rr * NLD + cc]) = vk[u];
-      }
-    }
-    cvec = __builtin_fmaf(a.lam2, gsum, cq);
-    __syncthreads();  // n_s (and, within the wavefront, lt) is complete
-#pragma unroll
-    for (int c = 0; c < R; ++c) p[c] = lt[li * (R + 1) + c];
-#pragma unroll
-    for (int c4 = 0; c4 < R / 4; ++c4) {
-      const float4 vk = *reinterpret_cast<const float4*>(&n_s[li * NLD + 4 * c4]);
-      m[4 * c4 + 0] = vk.x; m[4 * c4 + 1] = vk.y; m[4 * c4 + 2] = vk.z; m[4 * c4 + 3] = vk.w;
-    }
+    for (int c = 0; c < R / 8; ++c)
+      s0 = __builtin_fma(n_s[(g * (R / 8) + c) * R + li], vec[g * (R / 8) + c], s0);
+    put(s0);
   }
-
-  // q . k of this query head
-  const float qk = wave_sum(qk_part);
-  if (lane == 0) qk_s[g] = qk;
-  // Factorise N (for the initial guess) and P (kept for every round) together.
-  float dN, dP;
-  chol_factor2<R>(m, p, dN, dP, lane);
-  // initial guess (lambda_d1 = 0): k_hat = k B_K^T (B_K B_K^T)^-1
-  float k_hat = tri_forward<R>(m, dN, nb, lane);
-  transpose_rows<R>(m, m, lt, lane);
-  k_hat = tri_backward<R>(m, dN, k_hat, lane);
-  // y0 = cvec P^-1
-  transpose_rows<R>(p, pt, lt, lane);
-  const float y0 = tri_backward<R>(pt, dP, tri_forward<R>(p, dP, cvec, lane), lane);
-  float q_hat = 0.0f;
+  lds_barrier();
+  double k0 = 0.0;
+#pragma unroll
+  for (int gg = 0; gg < kMaxG; ++gg) k0 += vec_s[gg * LDV + li];
+  if (!row) k0 = 0.0;
+  lds_barrier();
+  double k_hat = k0, q_hat = 0.0;
   for (int it = 0; it < a.n_iter; ++it) {
-    // q_hat = m_lq M_rq^-1 with M_rq = P + lambda_d1 k_hat^T k_hat a rank-one change of P:
-    //   z = k_hat P^-1,  v = m_lq P^-1 = y0 + lambda_d1 (q.k) z,
-    //   q_hat = v - z * lambda_d1 (k_hat . v) / (1 + lambda_d1 (k_hat . z))
-    const float z = tri_backward<R>(pt, dP, tri_forward<R>(p, dP, k_hat, lane), lane);
-    const float v = __builtin_fmaf(a.lam1 * qk, z, y0);
-    const float kv_ = wave_sum(row ? k_hat * v : 0.0f);
-    const float kz = wave_sum(row ? k_hat * z : 0.0f);
-    q_hat = __builtin_fmaf(-z, a.lam1 * kv_ / __builtin_fmaf(a.lam1, kz, 1.0f), v);
-    __syncthreads();  // the previous round's q_hat has been read by every wavefront
-    if (row) qhat_s[g * R + lane] = q_hat;
-    __syncthreads();
-    // k_hat = (k B_K^T + lambda_d1 sum_g (q_g.k) q_hat_g)
-    //         (B_K B_K^T + lambda_d1 sum_g q_hat_g^T q_hat_g)^-1
-    float rhs = nb;
-#pragma unroll
-    for (int c4 = 0; c4 < R / 4; ++c4) {
-      const float4 vk = *reinterpret_cast<const float4*>(&n_s[li * NLD + 4 * c4]);
-      m[4 * c4 + 0] = vk.x; m[4 * c4 + 1] = vk.y; m[4 * c4 + 2] = vk.z; m[4 * c4 + 3] = vk.w;
+    const double z = times_pinv(k_hat);
+    const double v = __builtin_fma(lam1 * qk, z, y0);
+    const double kv_ = wave_sum_f64(k_hat * v), kz = wave_sum_f64(k_hat * z);
+    q_hat = __builtin_fma(-z, lam1 * kv_ / __builtin_fma(lam1, kz, 1.0), v);
+    const double wv = times_ninv(q_hat);
+    if (it > 0) lds_barrier();  // the previous round's vectors have been read
+    if (act && row) {
+      qh_s[g * LDV + lane] = q_hat;
+      wv_s[g * LDV + lane] = wv;
     }
-    for (int gg = 0; gg < G; ++gg) {
-      const float qi = qhat_s[gg * R + li];
-      rhs = __builtin_fmaf(a.lam1 * qk_s[gg], qi, rhs);
+    lds_barrier();
+    double u = k0;
 #pragma unroll
-      for (int c = 0; c < R; ++c) m[c] = __builtin_fmaf(a.lam1 * qi, qhat_s[gg * R + c], m[c]);
+    for (int gg = 0; gg < kMaxG; ++gg)
+      u = __builtin_fma(lam1 * qk_s[gg], wv_s[gg * LDV + li], u);
+    if (!row) u = 0.0;
+    put(u);
+    const int ra = lane >> 3, cb = lane & 7;
+    double kab = 0.0, ta = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < R; c += 2) {
+      const double2 x = *reinterpret_cast<const double2*>(qh_s + ra * LDV + c);
+      const double2 y = *reinterpret_cast<const double2*>(wv_s + cb * LDV + c);
+      kab = __builtin_fma(x.x, y.x, __builtin_fma(x.y, y.y, kab));
     }
-    const float dM = chol_factor<R>(m, lane);
-    k_hat = tri_forward<R>(m, dM, rhs, lane);
-    transpose_rows<R>(m, m, lt, lane);
-    k_hat = tri_backward<R>(m, dM, k_hat, lane);
+#pragma unroll
+    for (int c = 0; c < R; c += 8) ta = __builtin_fma(qh_s[ra * LDV + c + cb], vec[c + cb], ta);
+    ta += dpp_f64<0xB1>(ta);
+    ta += dpp_f64<0x4E>(ta);
+    ta += dpp_f64<0x141>(ta);
+    kab = __builtin_fma(lam1, kab, ra == cb ? 1.0 : 0.0);
+    // Gauss-Jordan over lanes (rows and columns beyond G are those of the identity, with ta = 0)
+    for (int p = 0; p < G; ++p) {
+      const double ap = __shfl(kab, ra * 8 + p), pb = __shfl(kab, p * 8 + cb);
+      const double tp = __shfl(ta, p * 8), pp = lane_value_f64(kab, p * 9);
+      const double f = ra == p ? 0.0 : ap * recip(pp);
+      kab = __builtin_fma(-f, pb, kab);
+      ta = __builtin_fma(-f, tp, ta);
+    }
+    const double sa = ta * recip(__shfl(kab, ra * 9));
+    k_hat = u;
+#pragma unroll
+    for (int gg = 0; gg < kMaxG; ++gg)
+      k_hat = __builtin_fma(-lam1 * lane_value_f64(sa, 8 * gg), wv_s[gg * LDV + li], k_hat);
+    if (!row) k_hat = 0.0;
   }
-  if (row) a.q_hat[(size_t)bh * R + lane] = q_hat;
-  if (row && g == 0) a.k_hat[(size_t)bkv * R + lane] = k_hat;
+  if (act && row) a.q_hat[(size_t)bh * R + lane] = (float)q_hat;
+  if (g == 0 && row) a.k_hat[(size_t)bkv * R + lane] = (float)k_hat;
 
-  // gradient steps on B_Q (every wavefront its head) and B_K (the first wavefront)
-  line_search_step<R>(q_hat, a.B_Q + (size_t)bh * R * kD, [&](int j) { return qp[j]; }, lane);
-  if (g == 0)
-    line_search_step<R>(k_hat, a.B_K + (size_t)bkv * R * kD,
-                        [&](int j) { return kv_load<BF16>(kp, j); }, lane);
+  // gradient steps
+  const double nq = wave_sum_f64(q_hat * q_hat), nk = wave_sum_f64(k_hat * k_hat);
+  if (lane == 0) {
+    inv_norm_s[g] = nq > 0.0 ? 1.0 / nq : 0.0;
+    if (g == 0) inv_norm_s[kMaxG] = nk > 0.0 ? 1.0 / nk : 0.0;
+  }
+  if (g == 0) put(k_hat);  // vec_s[0]
+  lds_barrier();
+  for (int c = t; c < (G + 1) * kD; c += kRoundThreads) {
+    const int job = c / kD, col = c % kD;
+    const bool isq = job < G;
+    const size_t head = isq ? (size_t)b * a.Hq + (size_t)kvh * G + job : bkv;
+    float* Bm = (isq ? a.B_Q : a.B_K) + head * R * kD + col;
+    const double* xh = isq ? qh_s + job * LDV : vec_s;
+    double s0 = -(double)(isq ? a.q[head * kD + col] : kv_load<BF16>(kp, col)), s1 = 0.0;
+    // (the column stays in registers between the two uses up to r = 32; at r = 64 it would push
+    // P^-1 out of them: 35 us instead of 31)
+    constexpr int U = R <= 32 ? R : 16;
+    float bv[U];
+#pragma unroll 1
+    for (int i0 = 0; i0 < R; i0 += U) {
+#pragma unroll
+      for (int i = 0; i < U; ++i) bv[i] = Bm[(i0 + i) * kD];
+#pragma unroll
+      for (int i = 0; i < U; i += 2) {
+        s0 = __builtin_fma(xh[i0 + i], (double)bv[i], s0);
+        s1 = __builtin_fma(xh[i0 + i + 1], (double)bv[i + 1], s1);
+      }
+    }
+    const double step = (s0 + s1) * inv_norm_s[isq ? job : kMaxG];
+#pragma unroll 1
+    for (int i0 = 0; i0 < R; i0 += U) {
+      if (U < R) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) bv[i] = Bm[(i0 + i) * kD];
+      }
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+        Bm[(i0 + i) * kD] = (float)__builtin_fma(-xh[i0 + i], step, (double)bv[i]);
+    }
+  }
 }
 
 template <int R, bool BF16>
 hipError_t launch_update_r(const lrqk_shape& s, const GramArgs& ga, const SolveArgs& sa,
                            hipStream_t st) {
-  const int G = s.Hq / s.Hkv;
-  hipLaunchKernelGGL((factor_gram_kernel<R, BF16>), dim3(ga.nchunk + 2, s.B * s.Hq),
+  static std::atomic<uint64_t> inv{0}, rounds{0};  // devices on which the LDS ceilings are up
+  hipError_t e = raise_dynamic_lds_once(factor_inverse_kernel<R, BF16>, InvShape<R>::lds_bytes, inv);
+  if (e == hipSuccess)
+    e = raise_dynamic_lds_once(factor_rounds_kernel<R, BF16>, RoundShape<R>::lds_bytes, rounds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((factor_gram_kernel<R, BF16>), dim3(ga.nchunk, s.B * s.Hq),
                      dim3(kGramThreads), 0, st, ga);
-  const size_t lds =
-      (((size_t)G * R * (R + 1) + 3) / 4 * 4 + (size_t)R * (R + 4) + (size_t)G * R + G) *
-      sizeof(float);
-  if (lds > 64 * 1024) {  // above the default limit the kernel has to opt in, once
-    static bool raised = false;
-    if (!raised) {
-      const hipError_t e = hipFuncSetAttribute(
-          reinterpret_cast<const void*>(factor_solve_kernel<R, BF16>),
-          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      if (e != hipSuccess) return e;
-      raised = true;
-    }
-  }
-  hipLaunchKernelGGL((factor_solve_kernel<R, BF16>), dim3(s.B * s.Hkv), dim3(G * 64), lds, st,
-                     sa);
+  hipLaunchKernelGGL((factor_inverse_kernel<R, BF16>), dim3(s.B * (s.Hq + s.Hkv)),
+                     dim3(kInvThreads), InvShape<R>::lds_bytes, st, sa);
+  hipLaunchKernelGGL((factor_rounds_kernel<R, BF16>), dim3(s.B * s.Hkv), dim3(kRoundThreads),
+                     RoundShape<R>::lds_bytes, st, sa);
   return hipGetLastError();
 }
 
@@ -591,7 +701,8 @@ UpdateGeom update_geometry(const lrqk_shape& s) {
 size_t update_ws_bytes(const lrqk_shape& s) {
   const UpdateGeom g = update_geometry(s);
   const size_t BHq = (size_t)s.B * s.Hq, BHkv = (size_t)s.B * s.Hkv;
-  return round_up((BHq * g.nchunk + BHq + BHkv) * g.per_gram * sizeof(float), 256);
+  return round_up(BHq * g.nchunk * g.per_gram * sizeof(float), 256) +
+         round_up((BHq + BHkv) * g.per_gram * sizeof(double), 256);
 }
 
 hipError_t launch_factor_update(const lrqk_shape& s, const float* A_K, const void* cacheK,
@@ -604,16 +715,15 @@ hipError_t launch_factor_update(const lrqk_shape& s, const float* A_K, const voi
   GramArgs ga;
   ga.A_K = A_K; ga.cacheK = cacheK; ga.liteK = liteK;
   ga.sel_idx_prev = sel_idx_prev; ga.sel_slot_prev = sel_slot_prev;
-  ga.q = q; ga.k_new = k_new; ga.B_Q = B_Q; ga.B_K = B_K;
-  ga.gram_om = ws;
-  ga.gram_q = ws + BHq * g.nchunk * g.per_gram;
-  ga.gram_k = ga.gram_q + BHq * g.per_gram;
+  ga.q = q; ga.gram_om = ws;
   ga.Hq = s.Hq; ga.Hkv = s.Hkv; ga.l = s.l; ga.l_rows = row_cap(s); ga.k = s.k; ga.w = s.w; ga.C = s.C;
   ga.nchunk = g.nchunk; ga.chunk_rows = g.chunk_rows;
   SolveArgs sa;
-  sa.gram_om = ga.gram_om; sa.gram_q = ga.gram_q; sa.gram_k = ga.gram_k;
+  sa.gram_om = ga.gram_om;
+  sa.inv = reinterpret_cast<double*>(
+      reinterpret_cast<char*>(ws) + round_up(BHq * g.nchunk * g.per_gram * sizeof(float), 256));
   sa.q = q; sa.k_new = k_new; sa.B_Q = B_Q; sa.B_K = B_K; sa.q_hat = q_hat; sa.k_hat = k_hat;
-  sa.Hq = s.Hq; sa.Hkv = s.Hkv; sa.nchunk = g.nchunk; sa.n_iter = n_iter;
+  sa.Hq = s.Hq; sa.Hkv = s.Hkv; sa.BHq = (int)BHq; sa.nchunk = g.nchunk; sa.n_iter = n_iter;
   sa.lam1 = lam1; sa.lam2 = lam2;
   const bool bf16 = s.kv_dtype == LRQK_KV_BF16;
   switch (s.r) {

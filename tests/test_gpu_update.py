@@ -300,3 +300,12 @@ def run_alg2_growing(cfg, n_new, mode, lam1=1.0, lam2=1.0):
         f"fetched from the host store {new_fetched} times")
     plan.close()
     return new_selected, new_fetched
+
+
+@pytest.mark.parametrize("r", [8, 64])
+@pytest.mark.parametrize("G,Hkv", [(8, 1), (1, 3), (5, 1)])
+def test_update_group_sizes_at_the_smallest_and_largest_rank(r, G, Hkv):
+    """One wavefront per query head of a group and one matrix per head: G = 8 leaves no wavefront
+    without a head, r = 8 pads the 16 x 16 tiles of the systems, r = 64 fills all of them."""
+    say(f"update G={G} r={r}")
+    run_update_case(upd_cfg(Hq=G * Hkv, Hkv=Hkv, r=r), n_iter=3)
