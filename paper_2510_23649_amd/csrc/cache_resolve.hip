@@ -6,6 +6,9 @@
 // (Limitations); here it is one workgroup per (batch, query head), entirely in
 // LDS.  Replacement rule for C >= k slots: least recently selected, ties by lower
 // slot; the j-th miss in ascending position takes the j-th victim.
+// Usual sizes: cache_resolve_kernel, the resolution of the fused step (assign_victims: a histogram
+// of the slots' ages, victims ranked class by class).  Caches so large that its lists do not fit
+// the LDS: cache_resolve_sort_kernel,
 //   1. every selected token looks up slot_of: hits refresh last_used, misses get
 //      their rank by a prefix count in position order;
 //   2. the slots not used in this step are the victim candidates; their keys
@@ -14,6 +17,7 @@
 // All of it is integer work with a fixed order, so the result is deterministic.
 #include "lrqk_device.h"
 #include "lrqk_internal.h"
+#include "select_common.h"
 
 namespace lrqk {
 namespace {
@@ -27,8 +31,149 @@ __global__ __launch_bounds__(256) void fill_i32_kernel(int32_t* p, size_t n, int
   if (i < n) p[i] = v;
 }
 
+// LDS of cache_resolve_kernel: last_used, token_of [C]; miss positions, their output indices,
+// victims [k]; age histogram; the sort of the rare cases (8 bytes a slot).
+__host__ __device__ inline size_t round256(size_t x) { return (x + 255) / 256 * 256; }
+struct ResolveArena {
+  size_t st_b, k_b, hist, sort, total;
+};
+__host__ __device__ inline ResolveArena resolve_arena(int k, int C) {
+  ResolveArena a;
+  a.st_b = round256((size_t)C * 4);
+  a.k_b = round256((size_t)k * 4);
+  a.hist = 2 * a.st_b + 3 * a.k_b;
+  a.sort = a.hist + (size_t)kAgeBins * 4;
+  int Cpad = 2;
+  while (Cpad < C) Cpad <<= 1;
+  a.total = a.sort + (size_t)Cpad * 8;
+  return a;
+}
+constexpr size_t kResolveLdsLimit = 150 * 1024;
+
+// Thread t owns k / 1024 consecutive entries of the selection (at most 4) and C / 1024 consecutive
+// slots (at most SPT).  A chain of short phases: 6 us at k = 1000, C = 2000 (24 us with a sort of
+// every slot).
+template <int SPT>
+__global__ __launch_bounds__(kT) void cache_resolve_kernel(
+    const int32_t* __restrict__ sel_idx, int32_t step, int l, int lrows, int C, int k,
+    int32_t* __restrict__ slot_of, int32_t* __restrict__ token_of,
+    int32_t* __restrict__ last_used, int32_t* __restrict__ sel_slot, uint8_t* __restrict__ hit,
+    int32_t* __restrict__ miss_tok, int32_t* __restrict__ miss_slot,
+    int32_t* __restrict__ n_miss) {
+  constexpr int PER = kMaxK / kT;
+  extern __shared__ __align__(16) unsigned char res_lds[];
+  __shared__ uint32_t wave_tot[4 * 2 * kWaves];  // four areas of 32 words, used in rotation
+  __shared__ uint32_t sh_bad, sh_ncls, sh_clip;
+  __shared__ uint32_t cls_age[kMaxCls], cls_base[kMaxCls];
+  const int bh = blockIdx.x, t = threadIdx.x;
+  const ResolveArena az = resolve_arena(k, C);
+  int32_t* const lu_s = reinterpret_cast<int32_t*>(res_lds);
+  int32_t* const to_s = reinterpret_cast<int32_t*>(res_lds + az.st_b);
+  int32_t* const mt_s = reinterpret_cast<int32_t*>(res_lds + 2 * az.st_b);
+  int32_t* const mj_s = reinterpret_cast<int32_t*>(res_lds + 2 * az.st_b + az.k_b);
+  int32_t* const vsorted = reinterpret_cast<int32_t*>(res_lds + 2 * az.st_b + 2 * az.k_b);
+  uint32_t* const ahist = reinterpret_cast<uint32_t*>(res_lds + az.hist);
+  const int32_t* __restrict__ sel = sel_idx + (size_t)bh * k;
+  int32_t* so = slot_of + (size_t)bh * lrows;
+  int32_t* to = token_of + (size_t)bh * C;
+  int32_t* lu = last_used + (size_t)bh * C;
+  int32_t* ss = sel_slot + (size_t)bh * k;
+  uint8_t* __restrict__ ht = hit + (size_t)bh * k;
+  int32_t* __restrict__ mt = miss_tok + (size_t)bh * k;
+  int32_t* ms = miss_slot + (size_t)bh * k;
+
+  // every load that does not depend on another, then the slot_of look-ups; entries that do not
+  // exist read ones that do
+  const int per = (k + kT - 1) / kT, spt = (C + kT - 1) / kT;
+  const int j0 = t * per;
+  int32_t tok[PER], slot[PER], lu_r[SPT], to_r[SPT];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) tok[i] = sel[min(j0 + i, k - 1)];
+#pragma unroll
+  for (int u = 0; u < SPT; ++u) {
+    const int sl = min(u * kT + t, C - 1);
+    lu_r[u] = lu[sl];
+    to_r[u] = to[sl];
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) slot[i] = so[min(max(tok[i], 0), l - 1)];
+  for (int i = t; i < kAgeBins; i += kT) ahist[i] = 0u;
+  if (t == 0) {
+    sh_bad = 0u;
+    sh_ncls = 0u;
+    sh_clip = 0u;
+  }
+#pragma unroll
+  for (int u = 0; u < SPT; ++u)
+    if (u * kT + t < C) {
+      lu_s[u * kT + t] = lu_r[u];
+      to_s[u * kT + t] = to_r[u];
+    }
+  uint32_t nmiss = 0;
+  bool valid[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const bool on = i < per && j0 + i < k;
+    valid[i] = on && tok[i] >= 0 && tok[i] < l;
+    if (slot[i] >= C) slot[i] = -1;  // corrupt map entry: treat as absent
+    nmiss += (valid[i] && slot[i] < 0) ? 1u : 0u;
+  }
+  uint32_t tot;
+  uint32_t rank = scan1(nmiss, wave_tot + 2 * 2 * kWaves, &tot);  // (orders the LDS writes above)
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int j = j0 + i;
+    if (i >= per || j >= k) continue;
+    const bool is_hit = valid[i] && slot[i] >= 0;
+    ht[j] = is_hit ? 1 : 0;
+    if (is_hit) {
+      ss[j] = slot[i];
+      lu[slot[i]] = step;
+      lu_s[slot[i]] = step;  // used in this step: never a victim
+    } else if (valid[i]) {
+      mt[rank] = tok[i];
+      mt_s[rank] = tok[i];
+      mj_s[rank] = j;
+      ++rank;
+    } else {
+      atomicOr(&sh_bad, 1u);
+      ss[j] = -1;
+    }
+  }
+  lds_barrier();
+  const int nm = (int)tot;
+  if (nm > 0) {
+    VictimWork v;
+    v.lu_s = lu_s;
+    v.to_s = to_s;
+    v.mt_s = mt_s;
+    v.mj_s = mj_s;
+    v.vsorted = vsorted;
+    v.ahist = ahist;
+    v.cls_age = cls_age;
+    v.cls_base = cls_base;
+    v.sh_ncls = &sh_ncls;
+    v.sh_clip = &sh_clip;
+    v.sh_bad = &sh_bad;
+    v.scan_areas = wave_tot;
+    v.sort_area = res_lds + az.sort;
+    v.so = so;
+    v.to = to;
+    v.lu = lu;
+    v.ms = ms;
+    v.ss = ss;
+    v.step = step;
+    v.C = C;
+    v.l = l;
+    v.spt = spt;
+    assign_victims<SPT>(v, nm);
+  }
+  lds_barrier();
+  if (t == 0) n_miss[bh] = sh_bad ? -1 : nm;
+}
+
 // dynamic LDS: uint64 keys[Cpad]
-__global__ __launch_bounds__(kResThreads) void cache_resolve_kernel(
+__global__ __launch_bounds__(kResThreads) void cache_resolve_sort_kernel(
     const int32_t* __restrict__ sel_idx, int32_t step, int l, int lrows, int C, int Cpad, int k,
     int32_t* __restrict__ slot_of, int32_t* __restrict__ token_of,
     int32_t* __restrict__ last_used, int32_t* __restrict__ sel_slot, uint8_t* __restrict__ hit,
@@ -158,14 +303,29 @@ hipError_t launch_cache_resolve(const lrqk_shape& s, const int32_t* sel_idx, int
                                 int32_t* slot_of, int32_t* token_of, int32_t* last_used,
                                 int32_t* sel_slot, uint8_t* hit, int32_t* miss_tok,
                                 int32_t* miss_slot, int32_t* n_miss, hipStream_t st) {
+  const size_t lds = resolve_arena(s.k, s.C).total;
+  if (lds <= kResolveLdsLimit) {
+    auto run = [&](auto kernel, std::atomic<uint64_t>& raised) {
+      const hipError_t e = raise_dynamic_lds_once(kernel, kResolveLdsLimit, raised);
+      if (e != hipSuccess) return e;
+      LRQK_LAUNCH(kernel, dim3(s.B * s.Hq), dim3(kT), lds, st, sel_idx, step, s.l, row_cap(s),
+                  s.C, s.k, slot_of, token_of, last_used, sel_slot, hit, miss_tok, miss_slot,
+                  n_miss);
+      return hipGetLastError();
+    };
+    static std::atomic<uint64_t> raised2{0}, raised4{0}, raised8{0};
+    if (s.C <= 2 * kT) return run(cache_resolve_kernel<2>, raised2);
+    if (s.C <= 4 * kT) return run(cache_resolve_kernel<4>, raised4);
+    return run(cache_resolve_kernel<8>, raised8);
+  }
   const int Cpad = next_pow2(s.C < 2 ? 2 : s.C);
-  const size_t lds = (size_t)Cpad * sizeof(uint64_t);
-  if (lds > 48 * 1024) {  // large caches need the dynamic-LDS ceiling raised once
+  const size_t sort_lds = (size_t)Cpad * sizeof(uint64_t);
+  if (sort_lds > 48 * 1024) {  // large caches need the dynamic-LDS ceiling raised once
     static std::atomic<uint64_t> raised{0};
-    const hipError_t e = raise_dynamic_lds_once(cache_resolve_kernel, 64 * 1024, raised);
+    const hipError_t e = raise_dynamic_lds_once(cache_resolve_sort_kernel, 64 * 1024, raised);
     if (e != hipSuccess) return e;
   }
-  LRQK_LAUNCH(cache_resolve_kernel, dim3(s.B * s.Hq), dim3(kResThreads), lds, st, sel_idx,
+  LRQK_LAUNCH(cache_resolve_sort_kernel, dim3(s.B * s.Hq), dim3(kResThreads), sort_lds, st, sel_idx,
                      step, s.l, row_cap(s), s.C, Cpad, s.k, slot_of, token_of, last_used, sel_slot, hit,
                      miss_tok, miss_slot, n_miss);
   return hipGetLastError();

@@ -51,8 +51,6 @@ constexpr size_t kPackedLdsLimit = 150 * 1024;
 
 __host__ __device__ inline size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
-constexpr int kMaxCls = 16;   // victim age classes numbered by the fast resolution
-
 struct PackedArena {
   size_t st_b, k_b, fixed, x_b, total;
 };
@@ -71,54 +69,6 @@ __host__ __device__ inline PackedArena packed_arena(int k, int n, int C) {
   a.x_b = exact > sort_b ? exact : sort_b;
   a.total = a.fixed + a.x_b;
   return a;
-}
-
-// Workgroup barrier that orders LDS traffic only: the wavefront's LDS operations have
-// completed before it arrives, its global loads and stores stay in flight (a __syncthreads
-// would wait for those too, i.e. expose a memory round trip at every barrier).  Used where
-// the threads exchange data through LDS alone.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// Prefix sum over the 16 wave totals held in wt[0..16): returns the sum of the totals of the
-// wavefronts before this one, and the grand total.  Lanes 0..15 of every wavefront read one
-// total each and scan them with DPP row shifts (one LDS read instead of sixteen per thread).
-__device__ __forceinline__ uint32_t waves_before(const uint32_t* wt, uint32_t* total) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  uint32_t v = wt[lane & 15];
-  uint32_t incl = v;
-  incl += dpp_zero_fill<0x111, 0xf>(incl);  // row_shr:1
-  incl += dpp_zero_fill<0x112, 0xf>(incl);  // row_shr:2
-  incl += dpp_zero_fill<0x114, 0xf>(incl);  // row_shr:4
-  incl += dpp_zero_fill<0x118, 0xf>(incl);  // row_shr:8
-  *total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 15);
-  return (uint32_t)__builtin_amdgcn_readlane((int)(incl - v), wv);
-}
-
-// Exclusive prefix sum over the 1024 threads and the total, with ONE LDS-only barrier.
-// wt: 16 words of LDS that no thread may still be reading from an earlier scan: consecutive
-// scans take different areas (scan_area), and an area comes round again only after two
-// other barriers.
-__device__ __forceinline__ uint32_t scan1(uint32_t v, uint32_t* wt, uint32_t* total) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint32_t incl = wave_inclusive_scan(v);
-  if (lane == 63) wt[wv] = incl;
-  lds_barrier();
-  return waves_before(wt, total) + incl - v;
-}
-// The same for two values at once.  wt: 32 words of LDS, as above.
-__device__ __forceinline__ void scan2(uint32_t v0, uint32_t v1, uint32_t* wt, uint32_t* ex0,
-                                      uint32_t* ex1, uint32_t* tot0, uint32_t* tot1) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint32_t i0 = wave_inclusive_scan(v0), i1 = wave_inclusive_scan(v1);
-  if (lane == 63) {
-    wt[wv] = i0;
-    wt[16 + wv] = i1;
-  }
-  lds_barrier();
-  *ex0 = waves_before(wt, tot0) + i0 - v0;
-  *ex1 = waves_before(wt + 16, tot1) + i1 - v1;
 }
 
 // Scan of a 2048-bin histogram from the top (thread t owns bins 2t, 2t+1) for two ranks at
@@ -154,155 +104,6 @@ __device__ __forceinline__ uint32_t find_two_from_top(const uint32_t* hist, uint
   return total;
 }
 
-// Victim slots for the nm missing positions of a head (Sec. 4.1 hit-and-miss cache; replacement
-// by least recent selection: victims in (last_used, slot) order, the j-th miss taking the j-th
-// victim), then eviction and installation in the maps.  Called by all 1024 threads.
-struct VictimWork {
-  // LDS
-  int32_t* lu_s;          // [C] last_used, already `step` where used in this step
-  const int32_t* to_s;    // [C] token_of before the step
-  const int32_t* mt_s;    // [nm] missing positions, ascending
-  const int32_t* mj_s;    // [nm] their indices in the outputs
-  int32_t* vsorted;       // [nm] receives the victims in rank order
-  uint32_t* ahist;        // [kAgeBins], zero
-  uint32_t* cls_age;      // [kMaxCls]
-  uint32_t* cls_base;     // [kMaxCls]
-  uint32_t* sh_ncls;      // zero
-  uint32_t* sh_clip;      // zero
-  uint32_t* sh_bad;
-  uint32_t* scan_areas;   // four areas of 32 words for the prefix counts
-  unsigned char* sort_area;  // 8 bytes per slot (C rounded up to a power of two): rare cases only
-  // this head's maps and outputs (global)
-  int32_t* so;
-  int32_t* to;
-  int32_t* lu;
-  int32_t* ms;
-  int32_t* ss;
-  int32_t step;
-  int C, l, spt;
-};
-template <int SPT>
-__device__ __forceinline__ void assign_victims(const VictimWork& v, int nm) {
-  const int t = threadIdx.x;
-  const int C = v.C, l = v.l, spt = v.spt;
-  const int32_t step = v.step;
-  auto scan_area = [&](int i) { return v.scan_areas + (i & 3) * 2 * kWaves; };
-  // ages of the slots not used in this step; thread t owns slots [s0, s1)
-  const int s0 = min(C, t * spt), s1 = min(C, s0 + spt);
-  uint32_t age[SPT];
-#pragma unroll
-  for (int u = 0; u < SPT; ++u) {
-    age[u] = 0xffffffffu;  // not eligible
-    if (u < spt && s0 + u < s1) {
-      const int32_t lv = v.lu_s[s0 + u];
-      if (lv != step) {
-        age[u] = min((uint32_t)(step - 1 - lv), (uint32_t)(kAgeBins - 1));
-        atomicAdd(&v.ahist[age[u]], 1u);
-      }
-    }
-  }
-  lds_barrier();
-  // scan the age classes from the oldest: eligible slots above each class, and the number of
-  // non-empty classes above it.  A non-empty class with fewer than nm slots above it holds
-  // victims; its number among those classes is its index in cls_age / cls_base.
-  uint32_t n_elig;
-  {
-    const uint32_t c0b = v.ahist[2 * t], c1b = v.ahist[2 * t + 1];
-    const uint32_t e0 = c0b ? 1u : 0u, e1 = c1b ? 1u : 0u;
-    uint32_t bc, be, ne;
-    scan2(c0b + c1b, e0 + e1, scan_area(3), &bc, &be, &n_elig, &ne);
-    const uint32_t above1 = n_elig - bc - c0b - c1b, ne_above1 = ne - be - e0 - e1;
-    const uint32_t above0 = above1 + c1b, ne_above0 = ne_above1 + e1;
-    if (c1b && above1 < (uint32_t)nm) {
-      if (ne_above1 < (uint32_t)kMaxCls) {
-        v.cls_age[ne_above1] = 2 * t + 1;
-        v.cls_base[ne_above1] = above1;
-      }
-      atomicMax(v.sh_ncls, ne_above1 + 1);
-      if (2 * t + 1 == kAgeBins - 1) *v.sh_clip = 1u;
-    }
-    if (c0b && above0 < (uint32_t)nm) {
-      if (ne_above0 < (uint32_t)kMaxCls) {
-        v.cls_age[ne_above0] = 2 * t;
-        v.cls_base[ne_above0] = above0;
-      }
-      atomicMax(v.sh_ncls, ne_above0 + 1);
-    }
-    lds_barrier();
-  }
-  const int ncls = (int)*v.sh_ncls;
-  // ages beyond the histogram's range share its last class, which then does not order them
-  const bool clipped = *v.sh_clip != 0u && step > kAgeBins - 1;
-  int nv = nm;  // number of victims found (< nm only if the caller reused `step`)
-  if (n_elig >= (uint32_t)nm && ncls <= kMaxCls && !clipped) {
-    // rank of a victim = slots in older classes + its index in its class, in slot order:
-    // four classes per prefix count (16-bit fields)
-    for (int c4 = 0; c4 < ncls; c4 += 4) {
-      uint32_t ca[4], cb[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        ca[c] = c4 + c < ncls ? v.cls_age[c4 + c] : 0xfffffffeu;
-        cb[c] = c4 + c < ncls ? v.cls_base[c4 + c] : 0u;
-      }
-      uint32_t lo = 0, hi = 0;
-#pragma unroll
-      for (int u = 0; u < SPT; ++u)
-        if (u < spt) {
-          lo += (age[u] == ca[0] ? 1u : 0u) + (age[u] == ca[1] ? 1u << 16 : 0u);
-          hi += (age[u] == ca[2] ? 1u : 0u) + (age[u] == ca[3] ? 1u << 16 : 0u);
-        }
-      uint32_t exlo, exhi, tl, th;
-      scan2(lo, hi, scan_area(c4 >> 2), &exlo, &exhi, &tl, &th);
-      uint32_t before[4] = {cb[0] + (exlo & 0xffffu), cb[1] + (exlo >> 16),
-                            cb[2] + (exhi & 0xffffu), cb[3] + (exhi >> 16)};
-#pragma unroll
-      for (int u = 0; u < SPT; ++u)
-        if (u < spt) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            if (age[u] == ca[c]) {
-              const uint32_t rk = before[c]++;
-              if (rk < (uint32_t)nm) v.vsorted[rk] = s0 + u;
-            }
-        }
-    }
-    lds_barrier();
-  } else {
-    // out of victims, too many classes, or ages beyond the histogram's range: sort every
-    // slot's (last_used, slot) key
-    uint64_t* const vlist = reinterpret_cast<uint64_t*>(v.sort_area);
-    int Cpad = 2;
-    while (Cpad < C) Cpad <<= 1;
-    for (int i = t; i < Cpad; i += kT) {
-      uint64_t key64 = ~0ull;
-      if (i < C && v.lu_s[i] != step)
-        key64 = (((uint64_t)(uint32_t)(v.lu_s[i] + 1)) << 32) | (uint32_t)i;
-      vlist[i] = key64;
-    }
-    bitonic_sort_lds(vlist, Cpad);
-    nv = (int)min((uint32_t)nm, n_elig);
-    for (int jj = t; jj < nv; jj += kT) v.vsorted[jj] = (int32_t)(uint32_t)vlist[jj];
-    __syncthreads();
-  }
-  for (int jj = t; jj < nm; jj += kT) {
-    if (jj >= nv) {  // ran out of victims (the caller reused `step`)
-      atomicOr(v.sh_bad, 1u);
-      v.ms[jj] = -1;
-      v.ss[v.mj_s[jj]] = -1;
-      continue;
-    }
-    const int32_t slot = v.vsorted[jj];
-    const int32_t tok = v.mt_s[jj];
-    const int32_t old = v.to_s[slot];
-    if (old >= 0 && old < l) v.so[old] = -1;
-    v.to[slot] = tok;
-    v.so[tok] = slot;
-    v.lu[slot] = step;
-    v.ms[jj] = slot;
-    v.ss[v.mj_s[jj]] = slot;
-  }
-}
-
 struct PackedArgs {
   const unsigned long long* bitmap;  // [BHq][words64]
   const float* cand_scores;          // [BHq][words64][kCandPerGroup]
@@ -330,7 +131,7 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
   __shared__ uint32_t wave_tot[4 * 2 * kWaves];  // four areas of 32 words, used in rotation
   auto scan_area = [&](int i) { return wave_tot + (i & 3) * 2 * kWaves; };
   __shared__ uint32_t res[4];
-  __shared__ uint32_t sh_ov, sh_small_n, sh_bad, sh_ncls, sh_clip;
+  __shared__ uint32_t sh_ov, sh_todo, sh_small_n, sh_bad, sh_ncls, sh_clip;
   __shared__ uint64_t sh_cut;
   __shared__ uint32_t cls_age[kMaxCls], cls_base[kMaxCls];
 
@@ -396,6 +197,7 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
   for (int i = t; i < 2048 + kAgeBins; i += kT) ahist[i] = 0u;  // ahist and hist0
   if (t == 0) {
     sh_ov = 0u;
+    sh_todo = 0u;
     sh_small_n = 0u;
     sh_bad = 0u;
     sh_ncls = 0u;
@@ -415,23 +217,29 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
   };
   // The first SLOTS candidates of a group stay in registers; the others (packed entries beyond
   // SLOTS, and candidates beyond the 8 packed ones, whose scores are computed again from A_K)
-  // are parked in LDS, in position order, in a run the thread reserves.
+  // are parked in LDS, in position order, in a run the thread reserves.  What has to be computed
+  // again is listed first and dealt out over all threads: a thread that did its own one after
+  // the other held everyone up (4 us of the 15 us kernel where a 16th of the context is selected).
   uint32_t key[GPT][SLOTS];
   unsigned long long bpos6[GPT];  // bit positions of the candidates in registers, 6 bits each
   auto bpos_of = [&](int g, int i) { return (int)((bpos6[g] >> (6 * i)) & 63ull); };
   int cnt[GPT];
-  int extra = 0;
+  int extra = 0, again = 0;
 #pragma unroll
   for (int g = 0; g < GPT; ++g) {
     cnt[g] = __popcll(mask[g]);
     extra += max(cnt[g] - SLOTS, 0);
+    again += max(cnt[g] - kCandPerGroup, 0);
   }
+  uint64_t* const todo = reinterpret_cast<uint64_t*>(X);  // (position, index in ov_key)
   int ov_base = 0;
   bool ov_ok = true;
   if (extra > 0) {
     ov_base = (int)atomicAdd(&sh_ov, (uint32_t)extra);
     ov_ok = ov_base + extra <= kOvCap;
   }
+  // (threads whose run fits have reserved at most kOvCap entries between them)
+  int td = again > 0 && ov_ok ? (int)atomicAdd(&sh_todo, (uint32_t)again) : 0;
   {
     int idx = ov_base;
 #pragma unroll
@@ -460,9 +268,7 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
         while (mb) {  // more candidates than the proxy pass packed
           const int bp = __builtin_ctzll(mb);
           mb &= mb - 1ull;
-          const uint32_t kk = order_key(proxy_score_of_row(Arow, qh, r, (t * GPT + g) * 64 + bp));
-          ov_key[idx++] = kk;
-          atomicAdd(&hist0[bin_of(kk)], 1u);
+          todo[td++] = ((uint64_t)(uint32_t)((t * GPT + g) * 64 + bp) << 32) | (uint32_t)idx++;
         }
       }
     }
@@ -512,6 +318,16 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
   float thr_next;
 
   lds_barrier();
+  const uint32_t n_todo = sh_todo;
+  if (n_todo > 0u) {  // uniform
+    for (uint32_t i = t; i < n_todo; i += kT) {
+      const uint64_t e = todo[i];
+      const uint32_t kk = order_key(proxy_score_of_row(Arow, qh, r, (int)(uint32_t)(e >> 32)));
+      ov_key[(uint32_t)e] = kk;
+      atomicAdd(&hist0[bin_of(kk)], 1u);
+    }
+    lds_barrier();
+  }
   uint32_t m = find_two_from_top(hist0, (uint32_t)k, rank_next, scan_area(0), res);
   uint32_t d0 = res[0], above0 = res[1], d_next = res[3];
   const bool fast = m >= (uint32_t)k && sh_ov <= (uint32_t)kOvCap;
@@ -643,7 +459,7 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
     uint32_t* const hist = reinterpret_cast<uint32_t*>(X);
     uint32_t* const bitmap_l = hist + kBins;
     uint32_t bin_next;
-    exact_select_from_scores<false>(sw, n, k, (l & 3) == 0, rank_next, hist, bitmap_l, nullptr,
+    exact_select_from_scores<false>(sw, n, k, rank_next, hist, bitmap_l, nullptr,
                                     wave_tot, res, &bin_next);
     // the selection as bits of the thread's groups; none of it is a candidate in registers
 #pragma unroll

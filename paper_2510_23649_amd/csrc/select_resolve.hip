@@ -94,7 +94,7 @@ __global__ __launch_bounds__(kT) void select_resolve_kernel(
   __shared__ uint32_t sh_nmiss, sh_bad;
 
   const int bh = blockIdx.x, t = threadIdx.x;
-  const int lane = t & 63, wv = t >> 6;
+  const int lane = t & 63;
   const ArenaSizes az = arena_sizes(k, n, C, RESOLVE);
   int32_t* const sel = reinterpret_cast<int32_t*>(lds_raw);
   unsigned char* const U = lds_raw + az.sel_b;
@@ -105,7 +105,6 @@ __global__ __launch_bounds__(kT) void select_resolve_kernel(
   uint32_t* const ckey = reinterpret_cast<uint32_t*>(clist + cap);
 
   const float* s = scores + (size_t)bh * l;
-  const bool vec_ok = (l & 3) == 0;
   const bool recompute = ext_bitmap != nullptr && A_K != nullptr;
   const float* __restrict__ Arow = nullptr;  // this head's A_K and q_hat (recompute only)
   const float* __restrict__ qh = nullptr;
@@ -129,14 +128,16 @@ __global__ __launch_bounds__(kT) void select_resolve_kernel(
     __syncthreads();
   } else {
   // ---- 1. sampled histogram -> b_lo ------------------------------------------------------
-  const int stride = (n >= 65536 && k >= 512) ? kSampleStride : 1;
+  // Long contexts are sampled, the first 4 positions of every 32 (evenly, however the large
+  // scores are clustered): 16384 and k >= 512 leave the estimate five standard deviations of
+  // margin, and a pass over all positions costs 5 us more at l = 50000.
+  const int stride = (n >= 16384 && k >= 512) ? kSampleStride : 1;
   for (int i = t; i < kBins; i += kT) hist[i] = 0u;
   __syncthreads();
   if (stride == 1) {
     for (int it0 = 0; it0 < n_iter; it0 += kBatch) {
       Raw4 raw[kBatch];
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) raw[u] = load_raw4(s, (it0 + u) * kIter + 4 * t, n, vec_ok);
+      load_batch(raw, s, it0, 1, n);
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         const Keys4 q = keys_of(raw[u], (it0 + u) * kIter + 4 * t, n);
@@ -146,18 +147,17 @@ __global__ __launch_bounds__(kT) void select_resolve_kernel(
       }
     }
   } else {
-    // wavefront wv samples its 256-position chunk of iterations it = (wv & 7) + 8 j
-    for (int it0 = (wv & 7); it0 < n_iter; it0 += kSampleStride * kBatch) {
+    const int pieces = n / (4 * kSampleStride);  // all of them whole
+    for (int p0 = 0; p0 < pieces; p0 += kT * kBatch) {
       Raw4 raw[kBatch];
 #pragma unroll
       for (int u = 0; u < kBatch; ++u)
-        raw[u] = load_raw4(s, (it0 + u * kSampleStride) * kIter + 4 * t, n, vec_ok);
+        raw[u] = load_raw4(s, min(p0 + u * kT + t, pieces - 1) * 4 * kSampleStride, n, true);
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
-        const Keys4 q = keys_of(raw[u], (it0 + u * kSampleStride) * kIter + 4 * t, n);
+        if (p0 + u * kT + t >= pieces) continue;
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-          if (q.ok[c]) atomicAdd(&hist[q.k[c] >> kBinShift], 1u);
+        for (int c = 0; c < 4; ++c) atomicAdd(&hist[order_key(raw[u].v[c]) >> kBinShift], 1u);
       }
     }
   }
@@ -172,8 +172,7 @@ __global__ __launch_bounds__(kT) void select_resolve_kernel(
   // ---- 2. bitmap of the positions with bin >= b_lo ----------------------------------------
   for (int it0 = 0; it0 < n_iter; it0 += kBatch) {
     Raw4 raw[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) raw[u] = load_raw4(s, (it0 + u) * kIter + 4 * t, n, vec_ok);
+    load_batch(raw, s, it0, 1, n);
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const int e = (it0 + u) * kIter + 4 * t;
@@ -294,7 +293,7 @@ __global__ __launch_bounds__(kT) void select_resolve_kernel(
       __syncthreads();
     }
     uint32_t bin_unused;
-    exact_select_from_scores<true>(s, n, k, vec_ok, (uint32_t)k, hist, bitmap, sel, wave_tot, res,
+    exact_select_from_scores<true>(s, n, k, (uint32_t)k, hist, bitmap, sel, wave_tot, res,
                              &bin_unused);
   }
   __syncthreads();

@@ -120,7 +120,43 @@ def test_select_topk_sampled_estimate_is_verified_not_trusted():
     assert np.array_equal(got, orc.select_topk(s, k, w))
 
 
+@pytest.mark.parametrize("l,w,k", [(16383, 0, 512), (16389, 5, 512), (16384, 0, 511),
+                                   (50001, 60, 1000), (4099, 3, 64), (3, 0, 2)])
+def test_select_topk_around_the_sampling_limit(l, w, k):
+    say(f"select_topk l={l} w={w} k={k}: odd row lengths, inputs built to mislead the 1-in-8 sample")
+    rng = np.random.default_rng(l)
+    sampled = np.arange(l) % 32 < 4
+    base = (rng.standard_normal(l) * 11.3).astype(np.float32)
+    s = np.stack([base, np.where(sampled, base - 200.0, base), np.where(sampled, base + 200.0, base),
+                  np.where(np.arange(l) < 2 * k, base + 50.0, base), np.round(base)])[None]
+    got = run_select(s.astype(np.float32), k, w)
+    assert np.array_equal(got, orc.select_topk(s.astype(np.float32), k, w))
+
+
 # ------------------------------------------------------------------------------- a3 + a4
+
+@pytest.mark.parametrize("k,C", [(1, 1), (1023, 1024), (1025, 2048), (2047, 2049), (2048, 4096),
+                                 (1024, 8192), (4096, 4097), (4096, 8192)])
+def test_resolve_sizes(k, C):
+    """Edges of the entries and slots per thread; (4096, 8192) is beyond the LDS of the usual
+    kernel and sorts."""
+    say(f"cache_resolve k={k} C={C}")
+    l, Hq, rng = 3 * k + 5000, 2, np.random.default_rng(k + C)
+    cfg = small_cfg(B=1, Hq=Hq, Hkv=1, l=l, r=8, k=k, w=0, C=C, n_heavy=1, pool_mult=1)
+    shp, sb, st = shape_of(cfg), StepBuffers(cfg), orc.CacheState(1, Hq, l, C)
+    maps = [torch.empty((1, Hq, n), dtype=torch.int32, device=DEV) for n in (l, C, C)]
+    L.lrqk_cache_init(shp, *maps)
+    pool = rng.permutation(l)[: 2 * k + 8]
+    for step in (0, 1, 2, 5000, 5001):     # 5000: ages beyond the victims' histogram
+        sel = np.stack([np.sort(rng.choice(pool, k, replace=False)) for _ in range(Hq)])[None]
+        sb.sel_idx.copy_(torch.from_numpy(sel.astype(np.int32)))
+        L.lrqk_cache_resolve(shp, sb.sel_idx, step, *maps, sb.sel_slot, sb.hit, sb.miss_tok,
+                             sb.miss_slot, sb.n_miss)
+        ref = orc.cache_resolve(sel.astype(np.int32), step, st)
+        compare_resolution(sb.to_np(), ref, f"step {step}")
+        for got, want in zip(maps, (st.slot_of, st.token_of, st.last_used)):
+            assert np.array_equal(got.cpu().numpy(), want), f"step {step}"
+
 
 @pytest.mark.parametrize("mode", ["staged", "direct"])
 @pytest.mark.parametrize("kvd,C", [("bf16", 320), ("bf16", 200), ("f32", 256)])
@@ -406,6 +442,8 @@ def test_group_fetch_alone_fills_the_same_caches_as_the_oracle():
     dict(B=1, Hq=6, Hkv=2, l=3000, r=32, k=100, w=10, C=150),       # G = 3: generic proxy kernel
     dict(B=1, Hq=2, Hkv=1, l=16384, r=32, k=4096, w=64, C=4096),    # a quarter of the context selected
     dict(B=1, Hq=2, Hkv=1, l=12000, r=32, k=1400, w=64, C=2048),    # about 10 candidates per group
+    dict(B=1, Hq=2, Hkv=1, l=12000, r=16, k=1400, w=64, C=2048),    # ... their scores computed again, short rows
+    dict(B=1, Hq=2, Hkv=1, l=6001, r=64, k=900, w=7, C=1000),       # ... and long ones
     dict(B=2, Hq=4, Hkv=4, l=70, r=16, k=20, w=3, C=25),            # a context of two 64-position groups
     dict(B=1, Hq=8, Hkv=2, l=64, r=32, k=64, w=0, C=64),            # one group, everything selected, no lite rows
 ])
