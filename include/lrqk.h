@@ -349,8 +349,8 @@ int lrqk_decode_step(lrqk_plan* plan, const lrqk_shape* shape, int32_t step,
  * rows l-w .. l-1, K rows in layer->liteK); q K_Om^T is the raw dot product.  Entries of the
  * previous selection with a position outside [0, l) or a slot outside [0, C) are left out.
  * The loop runs exactly n_iter rounds (the paper uses at most 2); there is no tolerance test.
- * Sums over rows are fp32 (App. B.1), the r x r systems fp64, results fp32.  Supported ranks:
- * r in {8, 16, 32, 64}.
+ * Sums over rows are fp32 (App. B.1), the r x r systems fp64 (fp32 at r <= 16), results fp32.
+ * Supported ranks: r in {8, 16, 32, 64}.
  *   layer          A_K, cacheK and liteK are read (device)
  *   sel_idx_prev, sel_slot_prev  device int32 [B,Hq,k], as written by the previous step
  *   q              device fp32 [B,Hq,d]

@@ -20,7 +20,8 @@ LIB = os.path.join(PKG, "liblrqk.so")
 
 SOURCES = ["api.hip", "proxy_scores.hip", "select_topk.hip", "cache_resolve.hip", "select_resolve.hip",
            "select_packed.hip",
-           "sparse_attend.hip", "fetch.hip", "factor_update.hip", "append_token.hip", "prefill.hip",
+           "sparse_attend.hip", "fetch.hip", "factor_update.hip", "factor_update_small.hip",
+           "append_token.hip", "prefill.hip",
            "instrument.hip", "noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -2,7 +2,7 @@
 // two gradient steps; Sec. 4.2 update rules for q_hat_t, k_hat_t, B_Q, B_K; App. A.2 optimal
 // step lengths).
 //
-// Three launches.
+// Three launches at r = 32 and 64 (r = 8 and 16: factor_update_small.hip, which says why).
 //
 //  1. factor_gram_kernel: the sums over the rows of Omega of a query head (the k rows selected at
 //     the previous step, read from their cache slots, and the w lite rows):  S = sum_i a_i^T a_i
@@ -15,7 +15,7 @@
 //     of these two), a workgroup per matrix.
 //  3. factor_rounds_kernel: the n_iter rounds and the line-search gradient steps on B_Q and B_K in
 //     place, a workgroup per (batch, KV head).
-// us at k = 2048, w = 64, 32 + 8 heads, r = 32: 8 + 10 + 13; at 8 x (28 + 4) heads, k = 1024, r = 64:
+// Times in us at k = 2048, w = 64, 32 + 8 heads, r = 32: 8 + 10 + 13; at 8 x (28 + 4) heads, k = 1024, r = 64:
 // 38 + 28 + 31.  (Factorising in fp32 with a row per lane, P once and the k_hat system in every
 // round, all in one wavefront per head, launches 2 and 3 took 30 and 114 us.)  What is left is
 // latency: the loads at the start of each launch, a chain of r / 4 elimination steps (0.5 us each
@@ -369,8 +369,6 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
       for (int v = 0; v < 4; ++v) d[u][v] *= (double)a.lam2;
   }
   if (t < kD) xs[t] = xv;
-  if (16 * Z::RT > R)
-    for (int e = t; e < (16 * Z::RT - R) * kLdb; e += kInvThreads) X[R * kLdb + e] = 0.0;
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     const int e = 4 * (t + kInvThreads * j);
@@ -406,13 +404,6 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
       const double* xb = X + (16 * (tc0 + u) + c16) * kLdb + k;
 #pragma unroll 8
       for (int s = 0; s < kD; s += 4) d[u] = mfma_f64(xa[s], xb[s], d[u]);
-      if (R % 16 != 0) {  // the padding is the identity
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int i = 16 * tr + 4 * v + k, j = 16 * (tc0 + u) + c16;
-          if (i >= R || j >= R) d[u][v] = i == j ? 1.0 : 0.0;
-        }
-      }
     }
   }
   // in-place inversion: a step's pivot columns start again as columns of the identity
@@ -699,6 +690,7 @@ UpdateGeom update_geometry(const lrqk_shape& s) {
 }
 
 size_t update_ws_bytes(const lrqk_shape& s) {
+  if (s.r <= 16) return update_small_ws_bytes(s);
   const UpdateGeom g = update_geometry(s);
   const size_t BHq = (size_t)s.B * s.Hq, BHkv = (size_t)s.B * s.Hkv;
   return round_up(BHq * g.nchunk * g.per_gram * sizeof(float), 256) +
@@ -710,6 +702,9 @@ hipError_t launch_factor_update(const lrqk_shape& s, const float* A_K, const voi
                                 const int32_t* sel_slot_prev, const float* q, const void* k_new,
                                 float* B_Q, float* B_K, float lam1, float lam2, int n_iter,
                                 float* q_hat, float* k_hat, float* ws, hipStream_t st) {
+  if (s.r <= 16)
+    return launch_factor_update_small(s, A_K, cacheK, liteK, sel_idx_prev, sel_slot_prev, q, k_new,
+                                      B_Q, B_K, lam1, lam2, n_iter, q_hat, k_hat, ws, st);
   const UpdateGeom g = update_geometry(s);
   const size_t BHq = (size_t)s.B * s.Hq;
   GramArgs ga;
@@ -727,8 +722,6 @@ hipError_t launch_factor_update(const lrqk_shape& s, const float* A_K, const voi
   sa.lam1 = lam1; sa.lam2 = lam2;
   const bool bf16 = s.kv_dtype == LRQK_KV_BF16;
   switch (s.r) {
-    case 8: return launch_update_dtype<8>(bf16, s, ga, sa, st);
-    case 16: return launch_update_dtype<16>(bf16, s, ga, sa, st);
     case 32: return launch_update_dtype<32>(bf16, s, ga, sa, st);
     case 64: return launch_update_dtype<64>(bf16, s, ga, sa, st);
     default: return hipErrorInvalidValue;

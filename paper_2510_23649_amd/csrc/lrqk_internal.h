@@ -210,6 +210,13 @@ hipError_t launch_factor_update(const lrqk_shape& s, const float* A_K, const voi
                                 const int32_t* sel_slot_prev, const float* q, const void* k_new,
                                 float* B_Q, float* B_K, float lam1, float lam2, int n_iter,
                                 float* q_hat, float* k_hat, float* ws, hipStream_t st);
+// r <= 16
+size_t update_small_ws_bytes(const lrqk_shape& s);
+hipError_t launch_factor_update_small(const lrqk_shape& s, const float* A_K, const void* cacheK,
+                                const void* liteK, const int32_t* sel_idx_prev,
+                                const int32_t* sel_slot_prev, const float* q, const void* k_new,
+                                float* B_Q, float* B_K, float lam1, float lam2, int n_iter,
+                                float* q_hat, float* k_hat, float* ws, hipStream_t st);
 
 // The new token's rows: A_K[., l, :], K/V store row l, lite ring row l % w, slot_of[., l] = -1.
 hipError_t launch_append_token(const lrqk_shape& s, float* A_K, void* K_host, void* V_host,
