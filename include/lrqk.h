@@ -400,8 +400,8 @@ int lrqk_append_token(const lrqk_shape* shape, const lrqk_layer* layer, const fl
  *   A_Q <- Q (K^T A_K + lambda_pQ B_Q^T)(A_K^T A_K + lambda_pQ B_Q B_Q^T)^-1   per query head
  * in this order (G = 1 gives the paper's rules).  B_Q, B_K are those computed at the top of
  * the last round.  Exactly n_iter rounds (the paper uses at most 2); no convergence test.
- * fp32 results (App. B.1): fp32 operands enter the matrix cores as exact sums of bf16 terms,
- * the r x d algebra is fp64.  Supported ranks: r in {8, 16, 32, 64}.
+ * fp32 results (App. B.1): fp32 operands enter the matrix cores as sums of three bf16 terms,
+ * d x d sums and the r x d algebra are fp64.  Supported ranks: r in {8, 16, 32, 64}.
  * Of `shape`, B, Hq, Hkv, d, l, r, kv_dtype and l_cap are used.
  *   Q     device kv_dtype [B,Hq,l,d]     read
  *   K     device kv_dtype [B,Hkv,l,d]    read

@@ -15,14 +15,15 @@
 //
 // (With a pass over Q and K in every update, X^T Y and X^T X from the fp32 matrix cores and the
 // solves in fp32, the whole took 2.35 ms at 32 + 8 heads, l = 131072, r = 32, bf16, two rounds;
-// now 0.91 ms.)
+// now 1.05 ms.)
 //
 // Precision.  The long products run on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16) with
-// every fp32 operand split into three bf16 terms (x = x0 + x1 + x2 exactly: 3 x 8 bits of
-// significand) and the products x_i y_j with i + j <= 2, fp32 accumulation; what is left out is
-// below 2^-26 of a product.  bf16 rows are one term.  The r x d algebra is fp64.  Distance from the
-// factors computed in 64 bits, |.|_2, worst of the four: 9e-6 (with fp32 throughout 2.2e-4) at l = 131072,
-// r = 32; 1.9e-5 (1.8e-4) at l = 4096, r = 16; 9e-6 (1.6e-4) at l = 30011, r = 64.
+// every fp32 operand split into three bf16 terms, x = x0 + x1 + x2, 8 bits of significand each, and
+// the products x_i y_j with i + j <= 2, accumulated in fp32: what is left out is at most about 2^-24
+// of a product, 2^-27 in the mean square.  bf16 rows are one term.  G is better than that (below).
+// The r x d algebra is fp64.  Distance from the factors computed in 64 bits, |.|_2, worst of the four,
+// on near-rank-r data, in brackets with sums over A_Q and A_K in fp32: 7e-6 (3e-4) at l = 131072,
+// r = 32; 2.4e-6 (1.2e-4) at l = 4096, r = 16; 5e-6 (1.5e-4) at l = 30011, r = 64.
 #include <type_traits>
 
 #include "lrqk_alg64.h"
@@ -37,9 +38,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // D(32x32) = A(32x16) B(16x32) + C; lane i + 32 h supplies A[i][8h .. 8h+7] and B[8h .. 8h+7][i];
 // register v of lane l holds D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32]
@@ -49,15 +48,25 @@ __device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 c) {
 __device__ __forceinline__ int mfma_row(int v, int lane) {
   return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
 }
-// x0, x1 as three bf16 pairs (packed in dwords) that add up to them exactly
-__device__ __forceinline__ void split3(float x0, float x1, uint32_t (&s)[3]) {
+__device__ __forceinline__ uint32_t pack_bf16(float x0, float x1) {
+  const f32x2 x = {x0, x1};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+}
+// x0, x1 as three bf16 pairs (packed in dwords) that add up to them, the first of them the multiples
+// of a grid (see prefill_reduce_kernel) that are nearest to them.  Without a grid the sum is exact.
+__device__ __forceinline__ void split3(float x0, float x1, uint32_t (&s)[3], float grid = 0.0f) {
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    const f32x2 x = {x0, x1};
-    s[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+    s[i] = i == 0 ? pack_bf16((x0 + grid) - grid, (x1 + grid) - grid) : pack_bf16(x0, x1);
     x0 -= __uint_as_float(s[i] << 16);
     x1 -= __uint_as_float(s[i] & 0xffff0000u);
   }
+}
+// the same for bf16 numbers, which two terms give exactly
+__device__ __forceinline__ void split2(float x0, float x1, float grid, uint32_t& hi, uint32_t& lo) {
+  const float g0 = (x0 + grid) - grid, g1 = (x1 + grid) - grid;
+  hi = pack_bf16(g0, g1);
+  lo = pack_bf16(x0 - g0, x1 - g1);
 }
 
 constexpr int kPfThreads = 256;
@@ -67,57 +76,72 @@ struct PfShape {
   static constexpr int RB = (R + 31) / 32;  // 32-wide blocks of the rank dimension
   static constexpr int RP = 32 * RB;        // rank padded to the MFMA block
   // 32 x 32 blocks of a chunk's partial, each as 16 registers x 64 lanes: 10 of G (the upper
-  // ones), 4 RB of S, HB of H, 4 of the second-order diagonal terms of G (fp32 rows)
-  static constexpr int HB = RB == 1 ? 4 : 8;
-  static constexpr int SB0 = 10, HB0 = 10 + 4 * RB, GB0 = HB0 + HB, PB = GB0 + 4;
+  // ones) in fp64, then 4 RB of S and HB of H in fp32
+  static constexpr int GB = 10, HB = RB == 1 ? 4 : 8;
+  static constexpr int HB0 = 4 * RB, FB = HB0 + HB;                         // fp32 blocks
+  static constexpr size_t part_bytes = (size_t)(GB * 8 + FB * 4) * 1024;
   static constexpr size_t mpack_units = (size_t)3 * RB * 8 * 64;  // 16-byte units of M per head
 };
 
 // ------------------------------------------------------------------------------------------
-// Reduce.  A workgroup (8 wavefronts) walks a chunk of rows in tiles.  A tile of Y is 256 bytes
-// a row and plane (bf16 rows: one plane, fp32 rows: the three terms) in LDS, a tile of A0 three
-// planes; the next tile's global loads are issued before the current tile's products.  The
-// products contract over the rows while the rows are what is contiguous in memory:
-// ds_read_b64_tr_b16 delivers four rows of a column to a lane, two of them make an operand.
-// A row is four units of 64 bytes (32 columns); unit u of row i is kept at u ^ (i % 4), so that
-// the four rows a transposing read takes together lie in different banks.
+// Reduce.  A workgroup (8 wavefronts) walks a chunk of rows in tiles of 64, two in LDS in turn.
+//
+// G has to be better than fp32.  H of the next X is M^T G M and where Y is strong in directions that
+// M suppresses, the rounding of G enters as |M|^2 |Y|^2 while H itself is only |X|^2 large (a sum over
+// X proper, which a pass over Y per update would give, loses |M| |Y| |X|).  So every element is split
+// on a grid of its column: y = y0 + y1 (+ y2 for fp32 rows), y0 the nearest multiple of a power of
+// two q, about 2^-5 of the column's typical size, y1 and y2 the rest.  Products y0 y0' are whole
+// multiples of q q' of some 12 bits, so that fp32 accumulators add up 512 rows of them WITHOUT
+// rounding; what is rounded are the products with y1, a hundred times smaller.  (Where a column's
+// sizes vary too much for that, the sums round as any fp32 sum: nothing depends on the grid but the
+// last bits.)  bf16 rows: y1 is exact, and y0 y1' + y1 y' with the whole y' makes three products;
+// fp32 rows: all but y2 y2'.  Every 512 rows the accumulators go to fp64.
+// One fp32 accumulation of y y' instead left the factors 2 to 20 times further from their 64-bit
+// values than sums over X in fp32, for keys with a mean of 30 sigma or queries and keys whose
+// spectra lie 1000 : 1 apart; now they are nearer (tests: test_prefill_strong_directions).
+//
+// The products contract over the rows while the rows are what is contiguous in memory: a thread
+// takes eight rows of two columns, which makes whole operands (8 rows of a column, 16 bytes).
 // Wavefront c < 4 owns the blocks (c, c), (c, c + 1) of G (indices modulo 4); wavefront 4 + c
 // column block c of S and, c < 2, block (c, c + 2) of G.  With A0 = a0 + a1 + a2,
 // H = D + U + U^T, D = a0^T a0 + a1^T a1, U = a0^T a1 + a0^T a2: r <= 32: wavefront 6 does D, 7 U;
 // r = 64: wavefronts 4, 5 the diagonal blocks of U, 6, 7 those of D and block (0, 1) of H.
 // a1^T a1 has accumulators of its own: its diagonal is a sum of squares 2^-18 the size of the
 // main term's, and each addend would round away against that sum (H 2e-6 too small after 11000
-// rows).  The same for the diagonal blocks of G with fp32 rows.
-// Bound by HBM: 2.0 GB in 0.40 ms = 5.0 TB/s at 32 + 8 heads, l = 131072, r = 32 (a large copy:
-// 5.1 TB/s); a SIMD needs 7 MFMAs of 32 cycles per 16 rows.  256 registers a wavefront hold one
-// workgroup on a CU: the LDS takes two tiles.
+// rows).
+// 2.0 GB in 0.58 ms at 32 + 8 heads, l = 131072, r = 32 (0.43 ms with y y' alone), 0.29 ms (0.22) at
+// 2 x (28 + 4) heads, l = 30011, r = 64: 48 MFMAs of 32 cycles per SIMD and tile are 0.26 ms at the
+// 1.9 GHz that this load runs at, everything but the loads 0.46 ms.  Operands read with
+// ds_read_b64_tr_b16 from row-major tiles, two tiles of loads in flight, or products reordered
+// measured the same.  256 registers a wavefront hold one workgroup on a CU: the LDS takes two tiles.
 constexpr int kRedThreads = 512;
-constexpr int kFlushRows = 512;
+constexpr int kBufferFlags = 0x00027000;  // raw 32-bit buffer
+constexpr int kFlushRows = 256;  // of S and H; twice as many of G
+constexpr int kScaleRows = 32;   // rows from which the grids of a head's columns are taken
 template <int R, int NS>
 struct PfReduce {
-  static constexpr int TR = NS > 1 ? 64 : R > 32 ? 96 : 128;  // rows per tile
-  static constexpr int kYPlane = TR * 256;                    // bytes
+  static constexpr int NP = 3;              // planes of Y: y0, y1 and y (bf16 rows) or y2
+  static constexpr int TR = 64;             // rows per tile
+  static constexpr int kRows = 2 * TR;      // ... and pass of the loop
+  static constexpr int kYPlane = TR * 256;  // bytes
   static constexpr int kAPlane = TR * 2 * PfShape<R>::RP;
-  static constexpr int kTile = NS * kYPlane + 3 * kAPlane;
-  static constexpr size_t lds_bytes = 2 * (size_t)kTile;      // two tiles in turn
+  static constexpr int kTile = NP * kYPlane + 3 * kAPlane;
+  static constexpr size_t lds_bytes = 2 * (size_t)kTile;
   static constexpr int kFlushTiles = kFlushRows / TR;
 };
 
 template <int R, int NS>
 __global__ __launch_bounds__(kRedThreads, 2) void prefill_reduce_kernel(
     const void* __restrict__ Q, const void* __restrict__ K, const float* __restrict__ A_Q,
-    const float* __restrict__ A_K, float* __restrict__ part, int BHq, int l, int lk, int nchunk,
-    int tiles_per_chunk) {
+    const float* __restrict__ A_K, void* __restrict__ part, int BHq, int l, int lk, int nchunk,
+    int units_per_chunk) {
   using S = PfShape<R>;
   using T = PfReduce<R, NS>;
-  constexpr int RB = S::RB, TR = T::TR;
-  constexpr int ROW16 = NS == 1 ? 16 : 32;      // 16-byte pieces per row of Y
-  constexpr int NY = TR * ROW16 / kRedThreads;  // ... per thread and tile
-  constexpr int NA4 = TR * R / 4;               // 16-byte pieces of a tile of A0
-  constexpr int NA = (NA4 + kRedThreads - 1) / kRedThreads;
+  constexpr int RB = S::RB, TR = T::TR, NP = T::NP;
+  constexpr int YB = NS == 1 ? 256 : 512;                           // bytes of a row of Y
+  constexpr int NA = (TR / 4 * R + kRedThreads - 1) / kRedThreads;  // pieces of A0 per thread
   extern __shared__ __align__(16) unsigned char pf_lds[];
-  unsigned char* Yl = pf_lds;  // this tile's
-  unsigned char* Al = pf_lds + NS * T::kYPlane;
+  __shared__ uint32_t exps[kD];
 
   const int bh = blockIdx.x / nchunk, chunk = blockIdx.x - bh * nchunk;  // Q heads, then K heads
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -125,211 +149,328 @@ __global__ __launch_bounds__(kRedThreads, 2) void prefill_reduce_kernel(
   const bool sums = w >= 4;    // S and what shares its wavefronts, or G
   const bool isq = bh < BHq;
   const size_t head = isq ? bh : bh - BHq;
-  const uint4* __restrict__ Yh =
-      static_cast<const uint4*>(isq ? Q : K) + head * (size_t)l * ROW16;
+  const char* __restrict__ Yh = static_cast<const char*>(isq ? Q : K) + head * (size_t)l * YB;
   const float* __restrict__ Ah = isq ? A_Q + head * (size_t)l * R : A_K + head * (size_t)lk * R;
-  const int row_begin = chunk * TR * tiles_per_chunk;
-  const int row_end = min(l, row_begin + TR * tiles_per_chunk);
+  const int row_begin = chunk * T::kRows * units_per_chunk;
+  const int row_end = min(l, row_begin + T::kRows * units_per_chunk);
 
   if (S::RP > R) {  // padding columns of A0 stay zero
-    for (int i = t; i < 2 * T::kTile / 16; i += kRedThreads)
-      reinterpret_cast<uint4*>(pf_lds)[i] = make_uint4(0u, 0u, 0u, 0u);
-    lds_barrier();
+    for (int i = t; i < 2 * 3 * T::kAPlane / 16; i += kRedThreads)
+      reinterpret_cast<uint4*>(pf_lds + NP * T::kYPlane +
+                               (i < 3 * T::kAPlane / 16 ? 0 : NP * T::kYPlane))[i] =
+          make_uint4(0u, 0u, 0u, 0u);
   }
 
-  // (addresses past the end are clamped and the values zeroed later: a load in a branch of its
-  // own would be waited for before the next is issued)
-  uint4 py[NY];
-  float4 pa[NA];
-  auto prefetch = [&](int row0) {
-#pragma unroll
-    for (int j = 0; j < NY; ++j) {
-      const int q = t + kRedThreads * j, row = min(row0 + q / ROW16, row_end - 1);
-      py[j] = Yh[(size_t)row * ROW16 + q % ROW16];
-    }
-#pragma unroll
-    for (int j = 0; j < NA; ++j) {
-      const int q = t + kRedThreads * j, row = min(row0 + q / (R / 4), row_end - 1);
-      pa[j] = reinterpret_cast<const float4*>(Ah + (size_t)row * R)[q % (R / 4)];
-    }
+  // On its way through registers: rows 8 w .. 8 w + 7 of the thread's two columns of Y, and rows
+  // 4 g .. 4 g + 3 of a column of A0, g = q / R, q = t + 512 j.  A tile is contiguous in memory; rows
+  // past the end of the chunk are outside the buffers that the loads go through and come as zeros.
+  struct Pieces {
+    uint32_t y[8][NS == 1 ? 1 : 2];
+    uint32_t a[NA][4];
   };
-  prefetch(row_begin);
+  Pieces next;
+  auto fetch = [&](int row0) {
+    Pieces& p = next;
+    const int rows = __builtin_amdgcn_readfirstlane(max(0, min(TR, row_end - row0)));
+    const auto yb = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(Yh + (size_t)row0 * YB), 0, rows * YB, kBufferFlags);
+    const auto ab = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(Ah + (size_t)row0 * R), 0, rows * R * 4, kBufferFlags);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if constexpr (NS == 1) {
+        p.y[i][0] = __builtin_amdgcn_raw_buffer_load_b32(yb, (8 * w + i) * YB + 4 * lane, 0, 0);
+      } else {
+        const uint2 v = __builtin_bit_cast(
+            uint2, __builtin_amdgcn_raw_buffer_load_b64(yb, (8 * w + i) * YB + 8 * lane, 0, 0));
+        p.y[i][0] = v.x;
+        p.y[i][NS == 1 ? 0 : 1] = v.y;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NA; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int q = t + kRedThreads * j;
+        p.a[j][i] = __builtin_amdgcn_raw_buffer_load_b32(ab, (q / R * 4 + i) * R * 4 + q % R * 4, 0, 0);
+      }
+  };
+  // The grids of this thread's columns: q = 2^-5 times the mean binary exponent of kScaleRows rows
+  // spread over the head.  (y + grid) - grid is y rounded to a multiple of q.
+  float grid[2];
+  {
+    uint32_t sc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const char* row = Yh + (size_t)((long)l * (4 * w + i) / kScaleRows) * YB;
+      if constexpr (NS == 1) {
+        const uint32_t v = reinterpret_cast<const uint32_t*>(row)[lane];
+        sc[i][0] = v << 16;
+        sc[i][1] = v;
+      } else {
+        const uint2 v = reinterpret_cast<const uint2*>(row)[lane];
+        sc[i][0] = v.x;
+        sc[i][1] = v.y;
+      }
+    }
+    fetch(row_begin);
+    if (t < kD) exps[t] = 0u;
+    lds_barrier();
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      uint32_t sum = 0u;  // of the exponents of numbers that are not zero, and 2^16 times how many
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t e = (sc[i][c] >> 23) & 255u;
+        sum += e > 0u ? 0x10000u + e : 0u;
+      }
+      atomicAdd(&exps[2 * lane + c], sum);
+    }
+    lds_barrier();
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int sum = exps[2 * lane + c] & 0xffff, n = exps[2 * lane + c] >> 16;
+      const int e = n > 0 ? (sum + n / 2) / n - 5 + 23 : 0;
+      grid[c] = n > 0 ? __uint_as_float((uint32_t)min(e, 254) << 23 | 0x400000u) : 0.0f;
+    }
+  }
 
-  // transposing reads: this lane's row within 4, its 8 bytes of a 64-byte unit, its row of 16
-  const int rl = (lane & 15) >> 2, off = 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
-  const int row_l = 8 * (lane >> 5) + rl;
-  auto tr_pair = [&](const unsigned char* p, int step) {  // p: first four rows; step: four rows
-    union { s16x4 h[2]; bf16x8 v; } o;
-    o.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
-    o.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + step));
-    return o.v;
+  // A tile in LDS, plane by plane: unit (8 rows r, column c) of 16 bytes is one lane's part of an
+  // operand, the columns of a block of 32 in the order 0, 2 .. 30, 1, 3 .. 31 (column_of), so that
+  // both the stores and the reads of a wavefront are contiguous.
+  const unsigned char* const yl = pf_lds + ((lane >> 5) * kD + (lane & 31)) * 16;
+  const unsigned char* const al = pf_lds + NP * T::kYPlane + ((lane >> 5) * S::RP + (lane & 31)) * 16;
+  auto y_op = [&](int half, int plane, int ks, int c) {
+    return *reinterpret_cast<const bf16x8*>(yl + half * T::kTile + plane * T::kYPlane +
+                                            ks * (2 * kD * 16) + c * 512);
   };
-  auto y_op = [&](int plane, int ks, int c) {
-    return tr_pair(Yl + plane * T::kYPlane + (ks * 16 + row_l) * 256 + ((c ^ rl) << 6) + off,
-                   4 * 256);
+  auto a_op = [&](int half, int plane, int ks, int rb) {
+    return *reinterpret_cast<const bf16x8*>(al + half * T::kTile + plane * T::kAPlane +
+                                            ks * (2 * S::RP * 16) + rb * 512);
   };
-  auto a_op = [&](int plane, int ks, int rb) {
-    const int unit = RB == 1 ? 0 : (rb ^ (rl >> 1)) << 6;
-    return tr_pair(Al + plane * T::kAPlane + (ks * 16 + row_l) * (2 * S::RP) + unit + off,
-                   4 * 2 * S::RP);
+  auto put_y = [&](int half, int c) {  // column c of the thread's two
+    const Pieces& p = next;
+    uint32_t s[3][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (NS == 1) {
+        const uint32_t v0 = p.y[2 * i][0], v1 = p.y[2 * i + 1][0];
+        s[2][i] = c == 0 ? (v0 & 0xffffu) | (v1 << 16) : (v0 >> 16) | (v1 & 0xffff0000u);
+        const float x0 = __uint_as_float(c == 0 ? v0 << 16 : v0 & 0xffff0000u);
+        const float x1 = __uint_as_float(c == 0 ? v1 << 16 : v1 & 0xffff0000u);
+        split2(x0, x1, grid[c], s[0][i], s[1][i]);
+      } else {
+        uint32_t x[3];
+        split3(__uint_as_float(p.y[2 * i][NS == 1 ? 0 : c]),
+               __uint_as_float(p.y[2 * i + 1][NS == 1 ? 0 : c]), x, grid[c]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) s[k][i] = x[k];
+      }
+    }
+    unsigned char* const to =
+        pf_lds + half * T::kTile + (w * kD + 32 * (lane >> 4) + (lane & 15) + 16 * c) * 16;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      *reinterpret_cast<uint4*>(to + k * T::kYPlane) = make_uint4(s[k][0], s[k][1], s[k][2], s[k][3]);
   };
+  auto put_a = [&](int half, int j) {
+    const Pieces& p = next;
+    const int q = t + kRedThreads * j, g = q / R;
+    if (TR / 4 * R % kRedThreads != 0 && q >= TR / 4 * R) return;
+    uint32_t s0[3], s1[3];
+    split3(__uint_as_float(p.a[j][0]), __uint_as_float(p.a[j][1]), s0);
+    split3(__uint_as_float(p.a[j][2]), __uint_as_float(p.a[j][3]), s1);
+    unsigned char* const to =
+        pf_lds + half * T::kTile + NP * T::kYPlane + ((g >> 1) * S::RP + q % R) * 16 + 8 * (g & 1);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      *reinterpret_cast<uint2*>(to + k * T::kAPlane) = make_uint2(s0[k], s1[k]);
+  };
+  put_y(0, 0);
+  put_y(0, 1);
+#pragma unroll
+  for (int j = 0; j < NA; ++j) put_a(0, j);
+  fetch(row_begin + TR);
+  lds_barrier();
 
   // One barrier per tile: a wavefront that stores a tile while others still read the one before
-  // writes the other half of the LDS.  The whole walk is compiled once for each role of a
+  // writes the other half of the LDS.  The walk is compiled once for each role of a
   // wavefront (0: G; 1, 2, 3: S with what column blocks 0 and 1, 2, 3 add to it): with the roles
   // as branches around the products the accumulators were copied at every step (0.76 ms instead
   // of 0.40 ms at l = 131072, r = 32, 32 + 8 heads).  Every role passes the same barriers.
   auto walk = [&](auto role) {
     constexpr int ROLE = decltype(role)::value;
-    // G wavefronts: (cb, cb), (cb, cb + 1), second-order part of (cb, cb); the others: S, then
-    // (cb, cb + 2) of G or parts of H.  acc2: see flush
-    constexpr int NACC = RB + 1 + RB;
-    f32x16 acc[NACC], acc2[RB + 1];
+    constexpr int NG = ROLE == 0 ? 2 : ROLE == 1 ? 1 : 0;   // blocks of G
+    constexpr int NACC = ROLE == 0 ? 0 : ROLE == 1 ? RB + RB - 1 : RB + 1 + RB;  // S, parts of H
+    constexpr int NFL = ROLE == 0 ? 0 : ROLE == 1 ? NACC : 2 * RB;               // flushed ones
+    double g[NG + 1][16];
+    f32x16 ghi[NG + 1], glo[NG + 1], acc[NACC + 1], acc2[NFL + 1];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
 #pragma unroll
+      for (int i = 0; i < NG; ++i) {
+        g[i][v] = 0.0;
+        ghi[i][v] = glo[i][v] = 0.0f;
+      }
+#pragma unroll
       for (int i = 0; i < NACC; ++i) acc[i][v] = 0.0f;
 #pragma unroll
-      for (int i = 0; i <= RB; ++i) acc2[i][v] = 0.0f;
+      for (int i = 0; i < NFL; ++i) acc2[i][v] = 0.0f;
     }
-    // What the accumulators hold goes to second ones every kFlushRows rows: rounding errors follow
-    // the size of the sum they are made in, and the second round's factors amplify those of S and G
-    // (without: A_Q twice as far off at l = 131072).
-    auto flush = [&]() {
+    // From time to time the accumulators of G go to fp64 ones, those of S, D and the off-diagonal
+    // products of H to second fp32 ones: rounding errors follow the size of the sum that they are
+    // made in, however many rows a chunk has, and the second round's factors amplify those of S.
+    // (The second-order parts of H and, at r <= 32, a0^T a2 may stay: they are 2^-17 of it.)
+    auto flush_sums = [&]() {
 #pragma unroll
-      for (int i = 0; i <= RB; ++i)
+      for (int i = 0; i < NFL; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           acc2[i][v] += acc[i][v];
           acc[i][v] = 0.0f;
         }
     };
+    auto flush_gram = [&]() {
+#pragma unroll
+      for (int i = 0; i < NG; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          g[i][v] += (double)ghi[i][v] + (double)glo[i][v];
+          ghi[i][v] = glo[i][v] = 0.0f;
+        }
+    };
 
-    int tile = 0;
-    for (int row0 = row_begin; row0 < row_end; row0 += TR, ++tile) {
-      Yl = pf_lds + (tile & 1) * T::kTile;
-      Al = Yl + NS * T::kYPlane;
+    // The operands of 16 rows, and their products.
+    struct Ops {
+      bf16x8 y[NP], z[NP], a[RB][3];
+    };
+    auto load = [&](int half, int ks) {
+      Ops o;
 #pragma unroll
-      for (int j = 0; j < NY; ++j) {
-        const int q = t + kRedThreads * j, row = q / ROW16, c = q % ROW16;
-        if (row0 + row >= row_end) py[j] = make_uint4(0u, 0u, 0u, 0u);
-        if (NS == 1) {
-          *reinterpret_cast<uint4*>(Yl + row * 256 + (((c >> 2) ^ (row & 3)) << 6) + 16 * (c & 3)) =
-              py[j];
-        } else {
-          uint32_t lo[3], hi[3];
-          split3(__uint_as_float(py[j].x), __uint_as_float(py[j].y), lo);
-          split3(__uint_as_float(py[j].z), __uint_as_float(py[j].w), hi);
+      for (int p = 0; p < NP; ++p) {
+        if (ROLE <= 1 || NS > 1 || p == 2) o.y[p] = y_op(half, p, ks, cb);
+        if (ROLE <= 1) o.z[p] = y_op(half, p, ks, (cb + (ROLE == 0 ? 1 : 2)) & 3);
+        if (ROLE > 0) {
 #pragma unroll
-          for (int p = 0; p < NS; ++p)
-            *reinterpret_cast<uint2*>(Yl + p * T::kYPlane + row * 256 +
-                                      (((c >> 3) ^ (row & 3)) << 6) + 8 * (c & 7)) =
-                make_uint2(lo[p], hi[p]);
+          for (int rb = 0; rb < RB; ++rb) o.a[rb][p] = a_op(half, p, ks, rb);
         }
       }
+      return o;
+    };
+    auto multiply = [&](const Ops& o) {
+      if constexpr (ROLE <= 1) {  // blocks of G: the leading products, and the small ones
+        if constexpr (ROLE == 0) ghi[0] = mfma_bf16(o.y[0], o.y[0], ghi[0]);
+        ghi[NG - 1] = mfma_bf16(o.y[0], o.z[0], ghi[NG - 1]);
 #pragma unroll
-      for (int j = 0; j < NA; ++j) {
-        const int q = t + kRedThreads * j, row = q / (R / 4), c = q % (R / 4);
-        if (NA4 % kRedThreads == 0 || q < NA4) {
-          if (row0 + row >= row_end) pa[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-          uint32_t lo[3], hi[3];
-          split3(pa[j].x, pa[j].y, lo);
-          split3(pa[j].z, pa[j].w, hi);
-          const int unit = RB == 1 ? 0 : ((c >> 3) ^ ((row >> 1) & 1)) << 6;
+        for (int i = 0; i < NP; ++i)
 #pragma unroll
-          for (int p = 0; p < 3; ++p)
-            *reinterpret_cast<uint2*>(Al + p * T::kAPlane + row * (2 * S::RP) + unit + 8 * (c & 7)) =
-                make_uint2(lo[p], hi[p]);
-        }
+          for (int j = 0; j < NP; ++j)
+            if (NS == 1 ? (i == 0 && j == 1) || (i == 1 && j == 2) : i + j > 0 && i + j < 4) {
+              if constexpr (ROLE == 0) glo[0] = mfma_bf16(o.y[i], o.y[j], glo[0]);
+              glo[NG - 1] = mfma_bf16(o.y[i], o.z[j], glo[NG - 1]);
+            }
       }
-      if (row0 + TR < row_end) prefetch(row0 + TR);
-      if (tile % T::kFlushTiles == 0) flush();
-      lds_barrier();
-
-#pragma unroll 2
-      for (int ks = 0; ks < TR / 16; ++ks) {
-        bf16x8 y0[NS];
+      if constexpr (ROLE > 0) {
 #pragma unroll
-        for (int p = 0; p < NS; ++p) y0[p] = y_op(p, ks, cb);
-        if constexpr (ROLE == 0) {
-          bf16x8 y1[NS];
+        for (int i = 0; i < 3; ++i)
 #pragma unroll
-          for (int p = 0; p < NS; ++p) y1[p] = y_op(p, ks, (cb + 1) & 3);
+          for (int j = 0; j < NP; ++j)
+            if (NS == 1 ? j == 2 : i + j < 3) {
 #pragma unroll
-          for (int i = 0; i < NS; ++i)
-#pragma unroll
-            for (int j = 0; i + j < 3 && j < NS; ++j) {
-              if (i == 1 && j == 1)
-                acc[2] = mfma_bf16(y0[i], y0[j], acc[2]);
-              else
-                acc[0] = mfma_bf16(y0[i], y0[j], acc[0]);
-              acc[1] = mfma_bf16(y0[i], y1[j], acc[1]);
+              for (int rb = 0; rb < RB; ++rb) acc[rb] = mfma_bf16(o.a[rb][i], o.y[j], acc[rb]);
             }
-        } else {
-          bf16x8 a[RB][3];
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int p = 0; p < 3; ++p) a[rb][p] = a_op(p, ks, rb);
-#pragma unroll
-          for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; i + j < 3 && j < NS; ++j)
-#pragma unroll
-              for (int rb = 0; rb < RB; ++rb) acc[rb] = mfma_bf16(a[rb][i], y0[j], acc[rb]);
-          f32x16& e0 = acc[RB];
-          f32x16& e1 = acc[RB + 1];
-          f32x16& e2 = acc[NACC - 1];
-          if constexpr (ROLE == 1) {
-            bf16x8 y2[NS];
-#pragma unroll
-            for (int p = 0; p < NS; ++p) y2[p] = y_op(p, ks, cb + 2);
-#pragma unroll
-            for (int i = 0; i < NS; ++i)
-#pragma unroll
-              for (int j = 0; i + j < 3 && j < NS; ++j) e0 = mfma_bf16(y0[i], y2[j], e0);
-            if constexpr (RB > 1) {  // U of diagonal block cb
-              const bf16x8 b0 = a_op(0, ks, cb);
-              e1 = mfma_bf16(b0, a_op(1, ks, cb), e1);
-              e1 = mfma_bf16(b0, a_op(2, ks, cb), e1);
-            }
-          } else if constexpr (ROLE == 2) {
-            e0 = mfma_bf16(a[0][0], a[0][0], e0);
-            e2 = mfma_bf16(a[0][1], a[0][1], e2);
-            if constexpr (RB > 1) e1 = mfma_bf16(a[0][0], a[RB - 1][0], e1);
-          } else if constexpr (RB == 1) {
-            e0 = mfma_bf16(a[0][0], a[0][1], e0);
-            e1 = mfma_bf16(a[0][0], a[0][2], e1);
-          } else {
-            constexpr int B1 = RB - 1;
-            e1 = mfma_bf16(a[0][0], a[B1][1], e1);
-            e0 = mfma_bf16(a[B1][0], a[B1][0], e0);
-            e1 = mfma_bf16(a[0][1], a[B1][0], e1);
-            e2 = mfma_bf16(a[B1][1], a[B1][1], e2);
-            e1 = mfma_bf16(a[0][0], a[B1][2], e1);
-            e1 = mfma_bf16(a[0][2], a[B1][0], e1);
-            e1 = mfma_bf16(a[0][1], a[B1][1], e1);
+        f32x16& e0 = acc[RB];
+        f32x16& e1 = acc[RB == 1 ? NACC - 1 : RB + 1];
+        f32x16& e2 = acc[NACC - 1];
+        if constexpr (ROLE == 1) {
+          if constexpr (RB > 1) {  // U of diagonal block cb
+            const auto& b = o.a[0];
+            const auto& c = o.a[RB - 1];
+            const bf16x8 b0 = cb == 0 ? b[0] : c[0];
+            e0 = mfma_bf16(b0, cb == 0 ? b[1] : c[1], e0);
+            e0 = mfma_bf16(b0, cb == 0 ? b[2] : c[2], e0);
           }
+        } else if constexpr (ROLE == 2) {
+          e0 = mfma_bf16(o.a[0][0], o.a[0][0], e0);
+          e2 = mfma_bf16(o.a[0][1], o.a[0][1], e2);
+          if constexpr (RB > 1) e1 = mfma_bf16(o.a[0][0], o.a[RB - 1][0], e1);
+        } else if constexpr (RB == 1) {
+          e0 = mfma_bf16(o.a[0][0], o.a[0][1], e0);
+          e1 = mfma_bf16(o.a[0][0], o.a[0][2], e1);
+        } else {
+          constexpr int B1 = RB - 1;
+          e1 = mfma_bf16(o.a[0][0], o.a[B1][1], e1);
+          e0 = mfma_bf16(o.a[B1][0], o.a[B1][0], e0);
+          e1 = mfma_bf16(o.a[0][1], o.a[B1][0], e1);
+          e2 = mfma_bf16(o.a[B1][1], o.a[B1][1], e2);
+          e1 = mfma_bf16(o.a[0][0], o.a[B1][2], e1);
+          e1 = mfma_bf16(o.a[0][2], o.a[B1][0], e1);
+          e1 = mfma_bf16(o.a[0][1], o.a[B1][1], e1);
         }
       }
+    };
+    // One tile's products.  The next tile goes to the other half of the LDS between them, and its
+    // registers take the loads of the one after.  r <= 32: a step's operands are read during the
+    // step before; the barrier stands before the last step, whose operands every wavefront has by
+    // then, so that the next tile's first ones are read behind it.
+    constexpr bool kAhead = RB == 1;
+    constexpr int kSteps = TR / 16;
+    Ops ops;
+    if (kAhead) ops = load(0, 0);
+    auto body = [&](int row0, int cur) {
+#pragma unroll
+      for (int ks = 0; ks < kSteps; ++ks) {
+        const bool last = ks == kSteps - 1;
+        if (kAhead && last) {
+          fetch(row0 + 2 * TR);
+          lds_barrier();
+        }
+        const Ops o = kAhead && !last ? load(cur, ks + 1) : kAhead ? load(cur ^ 1, 0) : load(cur, ks);
+        if (ks < 2) put_y(cur ^ 1, ks);
+        if (ks >= 2 && ks - 2 < NA) put_a(cur ^ 1, ks - 2);
+        multiply(kAhead ? ops : o);
+        if (kAhead) ops = o;
+      }
+      if (!kAhead) {
+        fetch(row0 + 2 * TR);
+        lds_barrier();
+      }
+    };
+    // (the second of a pass's two tiles is empty where the rows have run out)
+    for (int row0 = row_begin, tile = 0; row0 < row_end; row0 += 2 * TR, tile += 2) {
+      if (tile % T::kFlushTiles == 0) flush_sums();
+      if (tile % (2 * T::kFlushTiles) == 0) flush_gram();
+      body(row0, 0);
+      body(row0 + TR, 1);
     }
 
-    flush();
-    float* out = part + (size_t)blockIdx.x * (S::PB * 1024) + lane;
+    flush_sums();
+    flush_gram();
+    double* const gout =
+        reinterpret_cast<double*>(reinterpret_cast<char*>(part) + blockIdx.x * S::part_bytes) + lane;
+    float* const out = reinterpret_cast<float*>(gout - lane + S::GB * 1024) + lane;
+    auto put_g = [&](int block, const double (&x)[16]) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) gout[block * 1024 + v * 64] = x[v];
+    };
     auto put = [&](int block, const f32x16& x) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) out[block * 1024 + v * 64] = x[v];
     };
     if constexpr (ROLE == 0) {
-      put(cb, acc2[0]);
-      put(4 + cb, acc2[1]);
-      if constexpr (NS > 1) put(S::GB0 + cb, RB == 1 ? acc[NACC - 1] : acc2[RB]);
+      put_g(cb, g[0]);
+      put_g(4 + cb, g[1]);
     } else {
+      if constexpr (ROLE == 1) put_g(8 + cb, g[0]);
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) put(S::SB0 + 4 * rb + cb, acc2[rb]);
-      put(cb < 2 ? 8 + cb : S::HB0 + cb - 2, acc2[RB]);
-      if constexpr (RB > 1) put(S::HB0 + 2 + cb, acc[RB + 1]);
-      if (cb >= 2) put(S::GB0 - 4 + cb, acc[NACC - 1]);
+      for (int rb = 0; rb < RB; ++rb) put(4 * rb + cb, acc2[rb]);
+      if constexpr (ROLE == 1) {
+        if constexpr (RB > 1) put(S::HB0 + 2 + cb, acc2[RB]);
+      } else {
+        put(S::HB0 + cb - 2, acc2[RB]);
+        if constexpr (RB > 1) put(S::HB0 + 2 + cb, acc2[RB + 1]);
+        put(S::FB - 4 + cb, acc[NACC - 1]);
+      }
     }
   };
   if (!sums)
@@ -342,55 +483,65 @@ __global__ __launch_bounds__(kRedThreads, 2) void prefill_reduce_kernel(
     walk(std::integral_constant<int, 3>{});
 }
 
+// The column of Y that stands at place i of a block of 32.
+__device__ __forceinline__ int column_of(int i) { return 2 * (i & 15) + (i >> 4); }
+
 // Place of element (i, j) of a 32 x 32 block among its 16 x 64 accumulator values.
 __device__ __forceinline__ int acc_index(int i, int j) {
   return (4 * (i >> 3) + (i & 3)) * 64 + 32 * ((i >> 2) & 1) + j;
 }
 
 // The chunk partials of a head added in chunk order, in fp64: G [d][d], S [r][d], H [r][r].
-template <int R, int NS>
-__global__ __launch_bounds__(256) void prefill_sum_kernel(const float* __restrict__ part,
+template <int R>
+__global__ __launch_bounds__(256) void prefill_sum_kernel(const void* __restrict__ part,
                                                           double* __restrict__ G,
                                                           double* __restrict__ Sm,
                                                           double* __restrict__ H, int nchunk) {
   using S = PfShape<R>;
-  constexpr int kBlocks = (S::HB0 * 1024 + R * R + 255) / 256;  // workgroups per head
+  constexpr int kBlocks = ((S::GB + S::HB0) * 1024 + R * R + 255) / 256;  // workgroups per head
   const size_t head = blockIdx.x / kBlocks;
-  const int e = blockIdx.x % kBlocks * 256 + threadIdx.x;
-  const float* __restrict__ p = part + head * nchunk * (size_t)(S::PB * 1024);
-  auto total = [&](int at) {
+  int e = blockIdx.x % kBlocks * 256 + threadIdx.x;
+  const char* p = static_cast<const char*>(part) + head * nchunk * S::part_bytes;
+  auto total = [&](const auto* q) {  // q: the element in the first chunk's partial
     double acc = 0.0;
-    const float* q = p + at;
+    constexpr size_t stride = S::part_bytes / sizeof(*q);
     for (int c0 = 0; c0 < nchunk; c0 += 8) {  // (eight loads in flight, those past the end unused)
-      float v[8];
+      std::remove_cv_t<std::remove_reference_t<decltype(*q)>> v[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = q[(size_t)min(c0 + j, nchunk - 1) * (S::PB * 1024)];
+      for (int j = 0; j < 8; ++j) v[j] = q[(size_t)min(c0 + j, nchunk - 1) * stride];
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc += c0 + j < nchunk ? (double)v[j] : 0.0;
     }
     return acc;
   };
+  auto place = [](int e, int& row, int& col) {
+    row = mfma_row((e >> 6) & 15, e & 63);
+    col = column_of(e & 31);
+  };
+  int row, col;
+  if (e < S::GB * 1024) {
+    place(e, row, col);
+    row = column_of(row);
+    const int bi = (e >> 10) & 3, bj = (bi + (e >> 12)) & 3;
+    const double x = total(reinterpret_cast<const double*>(p) + e);
+    double* Gh = G + head * kD * kD;
+    Gh[(32 * bi + row) * kD + 32 * bj + col] = x;
+    if (bi != bj) Gh[(32 * bj + col) * kD + 32 * bi + row] = x;
+    return;
+  }
+  const float* f = reinterpret_cast<const float*>(p + (size_t)S::GB * 8 * 1024);
+  e -= S::GB * 1024;
   if (e < S::HB0 * 1024) {
-    const int block = e >> 10, v = (e >> 6) & 15, lane = e & 63;
-    const int row = mfma_row(v, lane), col = lane & 31;
-    if (block < S::SB0) {
-      const int bi = block & 3, bj = (bi + (block >> 2)) & 3;
-      double x = total(e);
-      if (NS > 1 && block < 4) x += total(e + S::GB0 * 1024);
-      double* Gh = G + head * kD * kD;
-      Gh[(32 * bi + row) * kD + 32 * bj + col] = x;
-      if (bi != bj) Gh[(32 * bj + col) * kD + 32 * bi + row] = x;
-    } else {
-      const int i = 32 * ((block - S::SB0) >> 2) + row, j = 32 * ((block - S::SB0) & 3) + col;
-      if (i < R) Sm[(head * R + i) * kD + j] = total(e);
-    }
+    place(e, row, col);
+    const int i = 32 * (e >> 12) + row, j = 32 * ((e >> 10) & 3) + col;
+    if (i < R) Sm[(head * R + i) * kD + j] = total(f + e);
     return;
   }
   const int h = e - S::HB0 * 1024;
   if (h >= R * R) return;
   int i = h / R, j = h % R;
   double x = 0.0;
-  auto add = [&](int block, int i, int j) { x += total((S::HB0 + block) * 1024 + acc_index(i, j)); };
+  auto add = [&](int block, int i, int j) { x += total(f + (S::HB0 + block) * 1024 + acc_index(i, j)); };
   if (S::RB == 1) {
     add(0, i, j);  // D, U, second-order parts of D and U
     add(2, i, j);
@@ -857,12 +1008,12 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_apply_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
-// Chunks of rows per head: the fewest workgroup rounds (one workgroup per CU) times the tiles
-// of a workgroup, a partial costing about as much as four tiles.  At most kPfSlots partials
+// Chunks of rows per head: the fewest workgroup rounds (one workgroup per CU) times the passes
+// of a workgroup, a partial costing about as much as four passes.  At most kPfSlots partials
 // unless there are more heads than that.
 constexpr int kPfSlots = 1024;
-int reduce_chunks(int heads, int l, int TR) {
-  const int tiles = ceil_div(l, TR);
+int reduce_chunks(int heads, int l, int rows) {
+  const int tiles = ceil_div(l, rows);
   const int most = heads >= kPfSlots ? 1 : min(tiles, kPfSlots / heads);
   int best = 1;
   long best_cost = 0;
@@ -878,7 +1029,7 @@ int reduce_chunks(int heads, int l, int TR) {
 }
 
 struct PrefillWs {
-  float* part;
+  void* part;
   double *G, *S, *H, *BQ;
   uint4* M;
   size_t bytes;
@@ -888,7 +1039,7 @@ PrefillWs carve_prefill(void* base, const lrqk_shape& s) {
   using S = PfShape<R>;
   const size_t BHq = (size_t)s.B * s.Hq, heads = BHq + (size_t)s.B * s.Hkv;
   // room for the partials of any shape that is no larger than this one
-  const size_t tiles = (size_t)ceil_div(s.l, 64);
+  const size_t tiles = (size_t)ceil_div(s.l, PfReduce<R, 1>::kRows);
   const size_t most = heads > kPfSlots ? heads : (size_t)kPfSlots;
   const size_t parts = heads * tiles < most ? heads * tiles : most;
   PrefillWs w;
@@ -898,7 +1049,7 @@ PrefillWs carve_prefill(void* base, const lrqk_shape& s) {
     off += round_up(n, 256);
     return static_cast<void*>(p);
   };
-  w.part = static_cast<float*>(take(parts * S::PB * 1024 * sizeof(float)));
+  w.part = take(parts * S::part_bytes);
   w.G = static_cast<double*>(take(heads * kD * kD * sizeof(double)));
   w.S = static_cast<double*>(take(heads * R * kD * sizeof(double)));
   w.H = static_cast<double*>(take(heads * R * R * sizeof(double)));
@@ -930,13 +1081,14 @@ hipError_t run_prefill(const lrqk_shape& s, const void* Q, const void* K, float*
   const int BHq = s.B * s.Hq, BHkv = s.B * s.Hkv, heads = BHq + BHkv, l = s.l, lk = row_cap(s);
   hipError_t e = PfKernels<R, NS>::allow();
   if (e != hipSuccess) return e;
-  constexpr int TR = PfReduce<R, NS>::TR;
-  const int per_chunk = ceil_div(ceil_div(l, TR), reduce_chunks(heads, l, TR));
-  const int nchunk = ceil_div(ceil_div(l, TR), per_chunk);
+  constexpr int kRows = PfReduce<R, NS>::kRows;
+  const int per_chunk = ceil_div(ceil_div(l, kRows), reduce_chunks(heads, l, kRows));
+  const int nchunk = ceil_div(ceil_div(l, kRows), per_chunk);
   hipLaunchKernelGGL((prefill_reduce_kernel<R, NS>), dim3(nchunk * heads), dim3(kRedThreads),
                      (PfReduce<R, NS>::lds_bytes), st, Q, K, A_Q, A_K, w.part, BHq, l, lk, nchunk,
                      per_chunk);
-  hipLaunchKernelGGL((prefill_sum_kernel<R, NS>), dim3(ceil_div(S::HB0 * 1024 + R * R, 256) * heads),
+  hipLaunchKernelGGL((prefill_sum_kernel<R>),
+                     dim3(ceil_div((S::GB + S::HB0) * 1024 + R * R, 256) * heads),
                      dim3(256), 0, st, w.part, w.G, w.S, w.H, nchunk);
   PfState a;
   a.G = w.G; a.S = w.S; a.H = w.H; a.BQ = w.BQ; a.M = w.M; a.B_Q = B_Q; a.B_K = B_K;

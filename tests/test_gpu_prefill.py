@@ -195,6 +195,78 @@ def test_prefill_eight_heads_a_group_and_many_chunks():
     run_prefill_case(pf_cfg(Hq=8, Hkv=1, l=20011, r=16, kv_dtype="f32"))
 
 
+def strong_directions(kind, size, l, r, G, dtype, seed):
+    """Queries and keys that are strong in different directions, none of them an axis.
+    mean: near-rank-r data, all keys shifted by `size` along a direction that the queries lack;
+    spread: full-rank data, singular values falling from 1 to 1 / size, the queries' in the
+    opposite order."""
+    gen = torch.Generator().manual_seed(seed)
+
+    def randn(*n):
+        return torch.randn(*n, generator=gen, dtype=torch.float64)
+
+    if kind == "mean":
+        u = randn(128)
+        u /= u.norm()
+
+        def near_low_rank():
+            return randn(l, r) @ randn(r, 128) / r ** 0.5 + 0.05 * randn(l, 128)
+
+        K = near_low_rank() + size * u
+        Q = [near_low_rank() for _ in range(G)]
+        Q = [x - (x @ u)[:, None] * u for x in Q]
+    else:
+        V = torch.linalg.qr(randn(128, 128))[0]
+        s = size ** (-torch.arange(128, dtype=torch.float64) / 127)
+        K = (randn(l, 128) * s) @ V.T
+        Q = [(randn(l, 128) * s.flip(0)) @ V.T for _ in range(G)]
+    return (torch.stack(Q)[None].to(dtype), K[None, None].to(dtype),
+            randn(1, G, l, r).float(), randn(1, 1, l, r).float())
+
+
+def distances(Q, K, A_Q0, A_K0, lam_q=1.0, lam_k=1.0, n_iter=2):
+    """|got - oracle| / |oracle| of the four factors, 2-norms."""
+    B, Hq, l, d = Q.shape
+    r = A_Q0.shape[-1]
+    shp = L.Shape.make(B=B, Hq=Hq, Hkv=K.shape[1], l=l, r=r, k=16, w=0, C_slots=16,
+                       kv_dtype=L.LRQK_KV_BF16 if Q.dtype == torch.bfloat16 else L.LRQK_KV_F32)
+    ref = pre.prefill_factorize(as_numpy(Q), as_numpy(K), as_numpy(A_Q0), as_numpy(A_K0), lam_q,
+                                lam_k, n_iter)
+    got = dict(A_Q=A_Q0.to(DEV), A_K=A_K0.to(DEV), B_Q=torch.empty((B, Hq, r, d), device=DEV),
+               B_K=torch.empty((B, K.shape[1], r, d), device=DEV))
+    L.lrqk_prefill_factorize(shp, Q.to(DEV), K.to(DEV), got["A_Q"], got["A_K"], got["B_Q"],
+                             got["B_K"], lam_q, lam_k, n_iter,
+                             workspace(L.lrqk_workspace_bytes(shp, L.LRQK_WS_PREFILL)))
+    torch.cuda.synchronize()
+    return {n: float(np.linalg.norm(x.cpu().numpy() - ref[n]) / np.linalg.norm(ref[n]))
+            for n, x in got.items()}
+
+
+# d x d sums have to be so good that the factors are no further off than with sums over A_Q and A_K
+# themselves, although their rounding enters with |M|^2 |K|^2 and not |M| |K| |A_K|.  The figures are
+# what kernels that make such sums in fp32 (a pass over Q and K per update) measure on this very
+# data; two correct computations differ by chance, so half as much again is allowed.  With Y^T Y
+# itself in fp32 the distances are up to 20 times these.
+@pytest.mark.parametrize("kind,size,l,r,dtype,A_Q,A_K,B_Q,B_K", [
+    ("mean", 10.0, 4096, 32, torch.bfloat16, 2.3e-5, 6.5e-6, 1.5e-4, 1.2e-4),
+    ("mean", 30.0, 4096, 32, torch.float32, 3.9e-5, 7.9e-6, 1.6e-4, 2.4e-4),
+    ("mean", 100.0, 4096, 32, torch.bfloat16, 5.7e-5, 2.1e-5, 3.0e-4, 5.0e-5),
+    ("mean", 100.0, 4096, 32, torch.float32, 5.4e-5, 3.1e-5, 3.5e-4, 6.7e-5),
+    ("mean", 30.0, 30011, 64, torch.bfloat16, 3.3e-5, 7.8e-6, 1.5e-4, 3.3e-4),
+    ("spread", 100.0, 4096, 32, torch.bfloat16, 9.3e-6, 9.2e-6, 2.5e-6, 1.8e-5),
+    ("spread", 1000.0, 4096, 16, torch.float32, 1.1e-5, 1.5e-4, 1.1e-6, 1.1e-4),
+    ("spread", 1000.0, 20000, 64, torch.bfloat16, 8.7e-5, 9.3e-5, 8.4e-6, 1.2e-4),
+    ("spread", 1000.0, 20000, 64, torch.float32, 9.2e-5, 1.0e-4, 7.9e-6, 1.3e-4),
+    ("spread", 10000.0, 65536, 32, torch.bfloat16, 1.0e-4, 4.6e-4, 1.3e-5, 3.8e-4)])
+def test_prefill_strong_directions(kind, size, l, r, dtype, A_Q, A_K, B_Q, B_K):
+    say(f"prefill {kind} {size:g}, l={l} r={r} {dtype}")
+    got = distances(*strong_directions(kind, size, l, r, 4, dtype, seed=l + r))
+    fp32_sums = dict(A_Q=A_Q, A_K=A_K, B_Q=B_Q, B_K=B_K)
+    say("   " + "  ".join(f"{n} {got[n]:.1e} ({fp32_sums[n]:.1e})" for n in got))
+    for n in got:
+        assert got[n] <= 1.5 * fp32_sums[n], n
+
+
 def test_prefill_rejects_bad_arguments():
     t = torch.zeros(1 << 16, device=DEV)
     shp = L.Shape.make(B=1, Hq=2, Hkv=1, l=512, r=12, k=16, w=0, C_slots=16)
