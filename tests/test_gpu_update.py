@@ -1,9 +1,11 @@
 """GPU parity of the decode-time factor update (lrqk_factor_update) against the CPU oracle
 (oracle/lrqk_update_oracle.py), through the C ABI.
 
-The update is fp32 linear algebra (Gram sums over the k + w rows of Omega, r x r Cholesky
-solves); the oracle is float64.  Tolerance: the forward error of a backward-stable fp32
-solve is about r * 2^-24 * cond(M) relative to the solution's norm; the synthetic workloads
+The Gram sums over the k + w rows of Omega are fp32; the r x r systems are fp32 Cholesky solves at
+r <= 16 and fp64 inverses (other kernels, hence most tests at both) from r = 32 on; the oracle is
+float64.  Tolerance: the forward error of a backward-stable fp32
+solve is about r * 2^-24 * cond(M) relative to the solution's norm (that of fp32 sums alone is
+smaller); the synthetic workloads
 have cond(M) of a few tens (A_Om^T A_Om dominates M, and its spectrum is that of k + w
 Gaussian rows plus the planted plane), so with r <= 64 the bound is 64 * 6e-8 * ~10 = 4e-5.
 The tests allow REL_TOL = 5e-5 of the largest entry of each output array and print what
@@ -109,10 +111,11 @@ def test_factor_update_ranks(r):
     run_update_case(upd_cfg(r=r))
 
 
+@pytest.mark.parametrize("r", [16, 32])
 @pytest.mark.parametrize("G,Hkv", [(1, 3), (2, 2), (7, 1), (8, 1)])
-def test_factor_update_group_sizes(G, Hkv):
-    say(f"factor update G={G}")
-    run_update_case(upd_cfg(B=1, Hq=G * Hkv, Hkv=Hkv, r=16))
+def test_factor_update_group_sizes(G, Hkv, r):
+    say(f"factor update G={G} r={r}")
+    run_update_case(upd_cfg(B=1, Hq=G * Hkv, Hkv=Hkv, r=r))
 
 
 def test_factor_update_fp32_rows_and_ragged_sizes():
@@ -120,21 +123,24 @@ def test_factor_update_fp32_rows_and_ragged_sizes():
     run_update_case(upd_cfg(B=1, Hq=4, Hkv=2, l=2777, k=263, w=37, C=263, kv_dtype="f32"))
 
 
+@pytest.mark.parametrize("r", [16, 32, 64])
 @pytest.mark.parametrize("lam1,lam2,n_iter", [(0.0, 0.0, 1), (1.0, 0.0, 2), (0.0, 1.0, 1),
                                               (0.5, 2.0, 4)])
-def test_factor_update_lambdas_and_rounds(lam1, lam2, n_iter):
-    say(f"factor update lambda_d1={lam1} lambda_d2={lam2} rounds={n_iter}")
-    run_update_case(upd_cfg(B=1, Hq=4, Hkv=2, r=16), lam1, lam2, n_iter)
+def test_factor_update_lambdas_and_rounds(lam1, lam2, n_iter, r):
+    say(f"factor update lambda_d1={lam1} lambda_d2={lam2} rounds={n_iter} r={r}")
+    run_update_case(upd_cfg(B=1, Hq=4, Hkv=2, r=r), lam1, lam2, n_iter)
 
 
-def test_factor_update_skips_entries_without_a_slot():
-    say("factor update, 6 entries per head of the previous selection have no valid slot")
-    run_update_case(upd_cfg(B=1, Hq=4, Hkv=2, r=16), drop=6)
+@pytest.mark.parametrize("r", [16, 32, 64])
+def test_factor_update_skips_entries_without_a_slot(r):
+    say(f"factor update r={r}, 6 entries per head of the previous selection have no valid slot")
+    run_update_case(upd_cfg(B=1, Hq=4, Hkv=2, r=r), drop=6)
 
 
-def test_factor_update_no_lite_window():
-    say("factor update with w = 0")
-    run_update_case(upd_cfg(B=1, Hq=2, Hkv=1, r=16, w=0))
+@pytest.mark.parametrize("r", [16, 32, 64])
+def test_factor_update_no_lite_window(r):
+    say(f"factor update with w = 0, r={r}")
+    run_update_case(upd_cfg(B=1, Hq=2, Hkv=1, r=r, w=0))
 
 
 def test_factor_update_at_the_headline_shape():
@@ -302,10 +308,81 @@ def run_alg2_growing(cfg, n_new, mode, lam1=1.0, lam2=1.0):
     return new_selected, new_fetched
 
 
-@pytest.mark.parametrize("r", [8, 64])
+@pytest.mark.parametrize("r", [8, 32, 64])
 @pytest.mark.parametrize("G,Hkv", [(8, 1), (1, 3), (5, 1)])
 def test_update_group_sizes_at_the_smallest_and_largest_rank(r, G, Hkv):
     """One wavefront per query head of a group and one matrix per head: G = 8 leaves no wavefront
-    without a head, r = 8 pads the 16 x 16 tiles of the systems, r = 64 fills all of them."""
+    without a head.  r = 8: the smallest system; r = 32: 2 x 2 tiles, which half the wavefronts of
+    an inversion own, r = 64: 4 x 4, two for every wavefront."""
     say(f"update G={G} r={r}")
     run_update_case(upd_cfg(Hq=G * Hkv, Hkv=Hkv, r=r), n_iter=3)
+
+
+def small_update(r, B_Q, B_K, q, k_new, lam1=1.0, lam2=1.0, n_iter=2, seed=3):
+    """The update on a hand-made layer (4 query heads on 2 KV heads, Omega = 48 rows): what came
+    out of the library, and of the oracle."""
+    gen = torch.Generator().manual_seed(seed)
+    B, Hq, Hkv, l, k, C, d = 1, 4, 2, 500, 48, 64, 128
+    A_K = torch.randn(B, Hkv, l, r, generator=gen)
+    K = torch.randn(B, Hkv, l, d, generator=gen)
+    sel = torch.stack([torch.randperm(l, generator=gen)[:k].sort().values for _ in range(Hq)])[None]
+    cacheK = torch.zeros(B, Hq, C, d)
+    for h in range(Hq):
+        cacheK[0, h, :k] = K[0, h // 2, sel[0, h]]
+    slots = torch.arange(k).expand(B, Hq, k)
+    shp = L.Shape.make(B=B, Hq=Hq, Hkv=Hkv, l=l, r=r, k=k, w=0, C_slots=C,
+                       kv_dtype=L.LRQK_KV_F32)
+    A_Kd, cacheKd = A_K.to(DEV), cacheK.to(DEV)
+    unused = torch.zeros(16, dtype=torch.int32, device=DEV)
+    lay = L.make_layer(A_K=A_Kd, K_host=None, V_host=None, liteK=None, liteV=None, slot_of=unused,
+                       token_of=unused, last_used=unused, cacheK=cacheKd, cacheV=cacheKd)
+    got = dict(q_hat=torch.empty((B, Hq, r), device=DEV), k_hat=torch.empty((B, Hkv, r), device=DEV),
+               B_Q=B_Q.to(DEV), B_K=B_K.to(DEV))
+    L.lrqk_factor_update(shp, lay, sel.int().to(DEV).contiguous(), slots.int().to(DEV).contiguous(),
+                         q.to(DEV), k_new.to(DEV), got["B_Q"], got["B_K"], lam1, lam2, n_iter,
+                         got["q_hat"], got["k_hat"],
+                         workspace(L.lrqk_workspace_bytes(shp, L.LRQK_WS_UPDATE)))
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        ref = upd.factor_update(as_numpy(q), as_numpy(k_new), as_numpy(B_Q), as_numpy(B_K),
+                                as_numpy(A_K), as_numpy(K), sel.numpy(), lam1, lam2, n_iter)
+    return {n: x.cpu().numpy() for n, x in got.items()}, ref
+
+
+def small_inputs(r, seed=4):
+    gen = torch.Generator().manual_seed(seed)
+    return [torch.randn(*n, generator=gen) for n in
+            ((1, 4, r, 128), (1, 2, r, 128), (1, 4, 128), (1, 2, 128))]
+
+
+@pytest.mark.parametrize("r", [32, 64])
+def test_update_with_a_nearly_singular_key_basis(r):
+    """B_K with singular values down to 1e-4 of the largest: N = B_K B_K^T has a condition number of
+    about 1e8 and is inverted as such.  With lambda_d1 = 0 nothing but N enters k_hat: its error is
+    that of an fp64 solve, some r cond(N) 2^-53 = 7e-7, and of the fp32 result."""
+    B_Q, B_K, q, k_new = small_inputs(r)
+    U, s, Vt = torch.linalg.svd(B_K.double(), full_matrices=False)
+    s = torch.logspace(0, -4, r, dtype=torch.float64)
+    B_K = ((U * s) @ Vt).float()
+    got, ref = small_update(r, B_Q, B_K, q, k_new, lam1=0.0)
+    N = B_K[0, 0].double() @ B_K[0, 0].double().T
+    cond = float(torch.linalg.cond(N))
+    tol = 2.0 ** -23 + r * cond * 2.0 ** -53
+    rel = np.abs(got["k_hat"] - ref["k_hat"]).max() / np.abs(ref["k_hat"]).max()
+    say(f"nearly singular B_K r={r}: cond(N) {cond:.1e}, k_hat {rel:.1e} (tolerance {tol:.1e})")
+    assert 1e7 < cond < 1e9 and rel <= tol
+    for n in ("B_Q", "B_K", "q_hat"):
+        assert np.abs(got[n] - ref[n]).max() <= REL_TOL * np.abs(ref[n]).max(), n
+
+
+@pytest.mark.parametrize("r", [8, 32, 64])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_update_nan_and_infinity_stay_in_their_group(r, bad):
+    B_Q, B_K, q, k_new = small_inputs(r)
+    clean, _ = small_update(r, B_Q, B_K, q, k_new)
+    q[0, 1, 7] = bad                                     # a query head of the first KV group
+    got, ref = small_update(r, B_Q, B_K, q, k_new)
+    for n in got:
+        half = got[n].shape[1] // 2
+        assert np.array_equal(got[n][:, half:], clean[n][:, half:]), n
+        assert not np.isfinite(ref[n][:, :half]).all() and not np.isfinite(got[n][:, :half]).all(), n
