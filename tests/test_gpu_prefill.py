@@ -1,14 +1,17 @@
 """GPU parity of the prefill factorisation (lrqk_prefill_factorize) against the CPU oracle
 (oracle/lrqk_prefill_oracle.py), through the C ABI.
 
-The kernels sum over the l rows on the fp32 matrix cores and solve r x r systems in fp32; the
-oracle is float64.  Each output is compared relative to the largest entry of its array.
-Tolerance: the forward error of an fp32 solve is about cond(M) * 2^-24 relative to the
+The kernels sum over the l rows on the bf16 matrix cores, fp32 operands as three bf16 terms, and do
+the r x d algebra in fp64; the oracle is float64.  Most tests compare each output relative to the
+largest entry of its array, with a tolerance that any computation with fp32 sums and solves meets:
+the forward error of an fp32 solve is about cond(M) * 2^-24 relative to the
 solution.  The first round inverts A^T A of N(0,1) factors (cond about 1.2); later rounds
 invert A^T A of factors that span near-rank-r data, whose condition number is 1e3 .. 4e4 for
 these inputs -- a property of the method in the paper's fp32, not of the kernel.  The test
 measures it (numpy.linalg.cond on the oracle's factors of the previous round) and allows
-max(2e-4, 4 * cond * 2^-24); it prints what it sees.
+max(2e-4, 4 * cond * 2^-24); it prints what it sees.  That finds wrong indices and formulas, not a
+lost term of the arithmetic: for those, test_prefill_distances and
+test_prefill_strong_directions compare 2-norms with what the kernels reach.
 """
 import numpy as np
 import pytest
@@ -240,6 +243,62 @@ def distances(Q, K, A_Q0, A_K0, lam_q=1.0, lam_k=1.0, n_iter=2):
     torch.cuda.synchronize()
     return {n: float(np.linalg.norm(x.cpu().numpy() - ref[n]) / np.linalg.norm(ref[n]))
             for n, x in got.items()}
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("r,l", [(8, 4096), (16, 4096), (32, 20000), (64, 5000)])
+def test_prefill_distances(r, l, dtype):
+    """Near-rank-r data.  One round with lambda = 0 inverts A^T A of N(0,1) factors for B_Q, B_K and
+    A_K (condition number about 1.2): what is left is the rounding of the sums, 256 rows at a time in
+    fp32, about 2^-24 of them a few times over, and of the result: 7e-7 allowed, 1e-7 .. 3.5e-7
+    measured.  With two bf16 terms of an fp32 operand instead of three it would be 2e-6.  A_Q
+    inverts A_K^T A_K of the new A_K, condition number some 10 (6e-6 allowed, 2e-6 measured); two rounds
+    amplify the error of the sums by those of the factors (8e-6, at most 1.9e-6 measured; 9e-4 with
+    sums and solves in fp32 throughout)."""
+    data = strong_directions("mean", 0.0, l, r, 4, dtype, seed=l + r)
+    one, two = distances(*data, 0.0, 0.0, 1), distances(*data)
+    say(f"prefill distances r={r} l={l} {dtype}: one round " +
+        " ".join(f"{n} {x:.1e}" for n, x in one.items()) + ", two " +
+        " ".join(f"{n} {x:.1e}" for n, x in two.items()))
+    assert max(one[n] for n in ("A_K", "B_Q", "B_K")) <= 7e-7 and one["A_Q"] <= 6e-6
+    assert max(two.values()) <= 8e-6
+
+
+def test_prefill_keys_of_lower_rank():
+    """Keys of rank 5 at r = 16: every system of the first round is regular all the same
+    (4e-7 measured; 1e-5 leaves room for the conditioning of other draws)."""
+    data = strong_directions("mean", 0.0, 3000, 16, 2, torch.float32, seed=5)
+    K = data[1][0, 0].double()
+    U, s, Vt = torch.linalg.svd(K, full_matrices=False)
+    s[5:] = 0.0
+    got = distances(data[0], ((U * s) @ Vt).float()[None, None], *data[2:], n_iter=1)
+    say("prefill, keys of rank 5: " + " ".join(f"{n} {x:.1e}" for n, x in got.items()))
+    assert max(got.values()) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_prefill_nan_and_infinity_stay_in_their_group(bad, dtype):
+    two = [strong_directions("mean", 0.0, 1100, 32, 2, dtype, seed=s) for s in (1, 2)]
+    Q, K, A_Q0, A_K0 = (torch.cat([a, b], 1) for a, b in zip(*two))
+    shp = L.Shape.make(B=1, Hq=4, Hkv=2, l=1100, r=32, k=16, w=0, C_slots=16,
+                       kv_dtype=L.LRQK_KV_BF16 if dtype == torch.bfloat16 else L.LRQK_KV_F32)
+
+    def run():
+        got = [A_Q0.to(DEV), A_K0.to(DEV), torch.empty((1, 4, 32, 128), device=DEV),
+               torch.empty((1, 2, 32, 128), device=DEV)]
+        L.lrqk_prefill_factorize(shp, Q.to(DEV), K.to(DEV), *got, 1.0, 1.0, 2,
+                                 workspace(L.lrqk_workspace_bytes(shp, L.LRQK_WS_PREFILL)))
+        torch.cuda.synchronize()
+        return [x.cpu() for x in got]
+
+    clean = run()
+    K[0, 0, 0, 3] = bad                                  # the first KV group; a row of the sample
+    K[0, 0, 1099, 100] = bad                             # that the grids come from, and the last one
+    for got, want in zip(run(), clean):
+        half = got.shape[1] // 2
+        assert torch.equal(got[:, half:], want[:, half:])
+        assert not torch.isfinite(got[:, :half]).any()
 
 
 # d x d sums have to be so good that the factors are no further off than with sums over A_Q and A_K
