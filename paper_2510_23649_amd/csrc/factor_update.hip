@@ -9,13 +9,13 @@
 //     (r x r) and g = sum_i u_i a_i (r), a_i = row of A_K, u_i = q . K_i.  The row list of a head is
 //     cut into chunks of at most 144 rows, one workgroup each, so that batch-1 steps still use
 //     hundreds of CUs; K rows are read by 16 lanes each exactly as the attention kernel reads
-//     them.  Partial sums per chunk go to the workspace: no atomics, the result does not depend
-//     on scheduling.
+//     them (update_gram.h).  Partial sums per chunk go to the workspace: no atomics, the result does
+//     not depend on scheduling.
 //  2. factor_inverse_kernel: P^-1 and N^-1 (what changes between rounds is a low-rank correction
 //     of these two), a workgroup per matrix.
 //  3. factor_rounds_kernel: the n_iter rounds and the line-search gradient steps on B_Q and B_K in
 //     place, a workgroup per (batch, KV head).
-// Times in us at k = 2048, w = 64, 32 + 8 heads, r = 32: 8 + 10 + 13; at 8 x (28 + 4) heads, k = 1024, r = 64:
+// Times in us at k = 2048, w = 64, 32 + 8 heads, r = 32: 11 + 10 + 13; at 8 x (28 + 4) heads, k = 1024, r = 64:
 // 38 + 28 + 31.  (Factorising in fp32 with a row per lane, P once and the k_hat system in every
 // round, all in one wavefront per head, launches 2 and 3 took 30 and 114 us.)  What is left is
 // latency: the loads at the start of each launch, a chain of r / 4 elimination steps (0.5 us each
@@ -25,260 +25,25 @@
 #include "lrqk_alg64.h"
 #include "lrqk_device.h"
 #include "lrqk_internal.h"
+#include "update_gram.h"
 
 namespace lrqk {
 namespace {
 
 using namespace alg64;
 
-constexpr int kGramThreads = 256;
-constexpr int kGramBatch = 144;  // rows staged in LDS at a time (a multiple of 16)
-
-template <int CTRL>
-__device__ __forceinline__ float fu_dpp(float v) {
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float row16_sum(float v) {
-  v += fu_dpp<0x128>(v);  // row_ror:8
-  v += fu_dpp<0x124>(v);  // row_ror:4
-  v += fu_dpp<0x122>(v);  // row_ror:2
-  v += fu_dpp<0x121>(v);  // row_ror:1
-  return v;
-}
-__device__ __forceinline__ float bf16_to_f32(uint16_t h) {
-  return __uint_as_float((uint32_t)h << 16);
-}
-template <bool BF16>
-__device__ __forceinline__ float kv_load(const void* row, int j) {
-  if (BF16) return bf16_to_f32(static_cast<const uint16_t*>(row)[j]);
-  return static_cast<const float*>(row)[j];
-}
-
-// q . K_row for the 16 lanes that share a row; lane c of the 16 takes elements 8c .. 8c+7.
-// The load and the arithmetic are separate so that a batch of loads can be issued together.
-template <bool BF16>
-struct RowPiece {
-  uint4 lo, hi;  // bf16: lo only
-};
-template <bool BF16>
-__device__ __forceinline__ RowPiece<BF16> load_piece(const void* row, int c) {
-  RowPiece<BF16> p;
-  if (BF16) {
-    p.lo = static_cast<const uint4*>(row)[c];
-    p.hi = p.lo;
-  } else {
-    p.lo = static_cast<const uint4*>(row)[2 * c];
-    p.hi = static_cast<const uint4*>(row)[2 * c + 1];
-  }
-  return p;
-}
-template <bool BF16>
-__device__ __forceinline__ float dot_piece(const RowPiece<BF16>& p, const float (&qv)[8]) {
-  float x[8];
-  if (BF16) {
-    const uint4 u = p.lo;
-    x[0] = __uint_as_float(u.x << 16); x[1] = __uint_as_float(u.x & 0xffff0000u);
-    x[2] = __uint_as_float(u.y << 16); x[3] = __uint_as_float(u.y & 0xffff0000u);
-    x[4] = __uint_as_float(u.z << 16); x[5] = __uint_as_float(u.z & 0xffff0000u);
-    x[6] = __uint_as_float(u.w << 16); x[7] = __uint_as_float(u.w & 0xffff0000u);
-  } else {
-    x[0] = __uint_as_float(p.lo.x); x[1] = __uint_as_float(p.lo.y);
-    x[2] = __uint_as_float(p.lo.z); x[3] = __uint_as_float(p.lo.w);
-    x[4] = __uint_as_float(p.hi.x); x[5] = __uint_as_float(p.hi.y);
-    x[6] = __uint_as_float(p.hi.z); x[7] = __uint_as_float(p.hi.w);
-  }
-  float acc = 0.0f;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) acc = __builtin_fmaf(x[j], qv[j], acc);
-  return acc;
-}
-
-// S += sum_i a_i^T a_i and g += sum_i u_i a_i over the kGramBatch rows staged in LDS (a_s: row
-// stride LDA floats, rows past the end are zero), by the 256 threads of a workgroup.
-// S is a dense contraction over the rows and goes through v_mfma_f32_32x32x2_f32, whose two
-// operands are here the same numbers: lane i + 32 kk supplies A[i][kk] = B[kk][i] = element i
-// of row kk of the pair.  r <= 32: one 32 x 32 block (columns >= r read as zero), each
-// wavefront sums a quarter of the rows; r = 64: wavefront (bi, bj) owns block (bi, bj) of S
-// and sums all the rows.  g: thread t sums column t % r over every (256 / r)-th row.
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-template <int R>
-__device__ __forceinline__ void gram_accumulate(const float* a_s, const float* u_s, f32x16& sacc,
-                                                float& gpart, int t) {
-  constexpr int LDA = R + 4;
-  const int wave = t >> 6, lane = t & 63, li = lane & 31, lk = lane >> 5;
-  if constexpr (R <= 32) {
-    constexpr int kRows = kGramBatch / 4;  // rows per wavefront
-    static_assert(kRows % 2 == 0, "rows are consumed in pairs");
-#pragma unroll 6
-    for (int i = 0; i < kRows; i += 2) {
-      const float x = li < R ? a_s[(wave * kRows + i + lk) * LDA + li] : 0.0f;
-      sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, x, sacc, 0, 0, 0);
-    }
-  } else {
-    const int bi = wave >> 1, bj = wave & 1;
-#pragma unroll 6
-    for (int i = 0; i < kGramBatch; i += 2) {
-      const float xa = a_s[(i + lk) * LDA + 32 * bi + li];
-      const float xb = a_s[(i + lk) * LDA + 32 * bj + li];
-      sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa, xb, sacc, 0, 0, 0);
-    }
-  }
-  constexpr int kSub = kGramThreads / R;
-  const int gc = t % R;
-#pragma unroll 4
-  for (int i = t / R; i < kGramBatch; i += kSub) gpart = __builtin_fmaf(u_s[i], a_s[i * LDA + gc], gpart);
-}
-
-struct GramArgs {
-  const float* A_K;              // [B,Hkv,l_rows,r]
-  const void* cacheK;            // [B,Hq,C,d]
-  const void* liteK;             // [B,Hkv,w,d], row j holds the position p of [l-w,l), p % w == j
-  const int32_t* sel_idx_prev;   // [B,Hq,k]
-  const int32_t* sel_slot_prev;  // [B,Hq,k]
-  const float* q;                // [B,Hq,d]
-  float* gram_om;                // [B*Hq][nchunk][r*r + r]
-  int Hq, Hkv, l, l_rows, k, w, C, nchunk, chunk_rows;
-};
-
 template <int R, bool BF16>
-__global__ __launch_bounds__(kGramThreads) void factor_gram_kernel(GramArgs a) {
-  constexpr int kEntries = R * R;
-  constexpr int LDA = R + 4;  // padded LDS row, keeps 16-byte alignment
-  constexpr size_t ROWB = kD * (BF16 ? 2 : 4);
-  __shared__ __align__(16) float a_s[kGramBatch * LDA];
-  // r <= 32: the partial blocks of wavefronts 1..3; then the partial sums of g
-  __shared__ float red_s[R <= 32 ? 3 * 1024 : kGramThreads];
-  __shared__ float u_s[kGramBatch];
-  __shared__ int pos_s[kGramBatch];
-  __shared__ const char* krow_s[kGramBatch];
-
+__global__ __launch_bounds__(kGramThreads) void factor_gram_kernel(GramRows a) {
+  __shared__ GramLds<R> s;
   const int bh = blockIdx.y, job = blockIdx.x, t = threadIdx.x;
   const int b = bh / a.Hq, h = bh - b * a.Hq;
-  const int G = a.Hq / a.Hkv;
-  const int kvh = h / G;
-  const int bkv = b * a.Hkv + kvh;
-
+  const int bkv = b * a.Hkv + h / (a.Hq / a.Hkv);
   f32x16 sacc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) sacc[v] = 0.0f;
   float gpart = 0.0f;
-
-  float* out = a.gram_om + ((size_t)bh * a.nchunk + job) * (kEntries + R);
-  {
-    const int n_om = a.k + a.w;
-    const int i_begin = job * a.chunk_rows;
-    const int i_end = min(n_om, i_begin + a.chunk_rows);
-    const float* __restrict__ Ahead = a.A_K + (size_t)bkv * (size_t)a.l_rows * R;
-    const char* Kc = static_cast<const char*>(a.cacheK) + (size_t)bh * a.C * ROWB;
-    const char* Kl = static_cast<const char*>(a.liteK) + (size_t)bkv * a.w * ROWB;
-    const int c16 = t & 15, rsub = t >> 4;
-    float qv[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) qv[j] = a.q[(size_t)bh * kD + c16 * 8 + j];
-    const char* qrow = reinterpret_cast<const char*>(a.q + (size_t)bh * kD);
-    const int lite0 = a.l - a.w;  // first position of the lite window
-    for (int i0 = i_begin; i0 < i_end; i0 += kGramBatch) {
-      __syncthreads();  // the previous batch has been consumed
-      if (t < kGramBatch) {
-        const int i = i0 + t;
-        int pos = -1;
-        const char* krow = nullptr;
-        if (i < i_end) {
-          if (i < a.k) {
-            const int tok = a.sel_idx_prev[(size_t)bh * a.k + i];
-            const int slot = a.sel_slot_prev[(size_t)bh * a.k + i];
-            if (tok >= 0 && tok < a.l && slot >= 0 && slot < a.C) {
-              pos = tok;
-              krow = Kc + (size_t)slot * ROWB;
-            }
-          } else {
-            const int j = i - a.k;  // row of the lite ring
-            // the position in [l-w, l) that is congruent to j modulo w
-            int off = (j - lite0) % a.w;
-            if (off < 0) off += a.w;
-            pos = lite0 + off;
-            krow = Kl + (size_t)j * ROWB;
-          }
-        }
-        pos_s[t] = pos;
-        krow_s[t] = krow;
-      }
-      __syncthreads();
-      // All the loads of the batch are issued before anything waits for one of them; rows
-      // that do not exist read memory that does (the head's q, which is at least as long as
-      // a K row; row 0 of A_K) and are zeroed afterwards.
-      // u_i = q . K_i: 16 lanes per row, 16 rows per pass
-      constexpr int kPasses = kGramBatch / 16;
-      RowPiece<BF16> piece[kPasses];
-#pragma unroll
-      for (int pass = 0; pass < kPasses; ++pass) {
-        const char* krow = krow_s[pass * 16 + rsub];
-        piece[pass] = load_piece<BF16>(krow ? krow : qrow, c16);
-      }
-      // a_i = A_K[pos_i, :]
-      constexpr int kAPieces = (kGramBatch * (R / 4) + kGramThreads - 1) / kGramThreads;
-      float4 av[kAPieces];
-#pragma unroll
-      for (int u = 0; u < kAPieces; ++u) {
-        const int idx = t + u * kGramThreads;
-        const int rr = min(idx / (R / 4), kGramBatch - 1), c4 = idx % (R / 4);
-        const int pos = pos_s[rr];
-        av[u] = reinterpret_cast<const float4*>(Ahead + (size_t)max(pos, 0) * R)[c4];
-        if (pos < 0) av[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-#pragma unroll
-      for (int pass = 0; pass < kPasses; ++pass) {
-        const int rr = pass * 16 + rsub;
-        float dot = krow_s[rr] ? dot_piece<BF16>(piece[pass], qv) : 0.0f;
-        dot = row16_sum(dot);
-        if (c16 == 0) u_s[rr] = dot;
-      }
-#pragma unroll
-      for (int u = 0; u < kAPieces; ++u) {
-        const int idx = t + u * kGramThreads;
-        if (idx < kGramBatch * (R / 4))
-          *reinterpret_cast<float4*>(&a_s[idx / (R / 4) * LDA + 4 * (idx % (R / 4))]) = av[u];
-      }
-      __syncthreads();
-      gram_accumulate<R>(a_s, u_s, sacc, gpart, t);
-    }
-  }
-  // Register v of lane l of an accumulator holds element [8 (v / 4) + 4 (l / 32) + v % 4][l % 32]
-  // of its block.
-  const int wave = t >> 6, lane = t & 63;
-  if constexpr (R <= 32) {
-    __syncthreads();
-    if (wave > 0) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) red_s[(wave - 1) * 1024 + v * 64 + lane] = sacc[v];
-    }
-    __syncthreads();
-    if (wave == 0) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float sum = ((sacc[v] + red_s[v * 64 + lane]) + red_s[1024 + v * 64 + lane]) +
-                          red_s[2048 + v * 64 + lane];
-        const int pr = 8 * (v / 4) + 4 * (lane >> 5) + v % 4, qc = lane & 31;
-        if (pr < R && qc < R) out[pr * R + qc] = sum;
-      }
-    }
-  } else {
-    const int bi = wave >> 1, bj = wave & 1;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int pr = 32 * bi + 8 * (v / 4) + 4 * (lane >> 5) + v % 4, qc = 32 * bj + (lane & 31);
-      out[pr * R + qc] = sacc[v];
-    }
-  }
-  __syncthreads();
-  red_s[t] = gpart;
-  __syncthreads();
-  if (t < R) {
-    float g = 0.0f;
-    for (int sub = 0; sub < kGramThreads / R; ++sub) g += red_s[sub * R + t];
-    out[kEntries + t] = g;
-  }
+  gram_chunk<R, BF16>(a, s, bh, bkv, job, sacc, gpart, t);
+  gram_store<R>(s, sacc, gpart, a.gram_om + ((size_t)bh * a.nchunk + job) * (R * R + R), t);
 }
 
 struct SolveArgs {
@@ -306,7 +71,8 @@ constexpr int kInvThreads = 512;
 constexpr int kLdb = kD + 2;  // LDS row stride: 16 rows x 2 columns fall on 32 different bank pairs
 template <int R>
 struct InvShape {
-  static constexpr int RT = (R + 15) / 16;                    // RT x RT tiles
+  static_assert(R % 32 == 0, "no padding");
+  static constexpr int RT = R / 16;                           // RT x RT tiles
   static constexpr int TPW = RT * RT > 8 ? RT * RT / 8 : 1;   // tiles of a wavefront, one tile row
   static constexpr int kX = 16 * RT * kLdb, kP = RT * 64, kC = 16 * RT * 4;
   static constexpr size_t lds_bytes = ((size_t)kX + kD + 2 * (kP + kC)) * sizeof(double);
@@ -355,7 +121,7 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
 #pragma unroll
           for (int v = 0; v < 4; ++v)
             x[sc][u][v] = part[(size_t)min(s0 + sc, a.nchunk - 1) * (kEntries + R) +
-                               min(16 * tr + 4 * v + k, R - 1) * R + min(16 * (tc0 + u) + c16, R - 1)];
+                               (16 * tr + 4 * v + k) * R + 16 * (tc0 + u) + c16];
 #pragma unroll
       for (int sc = 0; sc < SB; ++sc)
 #pragma unroll
@@ -412,7 +178,6 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int p0 = 16 * pt + 4 * q;
-      if (p0 >= R) break;
       double* const P = Pl + (q & 1) * Z::kP;  // two copies in turn: one barrier a step
       double* const C = Cl + (q & 1) * Z::kC;
       if (own) {
@@ -447,7 +212,7 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int i = 16 * tr + 4 * v + k, j = 16 * (tc0 + u) + c16;
-        if (i < R && j < R) out[i * R + j] = d[u][v];
+        out[i * R + j] = d[u][v];
       }
   }
 }
@@ -652,7 +417,7 @@ __global__ __launch_bounds__(kRoundThreads) void factor_rounds_kernel(SolveArgs 
 }
 
 template <int R, bool BF16>
-hipError_t launch_update_r(const lrqk_shape& s, const GramArgs& ga, const SolveArgs& sa,
+hipError_t launch_update_r(const lrqk_shape& s, const GramRows& ga, const SolveArgs& sa,
                            hipStream_t st) {
   static std::atomic<uint64_t> inv{0}, rounds{0};  // devices on which the LDS ceilings are up
   hipError_t e = raise_dynamic_lds_once(factor_inverse_kernel<R, BF16>, InvShape<R>::lds_bytes, inv);
@@ -669,7 +434,7 @@ hipError_t launch_update_r(const lrqk_shape& s, const GramArgs& ga, const SolveA
 }
 
 template <int R>
-hipError_t launch_update_dtype(bool bf16, const lrqk_shape& s, const GramArgs& ga,
+hipError_t launch_update_dtype(bool bf16, const lrqk_shape& s, const GramRows& ga,
                                const SolveArgs& sa, hipStream_t st) {
   return bf16 ? launch_update_r<R, true>(s, ga, sa, st) : launch_update_r<R, false>(s, ga, sa, st);
 }
@@ -707,7 +472,7 @@ hipError_t launch_factor_update(const lrqk_shape& s, const float* A_K, const voi
                                       B_Q, B_K, lam1, lam2, n_iter, q_hat, k_hat, ws, st);
   const UpdateGeom g = update_geometry(s);
   const size_t BHq = (size_t)s.B * s.Hq;
-  GramArgs ga;
+  GramRows ga;
   ga.A_K = A_K; ga.cacheK = cacheK; ga.liteK = liteK;
   ga.sel_idx_prev = sel_idx_prev; ga.sel_slot_prev = sel_slot_prev;
   ga.q = q; ga.gram_om = ws;

@@ -5,7 +5,7 @@
 // the prefill factorisation and by the decode-time factor update.
 #pragma once
 
-#include <hip/hip_runtime.h>
+#include "lrqk_device.h"
 
 namespace lrqk {
 namespace alg64 {
@@ -18,10 +18,7 @@ __device__ __forceinline__ f64x4 mfma_f64(double a, double b, f64x4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// Orders LDS traffic only: loads from memory stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
+using dev::lds_barrier;
 
 // 1 / x: the hardware estimate and three Newton steps (an IEEE division would lengthen the chain
 // of every elimination step by half; the last bit does not matter here).

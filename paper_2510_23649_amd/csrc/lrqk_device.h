@@ -7,6 +7,14 @@
 namespace lrqk {
 namespace dev {
 
+// Workgroup barrier that orders LDS traffic only: the wavefront's LDS operations have
+// completed before it arrives, its global loads and stores stay in flight (a __syncthreads
+// would wait for those too, i.e. expose a memory round trip at every barrier).  Used where
+// the threads exchange data through LDS alone.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // Order-preserving key of a score: larger score <=> larger key; -0.0f ranks with +0.0f.
 __device__ __forceinline__ uint32_t order_key(float s) {
   uint32_t u = __float_as_uint(s);

@@ -1,6 +1,6 @@
 // Small dense linear algebra inside one wavefront (gfx950): r x r symmetric positive definite
-// systems with r <= 64, lane i holding row i of the matrix in registers.  Used by the
-// decode-time factor update at r <= 16.
+// systems, lane i holding row i of the matrix in registers.  Used by the decode-time factor update at
+// r <= 16.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -33,8 +33,8 @@ __device__ __forceinline__ void rank_one_downdate(float (&m)[R], float l) {
 
 // Building blocks; lane i (< R) holds row i of the matrix in m[], element i of a vector in a
 // scalar.  Every register index is a compile-time constant: the column loops of the
-// factorisations are written as pack expansions over the column number (a loop of that size
-// is beyond what the compiler agrees to unroll at r = 64), the others are fully unrolled.
+// factorisations are written as pack expansions over the column number, the others are fully
+// unrolled.
 //
 // Column J of a right-looking Cholesky factorisation M = L L^T, in place.
 template <int R, int J>

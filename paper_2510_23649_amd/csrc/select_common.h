@@ -20,14 +20,6 @@ constexpr int kSampleStride = 8;
 
 constexpr int kMaxCls = 16;   // victim age classes numbered by the fast resolution
 
-// Workgroup barrier that orders LDS traffic only: the wavefront's LDS operations have
-// completed before it arrives, its global loads and stores stay in flight (a __syncthreads
-// would wait for those too, i.e. expose a memory round trip at every barrier).  Used where
-// the threads exchange data through LDS alone.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // Prefix sum over the 16 wave totals held in wt[0..16): returns the sum of the totals of the
 // wavefronts before this one, and the grand total.  Lanes 0..15 of every wavefront read one
 // total each and scan them with DPP row shifts (one LDS read instead of sixteen per thread).
