@@ -401,7 +401,10 @@ int lrqk_append_token(const lrqk_shape* shape, const lrqk_layer* layer, const fl
  * in this order (G = 1 gives the paper's rules).  B_Q, B_K are those computed at the top of
  * the last round.  Exactly n_iter rounds (the paper uses at most 2); no convergence test.
  * fp32 results (App. B.1): fp32 operands enter the matrix cores as sums of three bf16 terms,
- * d x d sums and the r x d algebra are fp64.  Supported ranks: r in {8, 16, 32, 64}.
+ * d x d sums and the r x d algebra are fp64.  The sums over A_Q and A_K follow from the d x d sums
+ * of Q and K; those are good enough for the result not to be further off than with fp32 sums over
+ * A_Q and A_K themselves, also where queries and keys are strong in different directions.
+ * Supported ranks: r in {8, 16, 32, 64}.
  * Of `shape`, B, Hq, Hkv, d, l, r, kv_dtype and l_cap are used.
  *   Q     device kv_dtype [B,Hq,l,d]     read
  *   K     device kv_dtype [B,Hkv,l,d]    read

@@ -324,7 +324,9 @@ __device__ __forceinline__ void assign_victims(const VictimWork& v, int nm) {
   int nv = nm;  // number of victims found (< nm only if the caller reused `step`)
   if (n_elig >= (uint32_t)nm && ncls <= kMaxCls && !clipped) {
     // rank of a victim = slots in older classes + its index in its class, in slot order: two
-    // classes per prefix count (16-bit fields; there are mostly one to three)
+    // classes per prefix count (16-bit fields; there are mostly one to three).  Selection and
+    // resolution at 32K with 100 misses in 1, 4, 8, 15 classes: 11.6, 12.0, 13.1, 14.8 us; with four
+    // classes per count of two words 12.7, 12.8, 13.8, 15.4.
     for (int c2 = 0; c2 < ncls; c2 += 2) {
       const uint32_t ca0 = v.cls_age[c2], cb0 = v.cls_base[c2];
       const bool two = c2 + 1 < ncls;

@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
   const int32_t step = a.step;
   // ---- 0. every load that does not depend on the selection -----------------------------------
   // (from clamped addresses and without a branch: a load inside one is waited for before the
-  // next is issued.  Whole step at 4K context 24.4 -> 23.9 us, at 128K 235.3 -> 234.8.  Looking
+  // next is issued.  Whole step at 4K context 24.4 -> 23.9 us, of two layers at 128K 235.3 -> 234.8.  Looking
   // slot_of up for every candidate here, before the cut is known, hides the gather but makes
   // half as many again: no gain at 32K, and the registers spill at two groups per thread.)
   const int ngroups = (n + 63) >> 6;

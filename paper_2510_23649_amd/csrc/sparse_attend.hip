@@ -20,9 +20,9 @@
 //
 // A small launch is bound by the chain index -> row -> result, not by its bytes: the body is
 // compiled per mode and loads a row's slot, hit flag and token together and without a branch,
-// so that the chain is two loads long.  Whole decode step, before -> after (1 layer, bf16, 8 KV
-// heads): 4K context 25.3 -> 24.6 us, 32K 120.1 -> 118.3, 128K 237.7 -> 235.3, eight sequences
-// of 64K 309.2 -> 307.1.
+// so that the chain is two loads long.  Whole decode step, before -> after (bf16, 32 + 8 heads): 4K
+// context, one layer, 25.3 -> 24.6 us; two layers at 32K 120.1 -> 118.3, at 128K 237.7 -> 235.3.  A
+// batch of eight at 64K, bound by the host link and A_K, takes 306 to 309 us either way.
 #include <type_traits>
 
 #include "lrqk_internal.h"
