@@ -74,8 +74,9 @@ struct InvShape {
   static_assert(R % 32 == 0, "no padding");
   static constexpr int RT = R / 16;                           // RT x RT tiles
   static constexpr int TPW = RT * RT > 8 ? RT * RT / 8 : 1;   // tiles of a wavefront, one tile row
-  static constexpr int kX = 16 * RT * kLdb, kP = RT * 64, kC = 16 * RT * 4;
-  static constexpr size_t lds_bytes = ((size_t)kX + kD + 2 * (kP + kC)) * sizeof(double);
+  static constexpr int kX = 16 * RT * kLdb;
+  static_assert(sweep_doubles<RT, RT>() <= kX, "the elimination works in the memory of B");
+  static constexpr size_t lds_bytes = ((size_t)kX + kD) * sizeof(double);
 };
 
 template <int R, bool BF16>
@@ -86,8 +87,6 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
   extern __shared__ __align__(16) double inv_lds[];
   double* const X = inv_lds;            // [16 RT][kLdb]  B
   double* const xs = X + Z::kX;         // [d]  q or k
-  double* const Pl = xs + kD;
-  double* const Cl = Pl + 2 * Z::kP;
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int m = blockIdx.x;
   const bool isq = m < a.BHq;
@@ -172,40 +171,8 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
       for (int s = 0; s < kD; s += 4) d[u] = mfma_f64(xa[s], xb[s], d[u]);
     }
   }
-  // in-place inversion: a step's pivot columns start again as columns of the identity
-#pragma unroll 1
-  for (int pt = 0; pt < Z::RT; ++pt) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int p0 = 16 * pt + 4 * q;
-      double* const P = Pl + (q & 1) * Z::kP;  // two copies in turn: one barrier a step
-      double* const C = Cl + (q & 1) * Z::kC;
-      if (own) {
-#pragma unroll
-        for (int u = 0; u < Z::TPW; ++u) {
-          const int tc = tc0 + u;
-          const bool pivot_col = tc == pt && (c16 >> 2) == q;
-          const double unit = k == (lane & 3) ? 1.0 : 0.0;
-          if (tr == pt) P[tc * 64 + lane] = pivot_col ? unit : d[u][q];
-          if (tc == pt) {
-            if (pivot_col) {
-#pragma unroll
-              for (int v = 0; v < 4; ++v) C[(16 * tr + 4 * v + k) * 4 + (lane & 3)] = d[u][v];
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-              d[u][v] = pivot_col ? ((tr == pt && v == q) ? unit : 0.0) : d[u][v];
-          }
-        }
-      }
-      lds_barrier();
-      if (own) {
-        const double n = pivot_factor(C, p0, 16 * tr + c16, k);
-#pragma unroll
-        for (int u = 0; u < Z::TPW; ++u) d[u] = mfma_f64(n, P[(tc0 + u) * 64 + lane], d[u]);
-      }
-    }
-  }
+  lds_barrier();  // X has been read: the exchanged tiles take its place
+  sweep_tiles<Z::RT, Z::RT, Z::TPW, 1, true>(d, tr, tc0, X, lane);
   if (own) {
 #pragma unroll
     for (int u = 0; u < Z::TPW; ++u)

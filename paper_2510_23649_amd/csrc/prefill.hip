@@ -11,6 +11,7 @@
 //   3. n_iter times            B_K = H_K^-1 S_K, M_K, and S_K, H_K of A_K = K M_K
 //      (prefill_round_k)       and, in other workgroups, B_Q = H_Q^-1 S_Q;
 //      (prefill_round_q)       M_Q, and S_Q, H_Q of A_Q = Q M_Q unless it is the last round
+//      (prefill_group_kernel   before them at r = 64: sums over the query heads of a KV group)
 //   4. prefill_apply_kernel    A_K = K M_K, A_Q = Q M_Q
 //
 // (With a pass over Q and K in every update, X^T Y and X^T X from the fp32 matrix cores and the
@@ -25,6 +26,7 @@
 // on near-rank-r data, in brackets with sums over A_Q and A_K in fp32: 7e-6 (3e-4) at l = 131072,
 // r = 32; 2.4e-6 (1.2e-4) at l = 4096, r = 16; 5e-6 (1.5e-4) at l = 30011, r = 64.
 #include <type_traits>
+#include <utility>
 
 #include "lrqk_alg64.h"
 #include "lrqk_internal.h"
@@ -491,8 +493,9 @@ __device__ __forceinline__ int acc_index(int i, int j) {
   return (4 * (i >> 3) + (i & 3)) * 64 + 32 * ((i >> 2) & 1) + j;
 }
 
-// The chunk partials of a head added in chunk order, in fp64: G [d][d], S [r][d], H [r][r].
-template <int R>
+// The chunk partials of a head added in chunk order, in fp64: G [d][d], S [r][d], H [r][r] (the first of ADD
+// addends, the others zero).
+template <int R, int ADD>
 __global__ __launch_bounds__(256) void prefill_sum_kernel(const void* __restrict__ part,
                                                           double* __restrict__ G,
                                                           double* __restrict__ Sm,
@@ -523,10 +526,14 @@ __global__ __launch_bounds__(256) void prefill_sum_kernel(const void* __restrict
     place(e, row, col);
     row = column_of(row);
     const int bi = (e >> 10) & 3, bj = (bi + (e >> 12)) & 3;
+    // The diagonal blocks are symmetric but for the rounding of the small products, 1e-9 of them, which
+    // the solves, for which a system is symmetric, would not see in the same way as the products
+    // with G (B_Q 20 times further off at l = 20000, r = 32): their upper halves count.
+    if (bi == bj && row > col) return;
     const double x = total(reinterpret_cast<const double*>(p) + e);
     double* Gh = G + head * kD * kD;
     Gh[(32 * bi + row) * kD + 32 * bj + col] = x;
-    if (bi != bj) Gh[(32 * bj + col) * kD + 32 * bi + row] = x;
+    Gh[(32 * bj + col) * kD + 32 * bi + row] = x;
     return;
   }
   const float* f = reinterpret_cast<const float*>(p + (size_t)S::GB * 8 * 1024);
@@ -562,7 +569,9 @@ __global__ __launch_bounds__(256) void prefill_sum_kernel(const void* __restrict
     add(4, lo, hi - 32);
     add(5, lo, hi - 32);
   }
-  H[head * R * R + h] = x;
+  H[head * ADD * R * R + h] = x;
+#pragma unroll
+  for (int c = 1; c < ADD; ++c) H[(head * ADD + c) * R * R + h] = 0.0;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -575,96 +584,90 @@ struct PfAlg {
   static constexpr int RT = (R + 15) / 16;  // 16 x 16 tiles: RT x RT of the system,
   static constexpr int NT = RT + kD / 16;   // RT x 8 of the right-hand sides
   static constexpr int WPR = 8 / RT;        // wavefronts per tile row
-  static constexpr int TPW = (NT + WPR - 1) / WPR;  // tiles of a wavefront: columns c, c + WPR, ...
+  static constexpr int SYS = (RT + WPR - 1) / WPR;  // tiles of a wavefront: of the system (some do not
+  static constexpr int TPW = SYS + 8 / WPR;         // exist), all of them (tile_column)
   static constexpr int kX = 16 * RT * kLdx;         // doubles of an r x d matrix in LDS
-  static constexpr int kP = NT * 64, kC = 16 * RT * 4;  // pivot rows, pivot columns
-  static constexpr size_t lds_bytes = ((size_t)2 * kX + 2 * (kP + kC)) * sizeof(double);
+  // Where the chip has compute units to spare four workgroups share the sums S = X G, H = S X^T of a head:
+  // RS stretches of tile rows times CS of columns.  H comes in CS addends then, kept side by side.
+  static constexpr int RS = RT > 1 ? 2 : 1, CS = 4 / RS;
+  static constexpr int kH = CS * R * R;
+  static constexpr int kRaw = 4 * (TPW + SYS * (CS - 1));  // doubles of a wavefront's tiles in memory
+  // another one, and in its place during a solve the tiles that are exchanged
+  static constexpr int kY = sweep_doubles<RT, NT>() > kX ? sweep_doubles<RT, NT>() : kX;
+  static constexpr size_t lds_bytes = ((size_t)kX + kY) * sizeof(double);
 };
 
-// [A | Y] -> [I | A^-1 Y] by Gauss-Jordan elimination with 4 x 4 pivot blocks, A symmetric
-// positive definite (no pivoting needed).  A step takes the pivot block D, its rows P and columns
-// C through LDS (two copies in turn: one barrier a step) and adds N P to every tile, N = -C D^-1
-// and D^-1 - I for the pivot rows themselves: a rank-4 update, one MFMA per tile, whose operand
-// P is the register that the pivot rows' owners hold.
+// [A | Y] -> [. | A^-1 Y]; lds: Z::kY doubles, free again when every wavefront has returned.
 template <int R>
-__device__ __forceinline__ void solve_tiles(f64x4 (&d)[PfAlg<R>::TPW], double* Pl, double* Cl,
-                                            int w, int lane) {
+__device__ __forceinline__ void solve_tiles(f64x4 (&d)[PfAlg<R>::TPW], double* lds, int w, int lane) {
   using Z = PfAlg<R>;
-  const int tr = w / Z::WPR, tc0 = w % Z::WPR;
-  const int i = 16 * tr + (lane & 15), k = lane >> 4;
-#pragma unroll 1
-  for (int pt = 0; pt < (R + 15) / 16; ++pt) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int p0 = 16 * pt + 4 * q;  // first pivot
-      if (p0 >= R) break;
-      double* const P = Pl + (q & 1) * Z::kP;
-      double* const C = Cl + (q & 1) * Z::kC;
-#pragma unroll
-      for (int u = 0; u < Z::TPW; ++u) {
-        const int tc = tc0 + Z::WPR * u;
-        if (tr == pt && tc < Z::NT) P[tc * 64 + lane] = d[u][q];
-        if (tc == pt && ((lane & 15) >> 2) == q) {
-#pragma unroll
-          for (int v = 0; v < 4; ++v) C[(16 * tr + 4 * v + k) * 4 + (lane & 3)] = d[u][v];
-        }
-      }
-      lds_barrier();
-      const double n = pivot_factor(C, p0, i, k);
-#pragma unroll
-      for (int u = 0; u < Z::TPW; ++u) {
-        const int tc = tc0 + Z::WPR * u;
-        if (tc >= pt && tc < Z::NT) d[u] = mfma_f64(n, P[tc * 64 + lane], d[u]);
-      }
-    }
-  }
-  lds_barrier();
+  sweep_tiles<Z::RT, Z::NT, Z::TPW, Z::WPR, false>(d, w / Z::WPR, w % Z::WPR, lds, lane);
 }
 
-// The tiles of [H | S] of this wavefront, H [r][r] and S [r][d] in memory, added up over `n`
-// matrices that follow each other.  Every load is issued before the first is waited for: rows and
-// tiles that do not exist read ones that do.
+// The tiles of [H | S] of this wavefront, H [ADD][r][r] and S [r][d] in memory: register v of tile u, for
+// the system's tiles of every addend.  Nothing is waited for; rows that do not exist read ones that do.
+template <int R, int ADD = PfAlg<R>::CS>
+__device__ __forceinline__ void fetch_tiles(double (&x)[PfAlg<R>::kRaw], int w, int lane,
+                                            const double* __restrict__ H, const double* __restrict__ S) {
+  using Z = PfAlg<R>;
+  const int tr = w / Z::WPR, tc0 = w % Z::WPR;
+  int n = 0;
+#pragma unroll
+  for (int u = 0; u < Z::TPW; ++u) {
+    const int tc = tile_column<Z::RT, Z::WPR>(tc0, u), j = 16 * tc + (lane & 15);
+#pragma unroll
+    for (int c = 0; c < (u < Z::SYS ? ADD : 1); ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = min(16 * tr + 4 * v + (lane >> 4), R - 1);
+        if (u < Z::SYS)
+          x[n++] = tc < Z::RT ? H[c * R * R + i * R + min(j, R - 1)] : 0.0;
+        else
+          x[n++] = S[i * kD + j - 16 * Z::RT];
+      }
+  }
+}
+// d = them, or d += them; `use` false: zeros in their place.
+template <int R, int ADD = PfAlg<R>::CS>
+__device__ __forceinline__ void take_tiles(f64x4 (&d)[PfAlg<R>::TPW], const double (&x)[PfAlg<R>::kRaw],
+                                           bool add, bool use) {
+  using Z = PfAlg<R>;
+  int n = 0;
+#pragma unroll
+  for (int u = 0; u < Z::TPW; ++u)
+#pragma unroll
+    for (int c = 0; c < (u < Z::SYS ? ADD : 1); ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const double y = use ? x[n] : 0.0;
+        d[u][v] = add || c > 0 ? d[u][v] + y : y;
+        ++n;
+      }
+}
+// The padding of a system is the identity, that of its right-hand sides zero.
+template <int R>
+__device__ __forceinline__ void pad_tiles(f64x4 (&d)[PfAlg<R>::TPW], int w, int lane) {
+  using Z = PfAlg<R>;
+  if (R % 16 == 0) return;
+  const int tr = w / Z::WPR, tc0 = w % Z::WPR;
+#pragma unroll
+  for (int u = 0; u < Z::TPW; ++u)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 16 * tr + 4 * v + (lane >> 4);
+      const int j = 16 * tile_column<Z::RT, Z::WPR>(tc0, u) + (lane & 15);
+      if (i >= R || (u < Z::SYS && j >= R)) d[u][v] = (u < Z::SYS && i == j) ? 1.0 : 0.0;
+    }
+}
 template <int R>
 __device__ __forceinline__ void load_tiles(f64x4 (&d)[PfAlg<R>::TPW], int w, int lane,
                                            const double* __restrict__ H,
-                                           const double* __restrict__ S, int n) {
+                                           const double* __restrict__ S) {
   using Z = PfAlg<R>;
-  const int tr = w / Z::WPR, tc0 = w % Z::WPR;
-  const double* p[Z::TPW];
-  int row_stride[Z::TPW], stride[Z::TPW];
-#pragma unroll
-  for (int u = 0; u < Z::TPW; ++u) {
-    const int tc = min(tc0 + Z::WPR * u, Z::NT - 1);
-    const bool sys = tc < Z::RT;
-    const int j = 16 * tc + (lane & 15);
-    row_stride[u] = sys ? R : kD;
-    stride[u] = sys ? R * R : R * kD;
-    p[u] = sys ? H + min(j, R - 1) : S + (j - 16 * Z::RT);
-    d[u] = f64x4{0.0, 0.0, 0.0, 0.0};
-  }
-#pragma unroll 2
-  for (int g = 0; g < n; ++g) {
-    double x[Z::TPW][4];
-#pragma unroll
-    for (int u = 0; u < Z::TPW; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        x[u][v] = p[u][(size_t)g * stride[u] +
-                       min(16 * tr + 4 * v + (lane >> 4), R - 1) * row_stride[u]];
-#pragma unroll
-    for (int u = 0; u < Z::TPW; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) d[u][v] += x[u][v];
-  }
-  if (R % 16 != 0) {  // the padding of a system is the identity, that of its right-hand sides zero
-#pragma unroll
-    for (int u = 0; u < Z::TPW; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int tc = tc0 + Z::WPR * u, i = 16 * tr + 4 * v + (lane >> 4), j = 16 * tc + (lane & 15);
-        if (i >= R || (tc < Z::RT && j >= R)) d[u][v] = (tc < Z::RT && i == j) ? 1.0 : 0.0;
-      }
-  }
+  double x[Z::kRaw];
+  fetch_tiles<R>(x, w, lane, H, S);
+  take_tiles<R>(d, x, false, true);
+  pad_tiles<R>(d, w, lane);
 }
 
 // Right-hand-side tiles += lam X, X [r][d] in LDS.
@@ -674,9 +677,8 @@ __device__ __forceinline__ void add_rhs(f64x4 (&d)[PfAlg<R>::TPW], const double*
   using Z = PfAlg<R>;
   const int tr = w / Z::WPR, tc0 = w % Z::WPR;
 #pragma unroll
-  for (int u = 0; u < Z::TPW; ++u) {
-    const int tc = tc0 + Z::WPR * u;
-    if (tc < Z::RT || tc >= Z::NT) continue;
+  for (int u = Z::SYS; u < Z::TPW; ++u) {
+    const int tc = tile_column<Z::RT, Z::WPR>(tc0, u);
 #pragma unroll
     for (int v = 0; v < 4; ++v)
       d[u][v] = __builtin_fma(lam, X[(16 * tr + 4 * v + (lane >> 4)) * kLdx + 16 * (tc - Z::RT) +
@@ -691,9 +693,8 @@ __device__ __forceinline__ void store_solution(const f64x4 (&d)[PfAlg<R>::TPW], 
   using Z = PfAlg<R>;
   const int tr = w / Z::WPR, tc0 = w % Z::WPR;
 #pragma unroll
-  for (int u = 0; u < Z::TPW; ++u) {
-    const int tc = tc0 + Z::WPR * u;
-    if (tc < Z::RT || tc >= Z::NT) continue;
+  for (int u = Z::SYS; u < Z::TPW; ++u) {
+    const int tc = tile_column<Z::RT, Z::WPR>(tc0, u);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int i = 16 * tr + 4 * v + (lane >> 4);
@@ -702,67 +703,148 @@ __device__ __forceinline__ void store_solution(const f64x4 (&d)[PfAlg<R>::TPW], 
   }
 }
 
-// System tiles += lam X X^T, X [r][d] in LDS (rows up to the tile size are zero).
+// One wavefront's share of A B^T over d, A and B the 16 rows at `a` and `b` in LDS: one of `shares`
+// stretches of the sum.
+template <int SHARES>
+__device__ __forceinline__ f64x4 tile_product(const double* a, const double* b, int share, int lane) {
+  constexpr int kLen = kD / SHARES;
+  const int at = (lane & 15) * kLdx + (lane >> 4) + share * kLen;
+  f64x4 x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+  for (int s = 0; s < kLen; s += 4) x = mfma_f64(a[at + s], b[at + s], x);
+  return x;
+}
+
+// System tiles += lam X X^T, X [r][d] in LDS (rows up to the tile size are zero).  Y: LDS scratch.  At
+// r <= 32 there are more wavefronts than tiles: several share a tile (a chain of 32 MFMAs of 64 cycles by
+// its owner alone would be the longest part of a round at r = 16 after the solves).
 template <int R>
-__device__ __forceinline__ void add_gram(f64x4 (&d)[PfAlg<R>::TPW], const double* X, double lam,
-                                         int w, int lane) {
+__device__ __forceinline__ void add_gram(f64x4 (&d)[PfAlg<R>::TPW], const double* X, double* Y,
+                                         double lam, int w, int lane) {
   using Z = PfAlg<R>;
+  constexpr int kTiles = Z::RT * Z::RT, kShares = kTiles < 8 ? 8 / kTiles : 1;
   const int tr = w / Z::WPR, tc0 = w % Z::WPR;
+  if (kShares > 1) {
+    const int tile = w / kShares;
+    const f64x4 x = tile_product<kShares>(X + 16 * (tile / Z::RT) * kLdx, X + 16 * (tile % Z::RT) * kLdx,
+                                          w % kShares, lane);
 #pragma unroll
-  for (int u = 0; u < Z::TPW; ++u) {
+    for (int v = 0; v < 4; ++v) Y[w * 256 + v * 64 + lane] = x[v];
+    lds_barrier();
+  }
+#pragma unroll
+  for (int u = 0; u < Z::SYS; ++u) {
     const int tc = tc0 + Z::WPR * u;
     if (tc >= Z::RT) continue;
-    const double* xa = X + (16 * tr + (lane & 15)) * kLdx + (lane >> 4);
-    const double* xb = X + (16 * tc + (lane & 15)) * kLdx + (lane >> 4);
-#pragma unroll 8
-    for (int s = 0; s < kD; s += 4) d[u] = mfma_f64(lam * xa[s], xb[s], d[u]);
+    f64x4 x = {0.0, 0.0, 0.0, 0.0};
+    if (kShares > 1) {
+#pragma unroll
+      for (int i = 0; i < kShares; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] += Y[((tr * Z::RT + tc) * kShares + i) * 256 + v * 64 + lane];
+    } else {
+      x = tile_product<1>(X + 16 * tr * kLdx, X + 16 * tc * kLdx, 0, lane);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) d[u][v] = __builtin_fma(lam, x[v], d[u][v]);
   }
 }
 
-// This wavefront's operands of X G, G [d][d] in memory: columns 16 w .. 16 w + 15.
-__device__ __forceinline__ void load_gram(double (&g)[32], const double* __restrict__ G, int w,
-                                          int lane) {
-  const double* p = G + (lane >> 4) * kD + 16 * w + (lane & 15);
+// The share of a workgroup in the sums of a head, and of a wavefront in it: columns 16 col .. 16 col + 15
+// (with WC wavefronts side by side) and, of the sum over d, steps of 4 from step0 on, 32 / KS of them.
+// SHARED: four workgroups, RS x CS; otherwise one.
+template <int R, bool SHARED>
+struct PfPart {
+  using Z = PfAlg<R>;
+  static constexpr bool kShared = SHARED;
+  static constexpr int RS = SHARED ? Z::RS : 1, CS = SHARED ? Z::CS : 1;
+  static constexpr int WC = 8 / CS, KS = CS, kSteps = 32 / KS;
+  int row, addend, col, ks;
+  __device__ PfPart(int part, int w)
+      : row(part % RS), addend(part / RS), col(addend * WC + w % WC), ks(w / WC) {}
+};
+
+// This wavefront's operands of X G, G [d][d] in memory.
+template <class Q>
+__device__ __forceinline__ void load_gram(double (&g)[Q::kSteps], const double* __restrict__ G,
+                                          const Q& p, int lane) {
+  const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(G), 0, kD * kD * 8, kBufferFlags);
+  const int first = ((4 * Q::kSteps * p.ks + (lane >> 4)) * kD + 16 * p.col + (lane & 15)) * 8;
 #pragma unroll
-  for (int s = 0; s < 32; ++s) g[s] = p[4 * s * kD];
+  for (int s = 0; s < Q::kSteps; ++s)
+    g[s] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(buf, first, 4 * s * kD * 8, 0));
 }
 
-// S = X G and H = S X^T for X [r][d] in LDS; Ys [r][d]: LDS scratch.
-template <int R>
-__device__ __forceinline__ void sums_of(const double* X, double* Ys, const double (&g)[32],
-                                        double* __restrict__ Sm, double* __restrict__ H, int w,
-                                        int lane) {
+// This workgroup's part of S = X G and H = S X^T, X [r][d] in LDS: rows and columns of S, and of H the
+// addend that these columns make, in these rows.  Ys [r][d]: LDS scratch.
+template <int R, class Q>
+__device__ __forceinline__ void sums_of(const double* X, double* Ys, const double (&g)[Q::kSteps],
+                                        const Q& p, double* __restrict__ Sm,
+                                        double* __restrict__ H, int w, int lane) {
   using Z = PfAlg<R>;
-  const int c16 = lane & 15, k = lane >> 4;
-  f64x4 acc[Z::RT];
+  const int c16 = lane & 15, k = lane >> 4, t = w * 64 + lane;
+  constexpr int kRows = Z::RT / Q::RS;  // tile rows
+#pragma unroll 1
+  for (int rr = 0; rr < kRows; ++rr) {
+    const double* x = X + (16 * (p.row * kRows + rr) + c16) * kLdx + 4 * Q::kSteps * p.ks + k;
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int tr = 0; tr < Z::RT; ++tr) acc[tr] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int s = 0; s < Q::kSteps; ++s) acc = mfma_f64(x[4 * s], g[s], acc);
+    // (stretch ks of the sum in columns 16 WC ks .. of the row)
 #pragma unroll
-  for (int s = 0; s < 32; ++s)
-#pragma unroll
-    for (int tr = 0; tr < Z::RT; ++tr)
-      acc[tr] = mfma_f64(X[(16 * tr + c16) * kLdx + 4 * s + k], g[s], acc[tr]);
-#pragma unroll
-  for (int tr = 0; tr < Z::RT; ++tr)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = 16 * tr + 4 * v + k, j = 16 * w + c16;
-      Ys[i * kLdx + j] = acc[tr][v];
-      if (i < R) Sm[i * kD + j] = acc[tr][v];
-    }
+    for (int v = 0; v < 4; ++v)
+      Ys[(16 * rr + 4 * v + k) * kLdx + 16 * (Q::WC * p.ks + w % Q::WC) + c16] = acc[v];
+  }
   lds_barrier();
-  for (int tile = w; tile < Z::RT * Z::RT; tile += 8) {
-    const int tr = tile / Z::RT, tc = tile % Z::RT;
-    const double* ya = Ys + (16 * tr + c16) * kLdx + k;
-    const double* xb = X + (16 * tc + c16) * kLdx + k;
-    f64x4 h = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 8
-    for (int s = 0; s < kD; s += 4) h = mfma_f64(ya[s], xb[s], h);
+  constexpr int kCols = 16 * Q::WC;
+  for (int e = t; e < 16 * kRows * kCols; e += kAlgThreads) {
+    const int i = e / kCols, j = e % kCols, row = 16 * p.row * kRows + i;
+    double x = Ys[i * kLdx + j];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = 16 * tr + 4 * v + k, j = 16 * tc + c16;
-      if (i < R && j < R) H[i * R + j] = h[v];
+    for (int ks = 1; ks < Q::KS; ++ks) x += Ys[i * kLdx + kCols * ks + j];
+    if (Q::KS > 1) Ys[i * kLdx + j] = x;
+    if (row < R) Sm[row * kD + kCols * p.addend + j] = x;
+  }
+  if (Q::KS > 1) lds_barrier();
+  // H: kRows x RT tiles, each a sum over kCols; where there are fewer tiles than wavefronts several share one
+  constexpr int kTiles = kRows * Z::RT, kShares = kTiles < 8 ? 8 / kTiles : 1, kLen = kCols / kShares;
+  static_assert(kLen % 4 == 0, "whole steps");
+  H += p.addend * R * R;
+  f64x4 h[kTiles > 8 ? kTiles / 8 : 1];
+#pragma unroll
+  for (int n = 0; n < (kTiles > 8 ? kTiles / 8 : 1); ++n) {
+    const int tile = w / kShares + 8 * n, share = w % kShares;
+    const double* y = Ys + (16 * (tile / Z::RT) + c16) * kLdx + k + kLen * share;
+    const double* x = X + (16 * (tile % Z::RT) + c16) * kLdx + kCols * p.addend + k + kLen * share;
+    h[n] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+    for (int s = 0; s < kLen; s += 4) h[n] = mfma_f64(y[s], x[s], h[n]);
+  }
+  auto put = [&](int tile, int v, int l, double x) {
+    const int i = 16 * (p.row * kRows + tile / Z::RT) + 4 * v + (l >> 4), j = 16 * (tile % Z::RT) + (l & 15);
+    if (i >= R || j >= R) return;
+    H[i * R + j] = x;
+    if (!Q::kShared) {
+#pragma unroll
+      for (int c = 1; c < Z::CS; ++c) H[c * R * R + i * R + j] = 0.0;
     }
+  };
+  if (kShares > 1) {
+    lds_barrier();  // Ys has been read
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Ys[w * 256 + v * 64 + lane] = h[0][v];
+    lds_barrier();
+    for (int e = t; e < kTiles * 256; e += kAlgThreads) {
+      double x = 0.0;
+#pragma unroll
+      for (int i = 0; i < kShares; ++i) x += Ys[((e >> 8) * kShares + i) * 256 + (e & 255)];
+      put(e >> 8, (e >> 6) & 3, e & 63, x);
+    }
+  } else {
+#pragma unroll
+    for (int n = 0; n < (kTiles > 8 ? kTiles / 8 : 1); ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) put(w + 8 * n, v, lane, h[n][v]);
   }
 }
 
@@ -785,37 +867,83 @@ __device__ __forceinline__ void pack_operand(const double* Xt, uint4* __restrict
 }
 
 struct PfState {
-  const double* G;  // [BHq + BHkv][d][d]
-  double* S;        // [BHq + BHkv][r][d]
-  double* H;        // [BHq + BHkv][r][r]
-  double* BQ;       // [BHq][r][d]
-  uint4* M;         // [BHq + BHkv] packed operands
-  float* B_Q;       // results
+  const double* G;             // [BHq + BHkv][d][d]
+  double *S, *H;               // [BHq][r][d], [BHq][CS][r][r]: sums of A_Q
+  const double *SK, *HK;       // [BHkv][r][d], [BHkv][CS][r][r]: sums of A_K before the round
+  double *SK_new, *HK_new;     // ... and after its first half
+  double* group;               // [BHkv][r][r + d] (kGroupSums)
+  double* BQ;                  // [BHq][r][d]
+  uint4* M;                    // [BHq + BHkv] packed operands
+  float* B_Q;                  // results
   float* B_K;
   int Hq, Hkv, BHq, BHkv;
   double lam_pQ, lam_pK;
   bool last;  // last round: M is needed, the sums of the new A_Q are not
 };
 
-// First half of a round.  Workgroups [0, B Hkv), a KV head each:
+// At r = 64 the sums of a group's query heads, 0.7 to 0.9 MB at G = 7, are added up beforehand by all the
+// chip: [H | S] of the group, [r][r] and then [r][d].  One compute unit takes 17 us to read them, this
+// launch 4 us; at r = 32 (0.2 MB at G = 4) most of the reading lies under the first solve.
+template <int R>
+constexpr bool kGroupSums = R > 32;
+template <int R>
+__global__ __launch_bounds__(256) void prefill_group_kernel(const PfState a) {
+  using Z = PfAlg<R>;
+  constexpr int kSize = R * (R + kD), kBlocks = kSize / 256;
+  static_assert(kSize % 256 == 0 && R * R % 256 == 0, "whole workgroups");
+  const int bkv = blockIdx.x / kBlocks, e = (int)(blockIdx.x % kBlocks) * 256 + (int)threadIdx.x;
+  const int b = bkv / a.Hkv, G = a.Hq / a.Hkv;
+  const size_t q0 = (size_t)b * a.Hq + (size_t)(bkv - b * a.Hkv) * G;
+  double x = 0.0;
+  if (e < R * R) {
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int c = 0; c < Z::CS; ++c) x += a.H[(q0 + g) * Z::kH + c * R * R + e];
+  } else {
+#pragma unroll 4
+    for (int g = 0; g < G; ++g) x += a.S[(q0 + g) * R * kD + e - R * R];
+  }
+  a.group[(size_t)bkv * kSize + e] = x;
+}
+
+// First half of a round.  Workgroups [0, B Hkv) (4 B Hkv if SHARED), a KV head each:
 //   B_K = H_K^-1 S_K,
 //   M_K = (sum_g S_Q,g^T + lambda_pK B_K^T)(sum_g H_Q,g + lambda_pK B_K B_K^T)^-1,
 //   S_K, H_K of A_K = K M_K.
 // The others, a query head each: B_Q = H_Q^-1 S_Q (the next launch reads it).
-template <int R>
+// SHARED: the workgroups of a head all solve for the same M and share the sums.  G alone is 128 KB, 2 us
+// for one compute unit, and its products take a chain of MFMAs nearly as long as a solve at r = 16.
+template <int R, bool SHARED>
 __global__ __launch_bounds__(kAlgThreads) void prefill_round_k_kernel(const PfState a) {
   using Z = PfAlg<R>;
   extern __shared__ __align__(16) double pf_alg[];
   double* const X = pf_alg;
   double* const Ys = X + Z::kX;
-  double* const Pl = Ys + Z::kX;
-  double* const Cl = Pl + 2 * Z::kP;
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
-  const bool iskv = (int)blockIdx.x < a.BHkv;
-  const size_t own = iskv ? a.BHq + blockIdx.x : blockIdx.x - a.BHkv;  // row of S, H, G
+  constexpr int kParts = SHARED ? 4 : 1;
+  const bool iskv = (int)blockIdx.x < a.BHkv * kParts;
+  const int part = iskv ? (int)blockIdx.x % kParts : 0;
+  const size_t own = iskv ? (int)blockIdx.x / kParts : (int)blockIdx.x - a.BHkv * kParts;
+  const int b = (int)own / a.Hkv, kvh = (int)own - b * a.Hkv, G = a.Hq / a.Hkv;
+  const size_t q0 = (size_t)b * a.Hq + (size_t)kvh * G;  // a KV head's query heads
   f64x4 d[Z::TPW];
-  load_tiles<R>(d, w, lane, a.H + own * R * R, a.S + own * R * kD, 1);
-  solve_tiles<R>(d, Pl, Cl, w, lane);
+  load_tiles<R>(d, w, lane, (iskv ? a.HK : a.H) + own * Z::kH, (iskv ? a.SK : a.S) + own * R * kD);
+  // On its way during the first solve: the sums of the first query heads; during the second: G.
+  constexpr int kPre = R <= 16 ? 3 : R <= 32 ? 2 : 1;
+  using Part = PfPart<R, SHARED>;
+  const Part share(part, w);
+  double pre[kPre][Z::kRaw], gram[Part::kSteps];
+  if constexpr (kGroupSums<R>) {
+    const double* group = a.group + (iskv ? own : 0) * R * (R + kD);
+    fetch_tiles<R, 1>(pre[0], w, lane, group, group + R * R);
+  } else {
+#pragma unroll
+    for (int g = 0; g < kPre; ++g) {
+      const size_t head = iskv ? q0 + min(g, G - 1) : own;
+      fetch_tiles<R>(pre[g], w, lane, a.H + head * Z::kH, a.S + head * R * kD);
+    }
+  }
+  solve_tiles<R>(d, Ys, w, lane);
   if (!iskv) {
     double* BQ = a.BQ + own * R * kD;
     float* B_Q = a.B_Q + own * R * kD;
@@ -825,66 +953,77 @@ __global__ __launch_bounds__(kAlgThreads) void prefill_round_k_kernel(const PfSt
     });
     return;
   }
-  const int bkv = blockIdx.x, b = bkv / a.Hkv, kvh = bkv - b * a.Hkv, G = a.Hq / a.Hkv;
-  const size_t q0 = (size_t)b * a.Hq + (size_t)kvh * G;  // the group's query heads
   if (16 * Z::RT > R)
     for (int e = t; e < (16 * Z::RT - R) * kLdx; e += kAlgThreads) X[R * kLdx + e] = 0.0;
   {
-    float* B_K = a.B_K + (size_t)bkv * R * kD;
+    float* B_K = a.B_K + own * R * kD;
+    const bool keep = a.last && part == 0;
     store_solution<R>(d, w, lane, [&](int i, int j, double x) {
       X[i * kLdx + j] = x;
-      if (a.last) B_K[i * kD + j] = (float)x;
+      if (keep) B_K[i * kD + j] = (float)x;
     });
   }
+  // (the padding of the system is the identity, to which padding of X adds nothing)
+  if constexpr (kGroupSums<R>) {
+    take_tiles<R, 1>(d, pre[0], false, true);
+  } else {
+#pragma unroll
+    for (int g = 0; g < kPre; ++g) take_tiles<R>(d, pre[g], g > 0, g < G);
+#pragma unroll 2
+    for (int g = kPre; g < G; ++g) {
+      double x[Z::kRaw];
+      fetch_tiles<R>(x, w, lane, a.H + (q0 + g) * Z::kH, a.S + (q0 + g) * R * kD);
+      take_tiles<R>(d, x, true, true);
+    }
+  }
+  pad_tiles<R>(d, w, lane);
+  load_gram(gram, a.G + (a.BHq + own) * kD * kD, share, lane);
   lds_barrier();
-  // (the padding of the system comes in as the identity, to which padding of X adds nothing)
-  load_tiles<R>(d, w, lane, a.H + q0 * R * R, a.S + q0 * R * kD, G);
-  double gram[32];  // on its way during the second solve
-  load_gram(gram, a.G + own * kD * kD, w, lane);
   add_rhs<R>(d, X, a.lam_pK, w, lane);
-  add_gram<R>(d, X, a.lam_pK, w, lane);
+  add_gram<R>(d, X, Ys, a.lam_pK, w, lane);
   lds_barrier();  // X has been read
-  solve_tiles<R>(d, Pl, Cl, w, lane);
+  solve_tiles<R>(d, Ys, w, lane);
   store_solution<R>(d, w, lane, [&](int i, int j, double x) { X[i * kLdx + j] = x; });
   lds_barrier();
-  if (a.last) pack_operand<R>(X, a.M + own * PfShape<R>::mpack_units, t);
-  sums_of<R>(X, Ys, gram, a.S + own * R * kD, a.H + own * R * R, w, lane);
+  if (a.last && part == 0) pack_operand<R>(X, a.M + (a.BHq + own) * PfShape<R>::mpack_units, t);
+  sums_of<R>(X, Ys, gram, share, a.SK_new + own * R * kD, a.HK_new + own * Z::kH, w, lane);
 }
 
-// Second half, a query head per workgroup: with the sums of the new A_K,
+// Second half, a query head per workgroup (SHARED: per four): with the sums of the new A_K,
 //   M_Q = (S_K^T + lambda_pQ B_Q^T)(H_K + lambda_pQ B_Q B_Q^T)^-1,  and S_Q, H_Q of A_Q = Q M_Q.
-template <int R>
+template <int R, bool SHARED>
 __global__ __launch_bounds__(kAlgThreads) void prefill_round_q_kernel(const PfState a) {
   using Z = PfAlg<R>;
   extern __shared__ __align__(16) double pf_alg[];
   double* const X = pf_alg;
   double* const Ys = X + Z::kX;
-  double* const Pl = Ys + Z::kX;
-  double* const Cl = Pl + 2 * Z::kP;
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int bh = blockIdx.x, b = bh / a.Hq, kvh = (bh - b * a.Hq) / (a.Hq / a.Hkv);
-  const size_t kv = a.BHq + (size_t)b * a.Hkv + kvh;
+  constexpr int kParts = SHARED ? 4 : 1;
+  const int bh = blockIdx.x / kParts;
+  using Part = PfPart<R, SHARED>;
+  const Part share(blockIdx.x % kParts, w);
+  const int b = bh / a.Hq, kvh = (bh - b * a.Hq) / (a.Hq / a.Hkv);
+  const size_t kv = (size_t)b * a.Hkv + kvh;
   const double* BQ = a.BQ + (size_t)bh * R * kD;
   f64x4 d[Z::TPW];
-  load_tiles<R>(d, w, lane, a.H + kv * R * R, a.S + kv * R * kD, 1);
+  load_tiles<R>(d, w, lane, a.HK_new + kv * Z::kH, a.SK_new + kv * R * kD);
 #pragma unroll 8
   for (int e = t; e < R * kD; e += kAlgThreads) X[(e / kD) * kLdx + e % kD] = BQ[e];
   if (16 * Z::RT > R)
     for (int e = t; e < (16 * Z::RT - R) * kLdx; e += kAlgThreads) X[R * kLdx + e] = 0.0;
-  double gram[32];
-  if (!a.last) load_gram(gram, a.G + (size_t)bh * kD * kD, w, lane);
+  double gram[Part::kSteps];
+  if (!a.last) load_gram(gram, a.G + (size_t)bh * kD * kD, share, lane);
   lds_barrier();
   add_rhs<R>(d, X, a.lam_pQ, w, lane);
-  add_gram<R>(d, X, a.lam_pQ, w, lane);
+  add_gram<R>(d, X, Ys, a.lam_pQ, w, lane);
   lds_barrier();  // X has been read
-  solve_tiles<R>(d, Pl, Cl, w, lane);
+  solve_tiles<R>(d, Ys, w, lane);
   store_solution<R>(d, w, lane, [&](int i, int j, double x) { X[i * kLdx + j] = x; });
   lds_barrier();
   if (a.last)
     pack_operand<R>(X, a.M + (size_t)bh * PfShape<R>::mpack_units, t);
   else
-    sums_of<R>(X, Ys, gram, a.S + (size_t)bh * R * kD,
-               a.H + (size_t)bh * R * R, w, lane);
+    sums_of<R>(X, Ys, gram, share, a.S + (size_t)bh * R * kD, a.H + (size_t)bh * Z::kH, w, lane);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1030,7 +1169,7 @@ int reduce_chunks(int heads, int l, int rows) {
 
 struct PrefillWs {
   void* part;
-  double *G, *S, *H, *BQ;
+  double *G, *S, *H, *SK2, *HK2, *BQ, *group;  // (S and H: query heads, then KV heads)
   uint4* M;
   size_t bytes;
 };
@@ -1052,8 +1191,11 @@ PrefillWs carve_prefill(void* base, const lrqk_shape& s) {
   w.part = take(parts * S::part_bytes);
   w.G = static_cast<double*>(take(heads * kD * kD * sizeof(double)));
   w.S = static_cast<double*>(take(heads * R * kD * sizeof(double)));
-  w.H = static_cast<double*>(take(heads * R * R * sizeof(double)));
+  w.H = static_cast<double*>(take(heads * PfAlg<R>::kH * sizeof(double)));
+  w.SK2 = static_cast<double*>(take((heads - BHq) * R * kD * sizeof(double)));
+  w.HK2 = static_cast<double*>(take((heads - BHq) * PfAlg<R>::kH * sizeof(double)));
   w.BQ = static_cast<double*>(take(BHq * R * kD * sizeof(double)));
+  w.group = static_cast<double*>(take(kGroupSums<R> ? (heads - BHq) * R * (R + kD) * sizeof(double) : 0));
   w.M = static_cast<uint4*>(take(heads * S::mpack_units * sizeof(uint4)));
   w.bytes = off;
   return w;
@@ -1063,10 +1205,13 @@ PrefillWs carve_prefill(void* base, const lrqk_shape& s) {
 template <int R, int NS>
 struct PfKernels {
   static hipError_t allow() {
-    static std::atomic<uint64_t> reduce{0}, rk{0}, rq{0}, apply{0};
+    static std::atomic<uint64_t> reduce{0}, rk[2], rq[2], apply{0};
+    constexpr size_t lds = PfAlg<R>::lds_bytes;
     hipError_t e = raise_dynamic_lds_once(prefill_reduce_kernel<R, NS>, PfReduce<R, NS>::lds_bytes, reduce);
-    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_round_k_kernel<R>, PfAlg<R>::lds_bytes, rk);
-    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_round_q_kernel<R>, PfAlg<R>::lds_bytes, rq);
+    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_round_k_kernel<R, false>, lds, rk[0]);
+    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_round_k_kernel<R, true>, lds, rk[1]);
+    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_round_q_kernel<R, false>, lds, rq[0]);
+    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_round_q_kernel<R, true>, lds, rq[1]);
     if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_apply_kernel<R, NS>, apply_lds_bytes<R>(), apply);
     return e;
   }
@@ -1087,18 +1232,33 @@ hipError_t run_prefill(const lrqk_shape& s, const void* Q, const void* K, float*
   hipLaunchKernelGGL((prefill_reduce_kernel<R, NS>), dim3(nchunk * heads), dim3(kRedThreads),
                      (PfReduce<R, NS>::lds_bytes), st, Q, K, A_Q, A_K, w.part, BHq, l, lk, nchunk,
                      per_chunk);
-  hipLaunchKernelGGL((prefill_sum_kernel<R>),
+  hipLaunchKernelGGL((prefill_sum_kernel<R, PfAlg<R>::CS>),
                      dim3(ceil_div((S::GB + S::HB0) * 1024 + R * R, 256) * heads),
                      dim3(256), 0, st, w.part, w.G, w.S, w.H, nchunk);
   PfState a;
-  a.G = w.G; a.S = w.S; a.H = w.H; a.BQ = w.BQ; a.M = w.M; a.B_Q = B_Q; a.B_K = B_K;
+  a.G = w.G; a.S = w.S; a.H = w.H; a.BQ = w.BQ; a.M = w.M; a.group = w.group; a.B_Q = B_Q;
+  a.B_K = B_K;
   a.Hq = s.Hq; a.Hkv = s.Hkv; a.BHq = BHq; a.BHkv = BHkv; a.lam_pQ = lam_pQ; a.lam_pK = lam_pK;
+  // four workgroups per head while there is a compute unit for every one
+  const bool share_k = 4 * BHkv + BHq <= 256, share_q = 4 * BHq <= 256;
+  double *SK = w.S + (size_t)BHq * R * kD, *HK = w.H + (size_t)BHq * PfAlg<R>::kH;
+  double *SK_new = w.SK2, *HK_new = w.HK2;
+  constexpr size_t lds = PfAlg<R>::lds_bytes;
   for (int it = 0; it < n_iter; ++it) {
     a.last = it + 1 == n_iter;
-    hipLaunchKernelGGL((prefill_round_k_kernel<R>), dim3(heads), dim3(kAlgThreads),
-                       PfAlg<R>::lds_bytes, st, a);
-    hipLaunchKernelGGL((prefill_round_q_kernel<R>), dim3(BHq), dim3(kAlgThreads),
-                       PfAlg<R>::lds_bytes, st, a);
+    a.SK = SK; a.HK = HK; a.SK_new = SK_new; a.HK_new = HK_new;
+    if constexpr (kGroupSums<R>)
+      hipLaunchKernelGGL((prefill_group_kernel<R>), dim3(BHkv * (R * (R + kD) / 256)), dim3(256), 0, st, a);
+    if (share_k)
+      hipLaunchKernelGGL((prefill_round_k_kernel<R, true>), dim3(4 * BHkv + BHq), dim3(kAlgThreads), lds, st, a);
+    else
+      hipLaunchKernelGGL((prefill_round_k_kernel<R, false>), dim3(BHkv + BHq), dim3(kAlgThreads), lds, st, a);
+    if (share_q && !a.last)
+      hipLaunchKernelGGL((prefill_round_q_kernel<R, true>), dim3(4 * BHq), dim3(kAlgThreads), lds, st, a);
+    else
+      hipLaunchKernelGGL((prefill_round_q_kernel<R, false>), dim3(BHq), dim3(kAlgThreads), lds, st, a);
+    std::swap(SK, SK_new);
+    std::swap(HK, HK_new);
   }
   // 32-row units per wavefront: enough workgroups to fill the chip a few times over
   const int row_units = ceil_div(l, 32);

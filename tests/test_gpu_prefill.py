@@ -193,6 +193,15 @@ def test_prefill_tile_edges(r, l, kv_dtype):
     run_prefill_case(pf_cfg(r=r, l=l, kv_dtype=kv_dtype, k=32, C=32))
 
 
+@pytest.mark.parametrize("r", [8, 16, 32, 64])
+@pytest.mark.parametrize("B", [1, 10, 30])
+def test_prefill_shared_and_unshared_sums(B, r):
+    """The r x d algebra of a head by four workgroups or by one, as compute units are to spare: by four
+    for all (16 + 4 heads), for key heads only (80 + 20), by one (240 + 60).  Three rounds."""
+    say(f"prefill r={r}, {8 * B} + {2 * B} heads")
+    run_prefill_case(pf_cfg(B=B, Hq=8, Hkv=2, l=200, r=r, k=32, C=32), n_iter=3)
+
+
 def test_prefill_eight_heads_a_group_and_many_chunks():
     say("prefill G=8, 1 KV head, fp32 rows, l = 20011")
     run_prefill_case(pf_cfg(Hq=8, Hkv=1, l=20011, r=16, kv_dtype="f32"))
