@@ -14,14 +14,16 @@
 //  2. factor_inverse_kernel: P^-1 and N^-1 (what changes between rounds is a low-rank correction
 //     of these two), a workgroup per matrix.
 //  3. factor_rounds_kernel: the n_iter rounds and the line-search gradient steps on B_Q and B_K in
-//     place, a workgroup per (batch, KV head).
-// Times in us at k = 2048, w = 64, 32 + 8 heads, r = 32: 11 + 10 + 13; at 8 x (28 + 4) heads, k = 1024, r = 64:
-// 38 + 28 + 31.  (Factorising in fp32 with a row per lane, P once and the k_hat system in every
+//     place, workgroups per (batch, KV head).
+// Times in us at k = 2048, w = 64, 32 + 8 heads, r = 32: 9 + 10 + 9.5; at 8 x (28 + 4) heads, k = 1024, r = 64:
+// 38.5 + 23 + 22.  (Factorising in fp32 with a row per lane, P once and the k_hat system in every
 // round, all in one wavefront per head, launches 2 and 3 took 30 and 114 us.)  What is left is
-// latency: the loads at the start of each launch, a chain of r / 4 elimination steps (0.5 us each
-// at r = 32, 0.8 us at r = 64).
+// latency: the loads at the start of each launch (2 us; 5 to 9 us at the second shape, where every
+// compute unit reads 130 and 265 KB), the eliminations (3.5 and 9 us) and the rounds (2 and 5 us each).
 //
 // Sums over rows are fp32 (App. B.1 runs these updates in fp32), the rest fp64.
+#include <algorithm>
+
 #include "lrqk_alg64.h"
 #include "lrqk_device.h"
 #include "lrqk_internal.h"
@@ -55,9 +57,25 @@ struct SolveArgs {
   float* B_K;            // [B,Hkv,r,d]  updated in place
   float* q_hat;          // [B,Hq,r]
   float* k_hat;          // [B,Hkv,r]
-  int Hq, Hkv, BHq, nchunk, n_iter;
+  int Hq, Hkv, BHq, BHkv, nchunk, n_iter;
+  int parts;             // workgroups per KV head in the rounds
   float lam1, lam2;
 };
+
+// Workgroup i of `units` * parts as (unit, part).  Workgroups go to the eight compute dies in turn: all the
+// parts of a unit, and the same unit in every launch, on one of them where the units divide evenly, so
+// that what one launch leaves is in the L2 that the next one reads through: 90.8 -> 83.8 us for the whole at
+// 8 x (28 + 4) heads, r = 64, 27.5 -> 27.1 at 32 + 8 heads, r = 32.
+__device__ __forceinline__ void place(int i, int units, int parts, int& unit, int& part) {
+  if (units % 8 == 0) {
+    const int j = i >> 3;
+    unit = (i & 7) + 8 * (j / parts);
+    part = j % parts;
+  } else {
+    unit = i / parts;
+    part = i % parts;
+  }
+}
 
 // ---- 2. the inverses --------------------------------------------------------------------------
 // One workgroup of 8 wavefronts per matrix, all in fp64:
@@ -88,9 +106,12 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
   double* const X = inv_lds;            // [16 RT][kLdb]  B
   double* const xs = X + Z::kX;         // [d]  q or k
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int m = blockIdx.x;
-  const bool isq = m < a.BHq;
-  const size_t head = isq ? m : m - a.BHq;
+  const int G = a.Hq / a.Hkv;
+  int bkv, job;
+  place(blockIdx.x, a.BHkv, G + 1, bkv, job);
+  const bool isq = job < G;
+  const size_t head = isq ? (size_t)(bkv / a.Hkv) * a.Hq + (size_t)(bkv % a.Hkv) * G + job : bkv;
+  const size_t m = isq ? head : a.BHq + head;
   const float* __restrict__ Bm = (isq ? a.B_Q : a.B_K) + head * R * kD;
   const float* __restrict__ part = a.gram_om + head * a.nchunk * (size_t)(kEntries + R);
   const int tr = w * Z::TPW / Z::RT, tc0 = w * Z::TPW % Z::RT;
@@ -144,7 +165,7 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
   }
   lds_barrier();
   // c (or nb): 8 lanes a row
-  double* const out = a.inv + (size_t)m * (kEntries + R);
+  double* const out = a.inv + m * (kEntries + R);
   {
     const int row = t >> 3, part8 = t & 7;
     double c = 0.0;
@@ -185,201 +206,219 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
 }
 
 // ---- 3. the rounds ------------------------------------------------------------------------------
-// One workgroup per (batch, KV head), wavefront g < G per query head of the group; lane i holds
-// element i of a vector.  With P^-1 and N^-1 at hand a round is products of an r x r matrix with a
-// vector (the vector's elements as LDS broadcasts, the matrix symmetric: lane i reads column i):
+// A wavefront per query head of a group, two at r = 64; lane i holds element i of a vector.  With P^-1
+// and N^-1 at hand a round is products of r x r matrices with vectors (P^-1 in registers, symmetric: lane i
+// holds 32 elements of column i, 64 being more than fit beside the rest; the vector's elements as LDS
+// broadcasts; N^-1 in LDS, its products by MFMA):
 //   q_hat = m_lq M_rq^-1, M_rq = P + lambda_d1 k_hat^T k_hat a rank-one change of P:
 //     z = k_hat P^-1,  v = m_lq P^-1 = y0 + lambda_d1 (q.k) z  (y0 = c P^-1),
 //     q_hat = v - z * lambda_d1 (k_hat . v) / (1 + lambda_d1 (k_hat . z))
 //   k_hat = rhs M^-1, M = N + lambda_d1 Q^T Q (Q: the group's q_hat as rows) a rank-G change of N:
 //     W = Q N^-1,  u = rhs N^-1 = nb N^-1 + lambda_d1 sum_g (q_g.k) w_g,
 //     k_hat = u - lambda_d1 s W  with  (I + lambda_d1 W Q^T) s = Q u,
-//   a G x G system that every wavefront solves for itself, lane 8 a + b holding element (a, b).
+//   a G x G system that the first wavefront sets up in one tile, W Q^T and Q u from one chain of MFMAs,
+//   and solves with one or two pivot steps (shuffles between lanes, in every wavefront, took 2 us a round).
 // fp64 throughout, so that the corrections lose nothing.
 // Then one gradient step on 1/2 |x_hat B - x|^2 for every B_Q of the group and B_K (App. A.2): with
 // e = x_hat B - x the gradient is x_hat^T e and x_hat times it |x_hat|^2 e, so the step length
 // <e, |x_hat|^2 e> / | |x_hat|^2 e |^2 is 1 / |x_hat|^2 and a column of B needs nothing from the
-// others: a thread per column.  (e = 0 or x_hat = 0: B stays.)
-constexpr int kRoundThreads = kMaxG * 64;
+// others: eight rows of a column per thread.  (e = 0 or x_hat = 0: B stays.)
+// Those steps read and write G + 1 matrices, 256 KB at r = 64 and G = 7, which took one compute unit
+// 8 us.  So the matrices of a group are dealt out over `parts` workgroups, all of which go through the
+// rounds (on compute units that would be idle) and whose first matrix is on its way meanwhile.  The whole
+// call, 8 x (28 + 4) heads, r = 64, with 1, 2, 4, 8 of them: 101.7, 90.8, 85.7, 83.5 us; 32 + 8 heads, r = 32,
+// with 1 and 5: 29.5, 27.0; but 8 x (32 + 8) heads with 4 and 5, that is 256 and 320: 36.1, 43.8.
 template <int R>
 struct RoundShape {
+  static constexpr int kPerHead = R / 32;  // wavefronts per query head
+  static constexpr int kWaves = kMaxG * kPerHead, kThreads = 64 * kWaves;
+  static constexpr int kAcross = kThreads / kD;  // threads per column of B
+  static constexpr int kRows = R / kAcross;      // rows of a column per thread
   static constexpr int LDV = R + 2;  // LDS row stride of the exchanged vectors: 8 rows, 8 bank groups
+  // q_hat (padded to a tile); q_hat N^-1, u (padded); a vector per wavefront; parts of z
+  static constexpr int kVectors = 16 + 16 + kWaves + kWaves;
   static constexpr size_t lds_bytes =
-      ((size_t)R * R + 3 * kMaxG * LDV + kMaxG + kMaxG + 1) * sizeof(double);
+      ((size_t)R * R + kVectors * LDV + 128 + kAcross * kD + 3 * kMaxG + 1) * sizeof(double);
 };
 
 template <int R, bool BF16>
-__global__ __launch_bounds__(kRoundThreads) void factor_rounds_kernel(SolveArgs a) {
+__global__ __launch_bounds__(RoundShape<R>::kThreads) void factor_rounds_kernel(SolveArgs a) {
   using Z = RoundShape<R>;
   constexpr int kEntries = R * R, LDV = Z::LDV;
+  constexpr int kRoundThreads = Z::kThreads;
   constexpr size_t ROWB = kD * (BF16 ? 2 : 4);
   extern __shared__ __align__(16) double rnd_lds[];
   double* const n_s = rnd_lds;                  // [r][r]  N^-1
-  double* const qh_s = n_s + kEntries;          // [8][LDV]  q_hat of the group
-  double* const wv_s = qh_s + kMaxG * LDV;      // [8][LDV]  q_hat N^-1
-  double* const vec_s = wv_s + kMaxG * LDV;     // [8][LDV]  one vector per wavefront
-  double* const qk_s = vec_s + kMaxG * LDV;     // [8]
+  double* const qh_s = n_s + kEntries;          // [16][LDV]  q_hat of the group
+  double* const wv_s = qh_s + 16 * LDV;         // [16][LDV]  q_hat N^-1; row 8: u
+  double* const vec_s = wv_s + 16 * LDV;        // [kWaves][LDV]  one vector per wavefront
+  double* const z_s = vec_s + Z::kWaves * LDV;  // [kWaves][LDV]  part of a product with P^-1
+  double* const piv_s = z_s + Z::kWaves * LDV;  // [128]
+  double* const part_s = piv_s + 128;           // [kAcross][d]
+  double* const s_s = part_s + Z::kAcross * kD; // [8]  lambda_d1 s
+  double* const qk_s = s_s + kMaxG;             // [8]  lambda_d1 q.k
   double* const inv_norm_s = qk_s + kMaxG;      // [9]  1 / |x_hat|^2 of the group's q_hat, of k_hat
-  const int t = threadIdx.x, lane = t & 63, g = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int g = w % kMaxG, h = w / kMaxG;  // head, and which rows of P^-1
   const int G = a.Hq / a.Hkv;
-  const int bkv = blockIdx.x, b = bkv / a.Hkv, kvh = bkv - b * a.Hkv;
+  int bkv, part;
+  place(blockIdx.x, a.BHkv, a.parts, bkv, part);
+  const int b = bkv / a.Hkv, kvh = bkv - b * a.Hkv;
+  const size_t q0 = (size_t)b * a.Hq + (size_t)kvh * G;
   const bool act = g < G;
-  const int bh = b * a.Hq + kvh * G + (act ? g : 0);
+  const size_t bh = q0 + (act ? g : 0);
   const bool row = lane < R;
   const int li = row ? lane : 0;  // keeps the loads of idle lanes in bounds
-  const double* __restrict__ inv_q = a.inv + (size_t)bh * (kEntries + R);
+  const double* __restrict__ inv_q = a.inv + bh * (kEntries + R);
   const double* __restrict__ inv_k = a.inv + (size_t)(a.BHq + bkv) * (kEntries + R);
-  const float* qp = a.q + (size_t)bh * kD;
+  const float* qp = a.q + bh * kD;
   const char* kp = static_cast<const char*>(a.k_new) + (size_t)bkv * ROWB;
+  // the gradient steps: rows kRows sub .. of column col of a matrix
+  const int col = t & (kD - 1), sub = t / kD;
+  auto matrix = [&](int job) {
+    return (job < G ? a.B_Q + (q0 + job) * R * kD : a.B_K + (size_t)bkv * R * kD) +
+           sub * Z::kRows * kD + col;
+  };
 
-  double pinv[R];
-#pragma unroll
-  for (int c = 0; c < R; ++c) pinv[c] = inv_q[c * R + li];
-  const double cvec = inv_q[kEntries + li], nb = inv_k[kEntries + li];
   for (int e = t; e < kEntries / 2; e += kRoundThreads)
     reinterpret_cast<double2*>(n_s)[e] = reinterpret_cast<const double2*>(inv_k)[e];
-  for (int e = t; e < 2 * kMaxG * LDV; e += kRoundThreads) qh_s[e] = 0.0;  // and wv_s
+  double pinv[32];
+#pragma unroll
+  for (int c = 0; c < 32; ++c) pinv[c] = inv_q[(32 * h + c) * R + li];
+  const double cvec = inv_q[kEntries + li], nb = inv_k[kEntries + li];
+  float bv[Z::kRows];
+#pragma unroll
+  for (int i = 0; i < Z::kRows; ++i) bv[i] = matrix(part)[i * kD];
+  for (int e = t; e < 32 * LDV; e += kRoundThreads) qh_s[e] = 0.0;  // and wv_s
   const double qk = wave_sum_f64((double)qp[lane] * kv_load<BF16>(kp, lane) +
                                  (double)qp[lane + 64] * kv_load<BF16>(kp, lane + 64));
-  if (lane == 0) qk_s[g] = act ? qk : 0.0;
-  double* const vec = vec_s + g * LDV;
   const double lam1 = a.lam1;
+  if (lane == 0) qk_s[g] = act ? lam1 * qk : 0.0;
+  double* const vec = vec_s + w * LDV;
   // x M of the vector x that lane i holds element i of
   auto put = [&](double x) {
     __builtin_amdgcn_wave_barrier();
     if (row) vec[lane] = x;
     __builtin_amdgcn_wave_barrier();
   };
-  auto times_pinv = [&](double x) {
+  auto times_pinv = [&](double x) {  // (a barrier at r = 64)
     put(x);
     double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-    for (int c = 0; c < R; c += 2) {
-      const double2 v = *reinterpret_cast<const double2*>(vec + c);
+    for (int c = 0; c < 32; c += 2) {
+      const double2 v = *reinterpret_cast<const double2*>(vec + 32 * h + c);
       s0 = __builtin_fma(pinv[c], v.x, s0);
       s1 = __builtin_fma(pinv[c + 1], v.y, s1);
     }
-    return row ? s0 + s1 : 0.0;
-  };
-  auto times_ninv = [&](double x) {
-    put(x);
-    double s0 = 0.0, s1 = 0.0;
-#pragma unroll 16
-    for (int c = 0; c < R; c += 2) {
-      const double2 v = *reinterpret_cast<const double2*>(vec + c);
-      s0 = __builtin_fma(n_s[c * R + li], v.x, s0);
-      s1 = __builtin_fma(n_s[(c + 1) * R + li], v.y, s1);
+    s0 += s1;
+    if (Z::kPerHead > 1) {
+      if (row) z_s[w * LDV + lane] = s0;
+      lds_barrier();
+      s0 = z_s[g * LDV + li] + z_s[(g + kMaxG) * LDV + li];
     }
-    return row ? s0 + s1 : 0.0;
+    return row ? s0 : 0.0;
   };
   const double y0 = times_pinv(cvec);
   __syncthreads();  // n_s, qk_s; qh_s and wv_s are zero
-  // k0 = nb N^-1, also the initial guess (lambda_d1 = 0): every wavefront an eighth of the sum
+  // k0 = nb N^-1, also the initial guess (lambda_d1 = 0): every wavefront its share of the sum
   {
+    constexpr int kShare = R / Z::kWaves;
     put(nb);
     double s0 = 0.0;
 #pragma unroll
-    for (int c = 0; c < R / 8; ++c)
-      s0 = __builtin_fma(n_s[(g * (R / 8) + c) * R + li], vec[g * (R / 8) + c], s0);
+    for (int c = 0; c < kShare; ++c)
+      s0 = __builtin_fma(n_s[(w * kShare + c) * R + li], vec[w * kShare + c], s0);
     put(s0);
   }
   lds_barrier();
   double k0 = 0.0;
 #pragma unroll
-  for (int gg = 0; gg < kMaxG; ++gg) k0 += vec_s[gg * LDV + li];
+  for (int ww = 0; ww < Z::kWaves; ++ww) k0 += vec_s[ww * LDV + li];
   if (!row) k0 = 0.0;
   lds_barrier();
+  const int c16 = lane & 15, k4 = lane >> 4;
   double k_hat = k0, q_hat = 0.0;
+#pragma unroll 1
   for (int it = 0; it < a.n_iter; ++it) {
     const double z = times_pinv(k_hat);
     const double v = __builtin_fma(lam1 * qk, z, y0);
     const double kv_ = wave_sum_f64(k_hat * v), kz = wave_sum_f64(k_hat * z);
     q_hat = __builtin_fma(-z, lam1 * kv_ / __builtin_fma(lam1, kz, 1.0), v);
-    const double wv = times_ninv(q_hat);
-    if (it > 0) lds_barrier();  // the previous round's vectors have been read
-    if (act && row) {
-      qh_s[g * LDV + lane] = q_hat;
-      wv_s[g * LDV + lane] = wv;
+    if (act && row && h == 0) qh_s[g * LDV + lane] = q_hat;
+    lds_barrier();
+    const double* qa = qh_s + c16 * LDV + k4;
+    if (w < R / 16) {  // W, 16 columns a wavefront
+      f64x4 x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+      for (int c = 0; c < R; c += 4) x = mfma_f64(qa[c], n_s[(c + k4) * R + 16 * w + c16], x);
+#pragma unroll
+      for (int e = 0; e < 2; ++e) wv_s[(4 * e + k4) * LDV + 16 * w + c16] = x[e];
     }
     lds_barrier();
-    double u = k0;
+    if (w == 0) {
+      double u = k0;
 #pragma unroll
-    for (int gg = 0; gg < kMaxG; ++gg)
-      u = __builtin_fma(lam1 * qk_s[gg], wv_s[gg * LDV + li], u);
-    if (!row) u = 0.0;
-    put(u);
-    const int ra = lane >> 3, cb = lane & 7;
-    double kab = 0.0, ta = 0.0;
+      for (int gg = 0; gg < kMaxG; ++gg) u = __builtin_fma(qk_s[gg], wv_s[gg * LDV + li], u);
+      __builtin_amdgcn_wave_barrier();
+      if (row) wv_s[8 * LDV + lane] = u;
+      __builtin_amdgcn_wave_barrier();
+      // element (a, b) is q_hat_a . w_b, and (a, 8) is q_hat_a . u
+      const double* wb = wv_s + c16 * LDV + k4;
+      f64x4 d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 8
-    for (int c = 0; c < R; c += 2) {
-      const double2 x = *reinterpret_cast<const double2*>(qh_s + ra * LDV + c);
-      const double2 y = *reinterpret_cast<const double2*>(wv_s + cb * LDV + c);
-      kab = __builtin_fma(x.x, y.x, __builtin_fma(x.y, y.y, kab));
-    }
+      for (int c = 0; c < R; c += 4) d = mfma_f64(qa[c], wb[c], d);
 #pragma unroll
-    for (int c = 0; c < R; c += 8) ta = __builtin_fma(qh_s[ra * LDV + c + cb], vec[c + cb], ta);
-    ta += dpp_f64<0xB1>(ta);
-    ta += dpp_f64<0x4E>(ta);
-    ta += dpp_f64<0x141>(ta);
-    kab = __builtin_fma(lam1, kab, ra == cb ? 1.0 : 0.0);
-    // Gauss-Jordan over lanes (rows and columns beyond G are those of the identity, with ta = 0)
-    for (int p = 0; p < G; ++p) {
-      const double ap = __shfl(kab, ra * 8 + p), pb = __shfl(kab, p * 8 + cb);
-      const double tp = __shfl(ta, p * 8), pp = lane_value_f64(kab, p * 9);
-      const double f = ra == p ? 0.0 : ap * recip(pp);
-      kab = __builtin_fma(-f, pb, kab);
-      ta = __builtin_fma(-f, tp, ta);
+      for (int e = 0; e < 4; ++e)
+        if (c16 != 8) d[e] = __builtin_fma(lam1, d[e], 4 * e + k4 == c16 ? 1.0 : 0.0);
+      pivot_step(d, 0, piv_s, lane);
+      if (G > 4) pivot_step(d, 1, piv_s, lane);
+      if (c16 == 8) {
+        s_s[k4] = lam1 * d[0];
+        s_s[4 + k4] = G > 4 ? lam1 * d[1] : 0.0;
+      }
     }
-    const double sa = ta * recip(__shfl(kab, ra * 9));
-    k_hat = u;
+    lds_barrier();
+    k_hat = wv_s[8 * LDV + li];
 #pragma unroll
-    for (int gg = 0; gg < kMaxG; ++gg)
-      k_hat = __builtin_fma(-lam1 * lane_value_f64(sa, 8 * gg), wv_s[gg * LDV + li], k_hat);
+    for (int gg = 0; gg < kMaxG; ++gg) k_hat = __builtin_fma(-s_s[gg], wv_s[gg * LDV + li], k_hat);
     if (!row) k_hat = 0.0;
   }
-  if (act && row) a.q_hat[(size_t)bh * R + lane] = (float)q_hat;
-  if (g == 0 && row) a.k_hat[(size_t)bkv * R + lane] = (float)k_hat;
 
   // gradient steps
   const double nq = wave_sum_f64(q_hat * q_hat), nk = wave_sum_f64(k_hat * k_hat);
-  if (lane == 0) {
+  if (lane == 0 && h == 0) {
     inv_norm_s[g] = nq > 0.0 ? 1.0 / nq : 0.0;
     if (g == 0) inv_norm_s[kMaxG] = nk > 0.0 ? 1.0 / nk : 0.0;
   }
-  if (g == 0) put(k_hat);  // vec_s[0]
+  if (w == 0) put(k_hat);  // vec_s[0]
+  if (act && row && h == 0 && g % a.parts == part) a.q_hat[bh * R + lane] = (float)q_hat;
+  if (w == 0 && row && G % a.parts == part) a.k_hat[(size_t)bkv * R + lane] = (float)k_hat;
   lds_barrier();
-  for (int c = t; c < (G + 1) * kD; c += kRoundThreads) {
-    const int job = c / kD, col = c % kD;
+#pragma unroll 1
+  for (int job = part; job <= G; job += a.parts) {
     const bool isq = job < G;
-    const size_t head = isq ? (size_t)b * a.Hq + (size_t)kvh * G + job : bkv;
-    float* Bm = (isq ? a.B_Q : a.B_K) + head * R * kD + col;
-    const double* xh = isq ? qh_s + job * LDV : vec_s;
-    double s0 = -(double)(isq ? a.q[head * kD + col] : kv_load<BF16>(kp, col)), s1 = 0.0;
-    // (the column stays in registers between the two uses up to r = 32; at r = 64 it would push
-    // P^-1 out of them: 35 us instead of 31)
-    constexpr int U = R <= 32 ? R : 16;
-    float bv[U];
-#pragma unroll 1
-    for (int i0 = 0; i0 < R; i0 += U) {
+    float* Bm = matrix(job);
+    if (job != part) {
 #pragma unroll
-      for (int i = 0; i < U; ++i) bv[i] = Bm[(i0 + i) * kD];
-#pragma unroll
-      for (int i = 0; i < U; i += 2) {
-        s0 = __builtin_fma(xh[i0 + i], (double)bv[i], s0);
-        s1 = __builtin_fma(xh[i0 + i + 1], (double)bv[i + 1], s1);
-      }
+      for (int i = 0; i < Z::kRows; ++i) bv[i] = Bm[i * kD];
     }
-    const double step = (s0 + s1) * inv_norm_s[isq ? job : kMaxG];
-#pragma unroll 1
-    for (int i0 = 0; i0 < R; i0 += U) {
-      if (U < R) {
+    const double* xh = (isq ? qh_s + job * LDV : vec_s) + sub * Z::kRows;
+    double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-        for (int i = 0; i < U; ++i) bv[i] = Bm[(i0 + i) * kD];
-      }
-#pragma unroll
-      for (int i = 0; i < U; ++i)
-        Bm[(i0 + i) * kD] = (float)__builtin_fma(-xh[i0 + i], step, (double)bv[i]);
+    for (int i = 0; i < Z::kRows; i += 2) {
+      s0 = __builtin_fma(xh[i], (double)bv[i], s0);
+      s1 = __builtin_fma(xh[i + 1], (double)bv[i + 1], s1);
     }
+    part_s[sub * kD + col] = s0 + s1;
+    lds_barrier();
+    double e = -(double)(isq ? a.q[(q0 + job) * kD + col] : kv_load<BF16>(kp, col));
+#pragma unroll
+    for (int i = 0; i < Z::kAcross; ++i) e += part_s[i * kD + col];
+    const double step = e * inv_norm_s[isq ? job : kMaxG];
+#pragma unroll
+    for (int i = 0; i < Z::kRows; ++i)
+      Bm[i * kD] = (float)__builtin_fma(-xh[i], step, (double)bv[i]);
+    lds_barrier();  // part_s has been read
   }
 }
 
@@ -395,7 +434,7 @@ hipError_t launch_update_r(const lrqk_shape& s, const GramRows& ga, const SolveA
                      dim3(kGramThreads), 0, st, ga);
   hipLaunchKernelGGL((factor_inverse_kernel<R, BF16>), dim3(s.B * (s.Hq + s.Hkv)),
                      dim3(kInvThreads), InvShape<R>::lds_bytes, st, sa);
-  hipLaunchKernelGGL((factor_rounds_kernel<R, BF16>), dim3(s.B * s.Hkv), dim3(kRoundThreads),
+  hipLaunchKernelGGL((factor_rounds_kernel<R, BF16>), dim3(s.B * s.Hkv * sa.parts), dim3(RoundShape<R>::kThreads),
                      RoundShape<R>::lds_bytes, st, sa);
   return hipGetLastError();
 }
@@ -451,6 +490,9 @@ hipError_t launch_factor_update(const lrqk_shape& s, const float* A_K, const voi
       reinterpret_cast<char*>(ws) + round_up(BHq * g.nchunk * g.per_gram * sizeof(float), 256));
   sa.q = q; sa.k_new = k_new; sa.B_Q = B_Q; sa.B_K = B_K; sa.q_hat = q_hat; sa.k_hat = k_hat;
   sa.Hq = s.Hq; sa.Hkv = s.Hkv; sa.BHq = (int)BHq; sa.nchunk = g.nchunk; sa.n_iter = n_iter;
+  sa.BHkv = s.B * s.Hkv;
+  // as many as there are compute units for (one workgroup on each), at most one per matrix
+  sa.parts = std::max(1, std::min(s.Hq / s.Hkv + 1, 256 / sa.BHkv));
   sa.lam1 = lam1; sa.lam2 = lam2;
   const bool bf16 = s.kv_dtype == LRQK_KV_BF16;
   switch (s.r) {

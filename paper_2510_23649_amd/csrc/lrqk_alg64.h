@@ -56,28 +56,30 @@ __device__ __forceinline__ double pivot_factor(const double* D, const double* C,
   return k & 2 ? hi : lo;
 }
 
-// The operands N_q of the four steps of 4 pivots inside a symmetric positive definite 16 x 16 tile, by one
-// wavefront: in-place Gauss-Jordan elimination (a step's pivot columns start again as columns of the
-// identity).  The pivot columns are the pivot rows transposed, with the sign turned for rows that have been
-// pivots before.  P: 128 doubles of LDS that no other wavefront touches meanwhile; the LDS operations of
-// a wavefront keep their order, so nothing is waited for but the data.
-__device__ __forceinline__ f64x4 pivot_tile(f64x4 d, double* P, int lane) {
+// One step of in-place Gauss-Jordan elimination inside a 16 x 16 tile by one wavefront, the pivots rows
+// 4 q .. 4 q + 3 (a step's pivot columns start again as columns of the identity); returns the operand N_q by
+// which the pivot rows are multiplied.  The rows and columns up to the last pivot are symmetric positive
+// definite to begin with: the pivot columns are taken from the pivot rows, with the sign turned for rows
+// that have been pivots before.  P: 128 doubles of LDS that no other wavefront touches meanwhile; the LDS
+// operations of a wavefront keep their order, so nothing is waited for but the data.
+__device__ __forceinline__ double pivot_step(f64x4& d, int q, double* P, int lane) {
   const int k = lane >> 4, c16 = lane & 15, cq = c16 >> 2;
-  const double unit = k == (lane & 3) ? 1.0 : 0.0;
+  const double x = cq == q ? (k == (lane & 3) ? 1.0 : 0.0) : d[q];
+  P[lane] = d[q];
+  P[64 + lane] = cq > q ? -x : x;
+  __builtin_amdgcn_wave_barrier();
+  const double n = pivot_factor(P + 4 * q, P + 64, c16, k);
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int v = 0; v < 4; ++v) d[v] = v == q || cq == q ? 0.0 : d[v];
+  d = mfma_f64(n, x, d);
+  return n;
+}
+// The operands of all four steps.
+__device__ __forceinline__ f64x4 pivot_tile(f64x4 d, double* P, int lane) {
   f64x4 n;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const double x = cq == q ? unit : d[q];
-    P[lane] = d[q];
-    P[64 + lane] = cq > q ? -x : x;
-    __builtin_amdgcn_wave_barrier();
-    n[q] = pivot_factor(P + 4 * q, P + 64, c16, k);
-    __builtin_amdgcn_wave_barrier();
-    if (q == 3) break;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) d[v] = v == q || cq == q ? 0.0 : d[v];
-    d = mfma_f64(n[q], x, d);
-  }
+  for (int q = 0; q < 4; ++q) n[q] = pivot_step(d, q, P, lane);
   return n;
 }
 

@@ -118,6 +118,16 @@ def test_factor_update_group_sizes(G, Hkv, r):
     run_update_case(upd_cfg(B=1, Hq=G * Hkv, Hkv=Hkv, r=r))
 
 
+@pytest.mark.parametrize("r", [32, 64])
+@pytest.mark.parametrize("B,G,Hkv", [(3, 3, 8), (16, 2, 8), (33, 2, 8), (12, 8, 3)])
+def test_factor_update_matrices_dealt_out(B, G, Hkv, r):
+    """The rounds of a KV group in as many workgroups as it has matrices, in fewer (each takes
+    several: 16 x 8 and 12 x 3 groups) and in one (33 x 8 groups)."""
+    say(f"factor update r={r}, {B} x {Hkv} groups of {G}")
+    run_update_case(upd_cfg(B=B, Hq=G * Hkv, Hkv=Hkv, r=r, l=400, k=32, w=5, C=40, n_heavy=4,
+                            pool_mult=1))
+
+
 def test_factor_update_fp32_rows_and_ragged_sizes():
     say("factor update, fp32 K rows, sizes that leave ragged chunks")
     run_update_case(upd_cfg(B=1, Hq=4, Hkv=2, l=2777, k=263, w=37, C=263, kv_dtype="f32"))
