@@ -34,12 +34,32 @@ namespace {
 
 using namespace alg64;
 
+// Workgroup i of `units` * parts as (unit, part).  Workgroups go to the eight compute dies in turn: all the
+// parts of a unit, and the same unit in every launch, on one of them where the units divide evenly, so
+// that what one launch leaves is in the L2 that the next one reads through: 90.8 -> 83.8 us for the whole at
+// 8 x (28 + 4) heads, r = 64, 27.5 -> 27.1 at 32 + 8 heads, r = 32
+// (launches 2 and 3; for launch 1 see its launch).
+__device__ __forceinline__ void place(int i, int units, int parts, int& unit, int& part,
+                                      bool by_die = true) {
+  if (by_die && units % 8 == 0) {
+    const int j = i >> 3;
+    unit = (i & 7) + 8 * (j / parts);
+    part = j % parts;
+  } else {
+    unit = i / parts;
+    part = i % parts;
+  }
+}
+
 template <int R, bool BF16>
-__global__ __launch_bounds__(kGramThreads) void factor_gram_kernel(GramRows a) {
+__global__ __launch_bounds__(kGramThreads) void factor_gram_kernel(GramRows a, int BHkv,
+                                                                            bool by_die) {
   __shared__ GramLds<R> s;
-  const int bh = blockIdx.y, job = blockIdx.x, t = threadIdx.x;
-  const int b = bh / a.Hq, h = bh - b * a.Hq;
-  const int bkv = b * a.Hkv + h / (a.Hq / a.Hkv);
+  const int t = threadIdx.x, G = a.Hq / a.Hkv;
+  int bkv, part;
+  place(blockIdx.x, BHkv, G * a.nchunk, bkv, part, by_die);
+  const int job = part % a.nchunk;
+  const int bh = bkv / a.Hkv * a.Hq + bkv % a.Hkv * G + part / a.nchunk;
   f32x16 sacc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) sacc[v] = 0.0f;
@@ -61,21 +81,6 @@ struct SolveArgs {
   int parts;             // workgroups per KV head in the rounds
   float lam1, lam2;
 };
-
-// Workgroup i of `units` * parts as (unit, part).  Workgroups go to the eight compute dies in turn: all the
-// parts of a unit, and the same unit in every launch, on one of them where the units divide evenly, so
-// that what one launch leaves is in the L2 that the next one reads through: 90.8 -> 83.8 us for the whole at
-// 8 x (28 + 4) heads, r = 64, 27.5 -> 27.1 at 32 + 8 heads, r = 32.
-__device__ __forceinline__ void place(int i, int units, int parts, int& unit, int& part) {
-  if (units % 8 == 0) {
-    const int j = i >> 3;
-    unit = (i & 7) + 8 * (j / parts);
-    part = j % parts;
-  } else {
-    unit = i / parts;
-    part = i % parts;
-  }
-}
 
 // ---- 2. the inverses --------------------------------------------------------------------------
 // One workgroup of 8 wavefronts per matrix, all in fp64:
@@ -430,8 +435,11 @@ hipError_t launch_update_r(const lrqk_shape& s, const GramRows& ga, const SolveA
   if (e == hipSuccess)
     e = raise_dynamic_lds_once(factor_rounds_kernel<R, BF16>, RoundShape<R>::lds_bytes, rounds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((factor_gram_kernel<R, BF16>), dim3(ga.nchunk, s.B * s.Hq),
-                     dim3(kGramThreads), 0, st, ga);
+  // The partials to the die of their inverse as long as they fit its L2 (4 MB) with room to spare: 27.1 ->
+  // 26.4 us for the call at 32 + 8 heads, r = 32 (2 MB in all); 83.4 -> 84.6 at 8 x (28 + 4) heads, r = 64 (30).
+  const size_t partials = (size_t)s.B * s.Hq * ga.nchunk * (R * R + R) * sizeof(float);
+  hipLaunchKernelGGL((factor_gram_kernel<R, BF16>), dim3(ga.nchunk * s.B * s.Hq), dim3(kGramThreads), 0,
+                     st, ga, s.B * s.Hkv, partials <= (size_t)16 << 20);
   hipLaunchKernelGGL((factor_inverse_kernel<R, BF16>), dim3(s.B * (s.Hq + s.Hkv)),
                      dim3(kInvThreads), InvShape<R>::lds_bytes, st, sa);
   hipLaunchKernelGGL((factor_rounds_kernel<R, BF16>), dim3(s.B * s.Hkv * sa.parts), dim3(RoundShape<R>::kThreads),
