@@ -16,7 +16,7 @@
 //
 // (With a pass over Q and K in every update, X^T Y and X^T X from the fp32 matrix cores and the
 // solves in fp32, the whole took 2.35 ms at 32 + 8 heads, l = 131072, r = 32, bf16, two rounds;
-// now 1.05 ms.)
+// now 0.95 ms.)
 //
 // Precision.  The long products run on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16) with
 // every fp32 operand split into three bf16 terms, x = x0 + x1 + x2, 8 bits of significand each, and
@@ -118,6 +118,7 @@ struct PfShape {
 // measured the same.  256 registers a wavefront hold one workgroup on a CU: the LDS takes two tiles.
 constexpr int kRedThreads = 512;
 constexpr int kBufferFlags = 0x00027000;  // raw 32-bit buffer
+constexpr int kNt = 2;                    // non-temporal: A0 is read once, and leaves the caches to Y
 constexpr int kFlushRows = 256;  // of S and H; twice as many of G
 constexpr int kScaleRows = 32;   // rows from which the grids of a head's columns are taken
 template <int R, int NS>
@@ -194,7 +195,7 @@ __global__ __launch_bounds__(kRedThreads, 2) void prefill_reduce_kernel(
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int q = t + kRedThreads * j;
-        p.a[j][i] = __builtin_amdgcn_raw_buffer_load_b32(ab, (q / R * 4 + i) * R * 4 + q % R * 4, 0, 0);
+        p.a[j][i] = __builtin_amdgcn_raw_buffer_load_b32(ab, (q / R * 4 + i) * R * 4 + q % R * 4, 0, kNt);
       }
   };
   // The grids of this thread's columns: q = 2^-5 times the mean binary exponent of kScaleRows rows
@@ -1032,13 +1033,15 @@ __global__ __launch_bounds__(kAlgThreads) void prefill_round_q_kernel(const PfSt
 // "lane = row"; 16-byte piece c of row i is kept at c ^ (i % 16), so that 16 rows' reads of one
 // piece lie in different banks.  The next rows' loads are in flight during the products.  M is
 // the same for a whole head: in registers at r <= 32 (96 of them), in LDS at r = 64.
-// Bound by HBM (Y in, X out): 2.0 GB in 0.39 ms at 32 + 8 heads, l = 131072, r = 32.
+// Bound by HBM (Y in, X out): 2.0 GB in 0.36 ms at 32 + 8 heads, l = 131072, r = 32.  The rows go from the
+// last to the first: the last that the reduction read are still in the Infinity Cache (1018 -> 1006 us for
+// the whole call at that shape).
 template <int R>
 constexpr size_t apply_lds_bytes() {
   return 4 * 8192 + (R > 32 ? PfShape<R>::mpack_units * 16 : 0);
 }
 
-template <int R, int NS>
+template <int R, int NS, bool NT_LOAD, bool NT_STORE>
 __global__ __launch_bounds__(kPfThreads, 2) void prefill_apply_kernel(
     const void* __restrict__ Q, const void* __restrict__ K, const uint4* __restrict__ M,
     float* __restrict__ A_Q, float* __restrict__ A_K, int BHq, int l, int lk, int units,
@@ -1052,7 +1055,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_apply_kernel(
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   u32x4* const Yl = reinterpret_cast<u32x4*>(pf_lds) + w * 512;
   u32x4* const Ml = reinterpret_cast<u32x4*>(pf_lds) + 4 * 512;
-  const int bh = blockIdx.x / blocks_per_head, block = blockIdx.x - bh * blocks_per_head;
+  const int at = gridDim.x - 1 - blockIdx.x;  // from the last rows on: see above
+  const int bh = at / blocks_per_head, block = at - bh * blocks_per_head;
   const bool isq = bh < BHq;
   const size_t head = isq ? bh : bh - BHq;
   const u32x4* __restrict__ Yh = static_cast<const u32x4*>(isq ? Q : K) + head * (size_t)l * ROW16;
@@ -1079,7 +1083,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_apply_kernel(
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int row = min(row0 + 4 * j + (lane >> 4), last - 1);  // (results past the end are dropped)
-      pre[j] = Yh[(size_t)row * ROW16 + 16 * ph + (lane & 15)];
+      const u32x4* at = Yh + (size_t)row * ROW16 + 16 * ph + (lane & 15);
+      pre[j] = NT_LOAD ? __builtin_nontemporal_load(at) : *at;
     }
   };
   if (first >= last) return;  // (no barrier follows)
@@ -1139,7 +1144,11 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_apply_kernel(
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int row = row0 + mfma_row(v, lane);
-          if (row < last) Xh[(size_t)row * R + j] = acc[rb][v];
+          if (row >= last) continue;
+          if (NT_STORE)
+            __builtin_nontemporal_store(acc[rb][v], Xh + (size_t)row * R + j);
+          else
+            Xh[(size_t)row * R + j] = acc[rb][v];
         }
       }
     }
@@ -1148,8 +1157,9 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_apply_kernel(
 
 // ------------------------------------------------------------------------------------------
 // Chunks of rows per head: the fewest workgroup rounds (one workgroup per CU) times the passes
-// of a workgroup, a partial costing about as much as four passes.  At most kPfSlots partials
-// unless there are more heads than that.
+// of a workgroup, a partial costing its workgroup about as much as four passes, and as traffic, written
+// and read, a 64th of one (6 chunks instead of 19 at 32 + 8 heads, l = 131072, r = 32: 1006 -> 995 us for the
+// whole call).  At most kPfSlots partials unless there are more heads than that.
 constexpr int kPfSlots = 1024;
 int reduce_chunks(int heads, int l, int rows) {
   const int tiles = ceil_div(l, rows);
@@ -1158,7 +1168,7 @@ int reduce_chunks(int heads, int l, int rows) {
   long best_cost = 0;
   for (int n = 1; n <= most; ++n) {
     const int per = ceil_div(tiles, n);
-    const long cost = (long)ceil_div(heads * ceil_div(tiles, per), 256) * (per + 4);
+    const long cost = 64 * (long)ceil_div(heads * ceil_div(tiles, per), 256) * (per + 4) + heads * n;
     if (n == 1 || cost < best_cost) {
       best = n;
       best_cost = cost;
@@ -1205,14 +1215,17 @@ PrefillWs carve_prefill(void* base, const lrqk_shape& s) {
 template <int R, int NS>
 struct PfKernels {
   static hipError_t allow() {
-    static std::atomic<uint64_t> reduce{0}, rk[2], rq[2], apply{0};
+    static std::atomic<uint64_t> reduce{0}, rk[2], rq[2], apply[3];
     constexpr size_t lds = PfAlg<R>::lds_bytes;
     hipError_t e = raise_dynamic_lds_once(prefill_reduce_kernel<R, NS>, PfReduce<R, NS>::lds_bytes, reduce);
     if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_round_k_kernel<R, false>, lds, rk[0]);
     if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_round_k_kernel<R, true>, lds, rk[1]);
     if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_round_q_kernel<R, false>, lds, rq[0]);
     if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_round_q_kernel<R, true>, lds, rq[1]);
-    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_apply_kernel<R, NS>, apply_lds_bytes<R>(), apply);
+    constexpr size_t al = apply_lds_bytes<R>();
+    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_apply_kernel<R, NS, false, false>, al, apply[0]);
+    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_apply_kernel<R, NS, false, true>, al, apply[1]);
+    if (e == hipSuccess) e = raise_dynamic_lds_once(prefill_apply_kernel<R, NS, true, true>, al, apply[2]);
     return e;
   }
 };
@@ -1265,8 +1278,22 @@ hipError_t run_prefill(const lrqk_shape& s, const void* Q, const void* K, float*
   int units = 1;
   while (units < 16 && (long)ceil_div(row_units, 8 * units) * heads >= 2048) units *= 2;
   const int blocks = ceil_div(row_units, 4 * units);
-  hipLaunchKernelGGL((prefill_apply_kernel<R, NS>), dim3(blocks * heads), dim3(kPfThreads),
-                     apply_lds_bytes<R>(), st, Q, K, w.M, A_Q, A_K, BHq, l, lk, units, blocks);
+  // Non-temporal stores where A_Q and A_K exceed the L2s (32 MB), loads where Q and K exceed the
+  // Infinity Cache (256 MB).  Whole call, 32 + 8 heads, bf16, in us with neither, stores, both: l = 131072,
+  // r = 32: 1013, 980, 967; l = 16384: 185, 180, 187; l = 4096, r = 16: 78.9, 79.5, 82.0; 4 x (16 + 2) heads,
+  // l = 8192, r = 8 (19 MB out): 134, 137, 145.
+  const bool nt_load = (size_t)heads * l * kD * (NS == 1 ? 2 : 4) > (size_t)256 << 20;
+  const bool nt_store = nt_load || (size_t)heads * l * R * 4 > (size_t)32 << 20;
+  auto apply = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks * heads), dim3(kPfThreads), apply_lds_bytes<R>(), st, Q, K,
+                       w.M, A_Q, A_K, BHq, l, lk, units, blocks);
+  };
+  if (nt_load)
+    apply(prefill_apply_kernel<R, NS, true, true>);
+  else if (nt_store)
+    apply(prefill_apply_kernel<R, NS, false, true>);
+  else
+    apply(prefill_apply_kernel<R, NS, false, false>);
   return hipGetLastError();
 }
 

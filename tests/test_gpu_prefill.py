@@ -193,6 +193,13 @@ def test_prefill_tile_edges(r, l, kv_dtype):
     run_prefill_case(pf_cfg(r=r, l=l, kv_dtype=kv_dtype, k=32, C=32))
 
 
+@pytest.mark.parametrize("kv_dtype,l", [("bf16", 120001), ("f32", 60001)])
+def test_prefill_beyond_the_infinity_cache(kv_dtype, l):
+    """Rows of Q and K that exceed 256 MB: the last products read them with non-temporal loads."""
+    say(f"prefill l = {l}, {kv_dtype}, 8 query heads on 1 KV head")
+    run_prefill_case(pf_cfg(Hq=8, Hkv=1, l=l, r=8, kv_dtype=kv_dtype))
+
+
 @pytest.mark.parametrize("r", [8, 16, 32, 64])
 @pytest.mark.parametrize("B", [1, 10, 30])
 def test_prefill_shared_and_unshared_sums(B, r):
