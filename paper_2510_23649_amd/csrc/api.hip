@@ -125,7 +125,7 @@ struct lrqk_plan {
   uint32_t* thr_used;          // [BHq] the keys the last filtered proxy-score pass used
   float* samples;              // [BHq][kThrMaxSamples] sample scores behind thr
   unsigned long long* filter;  // [BHq][words64] candidate bitmap from the proxy-score pass
-  float* cand_scores;          // [BHq][words64][kCandPerGroup] the candidates' scores
+  float* cand_scores;          // [BHq][words64][cand_per_group] the candidates' scores
   void* select_ws;
   size_t select_bytes;
   float* partials;
@@ -406,7 +406,7 @@ int lrqk_plan_create(const lrqk_shape* max_shape, lrqk_plan** plan_out) {
   dmalloc((void**)&p->thr_used, BHq * 4);
   dmalloc((void**)&p->samples, BHq * (size_t)kThrMaxSamples * 4);
   dmalloc((void**)&p->filter, BHq * (size_t)filter_words64(s.l) * 8);
-  dmalloc((void**)&p->cand_scores, BHq * (size_t)filter_words64(s.l) * kCandPerGroup * 4);
+  dmalloc((void**)&p->cand_scores, BHq * cand_scores_per_head(s) * 4);
   dmalloc(&p->select_ws, p->select_bytes);
   dmalloc((void**)&p->partials, p->partial_bytes);
   dmalloc((void**)&p->sel_idx, BHq * s.k * 4);

@@ -33,23 +33,7 @@ namespace lrqk {
 namespace {
 
 using namespace alg64;
-
-// Workgroup i of `units` * parts as (unit, part).  Workgroups go to the eight compute dies in turn: all the
-// parts of a unit, and the same unit in every launch, on one of them where the units divide evenly, so
-// that what one launch leaves is in the L2 that the next one reads through: 90.8 -> 83.8 us for the whole at
-// 8 x (28 + 4) heads, r = 64, 27.5 -> 27.1 at 32 + 8 heads, r = 32
-// (launches 2 and 3; for launch 1 see its launch).
-__device__ __forceinline__ void place(int i, int units, int parts, int& unit, int& part,
-                                      bool by_die = true) {
-  if (by_die && units % 8 == 0) {
-    const int j = i >> 3;
-    unit = (i & 7) + 8 * (j / parts);
-    part = j % parts;
-  } else {
-    unit = i / parts;
-    part = i % parts;
-  }
-}
+using dev::place;
 
 template <int R, bool BF16>
 __global__ __launch_bounds__(kGramThreads) void factor_gram_kernel(GramRows a, int BHkv,

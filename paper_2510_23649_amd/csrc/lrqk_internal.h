@@ -114,8 +114,21 @@ constexpr int kThrMaxSamples = 16384;  // sample scores kept per head
 // samples: [BHq][kThrMaxSamples] floats
 hipError_t launch_proxy_threshold(const lrqk_shape& s, const float* A_K, const float* q_hat,
                                   float* samples, uint32_t* thr, hipStream_t st);
-constexpr int kCandPerGroup = 8;  // candidate scores kept per head and 64-row group
-// cand_scores: [BHq][words64][kCandPerGroup] floats
+// Candidate scores kept per head and 64-row group: 8; 16 where select_packed.hip selects from at most
+// 1024 groups with more than 2.5 of the 1.5 k candidates each.  There one group in ten to a hundred has
+// more than 8 candidates, and a single such group makes the selection wait for a row of A_K (3000 to 5000
+// cycles of 30000).  With fewer it hardly ever happens, and the entries are read whole: 16 at 224 heads,
+// l = 64K and 1.5 candidates a group took a step from 306.6 to 309.1 us.
+// cand_scores: [BHq][words64][cand_per_group] floats
+constexpr int kCandPerGroup = 8;
+int cand_per_group(const lrqk_shape& s);
+// the most that any shape of at most s.l positions takes for a head
+inline size_t cand_scores_per_head(const lrqk_shape& s) {
+  const size_t words = (size_t)filter_words64(s.l);
+  return words * kCandPerGroup > (words < 1024 ? words : 1024) * 2 * kCandPerGroup
+             ? words * kCandPerGroup
+             : (words < 1024 ? words : 1024) * 2 * kCandPerGroup;
+}
 // The threshold key of each head comes from `thr` (keys, e.g. from launch_proxy_threshold) or,
 // if `thr` is null, from thr_norm[head] * |q_hat[head]| (the value the previous step's
 // selection left for this layer).  Exactly one of the two is given.  thr_out [BHq] receives

@@ -37,7 +37,7 @@ __device__ __forceinline__ float4 load_streaming(const float4* p) {
 // FILTER: emit, INSTEAD of the scores, a bitmap per head of the positions in [0, n) whose
 // order key is >= thr[head] (one 64-bit ballot per wavefront and head, no atomics) and
 // the scores of those candidates, packed in position order into a slot of
-// kCandPerGroup floats per 64-row group (the i-th set bit of the group's ballot goes to
+// CPG = 8 or 16 floats per 64-row group (the i-th set bit of the group's ballot goes to
 // entry i; a group with more candidates than the slot holds keeps the first ones and
 // the selection kernel recomputes the others from A_K).  The fused step therefore never
 // writes the l-sized score array: about 5 MB leave this kernel instead of 16.8 MB at
@@ -47,7 +47,7 @@ __device__ __forceinline__ float4 load_streaming(const float4* p) {
 // step left behind: thr_norm[head] * |q_hat[head]| (a NaN there gives a key above every score:
 // no candidates, and the selection falls back to its exact route).  The keys used are written
 // to thr_out by the first workgroup of each KV head.
-template <int R, int G, bool FILTER>
+template <int R, int G, bool FILTER, int CPG = kCandPerGroup>
 __global__ __launch_bounds__(kTileRows) void proxy_scores_kernel(
     const float* __restrict__ A_K, const float* __restrict__ q_hat, float* __restrict__ scores,
     int l, int lrows, int Hq, int Hkv, int n, const uint32_t* __restrict__ thr,
@@ -160,13 +160,17 @@ __global__ __launch_bounds__(kTileRows) void proxy_scores_kernel(
     float* stage = reinterpret_cast<float*>(&tile[(t & ~63) * ROW4]);
     // The packed scores of all G heads are staged together and leave with one store
     // instruction (lane = head * 8 + entry), the G ballots with another (lane = head): the
-    // per-head part is the compare, the ballot and one LDS write.
+    // per-head part is the compare, the ballot and one LDS write.  Entries 8 to 15 of a group, where
+    // there are such (CPG = 16), leave with a store of their own if any head has more than 8
+    // candidates: rarely (all 16 at once, in one or two stores, cost 0.7 us at l = 32K, G = 4 and 10 us
+    // at l = 50K, r = 64, G = 7).
     static_assert(G * kCandPerGroup <= 64, "one lane per packed entry");
     if (lane < G * kCandPerGroup) stage[lane] = 0.0f;
     __builtin_amdgcn_wave_barrier();
     const unsigned long long below = (1ull << lane) - 1ull;
     const int my_head = lane >> 3;       // head of this lane in the two stores below
     unsigned long long mask_of_my_head = 0ull, mask_of_lane_head = 0ull;
+    bool more = false;  // uniform
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const uint32_t thr_g = *thr_slot(g);
@@ -174,8 +178,10 @@ __global__ __launch_bounds__(kTileRows) void proxy_scores_kernel(
       const bool in = row < n && dev::order_key(acc[g]) >= thr_g;
       const unsigned long long mask = __ballot(in);
       const int rank = __popcll(mask & below);
-      if (in && rank < kCandPerGroup) stage[g * kCandPerGroup + rank] = acc[g];
+      if (in && rank < CPG)
+        stage[g * kCandPerGroup + rank + (rank < kCandPerGroup ? 0 : 64 - kCandPerGroup)] = acc[g];
       if (my_head == g) mask_of_my_head = mask;
+      more |= CPG > kCandPerGroup && __popcll(mask) > kCandPerGroup;
       if (lane == g) mask_of_lane_head = mask;
     }
     __builtin_amdgcn_wave_barrier();
@@ -183,8 +189,10 @@ __global__ __launch_bounds__(kTileRows) void proxy_scores_kernel(
       const size_t grp = (size_t)(wrow >> 6);
       if (lane < G) bitmap[(bh0 + lane) * words64 + grp] = mask_of_lane_head;
       // a head without candidates in this group leaves its entries alone (they are not read)
-      if (lane < G * kCandPerGroup && mask_of_my_head != 0ull)
-        cand_scores[((bh0 + my_head) * words64 + grp) * kCandPerGroup + (lane & 7)] = stage[lane];
+      float* const to = cand_scores + ((bh0 + my_head) * words64 + grp) * CPG + (lane & 7);
+      if (lane < G * kCandPerGroup && mask_of_my_head != 0ull) *to = stage[lane];
+      if (more && lane < G * kCandPerGroup && __popcll(mask_of_my_head) > kCandPerGroup)
+        to[kCandPerGroup] = stage[64 + lane];
     }
   }
 }
@@ -356,7 +364,11 @@ hipError_t launch_fast(const lrqk_shape& s, const float* A_K, const float* q_hat
                        const FilterOut* f, hipStream_t st) {
   dim3 grid(ceil_div(s.l, kTileRows), s.B * s.Hkv);
   const int n = s.l - s.w;
-  if (f)
+  if (f && cand_per_group(s) > kCandPerGroup)
+    LRQK_LAUNCH((proxy_scores_kernel<R, G, true, 2 * kCandPerGroup>), grid, dim3(kTileRows), 0, st, A_K,
+                       q_hat, scores, s.l, row_cap(s), s.Hq, s.Hkv, n, f->thr, f->thr_norm,
+                       f->thr_out, f->bitmap, f->cand_scores, filter_words64(n));
+  else if (f)
     LRQK_LAUNCH((proxy_scores_kernel<R, G, true>), grid, dim3(kTileRows), 0, st, A_K,
                        q_hat, scores, s.l, row_cap(s), s.Hq, s.Hkv, n, f->thr, f->thr_norm,
                        f->thr_out, f->bitmap, f->cand_scores, filter_words64(n));

@@ -3,15 +3,17 @@
 // per group of 64 positions) and the candidates' scores packed 8 per group
 // (Alg. 2, top(., k); Sec. 4.1 active / lite tokens and the hit-and-miss cache).
 //
-// Thread t owns GPT consecutive groups, i.e. a contiguous run of positions, and keeps its
-// candidates in registers from the first load to the last store: "thread order" is
-// "position order", so nothing is ever listed or sorted, and every prefix count over the
-// threads is a count in position order.
-//   * one round of coalesced loads brings the thread's bitmap words and packed scores in
-//     (with what the resolution will need from the cache state: last_used and token_of go
-//     to LDS).  The first 8 (or 4) candidates of a group stay in registers, further ones are
-//     parked in LDS; a group with more than the 8 packed candidates computes the others
-//     again from A_K and q_hat with the proxy pass's fma chain;
+// What costs time here is not memory but a chain of short phases, and in them the instructions that a
+// wavefront issues for lanes that have nothing to do: candidates are few and unevenly spread over the
+// groups.  So they are listed once, in LDS and in position order, and dealt out evenly from then on:
+//   * one round of coalesced loads brings a thread's bitmap words and packed scores in (GPT
+//     consecutive groups; with what the resolution will need from the cache state: last_used and
+//     token_of go to LDS).  A prefix count over the candidates gives each its place in the list, an
+//     entry being (key, ~position) as one number, larger = better; candidates beyond the packed ones of
+//     a group get their score computed again from A_K and q_hat with the proxy pass's fma chain, dealt
+//     out over all threads;
+//   * thread t takes entries t E .. t E + E - 1 (E = entries / 1024, mostly 2 to 4) into registers: thread
+//     order is position order, and every prefix count over the threads is one in position order;
 //   * ONE histogram over (key - threshold key) >> s, 2048 bins (the candidates are the tail
 //     of the score distribution above the threshold, so they spread over the bins instead
 //     of piling into the two or three bins that fixed key bits would give), is scanned from
@@ -20,13 +22,21 @@
 //     with the right rank is the cut: the selection is every candidate at or above it.  A
 //     bin with many candidates (ties) goes through further 11-bit histogram levels and an
 //     ordered cut instead;
-//   * each thread then looks up slot_of for its own selected positions, and one prefix count
-//     over (selected, missing) gives it its place in the outputs;
+//   * a prefix count over the selected entries gives each its place in the outputs, and a bitmap of the
+//     selection with a count per 64 positions says for a position whether and where it stands there: every
+//     cache slot looks its token up (token_of is in LDS by then; slot_of is its inverse and is only
+//     written: to look up k positions in it means k cache lines, 4 cycles each at the least: 4500 cycles at
+//     k = 1024, 7500 at 2048).  What no slot has claimed is missing;
 //   * the same histogram yields the key at rank 1.5 k, which (divided by |q_hat|) is handed
 //     to the next step of the layer as its candidate threshold, so that steps after the
 //     first need no threshold estimate of their own.
-// A head whose candidates are unusable (fewer than k, or too many beyond the packed 8 per
-// group) recomputes all its scores into the workspace and selects exactly from them
+// (Before, a thread kept the candidates of its own groups in registers, 8 a group, from the first load to
+// the last store: every phase then had 8 to 16 predicated steps of which most lanes skipped most, and
+// slot_of was looked up.  The kernel at 128K, two groups a thread: 18.6 -> 17.6 us; at 50K, r = 64: 16.1 ->
+// 14.5; a whole step at 4K context, where one wavefront owned all the groups: 24.0 -> 21.5.)
+// Cycles at 2.3 GHz, one head at 32K: first loads 6200, list 3000, histogram 2000, scan 1900, cut 1800,
+// positions in output order 1800, slots 2200, outputs 1800, victims 6500.
+// A head whose candidates are unusable (fewer than k, or more than the list holds) recomputes all its scores into the workspace and selects exactly from them
 // (exact_select_from_scores): slower, same result.
 //
 // Resolution (Sec. 4.1; least recently selected victims in (last_used, slot) order): a
@@ -44,30 +54,46 @@
 namespace lrqk {
 namespace {
 
-constexpr int kOvCap = 2048;  // candidate keys beyond the packed 8 per group that a head may park
+constexpr int kPackedMaxK = 4 * kT;             // k
+constexpr int kMaxE = 8;                  // list entries per thread
+constexpr int kListCap = kMaxE * kT;      // candidates of a head
 constexpr int kSmall = 64;    // candidates of the threshold bin that one wavefront ranks directly
 constexpr int kMaxSpt = 8;    // cache slots per thread (C <= 8192)
 constexpr size_t kPackedLdsLimit = 150 * 1024;
 
 __host__ __device__ inline size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
+// LDS: last_used and token_of [C] each; age and key histograms; the threshold bin's entries; then, in one
+// area, one after the other,
+//   the list of candidates, or the exact route's histogram and bitmap;
+//   the selection in output order, its positions and slots [k] each from 3 k_b on, and its bitmap with the
+//   counts, each at the start of the area as far as they fit 3 k_b, behind the slots otherwise;
+//   [k] miss positions, their output indices, victims in rank order, and from 3 k_b on the all-slots
+//   sort of the rare resolution cases.
 struct PackedArena {
-  size_t st_b, k_b, fixed, x_b, total;
+  size_t st_b, k_b, bits_at, first_at, fixed, total;  // (bits_at, first_at: from the area's start)
+  int list_cap;
 };
 __host__ __device__ inline PackedArena packed_arena(int k, int n, int C) {
   PackedArena a;
-  a.st_b = up256((size_t)C * 4);  // last_used; token_of has the same size
-  a.k_b = up256((size_t)k * 4);   // miss positions; their output indices; victims in rank order
-  // hist0 + ahist + parked keys + the threshold bin's (key, position) pairs
-  a.fixed = 2 * a.st_b + 3 * a.k_b + 2 * 2048 * 4 + (size_t)kOvCap * 4 + up256((kSmall + 1) * 8);
-  // shared: exact route (histogram + selection bitmap) | further histogram levels | the
-  // all-slots sort of the rare resolution cases
+  a.st_b = up256((size_t)C * 4);
+  a.k_b = up256((size_t)k * 4);
+  a.fixed = 2 * a.st_b + (kAgeBins + 2048) * 4 + up256((kSmall + 1) * 8);
   const size_t exact = (size_t)kBins * 4 + up256(((size_t)n + 31) / 32 * 4);
   int Cpad = 2;
   while (Cpad < C) Cpad <<= 1;
   const size_t sort_b = (size_t)Cpad * 8;
-  a.x_b = exact > sort_b ? exact : sort_b;
-  a.total = a.fixed + a.x_b;
+  const size_t words = ((size_t)n + 63) / 64, bits_b = up256(words * 8), first_b = up256(words * 4);
+  a.bits_at = bits_b <= 3 * a.k_b ? 0 : 5 * a.k_b;
+  a.first_at = a.bits_at > 0 ? a.bits_at + bits_b : bits_b + first_b <= 3 * a.k_b ? bits_b : 5 * a.k_b;
+  const size_t out = 3 * a.k_b + (2 * a.k_b > sort_b ? 2 * a.k_b : sort_b);
+  size_t z = out > exact ? out : exact;
+  if (z < a.first_at + first_b) z = a.first_at + first_b;
+  // room for twice the candidates that the threshold aims at, more where it costs nothing
+  const size_t want = up256((size_t)(3 * k < kListCap ? 3 * k : kListCap) * 8);
+  if (z < want && a.fixed + want <= kPackedLdsLimit) z = want;
+  a.list_cap = (int)(z / 8) < kListCap ? (int)(z / 8) : kListCap;
+  a.total = a.fixed + z;
   return a;
 }
 
@@ -106,13 +132,13 @@ __device__ __forceinline__ uint32_t find_two_from_top(const uint32_t* hist, uint
 
 struct PackedArgs {
   const unsigned long long* bitmap;  // [BHq][words64]
-  const float* cand_scores;          // [BHq][words64][kCandPerGroup]
+  const float* cand_scores;          // [BHq][words64][cand_per_group]
   const uint32_t* thr_used;          // [BHq] key the proxy pass filtered with
   const float* A_K;
   const float* q_hat;
   float* scores_w;  // [BHq][l] scratch of a head that takes the exact route
   float* sel_thr;   // [BHq] threshold / |q_hat| handed to the layer's next step (may be null)
-  int words64, r, Hq, Hkv, l, lrows, n, k, C;
+  int words64, r, B, Hq, Hkv, l, lrows, n, k, C;
   int32_t step;
   int32_t* sel_idx;
   int32_t* slot_of;
@@ -125,34 +151,40 @@ struct PackedArgs {
   int32_t* n_miss;
 };
 
-template <int GPT, int SPT, int SLOTS>
+template <int GPT, int SPT, int CPG>
 __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ uint32_t wave_tot[4 * 2 * kWaves];  // four areas of 32 words, used in rotation
   auto scan_area = [&](int i) { return wave_tot + (i & 3) * 2 * kWaves; };
   __shared__ uint32_t res[4];
-  __shared__ uint32_t sh_ov, sh_todo, sh_small_n, sh_bad, sh_ncls, sh_clip;
+  __shared__ uint32_t sh_again, sh_small_n, sh_bad, sh_ncls, sh_clip;
   __shared__ uint64_t sh_cut;
   __shared__ __align__(16) float qh[128];
   __shared__ uint32_t cls_age[kMaxCls], cls_base[kMaxCls];
 
-  const int bh = blockIdx.x, t = threadIdx.x;
-  const int lane = t & 63, wv = t >> 6;
+  int bh, block;
+  place_head(blockIdx.x, a.B, a.Hq, a.Hkv, 1, bh, block);
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int n = a.n, k = a.k, C = a.C, l = a.l, r = a.r;
   const PackedArena az = packed_arena(k, n, C);
   int32_t* const lu_s = reinterpret_cast<int32_t*>(lds_raw);
   int32_t* const to_s = reinterpret_cast<int32_t*>(lds_raw + az.st_b);
-  int32_t* const mt_s = reinterpret_cast<int32_t*>(lds_raw + 2 * az.st_b);  // [k] miss positions
-  int32_t* const mj_s = reinterpret_cast<int32_t*>(lds_raw + 2 * az.st_b + az.k_b);  // their j
-  int32_t* const vsorted = reinterpret_cast<int32_t*>(lds_raw + 2 * az.st_b + 2 * az.k_b);
-  uint32_t* const ahist = reinterpret_cast<uint32_t*>(lds_raw + 2 * az.st_b + 3 * az.k_b);
+  uint32_t* const ahist = reinterpret_cast<uint32_t*>(lds_raw + 2 * az.st_b);
   uint32_t* const hist0 = ahist + kAgeBins;
-  uint32_t* const ov_key = hist0 + 2048;
-  uint64_t* const small = reinterpret_cast<uint64_t*>(ov_key + kOvCap);
-  unsigned char* const X = lds_raw + az.fixed;
-  // staging of the outputs in output order, over memory the selection no longer needs
-  int32_t* const sel_o = reinterpret_cast<int32_t*>(hist0);  // [k] <= hist0 + ov_key
-  int32_t* const slot_o = reinterpret_cast<int32_t*>(X);     // [k] slot, or -1 - miss rank
+  uint64_t* const small = reinterpret_cast<uint64_t*>(hist0 + 2048);
+  unsigned char* const Z = lds_raw + az.fixed;
+  uint64_t* const list = reinterpret_cast<uint64_t*>(Z);
+  // (in place of the list, once every thread holds its entries in registers)
+  int32_t* const mt_s = reinterpret_cast<int32_t*>(Z);                     // [k] miss positions
+  int32_t* const mj_s = reinterpret_cast<int32_t*>(Z + az.k_b);            // their j
+  int32_t* const vsorted = reinterpret_cast<int32_t*>(Z + 2 * az.k_b);
+  unsigned char* const X = Z + 3 * az.k_b;
+  int32_t* const sel_o = reinterpret_cast<int32_t*>(X);                    // [k]
+  int32_t* const slot_o = reinterpret_cast<int32_t*>(X + az.k_b);          // [k]
+  const int n_words = (n + 63) >> 6;
+  unsigned long long* const map_bits =                                     // [n_words]
+      reinterpret_cast<unsigned long long*>(Z + az.bits_at);
+  uint32_t* const map_first = reinterpret_cast<uint32_t*>(Z + az.first_at);  // [n_words]
 
   const int b = bh / a.Hq, h = bh - b * a.Hq, kvh = h / (a.Hq / a.Hkv);
   const float* __restrict__ Arow = a.A_K + ((size_t)b * a.Hkv + kvh) * (size_t)a.lrows * r;
@@ -162,22 +194,20 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
   const int32_t step = a.step;
   // ---- 0. every load that does not depend on the selection -----------------------------------
   // (from clamped addresses and without a branch: a load inside one is waited for before the
-  // next is issued.  Whole step at 4K context 24.4 -> 23.9 us, of two layers at 128K 235.3 -> 234.8.  Looking
-  // slot_of up for every candidate here, before the cut is known, hides the gather but makes
-  // half as many again: no gain at 32K, and the registers spill at two groups per thread.)
+  // next is issued.  Whole step at 4K context 24.4 -> 23.9 us, of two layers at 128K 235.3 -> 234.8.)
   const int ngroups = (n + 63) >> 6;
   const unsigned long long* __restrict__ bm = a.bitmap + (size_t)bh * a.words64;
   const float4* __restrict__ cs4 =
-      reinterpret_cast<const float4*>(a.cand_scores + (size_t)bh * a.words64 * kCandPerGroup);
+      reinterpret_cast<const float4*>(a.cand_scores + (size_t)bh * a.words64 * CPG);
   unsigned long long mask[GPT];
-  float4 sc[GPT][2];
+  float4 sc[GPT][CPG / 4];
 #pragma unroll
   for (int g = 0; g < GPT; ++g) {
     const int gi = min(t * GPT + g, ngroups - 1);
     mask[g] = bm[gi];
     // a group without candidates holds stale scores; they are never interpreted
-    sc[g][0] = cs4[2 * gi];
-    sc[g][1] = cs4[2 * gi + 1];
+#pragma unroll
+    for (int i = 0; i < CPG / 4; ++i) sc[g][i] = cs4[CPG / 4 * gi + i];
   }
   // cache state: coalesced loads (slot i by thread i mod 1024), handed over through LDS to
   // the threads that own contiguous runs of slots below
@@ -197,110 +227,46 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
 
   for (int i = t; i < 2048 + kAgeBins; i += kT) ahist[i] = 0u;  // ahist and hist0
   if (t == 0) {
-    sh_ov = 0u;
-    sh_todo = 0u;
+    sh_again = 0u;
     sh_small_n = 0u;
     sh_bad = 0u;
     sh_ncls = 0u;
     sh_clip = 0u;
   }
-  lds_barrier();
 
-  // ---- 1. the thread's candidates: key and position of each, histogram of the keys ---------------
-  // Every candidate's key is >= thr_key.  Bin of a key: (key - thr_key) >> s, the top bin
-  // taking everything beyond.  For a positive threshold s = 12 spreads the scores between the
-  // threshold and twice the threshold over the 2048 bins.
-  int s = (thr_key > 0x80800000u && thr_key < 0xff800000u) ? 12 : 21;
-  auto bin_of = [&](uint32_t kk) { return min((kk - thr_key) >> s, 2047u); };
+  // ---- 1. the list of candidates -------------------------------------------------------------------
   // (key, position) as one number: larger = better (higher key, or equal key and lower position)
-  auto value_of = [&](uint32_t kk, int g, int bpos) {
-    return ((uint64_t)kk << 32) | (uint32_t) ~(uint32_t)((t * GPT + g) * 64 + bpos);
-  };
-  // The first SLOTS candidates of a group stay in registers; the others (packed entries beyond
-  // SLOTS, and candidates beyond the 8 packed ones, whose scores are computed again from A_K)
-  // are parked in LDS, in position order, in a run the thread reserves.  What has to be computed
-  // again is listed first and dealt out over all threads: a thread that did its own one after
-  // the other held everyone up (4 us of the 15 us kernel where a 16th of the context is selected).
-  uint32_t key[GPT][SLOTS];
-  unsigned long long bpos6[GPT];  // bit positions of the candidates in registers, 6 bits each
-  auto bpos_of = [&](int g, int i) { return (int)((bpos6[g] >> (6 * i)) & 63ull); };
-  int cnt[GPT];
-  int extra = 0, again = 0;
+  auto value_of = [](uint32_t kk, int p) { return ((uint64_t)kk << 32) | (uint32_t)~(uint32_t)p; };
+  auto position_of = [](uint64_t v) { return (int)~(uint32_t)v; };
+  uint32_t own = 0;
 #pragma unroll
-  for (int g = 0; g < GPT; ++g) {
-    cnt[g] = __popcll(mask[g]);
-    extra += max(cnt[g] - SLOTS, 0);
-    again += max(cnt[g] - kCandPerGroup, 0);
-  }
-  uint64_t* const todo = reinterpret_cast<uint64_t*>(X);  // (position, index in ov_key)
-  int ov_base = 0;
-  bool ov_ok = true;
-  if (extra > 0) {
-    ov_base = (int)atomicAdd(&sh_ov, (uint32_t)extra);
-    ov_ok = ov_base + extra <= kOvCap;
-  }
-  // (threads whose run fits have reserved at most kOvCap entries between them)
-  int td = again > 0 && ov_ok ? (int)atomicAdd(&sh_todo, (uint32_t)again) : 0;
-  {
-    int idx = ov_base;
+  for (int g = 0; g < GPT; ++g) own += (uint32_t)__popcll(mask[g]);
+  uint32_t m;
+  uint32_t at = scan1(own, scan_area(0), &m);
+  const bool listed = m >= (uint32_t)k && m <= (uint32_t)az.list_cap;  // uniform
+  if (listed) {
 #pragma unroll
     for (int g = 0; g < GPT; ++g) {
-      const float v[kCandPerGroup] = {sc[g][0].x, sc[g][0].y, sc[g][0].z, sc[g][0].w,
-                                      sc[g][1].x, sc[g][1].y, sc[g][1].z, sc[g][1].w};
       unsigned long long mb = mask[g];
-      bpos6[g] = 0ull;
+      const int base = (t * GPT + g) * 64;
 #pragma unroll
-      for (int i = 0; i < kCandPerGroup; ++i) {
-        if (i < SLOTS) key[g][i] = 0u;
-        if (i < cnt[g]) {
-          const uint32_t kk = order_key(v[i]);
-          if (i < SLOTS) {
-            key[g][i] = kk;
-            bpos6[g] |= (unsigned long long)__builtin_ctzll(mb) << (6 * (i < SLOTS ? i : 0));
-            atomicAdd(&hist0[bin_of(kk)], 1u);
-          } else if (ov_ok) {
-            ov_key[idx++] = kk;
-            atomicAdd(&hist0[bin_of(kk)], 1u);
-          }
+      for (int i = 0; i < CPG; ++i)
+        if (mb) {
+          const float4 q = sc[g][i / 4];
+          const float v = i % 4 == 0 ? q.x : i % 4 == 1 ? q.y : i % 4 == 2 ? q.z : q.w;
+          list[at++] = value_of(order_key(v), base + __builtin_ctzll(mb));
           mb &= mb - 1ull;
         }
-      }
-      if (cnt[g] > kCandPerGroup && ov_ok) {
-        while (mb) {  // more candidates than the proxy pass packed
-          const int bp = __builtin_ctzll(mb);
+      if (mb) {
+        sh_again = 1u;
+        while (mb) {  // more candidates than the proxy pass packed: no key yet (no score's key is 0)
+          list[at++] = value_of(0u, base + __builtin_ctzll(mb));
           mb &= mb - 1ull;
-          todo[td++] = ((uint64_t)(uint32_t)((t * GPT + g) * 64 + bp) << 32) | (uint32_t)idx++;
         }
       }
     }
   }
-  // Calls f(key, group, bit) for each of the thread's candidates beyond those in registers.
-  auto for_each_extra = [&](auto&& f) {
-    if (extra == 0) return;
-    int idx = ov_base;
-#pragma unroll
-    for (int g = 0; g < GPT; ++g) {
-      if (cnt[g] <= SLOTS) continue;
-      unsigned long long mb = mask[g];
-#pragma unroll
-      for (int i = 0; i < SLOTS; ++i) mb &= mb - 1ull;
-      while (mb) {
-        const int bp = __builtin_ctzll(mb);
-        mb &= mb - 1ull;
-        f(ov_key[idx++], g, bp);
-      }
-    }
-  };
-  // ... and for all of them, those in registers first (any order will do for the callers)
-  auto for_each_candidate = [&](auto&& f) {
-#pragma unroll
-    for (int g = 0; g < GPT; ++g)
-#pragma unroll
-      for (int i = 0; i < SLOTS; ++i)
-        if (i < cnt[g]) f(key[g][i], g, bpos_of(g, i));
-    for_each_extra(f);
-  };
-  // q_hat and the cache state go to LDS while the histogram settles
+  // q_hat and the cache state go to LDS beside it
   if (t < r) qh[t] = q_r;
 #pragma unroll
   for (int u = 0; u < SPT; ++u)
@@ -308,54 +274,77 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
       lu_s[u * kT + t] = lu_r[u];
       to_s[u * kT + t] = to_r[u];
     }
-
-  const uint32_t rank_next = (uint32_t)k + (uint32_t)(k >> 1);  // candidates wanted next step
-  uint32_t selm[GPT];                                           // selected packed candidates
-  unsigned long long take_x[GPT];                               // selected ones beyond them
-#pragma unroll
-  for (int g = 0; g < GPT; ++g) {
-    selm[g] = 0u;
-    take_x[g] = 0ull;
-  }
-  float thr_next;
-
   lds_barrier();
-  const uint32_t n_todo = sh_todo;
-  if (n_todo > 0u) {  // uniform
-    for (uint32_t i = t; i < n_todo; i += kT) {
-      const uint64_t e = todo[i];
-      const uint32_t kk = order_key(proxy_score_of_row(Arow, qh, r, (int)(uint32_t)(e >> 32)));
-      ov_key[(uint32_t)e] = kk;
-      atomicAdd(&hist0[bin_of(kk)], 1u);
+  if (sh_again != 0u) {  // uniform
+    for (uint32_t i = t; i < m; i += kT) {
+      const uint64_t v = list[i];
+      if ((uint32_t)(v >> 32) != 0u) continue;
+      const int p = position_of(v);
+      list[i] = value_of(order_key(proxy_score_of_row(Arow, qh, r, p)), p);
     }
     lds_barrier();
   }
-  uint32_t m = find_two_from_top(hist0, (uint32_t)k, rank_next, scan_area(0), res);
-  uint32_t d0 = res[0], above0 = res[1], d_next = res[3];
-  const bool fast = m >= (uint32_t)k && sh_ov <= (uint32_t)kOvCap;
 
-  if (fast) {
+  auto clear_map = [&]() {
+    for (int i = t; i < n_words; i += kT) {
+      map_bits[i] = 0ull;
+      map_first[i] = 0xffffffffu;
+    }
+  };
+  const uint32_t rank_next = (uint32_t)k + (uint32_t)(k >> 1);  // candidates wanted next step
+  float thr_next;
+  uint64_t cut;
+  uint64_t val[kMaxE];  // the thread's entries; 0: none
+  uint32_t E = 0;
+  auto take_entries = [&](uint32_t n_entries) {
+    E = (n_entries + kT - 1) / kT;
+#pragma unroll
+    for (int e = 0; e < kMaxE; ++e) {
+      const uint32_t i = (uint32_t)t * E + e;
+      val[e] = 0ull;
+      if ((uint32_t)e < E && i < n_entries) val[e] = list[i];
+    }
+  };
+  if (listed) {
+    take_entries(m);
+    // ---- 2. the cut: histogram of the keys --------------------------------------------------------
+    // Every candidate's key is >= thr_key.  Bin of a key: (key - thr_key) >> s, the top bin
+    // taking everything beyond.  For a positive threshold s = 12 spreads the scores between the
+    // threshold and twice the threshold over the 2048 bins.
+    int s = (thr_key > 0x80800000u && thr_key < 0xff800000u) ? 12 : 21;
+    auto bin_of = [&](uint64_t v) { return min(((uint32_t)(v >> 32) - thr_key) >> s, 2047u); };
+    auto for_each = [&](auto&& f) {
+#pragma unroll
+      for (int e = 0; e < kMaxE; ++e) {
+        if ((uint32_t)e >= E) break;  // uniform
+        if (val[e] != 0ull) f(val[e]);
+      }
+    };
+    for_each([&](uint64_t v) { atomicAdd(&hist0[bin_of(v)], 1u); });
+    lds_barrier();
+    find_two_from_top(hist0, (uint32_t)k, rank_next, scan_area(1), res);
+    uint32_t d0 = res[0], above0 = res[1], d_next = res[3];
+    clear_map();  // (the list has been read)
     if (d0 == 2047u && s != 21) {
       // the k-th largest lies beyond twice the threshold: bin the whole key range instead
       s = 21;
       lds_barrier();  // res has been read
       for (int i = t; i < 2048; i += kT) hist0[i] = 0u;
       lds_barrier();
-      for_each_candidate([&](uint32_t kk, int, int) { atomicAdd(&hist0[bin_of(kk)], 1u); });
+      for_each([&](uint64_t v) { atomicAdd(&hist0[bin_of(v)], 1u); });
       lds_barrier();
-      m = find_two_from_top(hist0, (uint32_t)k, rank_next, scan_area(1), res);
+      find_two_from_top(hist0, (uint32_t)k, rank_next, scan_area(2), res);
       d0 = res[0];
       above0 = res[1];
       d_next = res[3];
     }
     const uint32_t c0 = hist0[d0];
     const uint32_t want1 = (uint32_t)k - above0;  // how many of bin d0 are selected
-    uint64_t cut;
     if (c0 <= (uint32_t)kSmall) {
       // the few candidates of bin d0 are ranked on (key, position); the want1-th of them is
       // the cut
-      for_each_candidate([&](uint32_t kk, int g, int bp) {
-        if (bin_of(kk) == d0) small[atomicAdd(&sh_small_n, 1u)] = value_of(kk, g, bp);
+      for_each([&](uint64_t v) {
+        if (bin_of(v) == d0) small[atomicAdd(&sh_small_n, 1u)] = v;
       });
       lds_barrier();
       {
@@ -374,17 +363,14 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
       // many candidates in the bin (ties): further histogram levels over the low s bits give
       // the exact key tau of the k-th largest; of the candidates with that key the first
       // need_eq in position order are selected, so the cut is the need_eq-th of them
-      uint32_t* const hist1 = reinterpret_cast<uint32_t*>(X);
+      uint32_t* const hist1 = ahist;  // (zero again afterwards)
       uint32_t known = d0, want = want1;
       int rem = s;
       while (rem > 0) {
         const int bits = rem < 11 ? rem : 11;
         const int nsh = rem - bits;
-        __syncthreads();  // res and hist1 of the previous level have been read
-        for (int i = t; i < 2048; i += kT) hist1[i] = 0u;
-        __syncthreads();
-        for_each_candidate([&](uint32_t kk, int, int) {
-          const uint32_t rel = kk - thr_key;
+        for_each([&](uint64_t v) {
+          const uint32_t rel = (uint32_t)(v >> 32) - thr_key;
           if ((rel >> rem) == known) atomicAdd(&hist1[(rel >> nsh) & ((1u << bits) - 1u)], 1u);
         });
         __syncthreads();
@@ -393,51 +379,22 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
         known = (known << bits) | dd;
         want -= ab;
         rem = nsh;
+        __syncthreads();  // res and hist1 have been read
+        for (int i = t; i < 2048; i += kT) hist1[i] = 0u;
+        __syncthreads();
       }
       // (bin d0 is never the catch-all top bin here, so rel >> s == d0 identifies it)
       const uint32_t tau = thr_key + known, need_eq = want;
-      // the thread's candidates with key tau, in position order
       uint32_t neq = 0;
-#pragma unroll
-      for (int g = 0; g < GPT; ++g) {
-#pragma unroll
-        for (int i = 0; i < SLOTS; ++i) neq += (i < cnt[g] && key[g][i] == tau) ? 1u : 0u;
-      }
-      for_each_extra([&](uint32_t kk, int, int) { neq += kk == tau ? 1u : 0u; });
+      for_each([&](uint64_t v) { neq += (uint32_t)(v >> 32) == tau ? 1u : 0u; });
       uint32_t tot;
       uint32_t eq_rank = block_exclusive_scan(neq, wave_tot, &tot);
-      if (eq_rank < need_eq && need_eq <= eq_rank + neq) {  // the need_eq-th is one of mine
-        int idx = ov_base;
-#pragma unroll
-        for (int g = 0; g < GPT; ++g) {
-          unsigned long long mb = mask[g];
-          int i = 0;
-          while (mb) {  // position order: packed ones, then the others
-            const int bp = __builtin_ctzll(mb);
-            mb &= mb - 1ull;
-            uint32_t kk = 0u;
-#pragma unroll
-            for (int ii = 0; ii < SLOTS; ++ii)
-              if (ii == i) kk = key[g][ii];
-            if (i >= SLOTS) kk = ov_key[idx++];
-            ++i;
-            if (kk == tau && ++eq_rank == need_eq) sh_cut = value_of(kk, g, bp);
-          }
-        }
-      }
+      for_each([&](uint64_t v) {  // (in position order)
+        if ((uint32_t)(v >> 32) == tau && ++eq_rank == need_eq) sh_cut = v;
+      });
       __syncthreads();
       cut = sh_cut;
     }
-    // ---- 2. the selection = candidates at or above the cut; their slot_of look-ups ---------------
-#pragma unroll
-    for (int g = 0; g < GPT; ++g) {
-#pragma unroll
-      for (int i = 0; i < SLOTS; ++i)
-        if (i < cnt[g] && value_of(key[g][i], g, bpos_of(g, i)) >= cut) selm[g] |= 1u << i;
-    }
-    for_each_extra([&](uint32_t kk, int g, int bp) {
-      if (value_of(kk, g, bp) >= cut) take_x[g] |= 1ull << bp;
-    });
     // threshold for the layer's next step: the lower edge of the bin that holds rank 1.5 k, or,
     // with fewer candidates than that, an extrapolation along an exponential tail through
     // (threshold used, m) and (the k-th largest, k)
@@ -458,24 +415,113 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
     for (int row = t; row < n; row += kT) sw[row] = proxy_score_of_row(Arow, qh, r, row);
     __threadfence_block();
     __syncthreads();
-    uint32_t* const hist = reinterpret_cast<uint32_t*>(X);
+    uint32_t* const hist = reinterpret_cast<uint32_t*>(Z);
     uint32_t* const bitmap_l = hist + kBins;
     uint32_t bin_next;
     exact_select_from_scores<false>(sw, n, k, rank_next, hist, bitmap_l, nullptr,
                                     wave_tot, res, &bin_next);
-    // the selection as bits of the thread's groups; none of it is a candidate in registers
+    // the selection, listed: every entry is at or above the cut
 #pragma unroll
     for (int g = 0; g < GPT; ++g) {
       const int gi = t * GPT + g;
-      cnt[g] = 0;
+      mask[g] = 0ull;
       if (gi < ngroups) {
         const uint32_t lo = bitmap_l[2 * gi];
         const uint32_t hi = (2 * gi + 1) * 32 < n ? bitmap_l[2 * gi + 1] : 0u;
-        take_x[g] = ((unsigned long long)hi << 32) | lo;
+        mask[g] = ((unsigned long long)hi << 32) | lo;
       }
     }
+    own = 0;
+#pragma unroll
+    for (int g = 0; g < GPT; ++g) own += (uint32_t)__popcll(mask[g]);
+    uint32_t tot;
+    at = block_exclusive_scan(own, wave_tot, &tot);  // (its barriers: the bitmap has been read)
+#pragma unroll
+    for (int g = 0; g < GPT; ++g) {
+      unsigned long long mb = mask[g];
+      while (mb) {
+        if (at < (uint32_t)k) list[at] = value_of(1u, (t * GPT + g) * 64 + __builtin_ctzll(mb));
+        ++at;
+        mb &= mb - 1ull;
+      }
+    }
+    __syncthreads();
+    take_entries((uint32_t)k);
+    __syncthreads();
+    clear_map();
+    cut = 1ull;
     thr_next = key_to_float(bin_next << kBinShift);  // lower edge of that 12-bit bin
   }
+  // ---- 3. the selection in output order, and the slots that hold it ------------------------------------
+  uint32_t nsel = 0;
+#pragma unroll
+  for (int e = 0; e < kMaxE; ++e) {
+    if (val[e] < cut) val[e] = 0ull;
+    nsel += val[e] != 0ull ? 1u : 0u;
+  }
+  uint32_t tot_sel;
+  uint32_t j = scan1(nsel, scan_area(3), &tot_sel);
+#pragma unroll
+  for (int e = 0; e < kMaxE; ++e) {
+    if ((uint32_t)e >= E) break;  // uniform
+    if (val[e] == 0ull || j >= (uint32_t)k) continue;  // (exactly k positions are selected)
+    const int p = position_of(val[e]);
+    sel_o[j] = p;
+    slot_o[j] = -1;
+    atomicOr(&map_bits[p >> 6], 1ull << (p & 63));
+    atomicMin(&map_first[p >> 6], j);
+    ++j;
+  }
+  lds_barrier();
+#pragma unroll
+  for (int u = 0; u < SPT; ++u) {
+    const int sl = u * kT + t;
+    const int p = to_r[u];
+    if (u >= spt || sl >= C || p < 0 || p >= n) continue;
+    const unsigned long long bits = map_bits[p >> 6];
+    if (((bits >> (p & 63)) & 1ull) == 0ull) continue;
+    const uint32_t jj = map_first[p >> 6] + (uint32_t)__popcll(bits & ((1ull << (p & 63)) - 1ull));
+    slot_o[jj] = sl;
+    lu[sl] = step;
+    lu_s[sl] = step;  // used in this step: never a victim
+  }
+  lds_barrier();
+  // the outputs, coalesced; entry jj = t + 1024 i, what is missing counted in output order
+  int32_t* __restrict__ out = a.sel_idx + (size_t)bh * k;
+  int32_t* __restrict__ ss = a.sel_slot + (size_t)bh * k;
+  uint8_t* __restrict__ ht = a.hit + (size_t)bh * k;
+  int32_t* __restrict__ mt = a.miss_tok + (size_t)bh * k;
+  int32_t* __restrict__ ms = a.miss_slot + (size_t)bh * k;
+  constexpr int kOut = kPackedMaxK / kT;
+  int32_t sl_o[kOut];
+  uint32_t mine[2] = {0u, 0u};  // missing of the thread's entries, 16 bits for each i
+#pragma unroll
+  for (int i = 0; i < kOut; ++i) {
+    const int jj = t + i * kT;
+    sl_o[i] = jj < k ? slot_o[jj] : 0;
+    if (sl_o[i] < 0) mine[i >> 1] += 1u << (16 * (i & 1));
+  }
+  uint32_t ex[2], tot[2];
+  scan2(mine[0], mine[1], scan_area(0), &ex[0], &ex[1], &tot[0], &tot[1]);
+  uint32_t before = 0;  // missing entries of smaller i
+#pragma unroll
+  for (int i = 0; i < kOut; ++i) {
+    const int jj = t + i * kT;
+    const uint32_t mrank = before + ((ex[i >> 1] >> (16 * (i & 1))) & 0xffffu);
+    before += (tot[i >> 1] >> (16 * (i & 1))) & 0xffffu;
+    if (jj >= k) continue;
+    const int p = sel_o[jj];
+    out[jj] = p;
+    ht[jj] = sl_o[i] >= 0 ? 1 : 0;
+    if (sl_o[i] >= 0) {
+      ss[jj] = sl_o[i];
+    } else {
+      mt[mrank] = p;
+      mt_s[mrank] = p;
+      mj_s[mrank] = jj;
+    }
+  }
+  const int nm = (int)before;
   if (wv == kWaves - 1) {
     // |q_hat|: the next step multiplies by its own
     float q2 = lane < r ? qh[lane] * qh[lane] : 0.0f;
@@ -488,94 +534,6 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
       a.sel_thr[bh] = (nrm > 0.0f && isfinite(v)) ? v : __uint_as_float(0x7fc00000u);
     }
   }
-
-  // slot_of of the thread's selected positions (selected packed candidates: in registers)
-  int32_t slot[GPT][SLOTS];
-  uint32_t nsel = 0, nmiss = 0;
-#pragma unroll
-  for (int g = 0; g < GPT; ++g) {
-    const int base = (t * GPT + g) * 64;
-#pragma unroll
-    for (int i = 0; i < SLOTS; ++i) {
-      slot[g][i] = 0;
-      if (selm[g] & (1u << i)) slot[g][i] = so[base + bpos_of(g, i)];
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < GPT; ++g) {
-    nsel += (uint32_t)__popc(selm[g]) + (uint32_t)__popcll(take_x[g]);
-#pragma unroll
-    for (int i = 0; i < SLOTS; ++i)
-      if (selm[g] & (1u << i)) {
-        if (slot[g][i] >= C) slot[g][i] = -1;  // corrupt map entry: treat as absent
-        nmiss += slot[g][i] < 0 ? 1u : 0u;
-      }
-    unsigned long long tb = take_x[g];
-    while (tb) {
-      const int32_t sl = so[(t * GPT + g) * 64 + __builtin_ctzll(tb)];
-      nmiss += (sl < 0 || sl >= C) ? 1u : 0u;
-      tb &= tb - 1ull;
-    }
-  }
-  // ---- 3. places in the outputs: one prefix count over (selected, missing) ---------------------------
-  uint32_t j, mrank, tot_sel, tot_miss;
-  scan2(nsel, nmiss, scan_area(2), &j, &mrank, &tot_sel, &tot_miss);
-  const int nm = (int)tot_miss;
-  int32_t* __restrict__ out = a.sel_idx + (size_t)bh * k;
-  int32_t* __restrict__ ss = a.sel_slot + (size_t)bh * k;
-  uint8_t* __restrict__ ht = a.hit + (size_t)bh * k;
-  int32_t* __restrict__ mt = a.miss_tok + (size_t)bh * k;
-  int32_t* __restrict__ ms = a.miss_slot + (size_t)bh * k;
-  {
-    // staged in LDS in output order (the thread's own entries are scattered lanes of many
-    // predicated stores); the global stores follow, coalesced.  (Every thread has made its
-    // decisions before the barrier of the prefix count above: the selection's LDS is free.)
-    auto emit = [&](int p, int32_t sl) {
-      if (j >= (uint32_t)k) return;  // cannot happen: exactly k positions are selected
-      sel_o[j] = p;
-      if (sl >= 0) {
-        slot_o[j] = sl;
-      } else {
-        slot_o[j] = -1 - (int32_t)mrank;
-        mt_s[mrank] = p;
-        mj_s[mrank] = (int32_t)j;
-        ++mrank;
-      }
-      ++j;
-    };
-#pragma unroll
-    for (int g = 0; g < GPT; ++g) {
-      const int base = (t * GPT + g) * 64;
-      // position order inside the group: the candidates in registers come first, in position
-      // order; the ones beyond them lie at higher positions
-#pragma unroll
-      for (int i = 0; i < SLOTS; ++i)
-        if (selm[g] & (1u << i)) emit(base + bpos_of(g, i), slot[g][i]);
-      unsigned long long tb = take_x[g];
-      while (tb) {
-        const int p = base + __builtin_ctzll(tb);
-        int32_t sl = so[p];
-        if (sl >= C) sl = -1;
-        emit(p, sl);
-        tb &= tb - 1ull;
-      }
-    }
-    lds_barrier();
-    for (int jj = t; jj < k; jj += kT) {
-      const int p = sel_o[jj];
-      const int32_t sl = slot_o[jj];
-      out[jj] = p;
-      ht[jj] = sl >= 0 ? 1 : 0;
-      if (sl >= 0) {
-        ss[jj] = sl;
-        lu[sl] = step;
-        lu_s[sl] = step;  // used in this step: never a victim
-      } else {
-        mt[-1 - sl] = p;
-      }
-    }
-  }
-  lds_barrier();
 
   // ---- 4. victims ------------------------------------------------------------------------------------
   if (nm > 0) {
@@ -608,42 +566,38 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
   if (t == 0) a.n_miss[bh] = sh_bad ? -1 : nm;
 }
 
-// Candidates of a group kept in registers: all 8 packed ones where a thread owns one or two
-// groups, 4 where it owns three or four (the registers would not hold more; at one or two
-// groups per thread 4, 6 or 8 measure the same).
-template <int GPT>
-constexpr int slots_in_registers() {
-  return GPT <= 2 ? kCandPerGroup : 4;
-}
-
-template <int GPT, int SPT>
+template <int GPT, int SPT, int CPG>
 hipError_t launch_inst(const PackedArgs& a, int BHq, size_t lds, hipStream_t st) {
   static std::atomic<uint64_t> raised{0};  // devices on which this instantiation's ceiling is up
   const hipError_t e =
-      raise_dynamic_lds_once(select_packed_kernel<GPT, SPT, slots_in_registers<GPT>()>,
+      raise_dynamic_lds_once(select_packed_kernel<GPT, SPT, CPG>,
                              kPackedLdsLimit, raised);
   if (e != hipSuccess) return e;
-  LRQK_LAUNCH((select_packed_kernel<GPT, SPT, slots_in_registers<GPT>()>), dim3(BHq), dim3(kT), lds,
-              st, a);
+  LRQK_LAUNCH((select_packed_kernel<GPT, SPT, CPG>), dim3(BHq), dim3(kT), lds, st, a);
   return hipGetLastError();
 }
-template <int GPT>
+template <int GPT, int CPG>
 hipError_t launch_gpt(const PackedArgs& a, int BHq, size_t lds, hipStream_t st) {
-  if (a.C <= 2 * kT) return launch_inst<GPT, 2>(a, BHq, lds, st);
-  if (a.C <= 4 * kT) return launch_inst<GPT, 4>(a, BHq, lds, st);
-  return launch_inst<GPT, 8>(a, BHq, lds, st);
+  if (a.C <= 2 * kT) return launch_inst<GPT, 2, CPG>(a, BHq, lds, st);
+  if (a.C <= 4 * kT) return launch_inst<GPT, 4, CPG>(a, BHq, lds, st);
+  return launch_inst<GPT, 8, CPG>(a, BHq, lds, st);
 }
 
 }  // namespace
 
+int cand_per_group(const lrqk_shape& s) {
+  const int groups = filter_words64(s.l - s.w);
+  return groups <= kT && 3L * s.k > 5L * groups && select_packed_fits(s) ? 2 * kCandPerGroup
+                                                                         : kCandPerGroup;
+}
+
 bool select_packed_fits(const lrqk_shape& s) {
   const int n = s.l - s.w;
   if (((n + 63) >> 6) > 4 * kT) return false;  // at most 4 groups of 64 positions per thread
-  if (s.C > kMaxSpt * kT) return false;
-  // Dense selections (k a sizeable fraction of the context) put more than 8 candidates into
-  // most groups: the 1.5 k candidates the threshold aims at, less the 8 per group that the proxy
-  // pass packs, must leave room in the area for the others
-  if ((long)s.k + s.k / 2 - (long)kCandPerGroup * ((n + 63) >> 6) > kOvCap / 2) return false;
+  if (s.C > kMaxSpt * kT || s.k > kPackedMaxK) return false;
+  // Dense selections (k a sizeable fraction of the context) put many candidates into most groups;
+  // of the 1.5 k that the threshold aims at, few may be left for their scores to be computed again
+  if ((long)s.k + s.k / 2 - (long)kCandPerGroup * ((n + 63) >> 6) > 1024) return false;
   return packed_arena(s.k, n, s.C).total <= kPackedLdsLimit;
 }
 
@@ -665,6 +619,7 @@ hipError_t launch_select_packed(const lrqk_shape& s, const unsigned long long* b
   a.sel_thr = sel_thr;
   a.words64 = filter_words64(n);
   a.r = s.r;
+  a.B = s.B;
   a.Hq = s.Hq;
   a.Hkv = s.Hkv;
   a.l = s.l;
@@ -685,10 +640,11 @@ hipError_t launch_select_packed(const lrqk_shape& s, const unsigned long long* b
   const size_t lds = packed_arena(s.k, n, s.C).total;
   const int groups = (n + 63) >> 6;
   const int BHq = s.B * s.Hq;
-  if (groups <= kT) return launch_gpt<1>(a, BHq, lds, st);
-  if (groups <= 2 * kT) return launch_gpt<2>(a, BHq, lds, st);
-  if (groups <= 3 * kT) return launch_gpt<3>(a, BHq, lds, st);
-  return launch_gpt<4>(a, BHq, lds, st);
+  if (cand_per_group(s) > kCandPerGroup) return launch_gpt<1, 2 * kCandPerGroup>(a, BHq, lds, st);
+  if (groups <= kT) return launch_gpt<1, kCandPerGroup>(a, BHq, lds, st);
+  if (groups <= 2 * kT) return launch_gpt<2, kCandPerGroup>(a, BHq, lds, st);
+  if (groups <= 3 * kT) return launch_gpt<3, kCandPerGroup>(a, BHq, lds, st);
+  return launch_gpt<4, kCandPerGroup>(a, BHq, lds, st);
 }
 
 }  // namespace lrqk

@@ -25,6 +25,7 @@
 // batch of eight at 64K, bound by the host link and A_K, takes 306 to 309 us either way.
 #include <type_traits>
 
+#include "lrqk_device.h"
 #include "lrqk_internal.h"
 
 namespace lrqk {
@@ -133,7 +134,9 @@ struct AttendArgs {
   const void* liteK;
   const void* liteV;
   float* partials;
-  int Hq, Hkv, C, k, w, rows_per_block, parts_per_head, part_offset;
+  int B, Hq, Hkv, C, k, w, rows_per_block, parts_per_head, part_offset;
+  int blocks;  // workgroups per head
+  bool by_die;
   float scale;
 };
 
@@ -297,7 +300,9 @@ __device__ __forceinline__ void attend_partial_body(const AttendArgs& a, int bx,
 
 template <bool BF16, int MODE>
 __global__ __launch_bounds__(kAttThreads) void attend_partial_kernel(const AttendArgs a) {
-  attend_partial_body<BF16, MODE>(a, blockIdx.x, blockIdx.y);
+  int bh, block;
+  dev::place_head(blockIdx.x, a.B, a.Hq, a.Hkv, a.blocks, bh, block, a.by_die);
+  attend_partial_body<BF16, MODE>(a, block, bh);
 }
 
 // Fetch shared by the query heads of a KV group (K and V exist once per KV head, Sec. 4
@@ -315,6 +320,7 @@ struct GroupFetchArgs {
   const int32_t* n_miss;
   int32_t* link_rows;   // [B,Hkv] rows read from the host store, or null (not counted)
   int Hq, Hkv, C, k;
+  int blocks;           // workgroups per head
 };
 template <bool BF16>
 __device__ __forceinline__ void group_fetch_body(const GroupFetchArgs& a, int fx, int nfx, int bh) {
@@ -376,7 +382,8 @@ __device__ __forceinline__ void group_fetch_body(const GroupFetchArgs& a, int fx
 
 template <bool BF16>
 __global__ __launch_bounds__(kAttThreads) void group_fetch_kernel(const GroupFetchArgs a) {
-  group_fetch_body<BF16>(a, blockIdx.x, gridDim.x, blockIdx.y);
+  const int bh = blockIdx.x / a.blocks, block = blockIdx.x - bh * a.blocks;
+  group_fetch_body<BF16>(a, block, a.blocks, bh);
 }
 
 // The attention over the rows that hit and the lite rows (blocks [0, n_attend) of a head) and
@@ -384,11 +391,13 @@ __global__ __launch_bounds__(kAttThreads) void group_fetch_kernel(const GroupFet
 // other, so the host-link reads run beside the HBM reads.
 template <bool BF16>
 __global__ __launch_bounds__(kAttThreads) void attend_hits_group_fetch_kernel(
-    const AttendArgs a, const GroupFetchArgs f, int n_attend) {
-  if ((int)blockIdx.x < n_attend)
-    attend_partial_body<BF16, kAttendHitsAndLite>(a, blockIdx.x, blockIdx.y);
+    const AttendArgs a, const GroupFetchArgs f) {
+  const int per_head = a.blocks + f.blocks;
+  const int bh = blockIdx.x / per_head, block = blockIdx.x - bh * per_head;
+  if (block < a.blocks)
+    attend_partial_body<BF16, kAttendHitsAndLite>(a, block, bh);
   else
-    group_fetch_body<BF16>(f, blockIdx.x - n_attend, gridDim.x - n_attend, blockIdx.y);
+    group_fetch_body<BF16>(f, block - a.blocks, f.blocks, bh);
 }
 
 constexpr int kCombThreads = 512;
@@ -399,12 +408,14 @@ constexpr int kCombMaxParts = 1024;
 // coalesced loads (thread = output dimension) and are summed through LDS.
 __global__ __launch_bounds__(kCombThreads) void attend_combine_kernel(
     const float* __restrict__ partials, int parts_per_head, int nparts,
-    float* __restrict__ out) {
+    float* __restrict__ out, int B, int Hq, int Hkv, bool by_die) {
   __shared__ float wgt[kCombMaxParts];
   __shared__ float red[kCombThreads / 64];
   __shared__ float accs[kCombThreads / kD][kD];
   __shared__ float sh_M, sh_S;
-  const int bh = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  int bh, block;
+  dev::place_head(blockIdx.x, B, Hq, Hkv, 1, bh, block, by_die);
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const float* __restrict__ P = partials + (size_t)bh * parts_per_head * kPartialStride;
   // block max of the part maxima
   float m = -INFINITY;
@@ -472,13 +483,20 @@ size_t attend_ws_bytes(int BHq, int k, int w, int phases) {
   return round_up((size_t)BHq * parts * kPartialStride * sizeof(float), 256);
 }
 
+// The workgroups of a head on the die of the selection and of the merge, where they are few: a step at
+// 4K context (9 for each of 32 heads) 24.1 -> 23.5 us, two layers at 32K (34) 118.2 -> 117.6; with more
+// of them (66 at 128K) the reads over the host link no longer start everywhere at once: 234.4 -> 235.6.
+static bool attend_by_die(const lrqk_shape& s, int parts_per_head) {
+  return s.B * s.Hq * parts_per_head <= 1536;
+}
+
 static AttendArgs make_attend_args(const lrqk_shape& s, const float* q,
                                    const void* cacheK, const void* cacheV,
                                    const int32_t* sel_slot, const uint8_t* hit,
                                    const int32_t* miss_slot, const int32_t* n_miss,
                                    const void* liteK, const void* liteV, float* partials,
-                                   int rows_per_block, int parts_per_head, int part_offset,
-                                   const void* K_host, const void* V_host,
+                                   int nblocks, int rows_per_block, int parts_per_head,
+                                   int part_offset, const void* K_host, const void* V_host,
                                    const int32_t* sel_idx) {
   AttendArgs a;
   a.fs = FetchSrc{static_cast<const char*>(K_host), static_cast<const char*>(V_host), sel_idx,
@@ -493,6 +511,7 @@ static AttendArgs make_attend_args(const lrqk_shape& s, const float* q,
   a.liteK = liteK;
   a.liteV = liteV;
   a.partials = partials;
+  a.B = s.B;
   a.Hq = s.Hq;
   a.Hkv = s.Hkv;
   a.C = s.C;
@@ -501,9 +520,14 @@ static AttendArgs make_attend_args(const lrqk_shape& s, const float* q,
   a.rows_per_block = rows_per_block;
   a.parts_per_head = parts_per_head;
   a.part_offset = part_offset;
+  a.blocks = nblocks;
+  a.by_die = attend_by_die(s, parts_per_head);
   a.scale = s.scale;
   return a;
 }
+
+// workgroups per head that the shared fetch is spread over (16 rows per pass each)
+static int group_fetch_blocks(const lrqk_shape& s) { return min(ceil_div(s.k, 16), 32); }
 
 static GroupFetchArgs make_group_fetch_args(const lrqk_shape& s, const void* K_host,
                                             const void* V_host, const int32_t* miss_tok,
@@ -522,6 +546,7 @@ static GroupFetchArgs make_group_fetch_args(const lrqk_shape& s, const void* K_h
   f.Hkv = s.Hkv;
   f.C = s.C;
   f.k = s.k;
+  f.blocks = group_fetch_blocks(s);
   return f;
 }
 
@@ -536,9 +561,9 @@ hipError_t launch_attend_partial(const lrqk_shape& s, int mode, const float* q, 
   if (mode == kAttendAllFetch && (!K_host || !V_host || !sel_idx || !hit))
     return hipErrorInvalidValue;
   const AttendArgs a = make_attend_args(s, q, cacheK, cacheV, sel_slot, hit, miss_slot,
-                                        n_miss, liteK, liteV, partials, rows_per_block,
+                                        n_miss, liteK, liteV, partials, nblocks, rows_per_block,
                                         parts_per_head, part_offset, K_host, V_host, sel_idx);
-  const dim3 grid(nblocks, s.B * s.Hq);
+  const dim3 grid(nblocks * s.B * s.Hq);
   auto run = [&](auto m) {
     constexpr int MODE = decltype(m)::value;
     if (s.kv_dtype == LRQK_KV_BF16)
@@ -556,16 +581,13 @@ hipError_t launch_attend_partial(const lrqk_shape& s, int mode, const float* q, 
   return hipGetLastError();
 }
 
-// workgroups per head that the shared fetch is spread over (16 rows per pass each)
-static int group_fetch_blocks(const lrqk_shape& s) { return min(ceil_div(s.k, 16), 32); }
-
 hipError_t launch_group_fetch(const lrqk_shape& s, const void* K_host, const void* V_host,
                               const int32_t* miss_tok, const int32_t* miss_slot,
                               const int32_t* n_miss, void* cacheK, void* cacheV,
                               int32_t* link_rows, hipStream_t st) {
   const GroupFetchArgs f = make_group_fetch_args(s, K_host, V_host, miss_tok, miss_slot, n_miss,
                                                  cacheK, cacheV, link_rows);
-  const dim3 grid(group_fetch_blocks(s), s.B * s.Hq);
+  const dim3 grid(f.blocks * s.B * s.Hq);
   if (s.kv_dtype == LRQK_KV_BF16)
     LRQK_LAUNCH((group_fetch_kernel<true>), grid, dim3(kAttThreads), 0, st, f);
   else
@@ -583,17 +605,15 @@ hipError_t launch_attend_hits_group_fetch(const lrqk_shape& s, const float* q, v
                                           const int32_t* n_miss, int32_t* link_rows,
                                           hipStream_t st) {
   const AttendArgs a = make_attend_args(s, q, cacheK, cacheV, sel_slot, hit,
-                                        nullptr, nullptr, liteK, liteV, partials, rows_per_block,
-                                        parts_per_head, 0, nullptr, nullptr, nullptr);
+                                        nullptr, nullptr, liteK, liteV, partials, nblocks,
+                                        rows_per_block, parts_per_head, 0, nullptr, nullptr, nullptr);
   const GroupFetchArgs f = make_group_fetch_args(s, K_host, V_host, miss_tok, miss_slot, n_miss,
                                                  cacheK, cacheV, link_rows);
-  const dim3 grid(nblocks + group_fetch_blocks(s), s.B * s.Hq);
+  const dim3 grid((nblocks + f.blocks) * s.B * s.Hq);
   if (s.kv_dtype == LRQK_KV_BF16)
-    LRQK_LAUNCH((attend_hits_group_fetch_kernel<true>), grid, dim3(kAttThreads), 0, st, a, f,
-                nblocks);
+    LRQK_LAUNCH((attend_hits_group_fetch_kernel<true>), grid, dim3(kAttThreads), 0, st, a, f);
   else
-    LRQK_LAUNCH((attend_hits_group_fetch_kernel<false>), grid, dim3(kAttThreads), 0, st, a, f,
-                nblocks);
+    LRQK_LAUNCH((attend_hits_group_fetch_kernel<false>), grid, dim3(kAttThreads), 0, st, a, f);
   return hipGetLastError();
 }
 
@@ -601,7 +621,8 @@ hipError_t launch_attend_combine(const lrqk_shape& s, const float* partials, int
                                  int nparts, float* out, hipStream_t st) {
   if (nparts > kCombMaxParts) return hipErrorInvalidValue;
   LRQK_LAUNCH(attend_combine_kernel, dim3(s.B * s.Hq), dim3(kCombThreads), 0, st,
-                     partials, parts_per_head, nparts, out);
+                     partials, parts_per_head, nparts, out, s.B, s.Hq, s.Hkv,
+                     attend_by_die(s, parts_per_head));
   return hipGetLastError();
 }
 

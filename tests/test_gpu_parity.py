@@ -456,6 +456,21 @@ def test_decode_step_shape_sweep(shape, mode):
     run_steps_against_oracle(cfg, 4, mode, check_unfused=False, quiet=True)
 
 
+@pytest.mark.parametrize("shape", [
+    # l, k, w, C, r, G, Hkv
+    (4100, 480, 4, 700, 32, 4, 1),      # 11 candidates a group: more than 8, some more than 16
+    (65540, 100, 4, 200, 16, 7, 1),     # 1025 groups, few candidates: 8 entries, two groups a thread
+    (65536, 1800, 0, 1800, 16, 1, 2),   # 1024 groups, 2.6 candidates each: 16 entries
+    (60000, 40, 17, 8192, 16, 2, 2),    # position map behind the slots of a small selection
+    (131072, 4096, 64, 4096, 16, 2, 1)])  # more than 4096 candidates: over 4 entries a thread
+def test_decode_step_candidate_list(shape):
+    """The list of candidates around its sizes: entries packed per group, entries per thread, the
+    places of what follows it; heads on one compute die and not."""
+    l, k, w, C, r, G, Hkv = shape
+    run_steps_against_oracle(small_cfg(l=l, k=k, w=w, C=C, r=r, Hq=G * Hkv, Hkv=Hkv, B=8 // Hkv if
+                                       l < 5000 else 1), 3, "direct", check_unfused=False)
+
+
 def test_decode_step_step_counter_far_ahead_of_the_slots_ages():
     say("decode_step with step numbers that jump by thousands (ages beyond the victim histogram)")
     # steps 1, 2, 3, then 5000, 5001, 9000, 9001: the slots' ages exceed the 2048 classes of the
