@@ -16,7 +16,7 @@
 //
 // (With a pass over Q and K in every update, X^T Y and X^T X from the fp32 matrix cores and the
 // solves in fp32, the whole took 2.35 ms at 32 + 8 heads, l = 131072, r = 32, bf16, two rounds;
-// now 0.95 ms.)
+// now 0.93 ms.)
 //
 // Precision.  The long products run on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16) with
 // every fp32 operand split into three bf16 terms, x = x0 + x1 + x2, 8 bits of significand each, and
@@ -503,8 +503,14 @@ __global__ __launch_bounds__(256) void prefill_sum_kernel(const void* __restrict
                                                           double* __restrict__ H, int nchunk) {
   using S = PfShape<R>;
   constexpr int kBlocks = ((S::GB + S::HB0) * 1024 + R * R + 255) / 256;  // workgroups per head
-  const size_t head = blockIdx.x / kBlocks;
-  int e = blockIdx.x % kBlocks * 256 + threadIdx.x;
+  // A head's sum and its solves on one die: what one launch writes the next reads from that die's L2
+  // (the whole call, 32 + 8 heads, bf16: 79.6 -> 77.4 us at l = 4096, r = 16; 177.9 -> 175.4 at
+  // l = 16384, r = 32; 2 x (28 + 4) heads, l = 30011, r = 64: 593.9 -> 589.9).  With the chunks' partials
+  // on it as well nothing more is gained (77.6, 174.5, 594.0): they come from every die's share of Q and K.
+  int at, block;
+  dev::place(blockIdx.x, gridDim.x / kBlocks, kBlocks, at, block);
+  const size_t head = at;
+  int e = block * 256 + threadIdx.x;
   const char* p = static_cast<const char*>(part) + head * nchunk * S::part_bytes;
   auto total = [&](const auto* q) {  // q: the element in the first chunk's partial
     double acc = 0.0;
@@ -923,8 +929,9 @@ __global__ __launch_bounds__(kAlgThreads) void prefill_round_k_kernel(const PfSt
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   constexpr int kParts = SHARED ? 4 : 1;
   const bool iskv = (int)blockIdx.x < a.BHkv * kParts;
-  const int part = iskv ? (int)blockIdx.x % kParts : 0;
-  const size_t own = iskv ? (int)blockIdx.x / kParts : (int)blockIdx.x - a.BHkv * kParts;
+  int kv_at, kv_part;
+  dev::place(blockIdx.x, a.BHkv, kParts, kv_at, kv_part);
+  const size_t own = iskv ? kv_at : (int)blockIdx.x - a.BHkv * kParts;
   const int b = (int)own / a.Hkv, kvh = (int)own - b * a.Hkv, G = a.Hq / a.Hkv;
   const size_t q0 = (size_t)b * a.Hq + (size_t)kvh * G;  // a KV head's query heads
   f64x4 d[Z::TPW];
@@ -932,6 +939,7 @@ __global__ __launch_bounds__(kAlgThreads) void prefill_round_k_kernel(const PfSt
   // On its way during the first solve: the sums of the first query heads; during the second: G.
   constexpr int kPre = R <= 16 ? 3 : R <= 32 ? 2 : 1;
   using Part = PfPart<R, SHARED>;
+  const int part = iskv ? kv_part : 0;
   const Part share(part, w);
   double pre[kPre][Z::kRaw], gram[Part::kSteps];
   if constexpr (kGroupSums<R>) {
@@ -1000,9 +1008,10 @@ __global__ __launch_bounds__(kAlgThreads) void prefill_round_q_kernel(const PfSt
   double* const Ys = X + Z::kX;
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   constexpr int kParts = SHARED ? 4 : 1;
-  const int bh = blockIdx.x / kParts;
+  int bh, part;
+  dev::place(blockIdx.x, a.BHq, kParts, bh, part);
   using Part = PfPart<R, SHARED>;
-  const Part share(blockIdx.x % kParts, w);
+  const Part share(part, w);
   const int b = bh / a.Hq, kvh = (bh - b * a.Hq) / (a.Hq / a.Hkv);
   const size_t kv = (size_t)b * a.Hkv + kvh;
   const double* BQ = a.BQ + (size_t)bh * R * kD;
@@ -1274,9 +1283,10 @@ hipError_t run_prefill(const lrqk_shape& s, const void* Q, const void* K, float*
     std::swap(HK, HK_new);
   }
   // 32-row units per wavefront: enough workgroups to fill the chip a few times over
+  // (the whole call at l = 131072, r = 32, 32 + 8 heads, with at most 16, 8, 4 of them: 944, 920, 918 us)
   const int row_units = ceil_div(l, 32);
   int units = 1;
-  while (units < 16 && (long)ceil_div(row_units, 8 * units) * heads >= 2048) units *= 2;
+  while (units < 4 && (long)ceil_div(row_units, 8 * units) * heads >= 2048) units *= 2;
   const int blocks = ceil_div(row_units, 4 * units);
   // Non-temporal stores where A_Q and A_K exceed the L2s (32 MB), loads where Q and K exceed the
   // Infinity Cache (256 MB).  Whole call, 32 + 8 heads, bf16, in us with neither, stores, both: l = 131072,
