@@ -43,8 +43,8 @@
 // histogram of the ages of the slots not used in this step is scanned from the oldest; the
 // age classes that hold the n_miss oldest slots are numbered, and a victim's rank is the
 // number of slots in older classes plus its index inside its class in slot order -- one
-// more prefix count, whatever the number of victims.  Cache state is read from LDS: the
-// slot_of look-ups are the only dependent global round trip of the kernel.
+// more prefix count, whatever the number of victims.  Cache state is read from LDS: but for
+// candidates beyond the packed ones, nothing depends on a global load after the first round.
 //
 // All decisions are integer comparisons: the result is exact and independent of scheduling.
 #include "lrqk_device.h"
