@@ -157,7 +157,10 @@ int lrqk_select_topk(const lrqk_shape* shape, const float* scores, int32_t* sel_
  *   slot_of   int32 [B, Hq, l]  slot holding token i, or -1 if i is not on the GPU
  *   token_of  int32 [B, Hq, C]  token held by a slot, or -1 if the slot is empty
  *   last_used int32 [B, Hq, C]  step at which the slot's token was last selected, -1 if empty
- * slot_of and token_of are mutually inverse on the resident set.
+ * slot_of and token_of are mutually inverse on the resident set.  Whether a token is resident is
+ * read from slot_of alone: after slot_of[., i] = -1 (lrqk_append_token, or a caller that replaces
+ * rows of a context it has cut back) the next step that selects i fetches its row, whatever
+ * token_of says of the slot that held it.
  * lrqk_cache_init sets all three to -1 (an empty cache).
  */
 int lrqk_cache_init(const lrqk_shape* shape, int32_t* slot_of, int32_t* token_of,

@@ -22,20 +22,21 @@
 //     with the right rank is the cut: the selection is every candidate at or above it.  A
 //     bin with many candidates (ties) goes through further 11-bit histogram levels and an
 //     ordered cut instead;
-//   * a prefix count over the selected entries gives each its place in the outputs, and a bitmap of the
-//     selection with a count per 64 positions says for a position whether and where it stands there: every
-//     cache slot looks its token up (token_of is in LDS by then; slot_of is its inverse and is only
-//     written: to look up k positions in it means k cache lines, 4 cycles each at the least: 4500 cycles at
-//     k = 1024, 7500 at 2048).  What no slot has claimed is missing;
+//   * whether a position is in the cache, and where, is for slot_of to say (a caller that cuts its context
+//     back and goes on leaves slots whose token_of names a removed token; tests:
+//     test_context_cut_back_and_continued).  It is looked up for the entries from the bin of the cut on,
+//     while the cut is found: k cache lines, 4 cycles each at the least.  Looked up before the histogram,
+//     for all 1.5 k entries, or after the cut: a step at 4K context 20.7 instead of 21.0 us, two layers at
+//     128K 235.2 instead of 234.7.  (Every cache slot looking its token_of up in a map of the selection needs
+//     no such loads, 21.5 and 231.3 us, but answers from the wrong array.)  One prefix count over (selected,
+//     missing) gives every entry its place in the outputs;
 //   * the same histogram yields the key at rank 1.5 k, which (divided by |q_hat|) is handed
 //     to the next step of the layer as its candidate threshold, so that steps after the
 //     first need no threshold estimate of their own.
 // (Before, a thread kept the candidates of its own groups in registers, 8 a group, from the first load to
-// the last store: every phase then had 8 to 16 predicated steps of which most lanes skipped most, and
-// slot_of was looked up.  The kernel at 128K, two groups a thread: 18.6 -> 17.6 us; at 50K, r = 64: 16.1 ->
-// 14.5; a whole step at 4K context, where one wavefront owned all the groups: 24.0 -> 21.5.)
-// Cycles at 2.3 GHz, one head at 32K: first loads 6200, list 3000, histogram 2000, scan 1900, cut 1800,
-// positions in output order 1800, slots 2200, outputs 1800, victims 6500.
+// the last store: every phase then had 8 to 16 predicated steps of which most lanes skipped most.  A whole
+// step at 4K context, where one wavefront owned all the groups: 23.9 -> 21.0 us.)
+// Cycles at 2.3 GHz, one head at 32K: first loads 6200, list 3000, histogram 2000, scan 1900, victims 6500.
 // A head whose candidates are unusable (fewer than k, or more than the list holds) recomputes all its scores into the workspace and selects exactly from them
 // (exact_select_from_scores): slower, same result.
 //
@@ -44,7 +45,7 @@
 // age classes that hold the n_miss oldest slots are numbered, and a victim's rank is the
 // number of slots in older classes plus its index inside its class in slot order -- one
 // more prefix count, whatever the number of victims.  Cache state is read from LDS: but for
-// candidates beyond the packed ones, nothing depends on a global load after the first round.
+// candidates beyond the packed ones, the slot_of look-ups are the only dependent global round trip.
 //
 // All decisions are integer comparisons: the result is exact and independent of scheduling.
 #include "lrqk_device.h"
@@ -66,12 +67,10 @@ __host__ __device__ inline size_t up256(size_t x) { return (x + 255) / 256 * 256
 // LDS: last_used and token_of [C] each; age and key histograms; the threshold bin's entries; then, in one
 // area, one after the other,
 //   the list of candidates, or the exact route's histogram and bitmap;
-//   the selection in output order, its positions and slots [k] each from 3 k_b on, and its bitmap with the
-//   counts, each at the start of the area as far as they fit 3 k_b, behind the slots otherwise;
-//   [k] miss positions, their output indices, victims in rank order, and from 3 k_b on the all-slots
-//   sort of the rare resolution cases.
+//   [k] miss positions, their output indices, victims in rank order; from 3 k_b on the selection in output
+//   order, its positions and slots [k] each, and after them the all-slots sort of the rare resolution cases.
 struct PackedArena {
-  size_t st_b, k_b, bits_at, first_at, fixed, total;  // (bits_at, first_at: from the area's start)
+  size_t st_b, k_b, fixed, total;
   int list_cap;
 };
 __host__ __device__ inline PackedArena packed_arena(int k, int n, int C) {
@@ -83,12 +82,8 @@ __host__ __device__ inline PackedArena packed_arena(int k, int n, int C) {
   int Cpad = 2;
   while (Cpad < C) Cpad <<= 1;
   const size_t sort_b = (size_t)Cpad * 8;
-  const size_t words = ((size_t)n + 63) / 64, bits_b = up256(words * 8), first_b = up256(words * 4);
-  a.bits_at = bits_b <= 3 * a.k_b ? 0 : 5 * a.k_b;
-  a.first_at = a.bits_at > 0 ? a.bits_at + bits_b : bits_b + first_b <= 3 * a.k_b ? bits_b : 5 * a.k_b;
   const size_t out = 3 * a.k_b + (2 * a.k_b > sort_b ? 2 * a.k_b : sort_b);
   size_t z = out > exact ? out : exact;
-  if (z < a.first_at + first_b) z = a.first_at + first_b;
   // room for twice the candidates that the threshold aims at, more where it costs nothing
   const size_t want = up256((size_t)(3 * k < kListCap ? 3 * k : kListCap) * 8);
   if (z < want && a.fixed + want <= kPackedLdsLimit) z = want;
@@ -181,10 +176,6 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
   unsigned char* const X = Z + 3 * az.k_b;
   int32_t* const sel_o = reinterpret_cast<int32_t*>(X);                    // [k]
   int32_t* const slot_o = reinterpret_cast<int32_t*>(X + az.k_b);          // [k]
-  const int n_words = (n + 63) >> 6;
-  unsigned long long* const map_bits =                                     // [n_words]
-      reinterpret_cast<unsigned long long*>(Z + az.bits_at);
-  uint32_t* const map_first = reinterpret_cast<uint32_t*>(Z + az.first_at);  // [n_words]
 
   const int b = bh / a.Hq, h = bh - b * a.Hq, kvh = h / (a.Hq / a.Hkv);
   const float* __restrict__ Arow = a.A_K + ((size_t)b * a.Hkv + kvh) * (size_t)a.lrows * r;
@@ -285,12 +276,6 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
     lds_barrier();
   }
 
-  auto clear_map = [&]() {
-    for (int i = t; i < n_words; i += kT) {
-      map_bits[i] = 0ull;
-      map_first[i] = 0xffffffffu;
-    }
-  };
   const uint32_t rank_next = (uint32_t)k + (uint32_t)(k >> 1);  // candidates wanted next step
   float thr_next;
   uint64_t cut;
@@ -303,6 +288,23 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
       const uint32_t i = (uint32_t)t * E + e;
       val[e] = 0ull;
       if ((uint32_t)e < E && i < n_entries) val[e] = list[i];
+    }
+  };
+  // slot_of of the entries that may be selected (from clamped addresses, as above)
+  int32_t slot[kMaxE];
+#pragma unroll
+  for (int e = 0; e < kMaxE; ++e) slot[e] = -1;
+  auto look_up = [&]() {
+    auto load = [&](int e) { slot[e] = so[min(max(position_of(val[e]), 0), n - 1)]; };
+    load(0);
+    load(1);
+    if (E > 2u) {
+      load(2);
+      load(3);
+    }
+    if (E > 4u) {
+#pragma unroll
+      for (int e = 4; e < kMaxE; ++e) load(e);
     }
   };
   if (listed) {
@@ -324,7 +326,6 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
     lds_barrier();
     find_two_from_top(hist0, (uint32_t)k, rank_next, scan_area(1), res);
     uint32_t d0 = res[0], above0 = res[1], d_next = res[3];
-    clear_map();  // (the list has been read)
     if (d0 == 2047u && s != 21) {
       // the k-th largest lies beyond twice the threshold: bin the whole key range instead
       s = 21;
@@ -338,6 +339,10 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
       above0 = res[1];
       d_next = res[3];
     }
+#pragma unroll
+    for (int e = 0; e < kMaxE; ++e)
+      if (val[e] != 0ull && bin_of(val[e]) < d0) val[e] = 0ull;  // not selected
+    look_up();
     const uint32_t c0 = hist0[d0];
     const uint32_t want1 = (uint32_t)k - above0;  // how many of bin d0 are selected
     if (c0 <= (uint32_t)kSmall) {
@@ -447,81 +452,59 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
     }
     __syncthreads();
     take_entries((uint32_t)k);
+    look_up();
     __syncthreads();
-    clear_map();
     cut = 1ull;
     thr_next = key_to_float(bin_next << kBinShift);  // lower edge of that 12-bit bin
   }
-  // ---- 3. the selection in output order, and the slots that hold it ------------------------------------
-  uint32_t nsel = 0;
+  // ---- 3. places in the outputs: one prefix count over (selected, missing) ---------------------------
+  uint32_t nsel = 0, nmiss = 0;
 #pragma unroll
   for (int e = 0; e < kMaxE; ++e) {
     if (val[e] < cut) val[e] = 0ull;
+    if (slot[e] >= C) slot[e] = -1;  // corrupt map entry: treat as absent
     nsel += val[e] != 0ull ? 1u : 0u;
+    nmiss += val[e] != 0ull && slot[e] < 0 ? 1u : 0u;
   }
-  uint32_t tot_sel;
-  uint32_t j = scan1(nsel, scan_area(3), &tot_sel);
+  uint32_t j, mrank, tot_sel, tot_miss;
+  scan2(nsel, nmiss, scan_area(3), &j, &mrank, &tot_sel, &tot_miss);
+  const int nm = (int)tot_miss;
 #pragma unroll
   for (int e = 0; e < kMaxE; ++e) {
     if ((uint32_t)e >= E) break;  // uniform
     if (val[e] == 0ull || j >= (uint32_t)k) continue;  // (exactly k positions are selected)
     const int p = position_of(val[e]);
     sel_o[j] = p;
-    slot_o[j] = -1;
-    atomicOr(&map_bits[p >> 6], 1ull << (p & 63));
-    atomicMin(&map_first[p >> 6], j);
+    if (slot[e] >= 0) {
+      slot_o[j] = slot[e];
+    } else {
+      slot_o[j] = -1 - (int32_t)mrank;
+      mt_s[mrank] = p;
+      mj_s[mrank] = (int32_t)j;
+      ++mrank;
+    }
     ++j;
   }
   lds_barrier();
-#pragma unroll
-  for (int u = 0; u < SPT; ++u) {
-    const int sl = u * kT + t;
-    const int p = to_r[u];
-    if (u >= spt || sl >= C || p < 0 || p >= n) continue;
-    const unsigned long long bits = map_bits[p >> 6];
-    if (((bits >> (p & 63)) & 1ull) == 0ull) continue;
-    const uint32_t jj = map_first[p >> 6] + (uint32_t)__popcll(bits & ((1ull << (p & 63)) - 1ull));
-    slot_o[jj] = sl;
-    lu[sl] = step;
-    lu_s[sl] = step;  // used in this step: never a victim
-  }
-  lds_barrier();
-  // the outputs, coalesced; entry jj = t + 1024 i, what is missing counted in output order
+  // the outputs, coalesced
   int32_t* __restrict__ out = a.sel_idx + (size_t)bh * k;
   int32_t* __restrict__ ss = a.sel_slot + (size_t)bh * k;
   uint8_t* __restrict__ ht = a.hit + (size_t)bh * k;
   int32_t* __restrict__ mt = a.miss_tok + (size_t)bh * k;
   int32_t* __restrict__ ms = a.miss_slot + (size_t)bh * k;
-  constexpr int kOut = kPackedMaxK / kT;
-  int32_t sl_o[kOut];
-  uint32_t mine[2] = {0u, 0u};  // missing of the thread's entries, 16 bits for each i
-#pragma unroll
-  for (int i = 0; i < kOut; ++i) {
-    const int jj = t + i * kT;
-    sl_o[i] = jj < k ? slot_o[jj] : 0;
-    if (sl_o[i] < 0) mine[i >> 1] += 1u << (16 * (i & 1));
-  }
-  uint32_t ex[2], tot[2];
-  scan2(mine[0], mine[1], scan_area(0), &ex[0], &ex[1], &tot[0], &tot[1]);
-  uint32_t before = 0;  // missing entries of smaller i
-#pragma unroll
-  for (int i = 0; i < kOut; ++i) {
-    const int jj = t + i * kT;
-    const uint32_t mrank = before + ((ex[i >> 1] >> (16 * (i & 1))) & 0xffffu);
-    before += (tot[i >> 1] >> (16 * (i & 1))) & 0xffffu;
-    if (jj >= k) continue;
+  for (int jj = t; jj < k; jj += kT) {
     const int p = sel_o[jj];
+    const int32_t sl = slot_o[jj];
     out[jj] = p;
-    ht[jj] = sl_o[i] >= 0 ? 1 : 0;
-    if (sl_o[i] >= 0) {
-      ss[jj] = sl_o[i];
+    ht[jj] = sl >= 0 ? 1 : 0;
+    if (sl >= 0) {
+      ss[jj] = sl;
+      lu[sl] = step;
+      lu_s[sl] = step;  // used in this step: never a victim
     } else {
-      mt[mrank] = p;
-      mt_s[mrank] = p;
-      mj_s[mrank] = jj;
+      mt[-1 - sl] = p;
     }
   }
-  const int nm = (int)before;
   if (wv == kWaves - 1) {
     // |q_hat|: the next step multiplies by its own
     float q2 = lane < r ? qh[lane] * qh[lane] : 0.0f;
@@ -534,6 +517,8 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
       a.sel_thr[bh] = (nrm > 0.0f && isfinite(v)) ? v : __uint_as_float(0x7fc00000u);
     }
   }
+
+  lds_barrier();
 
   // ---- 4. victims ------------------------------------------------------------------------------------
   if (nm > 0) {

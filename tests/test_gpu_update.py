@@ -318,6 +318,73 @@ def run_alg2_growing(cfg, n_new, mode, lam1=1.0, lam2=1.0):
     return new_selected, new_fetched
 
 
+@pytest.mark.parametrize("mode", ["direct", "staged", "group"])
+@pytest.mark.parametrize("w", [0, 8])
+def test_context_cut_back_and_continued(w, mode):
+    """Positions 500 .. 599 have been cached when the context goes back to 500 tokens and other ones are
+    appended: slot_of says that those are not in the cache while token_of still names the removed ones.
+    With a slot for every position nothing is evicted, so that only slot_of tells the new rows from the
+    old."""
+    from oracle import lrqk_oracle as orc
+    from gpu_harness import compare_resolution, lite_ring
+    l0, l1 = 500, 600
+    cfg = upd_cfg(B=1, Hq=4, Hkv=2, l=l1, r=16, k=64, w=w, C=1024, n_heavy=4)
+    data = make_layer(cfg)
+    data.A_K[:, :, l0:l1 - w] *= 4.0                      # wanted before the cut
+    shape = L.Shape.make(B=1, Hq=4, Hkv=2, l=l1, r=16, k=64, w=w, C_slots=1024, scale=cfg.scale,
+                         kv_dtype=L.LRQK_KV_BF16, l_cap=l1)
+    lb = L.LayerBuffers(shape, data.A_K, data.K, data.V)
+    plan, sb = L.Plan(shape), StepBuffers(cfg)
+    fmode = dict(direct=L.LRQK_FETCH_DIRECT, staged=L.LRQK_FETCH_STAGED, group=L.LRQK_FETCH_GROUP)[mode]
+    A_np, K_np, V_np = (as_numpy(x).copy() for x in (data.A_K, data.K, data.V))
+    ost, ocK = orc.CacheState(1, 4, l1, 1024), np.zeros((1, 4, 1024, cfg.d), np.uint16)
+    ocV, out, qs = np.zeros_like(ocK), torch.empty((1, 4, cfg.d), device=DEV), QueryStream(data)
+
+    def step_and_compare(l, step, q, q_hat):
+        L.lrqk_decode_step(plan, shape.with_l(l), step, lb.struct, q_hat.to(DEV), q.to(DEV), out, fmode,
+                           sb.debug())
+        got = sb.to_np()
+        ref = orc.decode_step(*(np.ascontiguousarray(x) for x in (A_np[:, :, :l], as_numpy(q_hat),
+                                                                   as_numpy(q), K_np[:, :, :l],
+                                                                   V_np[:, :, :l])),
+                              ost, ocK, ocV, step, cfg.k, w, cfg.scale)
+        assert np.array_equal(got["sel_idx"], ref["sel_idx"]), f"l={l}: selection"
+        compare_resolution(got, ref, f"l={l}")
+        for name in ("slot_of", "token_of", "last_used"):
+            have = getattr(lb, name).cpu().numpy()
+            assert np.array_equal(have[..., :l] if name == "slot_of" else have, getattr(ost, name)), name
+        assert np.array_equal(as_numpy(lb.cacheK), ocK) and np.array_equal(as_numpy(lb.cacheV), ocV)
+        assert np.abs(out.cpu().numpy() - ref["out"]).max() <= 2e-3, f"l={l}: attention"
+        return ref
+
+    for step in range(3):
+        q, q_hat = qs.next()
+        step_and_compare(l1, step, q, q_hat)
+    cached = ost.slot_of[:, :, l0:] >= 0
+    ost.slot_of = np.ascontiguousarray(ost.slot_of[:, :, :l0])
+    if w:
+        lb.liteK.copy_(lite_ring(data.K, l0, w))
+        lb.liteV.copy_(lite_ring(data.V, l0, w))
+    gen, fetched_again = torch.Generator().manual_seed(5), 0
+    for i in range(30):
+        l = l0 + i
+        # a new token that the heads of its group want once it is out of the window
+        q, q_hat = qs.next()
+        k_hat = 6.0 * torch.nn.functional.normalize(q_hat, dim=-1).reshape(1, 2, 2, 16).sum(2)
+        k_new, v_new = (torch.randn(1, 2, cfg.d, generator=gen).bfloat16() for _ in range(2))
+        L.lrqk_append_token(shape.with_l(l), lb.struct, k_hat.to(DEV), k_new.to(DEV), v_new.to(DEV))
+        upd.append_token(A_np, K_np, V_np, l, k_hat.numpy(), as_numpy(k_new), as_numpy(v_new))
+        grow(ost)
+        ref = step_and_compare(l + 1, 3 + i, q, q_hat)
+        for h in range(4):
+            again = ref["miss_tok"][0, h, :ref["n_miss"][0, h]]
+            fetched_again += int(cached[0, h, again[again >= l0] - l0].sum())
+    say(f"context cut back, w={w} {mode}: {int(cached.sum())} cached rows cut off, "
+        f"{fetched_again} new ones fetched in their place")
+    assert fetched_again > 10
+    plan.close()
+
+
 @pytest.mark.parametrize("r", [8, 32, 64])
 @pytest.mark.parametrize("G,Hkv", [(8, 1), (1, 3), (5, 1)])
 def test_update_group_sizes_at_the_smallest_and_largest_rank(r, G, Hkv):
