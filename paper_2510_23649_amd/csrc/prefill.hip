@@ -16,7 +16,7 @@
 //
 // (With a pass over Q and K in every update, X^T Y and X^T X from the fp32 matrix cores and the
 // solves in fp32, the whole took 2.35 ms at 32 + 8 heads, l = 131072, r = 32, bf16, two rounds;
-// now 0.93 ms.)
+// now 0.94 ms.)
 //
 // Precision.  The long products run on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16) with
 // every fp32 operand split into three bf16 terms, x = x0 + x1 + x2, 8 bits of significand each, and
@@ -1166,9 +1166,11 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_apply_kernel(
 
 // ------------------------------------------------------------------------------------------
 // Chunks of rows per head: the fewest workgroup rounds (one workgroup per CU) times the passes
-// of a workgroup, a partial costing its workgroup about as much as four passes, and as traffic, written
-// and read, a 64th of one (6 chunks instead of 19 at 32 + 8 heads, l = 131072, r = 32: 1006 -> 995 us for the
-// whole call).  At most kPfSlots partials unless there are more heads than that.
+// of a workgroup, a partial costing about as much as four passes.  At most kPfSlots partials
+// unless there are more heads than that.  (Fewer and longer chunks would save the partials' traffic, 938 ->
+// 922 us for the whole call with 6 chunks instead of 19 at 32 + 8 heads, l = 131072, r = 32; but S and H are
+// in fp32 over a chunk and in fp64 only beyond it, and three times as many fp32 additions in a row
+// round three times as far off: test_prefill_long_sums, 6.3e-7 instead of 2.0e-7.)
 constexpr int kPfSlots = 1024;
 int reduce_chunks(int heads, int l, int rows) {
   const int tiles = ceil_div(l, rows);
@@ -1177,7 +1179,7 @@ int reduce_chunks(int heads, int l, int rows) {
   long best_cost = 0;
   for (int n = 1; n <= most; ++n) {
     const int per = ceil_div(tiles, n);
-    const long cost = 64 * (long)ceil_div(heads * ceil_div(tiles, per), 256) * (per + 4) + heads * n;
+    const long cost = (long)ceil_div(heads * ceil_div(tiles, per), 256) * (per + 4);
     if (n == 1 || cost < best_cost) {
       best = n;
       best_cost = cost;

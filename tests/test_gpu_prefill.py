@@ -342,6 +342,35 @@ def test_prefill_strong_directions(kind, size, l, r, dtype, A_Q, A_K, B_Q, B_K):
         assert got[n] <= 1.5 * fp32_sums[n], n
 
 
+def test_prefill_long_sums():
+    """Sums S and H of many rows at the head count of the longest chunks (32 + 8 heads, l = 131072: 6912
+    rows).  Of every 256 rows, which make one addition to a running sum, the first eight of A0 are a
+    multiple of the identity and the others zero: all addends are equal, and the additions round in
+    the same direction while the sum stays in one binade, which is how far apart long fp32 sums can drift.
+    B = H^-1 S is Y / A0 of those rows and shows the sums themselves.  27 additions, each off by
+    half of 2^-24 at most of a sum that has half its final size on average: 27 * 2^-26 = 4e-7 in the worst
+    column; over all columns 2.0e-7 (numpy's float32 and the kernel alike; 6.3e-7 with 85 additions, in
+    chunks of 21888 rows)."""
+    Hq, Hkv, l, r = 32, 8, 131072, 8
+    gen = torch.Generator().manual_seed(6)
+    rows = (1.0 + torch.rand(r, 128, generator=gen)).bfloat16()
+    a = 1.0 + torch.rand(r, generator=gen)
+    Y = rows.to(DEV).repeat(l // r, 1)
+    A0 = torch.nn.functional.pad(torch.diag(a), (0, 0, 0, 256 - r)).to(DEV).repeat(l // 256, 1)
+    Q, K, A_Q, A_K = (x.expand(1, H, *x.shape).contiguous() for x, H in
+                      ((Y, Hq), (Y, Hkv), (A0, Hq), (A0, Hkv)))
+    B_Q, B_K = (torch.empty((1, H, r, 128), device=DEV) for H in (Hq, Hkv))
+    shp = L.Shape.make(B=1, Hq=Hq, Hkv=Hkv, l=l, r=r, k=16, w=0, C_slots=16)
+    L.lrqk_prefill_factorize(shp, Q, K, A_Q, A_K, B_Q, B_K, 1.0, 1.0, 1,
+                             workspace(L.lrqk_workspace_bytes(shp, L.LRQK_WS_PREFILL)))
+    torch.cuda.synchronize()
+    want = rows.double() / a.double()[:, None]
+    for name, B in (("B_Q", B_Q), ("B_K", B_K)):
+        far = float((B[0].cpu().double() - want).norm(dim=(1, 2)).max() / want.norm())
+        say(f"prefill, long sums: {name} {far:.1e}")
+        assert far <= 27 * 2.0 ** -26, name
+
+
 def test_prefill_rejects_bad_arguments():
     t = torch.zeros(1 << 16, device=DEV)
     shp = L.Shape.make(B=1, Hq=2, Hkv=1, l=512, r=12, k=16, w=0, C_slots=16)
