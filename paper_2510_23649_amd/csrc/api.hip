@@ -638,13 +638,14 @@ int lrqk_decode_step(lrqk_plan* plan, const lrqk_shape* shape, int32_t step,
   if (mode == LRQK_FETCH_DIRECT) {
     // fetch and attention in one kernel: a row that missed is read from the pinned host store,
     // used, and written into its slot, while the other rows stream from HBM
+    const bool by_die = attend_by_die(s, g.nsplit);
     prof_arm(plan, LRQK_SLOT_ATTEND, 1);
     LRQK_HIP(launch_attend_partial(s, kAttendAllFetch, q, L->cacheK, L->cacheV, sel_slot, hit,
                                    nullptr, nullptr, L->liteK, L->liteV, plan->partials, g.nsplit,
                                    g.rows_per_block, parts_per_head, 0, st, L->K_host, L->V_host,
-                                   sel_idx));
+                                   sel_idx, by_die));
     prof_arm(plan, LRQK_SLOT_COMBINE, 1);
-    LRQK_HIP(launch_attend_combine(s, plan->partials, parts_per_head, g.nsplit, out, st));
+    LRQK_HIP(launch_attend_combine(s, plan->partials, parts_per_head, g.nsplit, out, st, by_die));
     prof_step_done(plan);
     if (total_miss_out) *total_miss_out = -1;
     return LRQK_OK;

@@ -34,11 +34,10 @@ __device__ __forceinline__ void place(int i, int units, int parts, int& unit, in
 }
 // The same with the KV heads of B sequences as units and `blocks` workgroups for each of their query
 // heads: query head bh, block.
-__device__ __forceinline__ void place_head(int i, int B, int Hq, int Hkv, int blocks, int& bh, int& block,
-                                           bool by_die = true) {
+__device__ __forceinline__ void place_head(int i, int B, int Hq, int Hkv, int blocks, int& bh, int& block) {
   const int G = Hq / Hkv;
   int bkv, part;
-  place(i, B * Hkv, G * blocks, bkv, part, by_die);
+  place(i, B * Hkv, G * blocks, bkv, part);
   const int g = blocks == 1 ? part : part / blocks;
   block = part - g * blocks;
   bh = bkv * G + g;  // ((b Hkv + kvh) G + g = b Hq + kvh G + g)

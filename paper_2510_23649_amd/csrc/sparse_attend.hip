@@ -136,7 +136,7 @@ struct AttendArgs {
   float* partials;
   int B, Hq, Hkv, C, k, w, rows_per_block, parts_per_head, part_offset;
   int blocks;  // workgroups per head
-  bool by_die;
+  bool by_die; // one-dimensional grid, dealt out by place_head; otherwise (blocks, heads)
   float scale;
 };
 
@@ -300,8 +300,8 @@ __device__ __forceinline__ void attend_partial_body(const AttendArgs& a, int bx,
 
 template <bool BF16, int MODE>
 __global__ __launch_bounds__(kAttThreads) void attend_partial_kernel(const AttendArgs a) {
-  int bh, block;
-  dev::place_head(blockIdx.x, a.B, a.Hq, a.Hkv, a.blocks, bh, block, a.by_die);
+  int bh = blockIdx.y, block = blockIdx.x;
+  if (a.by_die) dev::place_head(blockIdx.x, a.B, a.Hq, a.Hkv, a.blocks, bh, block);
   attend_partial_body<BF16, MODE>(a, block, bh);
 }
 
@@ -320,7 +320,6 @@ struct GroupFetchArgs {
   const int32_t* n_miss;
   int32_t* link_rows;   // [B,Hkv] rows read from the host store, or null (not counted)
   int Hq, Hkv, C, k;
-  int blocks;           // workgroups per head
 };
 template <bool BF16>
 __device__ __forceinline__ void group_fetch_body(const GroupFetchArgs& a, int fx, int nfx, int bh) {
@@ -382,8 +381,7 @@ __device__ __forceinline__ void group_fetch_body(const GroupFetchArgs& a, int fx
 
 template <bool BF16>
 __global__ __launch_bounds__(kAttThreads) void group_fetch_kernel(const GroupFetchArgs a) {
-  const int bh = blockIdx.x / a.blocks, block = blockIdx.x - bh * a.blocks;
-  group_fetch_body<BF16>(a, block, a.blocks, bh);
+  group_fetch_body<BF16>(a, blockIdx.x, gridDim.x, blockIdx.y);
 }
 
 // The attention over the rows that hit and the lite rows (blocks [0, n_attend) of a head) and
@@ -392,12 +390,10 @@ __global__ __launch_bounds__(kAttThreads) void group_fetch_kernel(const GroupFet
 template <bool BF16>
 __global__ __launch_bounds__(kAttThreads) void attend_hits_group_fetch_kernel(
     const AttendArgs a, const GroupFetchArgs f) {
-  const int per_head = a.blocks + f.blocks;
-  const int bh = blockIdx.x / per_head, block = blockIdx.x - bh * per_head;
-  if (block < a.blocks)
-    attend_partial_body<BF16, kAttendHitsAndLite>(a, block, bh);
+  if ((int)blockIdx.x < a.blocks)
+    attend_partial_body<BF16, kAttendHitsAndLite>(a, blockIdx.x, blockIdx.y);
   else
-    group_fetch_body<BF16>(f, block - a.blocks, f.blocks, bh);
+    group_fetch_body<BF16>(f, blockIdx.x - a.blocks, gridDim.x - a.blocks, blockIdx.y);
 }
 
 constexpr int kCombThreads = 512;
@@ -413,8 +409,8 @@ __global__ __launch_bounds__(kCombThreads) void attend_combine_kernel(
   __shared__ float red[kCombThreads / 64];
   __shared__ float accs[kCombThreads / kD][kD];
   __shared__ float sh_M, sh_S;
-  int bh, block;
-  dev::place_head(blockIdx.x, B, Hq, Hkv, 1, bh, block, by_die);
+  int bh = blockIdx.x, block;
+  if (by_die) dev::place_head(blockIdx.x, B, Hq, Hkv, 1, bh, block);
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const float* __restrict__ P = partials + (size_t)bh * parts_per_head * kPartialStride;
   // block max of the part maxima
@@ -483,12 +479,14 @@ size_t attend_ws_bytes(int BHq, int k, int w, int phases) {
   return round_up((size_t)BHq * parts * kPartialStride * sizeof(float), 256);
 }
 
-// The workgroups of a head on the die of the selection and of the merge, where they are few: a step at
-// 4K context (9 for each of 32 heads) 24.1 -> 23.5 us, two layers at 32K (34) 118.2 -> 117.6; with more
-// of them (66 at 128K) the reads over the host link no longer start everywhere at once: 234.4 -> 235.6.
-static bool attend_by_die(const lrqk_shape& s, int parts_per_head) {
-  return s.B * s.Hq * parts_per_head <= 1536;
-}
+// The workgroups of a head on the die of its selection and of its merge, where they are few: a step with
+// direct fetch at 32 + 8 heads with 9 workgroups a head (4K context) 21.9 -> 21.1 us, with 17 (8K) 37.4 -> 36.3,
+// with 26 (16K) 47.3 -> 45.8, two layers with 34 (32K) 116.5 -> 115.2.  Beyond it nothing: two layers with 66
+// (128K) 233.3 -> 233.0, one of 224 heads 306.3 -> 306.2 (there the link and A_K set the time).  The
+// stand-alone attention, whose rows another launch has fetched, gains nothing either (the chain of calls at
+// 50K 87.2, 87.4 us, at 20K, 16 + 2 heads, 51.3, 51.8).  Where heads are not placed the grid is (workgroups,
+// heads), without the divisions that take a one-dimensional one apart.
+bool attend_by_die(const lrqk_shape& s, int nblocks) { return s.B * s.Hq * nblocks <= 1536; }
 
 static AttendArgs make_attend_args(const lrqk_shape& s, const float* q,
                                    const void* cacheK, const void* cacheV,
@@ -496,8 +494,8 @@ static AttendArgs make_attend_args(const lrqk_shape& s, const float* q,
                                    const int32_t* miss_slot, const int32_t* n_miss,
                                    const void* liteK, const void* liteV, float* partials,
                                    int nblocks, int rows_per_block, int parts_per_head,
-                                   int part_offset, const void* K_host, const void* V_host,
-                                   const int32_t* sel_idx) {
+                                   int part_offset, bool by_die, const void* K_host,
+                                   const void* V_host, const int32_t* sel_idx) {
   AttendArgs a;
   a.fs = FetchSrc{static_cast<const char*>(K_host), static_cast<const char*>(V_host), sel_idx,
                   s.l, row_cap(s)};
@@ -521,7 +519,7 @@ static AttendArgs make_attend_args(const lrqk_shape& s, const float* q,
   a.parts_per_head = parts_per_head;
   a.part_offset = part_offset;
   a.blocks = nblocks;
-  a.by_die = attend_by_die(s, parts_per_head);
+  a.by_die = by_die;
   a.scale = s.scale;
   return a;
 }
@@ -546,7 +544,6 @@ static GroupFetchArgs make_group_fetch_args(const lrqk_shape& s, const void* K_h
   f.Hkv = s.Hkv;
   f.C = s.C;
   f.k = s.k;
-  f.blocks = group_fetch_blocks(s);
   return f;
 }
 
@@ -556,14 +553,14 @@ hipError_t launch_attend_partial(const lrqk_shape& s, int mode, const float* q, 
                                  const void* liteK, const void* liteV, float* partials,
                                  int nblocks, int rows_per_block, int parts_per_head,
                                  int part_offset, hipStream_t st, const void* K_host,
-                                 const void* V_host, const int32_t* sel_idx) {
+                                 const void* V_host, const int32_t* sel_idx, bool by_die) {
   if (nblocks <= 0) return hipSuccess;
   if (mode == kAttendAllFetch && (!K_host || !V_host || !sel_idx || !hit))
     return hipErrorInvalidValue;
   const AttendArgs a = make_attend_args(s, q, cacheK, cacheV, sel_slot, hit, miss_slot,
                                         n_miss, liteK, liteV, partials, nblocks, rows_per_block,
-                                        parts_per_head, part_offset, K_host, V_host, sel_idx);
-  const dim3 grid(nblocks * s.B * s.Hq);
+                                        parts_per_head, part_offset, by_die, K_host, V_host, sel_idx);
+  const dim3 grid = by_die ? dim3(nblocks * s.B * s.Hq) : dim3(nblocks, s.B * s.Hq);
   auto run = [&](auto m) {
     constexpr int MODE = decltype(m)::value;
     if (s.kv_dtype == LRQK_KV_BF16)
@@ -587,7 +584,7 @@ hipError_t launch_group_fetch(const lrqk_shape& s, const void* K_host, const voi
                               int32_t* link_rows, hipStream_t st) {
   const GroupFetchArgs f = make_group_fetch_args(s, K_host, V_host, miss_tok, miss_slot, n_miss,
                                                  cacheK, cacheV, link_rows);
-  const dim3 grid(f.blocks * s.B * s.Hq);
+  const dim3 grid(group_fetch_blocks(s), s.B * s.Hq);
   if (s.kv_dtype == LRQK_KV_BF16)
     LRQK_LAUNCH((group_fetch_kernel<true>), grid, dim3(kAttThreads), 0, st, f);
   else
@@ -606,10 +603,11 @@ hipError_t launch_attend_hits_group_fetch(const lrqk_shape& s, const float* q, v
                                           hipStream_t st) {
   const AttendArgs a = make_attend_args(s, q, cacheK, cacheV, sel_slot, hit,
                                         nullptr, nullptr, liteK, liteV, partials, nblocks,
-                                        rows_per_block, parts_per_head, 0, nullptr, nullptr, nullptr);
+                                        rows_per_block, parts_per_head, 0, false, nullptr, nullptr,
+                                        nullptr);
   const GroupFetchArgs f = make_group_fetch_args(s, K_host, V_host, miss_tok, miss_slot, n_miss,
                                                  cacheK, cacheV, link_rows);
-  const dim3 grid((nblocks + f.blocks) * s.B * s.Hq);
+  const dim3 grid(nblocks + group_fetch_blocks(s), s.B * s.Hq);
   if (s.kv_dtype == LRQK_KV_BF16)
     LRQK_LAUNCH((attend_hits_group_fetch_kernel<true>), grid, dim3(kAttThreads), 0, st, a, f);
   else
@@ -618,11 +616,11 @@ hipError_t launch_attend_hits_group_fetch(const lrqk_shape& s, const float* q, v
 }
 
 hipError_t launch_attend_combine(const lrqk_shape& s, const float* partials, int parts_per_head,
-                                 int nparts, float* out, hipStream_t st) {
+                                 int nparts, float* out, hipStream_t st, bool by_die) {
   if (nparts > kCombMaxParts) return hipErrorInvalidValue;
   LRQK_LAUNCH(attend_combine_kernel, dim3(s.B * s.Hq), dim3(kCombThreads), 0, st,
                      partials, parts_per_head, nparts, out, s.B, s.Hq, s.Hkv,
-                     attend_by_die(s, parts_per_head));
+                     by_die);
   return hipGetLastError();
 }
 
