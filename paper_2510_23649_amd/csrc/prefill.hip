@@ -771,6 +771,11 @@ struct PfPart {
       : row(part % RS), addend(part / RS), col(addend * WC + w % WC), ks(w / WC) {}
 };
 
+// Whether these operands (32 doubles a lane in the unshared form) are read after the solve before them
+// instead of under it: at r = 64 the solve's tiles leave no registers for them, 88 and 14 of which went to
+// memory (8 x (28 + 4) heads, the whole call at l = 2048: 397 -> 395 us, at l = 500: 302.6 -> 299.7).
+template <int R, bool SHARED>
+constexpr bool kGramLate = R > 32 && !SHARED;
 // This wavefront's operands of X G, G [d][d] in memory.
 template <class Q>
 __device__ __forceinline__ void load_gram(double (&g)[Q::kSteps], const double* __restrict__ G,
@@ -986,12 +991,14 @@ __global__ __launch_bounds__(kAlgThreads) void prefill_round_k_kernel(const PfSt
     }
   }
   pad_tiles<R>(d, w, lane);
-  load_gram(gram, a.G + (a.BHq + own) * kD * kD, share, lane);
+  const double* const Gm = a.G + (a.BHq + own) * kD * kD;
+  if (!kGramLate<R, SHARED>) load_gram(gram, Gm, share, lane);
   lds_barrier();
   add_rhs<R>(d, X, a.lam_pK, w, lane);
   add_gram<R>(d, X, Ys, a.lam_pK, w, lane);
   lds_barrier();  // X has been read
   solve_tiles<R>(d, Ys, w, lane);
+  if (kGramLate<R, SHARED>) load_gram(gram, Gm, share, lane);
   store_solution<R>(d, w, lane, [&](int i, int j, double x) { X[i * kLdx + j] = x; });
   lds_barrier();
   if (a.last && part == 0) pack_operand<R>(X, a.M + (a.BHq + own) * PfShape<R>::mpack_units, t);
@@ -1022,12 +1029,14 @@ __global__ __launch_bounds__(kAlgThreads) void prefill_round_q_kernel(const PfSt
   if (16 * Z::RT > R)
     for (int e = t; e < (16 * Z::RT - R) * kLdx; e += kAlgThreads) X[R * kLdx + e] = 0.0;
   double gram[Part::kSteps];
-  if (!a.last) load_gram(gram, a.G + (size_t)bh * kD * kD, share, lane);
+  const double* const Gm = a.G + (size_t)bh * kD * kD;
+  if (!kGramLate<R, SHARED> && !a.last) load_gram(gram, Gm, share, lane);
   lds_barrier();
   add_rhs<R>(d, X, a.lam_pQ, w, lane);
   add_gram<R>(d, X, Ys, a.lam_pQ, w, lane);
   lds_barrier();  // X has been read
   solve_tiles<R>(d, Ys, w, lane);
+  if (kGramLate<R, SHARED> && !a.last) load_gram(gram, Gm, share, lane);
   store_solution<R>(d, w, lane, [&](int i, int j, double x) { X[i * kLdx + j] = x; });
   lds_barrier();
   if (a.last)
