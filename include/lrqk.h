@@ -311,8 +311,9 @@ typedef struct lrqk_step_debug {
  * the way.
  * Selection (shapes the filtered proxy-score pass supports): the pass over A_K keeps only the
  * positions whose score reaches a per-head candidate threshold, and the selection is made
- * exactly among those; a head whose candidates turn out unusable (fewer than k) is redone
- * exactly from all its scores, so the threshold affects speed, never the result.  The
+ * exactly among those; a head whose candidates turn out unusable (fewer than k, or so many that
+ * more than half of its positions, or more than 8192 equal scores, would have to be gone through)
+ * is redone exactly from all its scores, so the threshold affects speed, never the result.  The
  * threshold is estimated from a sample of this step's scores (two small launches) when
  * layer->sel_thr is NULL or `mode` carries LRQK_SELECT_FRESH; otherwise it is
  * layer->sel_thr[b,h] * |q_hat[b,h]|, the value the previous step's selection left there (the

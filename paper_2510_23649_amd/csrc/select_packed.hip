@@ -26,10 +26,10 @@
 //     back and goes on leaves slots whose token_of names a removed token; tests:
 //     test_context_cut_back_and_continued).  It is looked up for the entries from the bin of the cut on,
 //     while the cut is found: k cache lines, 4 cycles each at the least.  Looked up before the histogram,
-//     for all 1.5 k entries, or after the cut: a step at 4K context 20.7 instead of 21.0 us, two layers at
-//     128K 235.2 instead of 234.7.  (Every cache slot looking its token_of up in a map of the selection needs
-//     no such loads, 21.5 and 231.3 us, but answers from the wrong array.)  One prefix count over (selected,
-//     missing) gives every entry its place in the outputs;
+//     for all 1.5 k entries, a step at 4K context takes 0.25 us less and two layers at 128K 0.5 us more.
+//     (Every cache slot looking its token_of up in a map of the selection needs no such loads, 0.5 us more
+//     at 4K, 3.4 us less at 128K, but answers from the wrong array.)  One prefix count over (selected, missing)
+//     gives every entry its place in the outputs;
 //   * the same histogram yields the key at rank 1.5 k, which (divided by |q_hat|) is handed
 //     to the next step of the layer as its candidate threshold, so that steps after the
 //     first need no threshold estimate of their own.
@@ -37,8 +37,17 @@
 // the last store: every phase then had 8 to 16 predicated steps of which most lanes skipped most.  A whole
 // step at 4K context, where one wavefront owned all the groups: 23.9 -> 21.0 us.)
 // Cycles at 2.3 GHz, one head at 32K: first loads 6200, list 3000, histogram 2000, scan 1900, victims 6500.
-// A head whose candidates are unusable (fewer than k, or more than the list holds) recomputes all its scores into the workspace and selects exactly from them
-// (exact_select_from_scores): slower, same result.
+// More candidates than the list holds (8192; a threshold carried into a step whose scores it is far too
+// low for): a histogram of all of them gives a higher threshold, about that of the 1.5 k largest, and the
+// list takes those.  A head with fewer than k candidates, with scores to be
+// computed again for more than half of its positions, or with more equal scores than the list holds,
+// computes all its scores into the workspace and selects exactly from them (exact_select_from_scores):
+// slower, same result.  A whole step at 32 + 8 heads with 4, 6, 12 times k candidates, in us, in
+// brackets with all scores computed: 32K, k = 1024: 36, 47, 70 (224); 128K, k = 2048: 65, 73, 147 (743); 34
+// and 57 with the usual 1.5.  (With 8 a group in registers and 2048 more in LDS it was 40, 254, 255
+// and 62, 69, 821.)
+// What is rare is out of the way of the instructions (__builtin_expect): a step at 4K 21.2 -> 20.9 us, two
+// layers at 128K 233.3 -> 231.4.
 //
 // Resolution (Sec. 4.1; least recently selected victims in (last_used, slot) order): a
 // histogram of the ages of the slots not used in this step is scanned from the oldest; the
@@ -71,7 +80,6 @@ __host__ __device__ inline size_t up256(size_t x) { return (x + 255) / 256 * 256
 //   order, its positions and slots [k] each, and after them the all-slots sort of the rare resolution cases.
 struct PackedArena {
   size_t st_b, k_b, fixed, total;
-  int list_cap;
 };
 __host__ __device__ inline PackedArena packed_arena(int k, int n, int C) {
   PackedArena a;
@@ -84,10 +92,8 @@ __host__ __device__ inline PackedArena packed_arena(int k, int n, int C) {
   const size_t sort_b = (size_t)Cpad * 8;
   const size_t out = 3 * a.k_b + (2 * a.k_b > sort_b ? 2 * a.k_b : sort_b);
   size_t z = out > exact ? out : exact;
-  // room for twice the candidates that the threshold aims at, more where it costs nothing
-  const size_t want = up256((size_t)(3 * k < kListCap ? 3 * k : kListCap) * 8);
-  if (z < want && a.fixed + want <= kPackedLdsLimit) z = want;
-  a.list_cap = (int)(z / 8) < kListCap ? (int)(z / 8) : kListCap;
+  // (one workgroup is on a compute unit in any case, for its registers: the list has its full size)
+  if (z < (size_t)kListCap * 8) z = (size_t)kListCap * 8;
   a.total = a.fixed + z;
   return a;
 }
@@ -210,7 +216,7 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
     lu_r[u] = lu[sl];
     to_r[u] = to[sl];
   }
-  const uint32_t thr_key = a.thr_used[bh];
+  uint32_t thr_key = a.thr_used[bh];
   const float q_r = a.q_hat[(size_t)bh * r + min(t, r - 1)];  // to LDS (r <= 128)
 #pragma unroll
   for (int g = 0; g < GPT; ++g)
@@ -234,8 +240,10 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
   for (int g = 0; g < GPT; ++g) own += (uint32_t)__popcll(mask[g]);
   uint32_t m;
   uint32_t at = scan1(own, scan_area(0), &m);
-  const bool listed = m >= (uint32_t)k && m <= (uint32_t)az.list_cap;  // uniform
-  if (listed) {
+  float* const sw = a.scores_w + (size_t)bh * l;
+  constexpr uint32_t cap = kListCap;
+  bool listed = m >= (uint32_t)k && m <= cap;  // uniform
+  if (__builtin_expect(listed, 1)) {
 #pragma unroll
     for (int g = 0; g < GPT; ++g) {
       unsigned long long mb = mask[g];
@@ -256,6 +264,91 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
         }
       }
     }
+  } else if (__builtin_expect(m > cap, 0)) {
+    // more than the list holds: those from a higher threshold on
+    if (t < r) qh[t] = q_r;
+    uint32_t beyond = 0, all_beyond;  // candidates without a packed score
+#pragma unroll
+    for (int g = 0; g < GPT; ++g) beyond += (uint32_t)max((int)__popcll(mask[g]) - CPG, 0);
+    const uint32_t ofs = scan1(beyond, scan_area(1), &all_beyond);
+    if (2u * all_beyond <= (uint32_t)n) {  // (with more, to compute every score is no dearer)
+      // the scores that are missing, into the workspace: listed and dealt out over all threads
+      uint32_t* const todo = reinterpret_cast<uint32_t*>(Z);
+      for (uint32_t b0 = 0; b0 < all_beyond; b0 += 2u * cap) {
+        const uint32_t b1 = min(b0 + 2u * cap, all_beyond);
+        uint32_t i = ofs;
+#pragma unroll
+        for (int g = 0; g < GPT; ++g) {
+          unsigned long long mb = mask[g];
+#pragma unroll
+          for (int c = 0; c < CPG; ++c) mb &= mb - 1ull;
+          for (; mb; mb &= mb - 1ull, ++i)
+            if (i >= b0 && i < b1) todo[i - b0] = (uint32_t)((t * GPT + g) * 64 + __builtin_ctzll(mb));
+        }
+        __syncthreads();
+        for (uint32_t u = b0 + t; u < b1; u += kT)
+          sw[todo[u - b0]] = proxy_score_of_row(Arow, qh, r, (int)todo[u - b0]);
+        __threadfence_block();
+        __syncthreads();
+      }
+      // the thread's candidates in position order
+      auto for_own = [&](auto&& f) {
+#pragma unroll
+        for (int g = 0; g < GPT; ++g) {
+          unsigned long long mb = mask[g];
+          const int base = (t * GPT + g) * 64;
+#pragma unroll
+          for (int i = 0; i < CPG; ++i)
+            if (mb) {
+              const float4 q = sc[g][i / 4];
+              f(order_key(i % 4 == 0 ? q.x : i % 4 == 1 ? q.y : i % 4 == 2 ? q.z : q.w),
+                base + __builtin_ctzll(mb));
+              mb &= mb - 1ull;
+            }
+          for (; mb; mb &= mb - 1ull) {
+            const int p = base + __builtin_ctzll(mb);
+            f(order_key(sw[p]), p);
+          }
+        }
+      };
+      // The lower edge of the bin that holds rank 1.5 k: bins of 2^-7 of a binade above a positive
+      // threshold, otherwise (and if the top bin, which takes everything beyond, is reached) of all keys;
+      // inside a bin with too many entries once more.
+      uint32_t base = thr_key, want = (uint32_t)k + (uint32_t)(k >> 1), above = 0, width = 0;
+      int s = thr_key > 0x80800000u && thr_key < 0xff800000u ? 16 : 21;
+      for (int level = 0;; ++level) {
+        for_own([&](uint32_t kk, int) {
+          if (kk >= base && (width == 0u || kk - base < width))
+            atomicAdd(&hist0[min((kk - base) >> s, 2047u)], 1u);
+        });
+        lds_barrier();
+        find_two_from_top(hist0, want, want, scan_area(2 + (level & 1)), res);
+        const uint32_t d = res[0], ab = res[1], c = hist0[d];
+        lds_barrier();  // res and hist0 have been read
+        for (int i = t; i < 2048; i += kT) hist0[i] = 0u;
+        lds_barrier();
+        if (width == 0u && d == 2047u && s == 16) {
+          s = 21;
+          continue;
+        }
+        base += d << s;
+        above += ab;
+        if (above + c <= cap || s == 0) break;
+        want -= ab;
+        width = 1u << s;
+        s = s > 11 ? s - 11 : 0;
+      }
+      own = 0;
+      for_own([&](uint32_t kk, int) { own += kk >= base ? 1u : 0u; });
+      at = scan1(own, scan_area(0), &m);
+      listed = m <= cap;
+      if (listed) {
+        for_own([&](uint32_t kk, int p) {
+          if (kk >= base) list[at++] = value_of(kk, p);
+        });
+        thr_key = base;  // what the rest takes for the threshold
+      }
+    }
   }
   // q_hat and the cache state go to LDS beside it
   if (t < r) qh[t] = q_r;
@@ -266,7 +359,7 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
       to_s[u * kT + t] = to_r[u];
     }
   lds_barrier();
-  if (sh_again != 0u) {  // uniform
+  if (__builtin_expect(sh_again != 0u, 0)) {  // uniform
     for (uint32_t i = t; i < m; i += kT) {
       const uint64_t v = list[i];
       if ((uint32_t)(v >> 32) != 0u) continue;
@@ -307,7 +400,7 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
       for (int e = 4; e < kMaxE; ++e) load(e);
     }
   };
-  if (listed) {
+  if (__builtin_expect(listed, 1)) {
     take_entries(m);
     // ---- 2. the cut: histogram of the keys --------------------------------------------------------
     // Every candidate's key is >= thr_key.  Bin of a key: (key - thr_key) >> s, the top bin
@@ -326,7 +419,7 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
     lds_barrier();
     find_two_from_top(hist0, (uint32_t)k, rank_next, scan_area(1), res);
     uint32_t d0 = res[0], above0 = res[1], d_next = res[3];
-    if (d0 == 2047u && s != 21) {
+    if (__builtin_expect(d0 == 2047u && s != 21, 0)) {
       // the k-th largest lies beyond twice the threshold: bin the whole key range instead
       s = 21;
       lds_barrier();  // res has been read
@@ -345,7 +438,7 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
     look_up();
     const uint32_t c0 = hist0[d0];
     const uint32_t want1 = (uint32_t)k - above0;  // how many of bin d0 are selected
-    if (c0 <= (uint32_t)kSmall) {
+    if (__builtin_expect(c0 <= (uint32_t)kSmall, 1)) {
       // the few candidates of bin d0 are ranked on (key, position); the want1-th of them is
       // the cut
       for_each([&](uint64_t v) {
@@ -416,7 +509,6 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
     }
   } else {
     // ---- exact route: all scores of this head, then selection from them ------------------------------
-    float* sw = a.scores_w + (size_t)bh * l;
     for (int row = t; row < n; row += kT) sw[row] = proxy_score_of_row(Arow, qh, r, row);
     __threadfence_block();
     __syncthreads();

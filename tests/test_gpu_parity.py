@@ -542,6 +542,57 @@ def test_decode_step_selection_far_above_a_stale_threshold():
     _crafted_steps(cfg, data, [qs.next() for _ in range(3)], mutate)
 
 
+def _spread(data, kind, rng):
+    """Changes A_K so that the scores of q_hat >= 0 queries are of the given kind."""
+    n = data.A_K.shape[2]
+    if kind == "ties":              # five different scores: more equal ones than the list holds
+        data.A_K[:] = data.A_K[:, :, torch.arange(n) % 5, :]
+    elif kind == "negative":
+        data.A_K.abs_().neg_()
+    elif kind == "narrow":          # all within 1e-4 of each other
+        data.A_K.mul_(1e-5).add_(1.0)
+    elif kind == "wide":            # some a millionfold
+        data.A_K.abs_()
+        data.A_K[:, :, torch.from_numpy(rng.choice(n - 64, 3000, replace=False))] *= 1e6
+
+
+@pytest.mark.parametrize("l,k,C,r,rank,kind", [
+    (70000, 1024, 2048, 32, 9000, ""),          # two groups a thread, a few more than the list holds
+    (70000, 1024, 2048, 32, 25000, ""),         # most of them without a packed score
+    (70000, 1024, 2048, 32, 60000, ""),         # so many that all scores are computed
+    (12000, 1400, 2048, 32, 9500, ""),          # 16 packed scores a group, dense
+    (70000, 1024, 2048, 32, 30000, "ties"), (70000, 1024, 2048, 32, 30000, "negative"),
+    (70000, 1024, 2048, 32, 30000, "narrow"), (70000, 1024, 2048, 32, 30000, "wide"),
+    (70000, 1024, 2048, 32, 8192, ""), (70000, 1024, 2048, 32, 8193, ""),       # the list's size
+    (262140, 4000, 4096, 16, 40000, "")])       # four groups a thread, several lists of missing scores
+def test_decode_step_threshold_far_too_low(l, k, C, r, rank, kind):
+    """A carried threshold that marks `rank` candidates, more than the list holds: the selection is exact
+    and what it leaves for the next step is near rank 1.5 k again (with scores spread as scores are; it is
+    the edge of a bin of 2^12 keys, 2^21 below zero)."""
+    say(f"decode_step: threshold at rank {rank} of {l} for k={k} {kind}")
+    cfg = small_cfg(B=1, Hq=2, Hkv=1, l=l, r=r, k=k, w=64, C=C, n_heavy=16)
+    data = make_layer(cfg)
+    _spread(data, kind, np.random.default_rng(7))
+    qs, n = QueryStream(data), l - 64
+    queries = [(q, q_hat.abs() if kind else q_hat) for q, q_hat in (qs.next() for _ in range(3))]
+    _, s32 = orc.proxy_scores(as_numpy(data.A_K), as_numpy(queries[1][1]))
+    norm = np.linalg.norm(as_numpy(queries[1][1]), axis=-1)
+    left = []
+
+    def mutate(i, dl):
+        if i == 2:
+            thr = np.sort(s32[..., :n], axis=-1)[..., n - rank]
+            thr = (thr - 1e-6 * np.abs(thr)) / norm
+            dl.sel_thr.copy_(torch.from_numpy(thr.astype(np.float32)))
+        if i == 3:
+            thr = dl.sel_thr.cpu().numpy() * norm
+            left.append((s32[..., :n] >= thr[..., None]).sum(-1))
+    _crafted_steps(cfg, data, queries, mutate)
+    say(f"   candidates for the next step: {left[0]}")
+    if kind in ("", "wide"):
+        assert (left[0] >= k).all() and (left[0] <= 2 * k).all()
+
+
 @pytest.mark.parametrize("n_classes", [3, 50])
 def test_decode_step_victims_spread_over_age_classes(n_classes):
     say(f"decode_step: one step with about 300 misses, victims drawn from {n_classes} age classes")
