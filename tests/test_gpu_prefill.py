@@ -204,7 +204,7 @@ def test_prefill_beyond_the_infinity_cache(kv_dtype, l):
 @pytest.mark.parametrize("B", [1, 10, 30])
 def test_prefill_shared_and_unshared_sums(B, r):
     """The r x d algebra of a head by four workgroups or by one, as compute units are to spare: by four
-    for all (16 + 4 heads), for key heads only (80 + 20), by one (240 + 60).  Three rounds."""
+    for all (8 + 2 heads), for key heads only (80 + 20), by one (240 + 60).  Three rounds."""
     say(f"prefill r={r}, {8 * B} + {2 * B} heads")
     run_prefill_case(pf_cfg(B=B, Hq=8, Hkv=2, l=200, r=r, k=32, C=32), n_iter=3)
 
@@ -278,6 +278,27 @@ def test_prefill_distances(r, l, dtype):
         " ".join(f"{n} {x:.1e}" for n, x in two.items()))
     assert max(one[n] for n in ("A_K", "B_Q", "B_K")) <= 7e-7 and one["A_Q"] <= 6e-6
     assert max(two.values()) <= 8e-6
+
+
+@pytest.mark.parametrize("r", [8, 16, 32, 64])
+@pytest.mark.parametrize("B", [16, 17, 32, 33])
+def test_prefill_limits_of_sharing(B, r):
+    """The last head counts at which four workgroups share the sums of a head and the first at which they
+    do not (4 B query heads: 64 and 68; 4 B + 4 times B key heads: 256 and 264), sums from several chunks
+    of rows.  Every copy of one sequence, at the distance that test_prefill_distances allows."""
+    Q, K, A_Q0, A_K0 = strong_directions("mean", 0.0, 3000, r, 4, torch.bfloat16, seed=30 + r)
+    ref = pre.prefill_factorize(as_numpy(Q), as_numpy(K), as_numpy(A_Q0), as_numpy(A_K0), 1.0, 1.0, 2)
+    Q, K, A_Q, A_K = (x.to(DEV).repeat(B, 1, 1, 1) for x in (Q, K, A_Q0, A_K0))
+    got = dict(A_Q=A_Q, A_K=A_K, B_Q=torch.empty((B, 4, r, 128), device=DEV),
+               B_K=torch.empty((B, 1, r, 128), device=DEV))
+    shp = L.Shape.make(B=B, Hq=4, Hkv=1, l=3000, r=r, k=16, w=0, C_slots=16)
+    L.lrqk_prefill_factorize(shp, Q, K, *got.values(), 1.0, 1.0, 2,
+                             workspace(L.lrqk_workspace_bytes(shp, L.LRQK_WS_PREFILL)))
+    torch.cuda.synchronize()
+    far = {n: max(float(np.linalg.norm(x[b].cpu().numpy() - ref[n][0]) / np.linalg.norm(ref[n][0]))
+                  for b in range(B)) for n, x in got.items()}
+    say(f"prefill r={r}, {4 * B} + {B} heads: " + " ".join(f"{n} {x:.1e}" for n, x in far.items()))
+    assert max(far.values()) <= 8e-6
 
 
 def test_prefill_keys_of_lower_rank():
