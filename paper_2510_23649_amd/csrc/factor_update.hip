@@ -15,8 +15,8 @@
 //     of these two), a workgroup per matrix.
 //  3. factor_rounds_kernel: the n_iter rounds and the line-search gradient steps on B_Q and B_K in
 //     place, workgroups per (batch, KV head).
-// Times in us at k = 2048, w = 64, 32 + 8 heads, r = 32: 9 + 10 + 9.5; at 8 x (28 + 4) heads, k = 1024, r = 64:
-// 38.5 + 23 + 22.  (Factorising in fp32 with a row per lane, P once and the k_hat system in every
+// Times in us at k = 2048, w = 64, 32 + 8 heads, r = 32: 9 + 10 + 9.7; at 8 x (28 + 4) heads, k = 1024, r = 64:
+// 38.4 + 22.9 + 26.4.  (Factorising in fp32 with a row per lane, P once and the k_hat system in every
 // round, all in one wavefront per head, launches 2 and 3 took 30 and 114 us.)  What is left is
 // latency: the loads at the start of each launch (2 us; 5 to 9 us at the second shape, where every
 // compute unit reads 130 and 265 KB), the eliminations (3.5 and 9 us) and the rounds (2 and 5 us each).
@@ -71,9 +71,9 @@ struct SolveArgs {
 //   query head:  P = B_Q B_Q^T + lambda_d2 A_Om^T A_Om,  c = q B_Q^T + lambda_d2 q K_Om^T A_Om
 //   KV head:     N = B_K B_K^T,                          nb = k B_K^T
 // The chunk partials of launch 1 are added in chunk order.  The matrix lies in 16 x 16 tiles in
-// the wavefronts' registers and is inverted in place by Gauss-Jordan elimination with 4 x 4 pivot
-// blocks, one MFMA per tile and step (lrqk_alg64.h).  Latency bound: r / 4 steps, each an exchange
-// through LDS, two reciprocals and the MFMAs.
+// the wavefronts' registers and is inverted in place by Gauss-Jordan elimination, a pivot tile at a
+// time (lrqk_alg64.h).  Latency bound: r / 16 steps, each four inversions of 4 x 4 blocks in one
+// wavefront, an exchange through LDS with two barriers, and the MFMAs.
 constexpr int kInvThreads = 512;
 constexpr int kLdb = kD + 2;  // LDS row stride: 16 rows x 2 columns fall on 32 different bank pairs
 template <int R>
@@ -215,8 +215,8 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
 // Those steps read and write G + 1 matrices, 256 KB at r = 64 and G = 7, which took one compute unit
 // 8 us.  So the matrices of a group are dealt out over `parts` workgroups, all of which go through the
 // rounds (on compute units that would be idle) and whose first matrix is on its way meanwhile.  The whole
-// call, 8 x (28 + 4) heads, r = 64, with 1, 2, 4, 8 of them: 101.7, 90.8, 85.7, 83.5 us; 32 + 8 heads, r = 32,
-// with 1 and 5: 29.5, 27.0; but 8 x (32 + 8) heads with 4 and 5, that is 256 and 320: 36.1, 43.8.
+// call, 8 x (28 + 4) heads, r = 64, with 1, 2, 4, 8 of them: 106.6, 95.9, 90.9, 88.7 us; 32 + 8 heads, r = 32,
+// with 1 and 5: 31.0, 28.5; but 8 x (32 + 8) heads with 4 and 5, that is 256 and 320: 36.1, 43.8.
 template <int R>
 struct RoundShape {
   static constexpr int kPerHead = R / 32;  // wavefronts per query head
@@ -419,8 +419,8 @@ hipError_t launch_update_r(const lrqk_shape& s, const GramRows& ga, const SolveA
   if (e == hipSuccess)
     e = raise_dynamic_lds_once(factor_rounds_kernel<R, BF16>, RoundShape<R>::lds_bytes, rounds);
   if (e != hipSuccess) return e;
-  // The partials to the die of their inverse as long as they fit its L2 (4 MB) with room to spare: 27.1 ->
-  // 26.4 us for the call at 32 + 8 heads, r = 32 (2 MB in all); 83.4 -> 84.6 at 8 x (28 + 4) heads, r = 64 (30).
+  // The partials to the die of their inverse as long as they fit its L2 (4 MB) with room to spare: 28.8 ->
+  // 28.5 us for the call at 32 + 8 heads, r = 32 (2 MB in all); 88.7 -> 89.9 at 8 x (28 + 4) heads, r = 64 (30).
   const size_t partials = (size_t)s.B * s.Hq * ga.nchunk * (R * R + R) * sizeof(float);
   hipLaunchKernelGGL((factor_gram_kernel<R, BF16>), dim3(ga.nchunk * s.B * s.Hq), dim3(kGramThreads), 0,
                      st, ga, s.B * s.Hkv, partials <= (size_t)16 << 20);

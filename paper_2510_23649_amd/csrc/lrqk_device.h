@@ -19,7 +19,7 @@ __device__ __forceinline__ void lds_barrier() {
 // parts of a unit, and the same unit in every launch, on one of them where the units divide evenly, so
 // that what one launch leaves is in the L2 that the next one reads through (32 KB by each of 256 workgroups
 // that read what another kernel's workgroup has written: 1850 cycles on the same die, 3670 otherwise).
-// Factor update at 8 x (28 + 4) heads, r = 64: 90.8 -> 83.8 us, 27.5 -> 27.1 at 32 + 8 heads, r = 32 (launches 2
+// Factor update at 8 x (28 + 4) heads, r = 64: 95.1 -> 88.7 us, 28.7 -> 28.5 at 32 + 8 heads, r = 32 (launches 2
 // and 3; for launch 1 see its launch).
 __device__ __forceinline__ void place(int i, int units, int parts, int& unit, int& part,
                                       bool by_die = true) {

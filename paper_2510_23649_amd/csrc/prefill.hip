@@ -1051,7 +1051,7 @@ __global__ __launch_bounds__(kAlgThreads) void prefill_round_q_kernel(const PfSt
 // "lane = row"; 16-byte piece c of row i is kept at c ^ (i % 16), so that 16 rows' reads of one
 // piece lie in different banks.  The next rows' loads are in flight during the products.  M is
 // the same for a whole head: in registers at r <= 32 (96 of them), in LDS at r = 64.
-// Bound by HBM (Y in, X out): 2.0 GB in 0.36 ms at 32 + 8 heads, l = 131072, r = 32.  The rows go from the
+// Bound by HBM (Y in, X out): 2.0 GB in 0.32 ms at 32 + 8 heads, l = 131072, r = 32.  The rows go from the
 // last to the first: the last that the reduction read are still in the Infinity Cache (1018 -> 1006 us for
 // the whole call at that shape).
 template <int R>
@@ -1294,7 +1294,7 @@ hipError_t run_prefill(const lrqk_shape& s, const void* Q, const void* K, float*
     std::swap(HK, HK_new);
   }
   // 32-row units per wavefront: enough workgroups to fill the chip a few times over
-  // (the whole call at l = 131072, r = 32, 32 + 8 heads, with at most 16, 8, 4 of them: 944, 920, 918 us)
+  // (the whole call at l = 131072, r = 32, 32 + 8 heads, with at most 16 or 8 of them: 26 and 2 us more)
   const int row_units = ceil_div(l, 32);
   int units = 1;
   while (units < 4 && (long)ceil_div(row_units, 8 * units) * heads >= 2048) units *= 2;
