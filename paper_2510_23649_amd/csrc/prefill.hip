@@ -131,6 +131,9 @@ struct PfReduce {
   static constexpr int kTile = NP * kYPlane + 3 * kAPlane;
   static constexpr size_t lds_bytes = 2 * (size_t)kTile;
   static constexpr int kFlushTiles = kFlushRows / TR;
+  // S and H beyond kFlushRows rows in fp64, not fp32: where there are registers for it (r = 8 and 16 would
+  // spill 38 of them, 446 -> 471 us for the whole call at l = 65536, r = 16; r = 64 spills as it is).
+  static constexpr bool kWideSums = R == 32;
 };
 
 template <int R, int NS>
@@ -307,7 +310,8 @@ __global__ __launch_bounds__(kRedThreads, 2) void prefill_reduce_kernel(
     constexpr int NACC = ROLE == 0 ? 0 : ROLE == 1 ? RB + RB - 1 : RB + 1 + RB;  // S, parts of H
     constexpr int NFL = ROLE == 0 ? 0 : ROLE == 1 ? NACC : 2 * RB;               // flushed ones
     double g[NG + 1][16];
-    f32x16 ghi[NG + 1], glo[NG + 1], acc[NACC + 1], acc2[NFL + 1];
+    f32x16 ghi[NG + 1], glo[NG + 1], acc[NACC + 1];
+    std::conditional_t<T::kWideSums, double, float> acc2[NFL + 1][16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
 #pragma unroll
@@ -318,10 +322,10 @@ __global__ __launch_bounds__(kRedThreads, 2) void prefill_reduce_kernel(
 #pragma unroll
       for (int i = 0; i < NACC; ++i) acc[i][v] = 0.0f;
 #pragma unroll
-      for (int i = 0; i < NFL; ++i) acc2[i][v] = 0.0f;
+      for (int i = 0; i < NFL; ++i) acc2[i][v] = 0;
     }
     // From time to time the accumulators of G go to fp64 ones, those of S, D and the off-diagonal
-    // products of H to second fp32 ones: rounding errors follow the size of the sum that they are
+    // products of H to second ones, of fp32 or fp64 (kWideSums): rounding errors follow the size of the sum that they are
     // made in, however many rows a chunk has, and the second round's factors amplify those of S.
     // (The second-order parts of H and, at r <= 32, a0^T a2 may stay: they are 2^-17 of it.)
     auto flush_sums = [&]() {
@@ -456,9 +460,9 @@ __global__ __launch_bounds__(kRedThreads, 2) void prefill_reduce_kernel(
 #pragma unroll
       for (int v = 0; v < 16; ++v) gout[block * 1024 + v * 64] = x[v];
     };
-    auto put = [&](int block, const f32x16& x) {
+    auto put = [&](int block, const auto& x) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) out[block * 1024 + v * 64] = x[v];
+      for (int v = 0; v < 16; ++v) out[block * 1024 + v * 64] = (float)x[v];
     };
     if constexpr (ROLE == 0) {
       put_g(cb, g[0]);
@@ -1176,19 +1180,22 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_apply_kernel(
 // ------------------------------------------------------------------------------------------
 // Chunks of rows per head: the fewest workgroup rounds (one workgroup per CU) times the passes
 // of a workgroup, a partial costing about as much as four passes.  At most kPfSlots partials
-// unless there are more heads than that.  (Fewer and longer chunks would save the partials' traffic, 938 ->
-// 922 us for the whole call with 6 chunks instead of 19 at 32 + 8 heads, l = 131072, r = 32; but S and H are
-// in fp32 over a chunk and in fp64 only beyond it, and three times as many fp32 additions in a row
-// round three times as far off: test_prefill_long_sums, 6.3e-7 instead of 2.0e-7.)
+// unless there are more heads than that.
+// `wide`: the sums of a chunk are as good however long it is (kWideSums), and a partial also costs its
+// traffic, written and read, a 64th of a round: 6 chunks instead of 19 at 32 + 8 heads, l = 131072, r = 32,
+// 956 -> 944 us for the whole call.  Not where S and H are in fp32 over a chunk and in fp64 only beyond it:
+// three times as many fp32 additions in a row round three times as far off (test_prefill_long_sums, 6.3e-7
+// instead of 2.0e-7).
 constexpr int kPfSlots = 1024;
-int reduce_chunks(int heads, int l, int rows) {
+int reduce_chunks(int heads, int l, int rows, bool wide) {
   const int tiles = ceil_div(l, rows);
   const int most = heads >= kPfSlots ? 1 : min(tiles, kPfSlots / heads);
   int best = 1;
   long best_cost = 0;
   for (int n = 1; n <= most; ++n) {
     const int per = ceil_div(tiles, n);
-    const long cost = (long)ceil_div(heads * ceil_div(tiles, per), 256) * (per + 4);
+    const long cost = 64 * (long)ceil_div(heads * ceil_div(tiles, per), 256) * (per + 4) +
+                      (wide ? (long)heads * n : 0);
     if (n == 1 || cost < best_cost) {
       best = n;
       best_cost = cost;
@@ -1260,7 +1267,7 @@ hipError_t run_prefill(const lrqk_shape& s, const void* Q, const void* K, float*
   hipError_t e = PfKernels<R, NS>::allow();
   if (e != hipSuccess) return e;
   constexpr int kRows = PfReduce<R, NS>::kRows;
-  const int per_chunk = ceil_div(ceil_div(l, kRows), reduce_chunks(heads, l, kRows));
+  const int per_chunk = ceil_div(ceil_div(l, kRows), reduce_chunks(heads, l, kRows, PfReduce<R, NS>::kWideSums));
   const int nchunk = ceil_div(ceil_div(l, kRows), per_chunk);
   hipLaunchKernelGGL((prefill_reduce_kernel<R, NS>), dim3(nchunk * heads), dim3(kRedThreads),
                      (PfReduce<R, NS>::lds_bytes), st, Q, K, A_Q, A_K, w.part, BHq, l, lk, nchunk,
