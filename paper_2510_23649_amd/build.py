@@ -19,7 +19,7 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "liblrqk.so")
 
 SOURCES = ["api.hip", "proxy_scores.hip", "select_topk.hip", "cache_resolve.hip", "select_resolve.hip",
-           "select_packed.hip",
+           "select_packed.hip", "select_scores.hip",
            "sparse_attend.hip", "fetch.hip", "factor_update.hip", "factor_update_small.hip",
            "append_token.hip", "prefill.hip",
            "instrument.hip", "noalloc.hip"]

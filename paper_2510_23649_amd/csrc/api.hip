@@ -229,7 +229,9 @@ int lrqk_select_topk(const lrqk_shape* shape, const float* scores, int32_t* sel_
   const SelectWs ws = carve_select_ws(workspace, shape->B * shape->Hq, shape->k);
   if (ws_bytes < ws.bytes) return LRQK_ENOMEM;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (select_resolve_fits(*shape, false))
+  if (select_scores_fits(*shape))
+    LRQK_HIP(launch_select_scores(*shape, scores, sel_idx, st));
+  else if (select_resolve_fits(*shape, false))
     LRQK_HIP(launch_select_only(*shape, scores, sel_idx, st));
   else
     LRQK_HIP(launch_select_topk(*shape, scores, sel_idx, ws, st));

@@ -139,6 +139,10 @@ hipError_t launch_proxy_scores_filter(const lrqk_shape& s, const float* A_K, con
                                       float* cand_scores, hipStream_t st);
 hipError_t launch_select_topk(const lrqk_shape& s, const float* scores, int32_t* sel_idx,
                               const SelectWs& ws, hipStream_t st);
+// One workgroup per head, its scores in registers (select_scores.hip).
+bool select_scores_fits(const lrqk_shape& s);
+hipError_t launch_select_scores(const lrqk_shape& s, const float* scores, int32_t* sel_idx,
+                                hipStream_t st);
 // One workgroup per head, everything in LDS (select_resolve.hip); usable when the
 // bitmap of l bits and the other buffers fit (select_resolve_fits).
 bool select_resolve_fits(const lrqk_shape& s, bool resolve);

@@ -60,6 +60,155 @@ __device__ __forceinline__ void scan2(uint32_t v0, uint32_t v1, uint32_t* wt, ui
   *ex1 = waves_before(wt + 16, tot1) + i1 - v1;
 }
 
+// (key, position) of a candidate as one number: larger = better (higher key, or equal key and lower position)
+__device__ __forceinline__ uint64_t value_of(uint32_t key, int p) {
+  return ((uint64_t)key << 32) | (uint32_t)~(uint32_t)p;
+}
+__device__ __forceinline__ int position_of(uint64_t v) { return (int)~(uint32_t)v; }
+
+constexpr int kSmall = 64;  // candidates of the threshold bin that one wavefront ranks directly
+
+// Scan of a 2048-bin histogram from the top (thread t owns bins 2t, 2t+1) for two ranks at
+// once: res[0] = the bin d that holds the want_a-th entry from the top, res[1] = the entries
+// above d, res[3] = the bin that holds the want_b-th entry (0xffffffff where there are fewer
+// entries than that).  Returns the number of entries.  LDS-only barriers.
+__device__ __forceinline__ uint32_t find_two_from_top(const uint32_t* hist, uint32_t want_a,
+                                                      uint32_t want_b, uint32_t* wt,
+                                                      uint32_t* res) {
+  const int t = threadIdx.x;
+  const uint32_t c0 = hist[2 * t], c1 = hist[2 * t + 1];
+  if (t == 0) {
+    res[0] = 0xffffffffu;
+    res[3] = 0xffffffffu;
+  }
+  uint32_t total;
+  const uint32_t below = scan1(c0 + c1, wt, &total);  // its barriers order the writes of res
+  const uint32_t above1 = total - below - c0 - c1;
+  const uint32_t above0 = above1 + c1;
+  if (above1 < want_a && want_a <= above1 + c1) {
+    res[0] = 2 * t + 1;
+    res[1] = above1;
+  } else if (above0 < want_a && want_a <= above0 + c0) {
+    res[0] = 2 * t;
+    res[1] = above0;
+  }
+  if (above1 < want_b && want_b <= above1 + c1) {
+    res[3] = 2 * t + 1;
+  } else if (above0 < want_b && want_b <= above0 + c0) {
+    res[3] = 2 * t;
+  }
+  lds_barrier();
+  return total;
+}
+
+// The value of the k-th largest of a head's candidates, whose keys are all >= thr_key, at least k of them,
+// in position order over the threads: entry e < E of a thread in val[e], 0: none.  Entries below the bin
+// that holds it are zeroed before `meanwhile` is called, whose loads then run under the rest.  *shift: the
+// width of a bin; *d_next: the bin of rank `rank_next` (0xffffffff: fewer entries than that).
+struct CutWork {
+  uint32_t* hist0;       // [2048], zero; taken
+  uint32_t* hist1;       // [2048], zero; zero again afterwards
+  uint64_t* small;       // [kSmall]
+  uint32_t* sh_small_n;  // zero
+  uint64_t* sh_cut;
+  uint32_t* wave_tot;    // four areas of 32 words; area 0 may still be in use
+  uint32_t* res;         // [4]
+};
+template <int MAXE, class F>
+__device__ __forceinline__ uint64_t cut_of_entries(uint64_t (&val)[MAXE], uint32_t E, uint32_t thr_key,
+                                                   uint32_t k, uint32_t rank_next, const CutWork& w,
+                                                   F meanwhile, int* shift, uint32_t* d_next) {
+  const int t = threadIdx.x, lane = t & 63;
+  auto scan_area = [&](int i) { return w.wave_tot + (i & 3) * 2 * kWaves; };
+  // Bin of a key: (key - thr_key) >> s, the top bin taking everything beyond.  For a positive
+  // threshold s = 12 spreads the scores between the threshold and twice the threshold over the 2048 bins.
+  int s = (thr_key > 0x80800000u && thr_key < 0xff800000u) ? 12 : 21;
+  auto bin_of = [&](uint64_t v) { return min(((uint32_t)(v >> 32) - thr_key) >> s, 2047u); };
+  auto for_each = [&](auto&& f) {
+#pragma unroll
+    for (int e = 0; e < MAXE; ++e) {
+      if ((uint32_t)e >= E) break;  // uniform
+      if (val[e] != 0ull) f(val[e]);
+    }
+  };
+  for_each([&](uint64_t v) { atomicAdd(&w.hist0[bin_of(v)], 1u); });
+  lds_barrier();
+  find_two_from_top(w.hist0, k, rank_next, scan_area(1), w.res);
+  uint32_t d0 = w.res[0], above0 = w.res[1];
+  *d_next = w.res[3];
+  if (__builtin_expect(d0 == 2047u && s != 21, 0)) {
+    // the k-th largest lies beyond twice the threshold: bin the whole key range instead
+    s = 21;
+    lds_barrier();  // res has been read
+    for (int i = t; i < 2048; i += kT) w.hist0[i] = 0u;
+    lds_barrier();
+    for_each([&](uint64_t v) { atomicAdd(&w.hist0[bin_of(v)], 1u); });
+    lds_barrier();
+    find_two_from_top(w.hist0, k, rank_next, scan_area(2), w.res);
+    d0 = w.res[0];
+    above0 = w.res[1];
+    *d_next = w.res[3];
+  }
+  *shift = s;
+#pragma unroll
+  for (int e = 0; e < MAXE; ++e)
+    if (val[e] != 0ull && bin_of(val[e]) < d0) val[e] = 0ull;  // not selected
+  meanwhile();
+  const uint32_t c0 = w.hist0[d0];
+  const uint32_t want1 = k - above0;  // how many of bin d0 are selected
+  if (__builtin_expect(c0 <= (uint32_t)kSmall, 1)) {
+    // the few candidates of bin d0 are ranked on (key, position); the want1-th of them is
+    // the cut
+    for_each([&](uint64_t v) {
+      if (bin_of(v) == d0) w.small[atomicAdd(w.sh_small_n, 1u)] = v;
+    });
+    lds_barrier();
+    // every wavefront ranks the bin for itself (no second barrier to hand the cut over)
+    const uint64_t mine = lane < (int)c0 ? w.small[lane] : 0ull;
+    uint32_t larger = 0;
+#pragma unroll 8
+    for (uint32_t jj = 0; jj < c0; ++jj) larger += w.small[jj] > mine ? 1u : 0u;
+    const unsigned long long is_cut = __ballot(lane < (int)c0 && larger == want1 - 1u);
+    const int src = __builtin_ctzll(is_cut);  // exactly one entry has that rank
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), src);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, src);
+    return ((uint64_t)hi << 32) | lo;
+  }
+  // many candidates in the bin (ties): further histogram levels over the low s bits give
+  // the exact key tau of the k-th largest; of the candidates with that key the first
+  // need_eq in position order are selected, so the cut is the need_eq-th of them
+  uint32_t known = d0, want = want1;
+  int rem = s;
+  while (rem > 0) {
+    const int bits = rem < 11 ? rem : 11;
+    const int nsh = rem - bits;
+    for_each([&](uint64_t v) {
+      const uint32_t rel = (uint32_t)(v >> 32) - thr_key;
+      if ((rel >> rem) == known) atomicAdd(&w.hist1[(rel >> nsh) & ((1u << bits) - 1u)], 1u);
+    });
+    __syncthreads();
+    find_from_top(w.hist1, want, w.wave_tot, w.res);
+    const uint32_t dd = w.res[0], ab = w.res[1];
+    known = (known << bits) | dd;
+    want -= ab;
+    rem = nsh;
+    __syncthreads();  // res and hist1 have been read
+    for (int i = t; i < 2048; i += kT) w.hist1[i] = 0u;
+    __syncthreads();
+  }
+  // (bin d0 is never the catch-all top bin here, so rel >> s == d0 identifies it)
+  const uint32_t tau = thr_key + known, need_eq = want;
+  uint32_t neq = 0;
+  for_each([&](uint64_t v) { neq += (uint32_t)(v >> 32) == tau ? 1u : 0u; });
+  uint32_t tot;
+  uint32_t eq_rank = block_exclusive_scan(neq, w.wave_tot, &tot);
+  for_each([&](uint64_t v) {  // (in position order)
+    if ((uint32_t)(v >> 32) == tau && ++eq_rank == need_eq) *w.sh_cut = v;
+  });
+  __syncthreads();
+  return *w.sh_cut;
+}
+
 struct Keys4 {
   uint32_t k[4];
   bool ok[4];

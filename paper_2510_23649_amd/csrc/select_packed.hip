@@ -67,7 +67,6 @@ namespace {
 constexpr int kPackedMaxK = 4 * kT;             // k
 constexpr int kMaxE = 8;                  // list entries per thread
 constexpr int kListCap = kMaxE * kT;      // candidates of a head
-constexpr int kSmall = 64;    // candidates of the threshold bin that one wavefront ranks directly
 constexpr int kMaxSpt = 8;    // cache slots per thread (C <= 8192)
 constexpr size_t kPackedLdsLimit = 150 * 1024;
 
@@ -96,39 +95,6 @@ __host__ __device__ inline PackedArena packed_arena(int k, int n, int C) {
   if (z < (size_t)kListCap * 8) z = (size_t)kListCap * 8;
   a.total = a.fixed + z;
   return a;
-}
-
-// Scan of a 2048-bin histogram from the top (thread t owns bins 2t, 2t+1) for two ranks at
-// once: res[0] = the bin d that holds the want_a-th entry from the top, res[1] = the entries
-// above d, res[3] = the bin that holds the want_b-th entry (0xffffffff where there are fewer
-// entries than that).  Returns the number of entries.  LDS-only barriers.
-__device__ __forceinline__ uint32_t find_two_from_top(const uint32_t* hist, uint32_t want_a,
-                                                      uint32_t want_b, uint32_t* wt,
-                                                      uint32_t* res) {
-  const int t = threadIdx.x;
-  const uint32_t c0 = hist[2 * t], c1 = hist[2 * t + 1];
-  if (t == 0) {
-    res[0] = 0xffffffffu;
-    res[3] = 0xffffffffu;
-  }
-  uint32_t total;
-  const uint32_t below = scan1(c0 + c1, wt, &total);  // its barriers order the writes of res
-  const uint32_t above1 = total - below - c0 - c1;
-  const uint32_t above0 = above1 + c1;
-  if (above1 < want_a && want_a <= above1 + c1) {
-    res[0] = 2 * t + 1;
-    res[1] = above1;
-  } else if (above0 < want_a && want_a <= above0 + c0) {
-    res[0] = 2 * t;
-    res[1] = above0;
-  }
-  if (above1 < want_b && want_b <= above1 + c1) {
-    res[3] = 2 * t + 1;
-  } else if (above0 < want_b && want_b <= above0 + c0) {
-    res[3] = 2 * t;
-  }
-  lds_barrier();
-  return total;
 }
 
 struct PackedArgs {
@@ -232,9 +198,6 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
   }
 
   // ---- 1. the list of candidates -------------------------------------------------------------------
-  // (key, position) as one number: larger = better (higher key, or equal key and lower position)
-  auto value_of = [](uint32_t kk, int p) { return ((uint64_t)kk << 32) | (uint32_t)~(uint32_t)p; };
-  auto position_of = [](uint64_t v) { return (int)~(uint32_t)v; };
   uint32_t own = 0;
 #pragma unroll
   for (int g = 0; g < GPT; ++g) own += (uint32_t)__popcll(mask[g]);
@@ -403,96 +366,17 @@ __global__ __launch_bounds__(kT) void select_packed_kernel(const PackedArgs a) {
   if (__builtin_expect(listed, 1)) {
     take_entries(m);
     // ---- 2. the cut: histogram of the keys --------------------------------------------------------
-    // Every candidate's key is >= thr_key.  Bin of a key: (key - thr_key) >> s, the top bin
-    // taking everything beyond.  For a positive threshold s = 12 spreads the scores between the
-    // threshold and twice the threshold over the 2048 bins.
-    int s = (thr_key > 0x80800000u && thr_key < 0xff800000u) ? 12 : 21;
-    auto bin_of = [&](uint64_t v) { return min(((uint32_t)(v >> 32) - thr_key) >> s, 2047u); };
-    auto for_each = [&](auto&& f) {
-#pragma unroll
-      for (int e = 0; e < kMaxE; ++e) {
-        if ((uint32_t)e >= E) break;  // uniform
-        if (val[e] != 0ull) f(val[e]);
-      }
-    };
-    for_each([&](uint64_t v) { atomicAdd(&hist0[bin_of(v)], 1u); });
-    lds_barrier();
-    find_two_from_top(hist0, (uint32_t)k, rank_next, scan_area(1), res);
-    uint32_t d0 = res[0], above0 = res[1], d_next = res[3];
-    if (__builtin_expect(d0 == 2047u && s != 21, 0)) {
-      // the k-th largest lies beyond twice the threshold: bin the whole key range instead
-      s = 21;
-      lds_barrier();  // res has been read
-      for (int i = t; i < 2048; i += kT) hist0[i] = 0u;
-      lds_barrier();
-      for_each([&](uint64_t v) { atomicAdd(&hist0[bin_of(v)], 1u); });
-      lds_barrier();
-      find_two_from_top(hist0, (uint32_t)k, rank_next, scan_area(2), res);
-      d0 = res[0];
-      above0 = res[1];
-      d_next = res[3];
-    }
-#pragma unroll
-    for (int e = 0; e < kMaxE; ++e)
-      if (val[e] != 0ull && bin_of(val[e]) < d0) val[e] = 0ull;  // not selected
-    look_up();
-    const uint32_t c0 = hist0[d0];
-    const uint32_t want1 = (uint32_t)k - above0;  // how many of bin d0 are selected
-    if (__builtin_expect(c0 <= (uint32_t)kSmall, 1)) {
-      // the few candidates of bin d0 are ranked on (key, position); the want1-th of them is
-      // the cut
-      for_each([&](uint64_t v) {
-        if (bin_of(v) == d0) small[atomicAdd(&sh_small_n, 1u)] = v;
-      });
-      lds_barrier();
-      {
-        // every wavefront ranks the bin for itself (no second barrier to hand the cut over)
-        const uint64_t mine = lane < (int)c0 ? small[lane] : 0ull;
-        uint32_t larger = 0;
-#pragma unroll 8
-        for (uint32_t jj = 0; jj < c0; ++jj) larger += small[jj] > mine ? 1u : 0u;
-        const unsigned long long is_cut = __ballot(lane < (int)c0 && larger == want1 - 1u);
-        const int src = __builtin_ctzll(is_cut);  // exactly one entry has that rank
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), src);
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, src);
-        cut = ((uint64_t)hi << 32) | lo;
-      }
-    } else {
-      // many candidates in the bin (ties): further histogram levels over the low s bits give
-      // the exact key tau of the k-th largest; of the candidates with that key the first
-      // need_eq in position order are selected, so the cut is the need_eq-th of them
-      uint32_t* const hist1 = ahist;  // (zero again afterwards)
-      uint32_t known = d0, want = want1;
-      int rem = s;
-      while (rem > 0) {
-        const int bits = rem < 11 ? rem : 11;
-        const int nsh = rem - bits;
-        for_each([&](uint64_t v) {
-          const uint32_t rel = (uint32_t)(v >> 32) - thr_key;
-          if ((rel >> rem) == known) atomicAdd(&hist1[(rel >> nsh) & ((1u << bits) - 1u)], 1u);
-        });
-        __syncthreads();
-        find_from_top(hist1, want, wave_tot, res);
-        const uint32_t dd = res[0], ab = res[1];
-        known = (known << bits) | dd;
-        want -= ab;
-        rem = nsh;
-        __syncthreads();  // res and hist1 have been read
-        for (int i = t; i < 2048; i += kT) hist1[i] = 0u;
-        __syncthreads();
-      }
-      // (bin d0 is never the catch-all top bin here, so rel >> s == d0 identifies it)
-      const uint32_t tau = thr_key + known, need_eq = want;
-      uint32_t neq = 0;
-      for_each([&](uint64_t v) { neq += (uint32_t)(v >> 32) == tau ? 1u : 0u; });
-      uint32_t tot;
-      uint32_t eq_rank = block_exclusive_scan(neq, wave_tot, &tot);
-      for_each([&](uint64_t v) {  // (in position order)
-        if ((uint32_t)(v >> 32) == tau && ++eq_rank == need_eq) sh_cut = v;
-      });
-      __syncthreads();
-      cut = sh_cut;
-    }
+    CutWork cw;
+    cw.hist0 = hist0;
+    cw.hist1 = ahist;
+    cw.small = small;
+    cw.sh_small_n = &sh_small_n;
+    cw.sh_cut = &sh_cut;
+    cw.wave_tot = wave_tot;
+    cw.res = res;
+    int s;
+    uint32_t d_next;
+    cut = cut_of_entries(val, E, thr_key, (uint32_t)k, rank_next, cw, look_up, &s, &d_next);
     // threshold for the layer's next step: the lower edge of the bin that holds rank 1.5 k, or,
     // with fewer candidates than that, an extrapolation along an exponential tail through
     // (threshold used, m) and (the k-th largest, k)

@@ -133,6 +133,24 @@ def test_select_topk_around_the_sampling_limit(l, w, k):
     assert np.array_equal(got, orc.select_topk(s.astype(np.float32), k, w))
 
 
+@pytest.mark.parametrize("l,w,k", [(1, 0, 1), (4096, 0, 4096), (4097, 0, 1), (8193, 1, 600), (16385, 0, 4000),
+                                   (24577, 1, 3000), (32769, 0, 512), (40961, 3, 4096), (53249, 0, 700),
+                                   (65536, 0, 4096), (65540, 4, 513), (65537, 0, 513)])
+def test_select_topk_scores_in_registers(l, w, k):
+    """Edges of the groups of 4096 scores, up to the last length that a head's registers hold and the first
+    beyond it; more candidates than the list holds, fewer than k, ties."""
+    say(f"select_topk l={l} w={w} k={k}: edges of the register route")
+    rng = np.random.default_rng(l + k)
+    e = np.arange(l)
+    sampled = (e % 4 == (e // 4096) % 4) & ((e % 4096 // 4 + e // 4096) % 2 == 0)
+    base = (rng.standard_normal(l) * 11.3).astype(np.float32)
+    s = np.stack([base, np.where(sampled, base - 200.0, base), np.where(sampled, base + 200.0, base),
+                  np.where(sampled, -1e30, np.round(base)), np.full(l, 2.5), -np.abs(base),
+                  np.where(e >= l - w - k, base + 50.0, base)])[None].astype(np.float32)
+    s[:, :, l - w:] = 1e6      # the lite window must never be listed
+    assert np.array_equal(run_select(s, k, w), orc.select_topk(s, k, w))
+
+
 # ------------------------------------------------------------------------------- a3 + a4
 
 @pytest.mark.parametrize("k,C", [(1, 1), (1023, 1024), (1025, 2048), (2047, 2049), (2048, 4096),
