@@ -79,52 +79,47 @@ __global__ __launch_bounds__(kGramThreads) void factor_gram_kernel(GramArgs a) {
   const int bkv = b * a.Hkv + kvh;
   if (job == a.nchunk + 1 && h != kvh * G) return;  // the B_K job runs once per KV head
 
-  f32x16 sacc;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) sacc[v] = 0.0f;
-  float gpart = 0.0f;
+  GramAcc<R> acc;
+  float gpart;
 
   float* out;
   if (job < a.nchunk) {
     out = a.gram_om + ((size_t)bh * a.nchunk + job) * (kEntries + R);
-    gram_chunk<R, BF16>(a, s, bh, bkv, job, sacc, gpart, t);
+    gram_chunk<R, BF16>(a, s, bh, bkv, job, acc, gpart, t);
   } else {
     // ---- B_Q of this query head, or B_K of this KV head, read column by column ------------
     const bool isq = job == a.nchunk;
     out = isq ? a.gram_q + (size_t)bh * (kEntries + R) : a.gram_k + (size_t)bkv * (kEntries + R);
     const float* __restrict__ Bm =
         isq ? a.B_Q + (size_t)bh * R * kD : a.B_K + (size_t)bkv * R * kD;
-    for (int i0 = 0; i0 < kD; i0 += kGramBatch) {
-      __syncthreads();
-      if (t < kGramBatch) {
-        const int i = i0 + t;
-        float u = 0.0f;
-        if (i < kD)
-          u = isq ? a.q[(size_t)bh * kD + i]
-                  : kv_load<BF16>(static_cast<const char*>(a.k_new) + (size_t)bkv * ROWB, i);
-        s.u[t] = u;
-      }
-      // every load is issued before the first is waited for (addresses clamped, the values
-      // past the end zeroed)
-      constexpr int kBPieces = (kGramBatch * R + kGramThreads - 1) / kGramThreads;
-      float bv[kBPieces];
-#pragma unroll
-      for (int u = 0; u < kBPieces; ++u) {
-        const int idx = t + u * kGramThreads;
-        const int c = min(idx / kGramBatch, R - 1), ii = idx % kGramBatch;
-        bv[u] = Bm[(size_t)c * kD + min(i0 + ii, kD - 1)];
-        if (i0 + ii >= kD) bv[u] = 0.0f;
-      }
-#pragma unroll
-      for (int u = 0; u < kBPieces; ++u) {
-        const int idx = t + u * kGramThreads;
-        if (idx < kGramBatch * R) s.a[idx % kGramBatch * LDA + idx / kGramBatch] = bv[u];
-      }
-      __syncthreads();
-      gram_accumulate<R>(s.a, s.u, sacc, gpart, t);
+    static_assert(kD <= kGramBatch, "one batch");
+    if (t < kGramBatch) {
+      float u = 0.0f;
+      if (t < kD)
+        u = isq ? a.q[(size_t)bh * kD + t]
+                : kv_load<BF16>(static_cast<const char*>(a.k_new) + (size_t)bkv * ROWB, t);
+      s.u[t] = u;
     }
+    // every load is issued before the first is waited for (addresses clamped, the values
+    // past the end zeroed)
+    constexpr int kBPieces = (kGramBatch * R + kGramThreads - 1) / kGramThreads;
+    float bv[kBPieces];
+#pragma unroll
+    for (int u = 0; u < kBPieces; ++u) {
+      const int idx = t + u * kGramThreads;
+      const int c = min(idx / kGramBatch, R - 1), ii = idx % kGramBatch;
+      bv[u] = Bm[(size_t)c * kD + min(ii, kD - 1)];
+      if (ii >= kD) bv[u] = 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < kBPieces; ++u) {
+      const int idx = t + u * kGramThreads;
+      if (idx < kGramBatch * R) s.a[idx % kGramBatch * LDA + idx / kGramBatch] = bv[u];
+    }
+    __syncthreads();
+    gram_accumulate<R>(s.a, s.u, acc, gpart, t);
   }
-  gram_store<R>(s, sacc, gpart, out, t);
+  gram_store<R>(s, acc, gpart, out, t);
 }
 
 struct SolveArgs {

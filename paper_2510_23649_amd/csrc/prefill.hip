@@ -36,35 +36,15 @@ namespace {
 
 using namespace alg64;
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+using dev::bf16x8;
+using dev::f32x16;
+using dev::mfma_bf16;
+using dev::mfma_row;
+using dev::pack_bf16;
+using dev::split3;
+using dev::u32x4;
 
-// D(32x32) = A(32x16) B(16x32) + C; lane i + 32 h supplies A[i][8h .. 8h+7] and B[8h .. 8h+7][i];
-// register v of lane l holds D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32]
-__device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ int mfma_row(int v, int lane) {
-  return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-}
-__device__ __forceinline__ uint32_t pack_bf16(float x0, float x1) {
-  const f32x2 x = {x0, x1};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
-}
-// x0, x1 as three bf16 pairs (packed in dwords) that add up to them, the first of them the multiples
-// of a grid (see prefill_reduce_kernel) that are nearest to them.  Without a grid the sum is exact.
-__device__ __forceinline__ void split3(float x0, float x1, uint32_t (&s)[3], float grid = 0.0f) {
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    s[i] = i == 0 ? pack_bf16((x0 + grid) - grid, (x1 + grid) - grid) : pack_bf16(x0, x1);
-    x0 -= __uint_as_float(s[i] << 16);
-    x1 -= __uint_as_float(s[i] & 0xffff0000u);
-  }
-}
-// the same for bf16 numbers, which two terms give exactly
+// split3 for bf16 numbers, which two terms give exactly
 __device__ __forceinline__ void split2(float x0, float x1, float grid, uint32_t& hi, uint32_t& lo) {
   const float g0 = (x0 + grid) - grid, g1 = (x1 + grid) - grid;
   hi = pack_bf16(g0, g1);

@@ -153,6 +153,18 @@ def test_factor_update_no_lite_window(r):
     run_update_case(upd_cfg(B=1, Hq=2, Hkv=1, r=r, w=0))
 
 
+@pytest.mark.parametrize("k,w,kvd", [(1, 0, "bf16"), (16, 1, "bf16"), (143, 1, "bf16"), (144, 1, "f32"),
+                                     (600, 37, "bf16"), (1100, 52, "f32")])
+def test_factor_update_row_counts_at_rank_64(k, w, kvd):
+    """Edges of the steps of 16 rows and chunks of 144, from one row on.  Sums of products of bf16 terms,
+    complete down to 2^-24 of a product: at most 54 fp32 additions a chunk, each half a unit in the last place of
+    a sum that grows with them (54 * 2^-25 / 2 = 8e-7), times the systems' condition of about 10 (with more rows
+    than the rank; REL_TOL alone otherwise)."""
+    say(f"factor update r=64, k={k} w={w}, {kvd} rows")
+    worst = run_update_case(upd_cfg(B=1, Hq=6, Hkv=2, r=64, k=k, w=w, C=2 * k, n_heavy=min(32, k), kv_dtype=kvd))
+    assert k + w < 2 * 64 or worst <= 8e-6
+
+
 def test_factor_update_at_the_headline_shape():
     say("factor update at l = 131072, k = 2048, w = 64, r = 32, 32 / 8 heads")
     run_update_case(get_config("c3").with_(layers=1))
