@@ -15,8 +15,8 @@
 //     of these two), a workgroup per matrix.
 //  3. factor_rounds_kernel: the n_iter rounds and the line-search gradient steps on B_Q and B_K in
 //     place, workgroups per (batch, KV head).
-// Times in us at k = 2048, w = 64, 32 + 8 heads, r = 32: 9 + 10 + 9.7; at 8 x (28 + 4) heads, k = 1024, r = 64:
-// 38.4 + 22.9 + 26.4.  (Factorising in fp32 with a row per lane, P once and the k_hat system in every
+// Times in us at k = 2048, w = 64, 32 + 8 heads, r = 32: 8.6 + 9.8 + 9.6; at 8 x (28 + 4) heads, k = 1024, r = 64:
+// 32 + 22 + 24.  (Factorising in fp32 with a row per lane, P once and the k_hat system in every
 // round, all in one wavefront per head, launches 2 and 3 took 30 and 114 us.)  What is left is
 // latency: the loads at the start of each launch (2 us; 5 to 9 us at the second shape, where every
 // compute unit reads 130 and 265 KB), the eliminations (3.5 and 9 us) and the rounds (2 and 5 us each).
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
   const size_t head = isq ? (size_t)(bkv / a.Hkv) * a.Hq + (size_t)(bkv % a.Hkv) * G + job : bkv;
   const size_t m = isq ? head : a.BHq + head;
   const float* __restrict__ Bm = (isq ? a.B_Q : a.B_K) + head * R * kD;
-  const float* __restrict__ part = a.gram_om + head * a.nchunk * (size_t)(kEntries + R);
+  const float* __restrict__ part = a.gram_om + (isq ? head : 0) * a.nchunk * (size_t)(kEntries + R);
   const int tr = w * Z::TPW / Z::RT, tc0 = w * Z::TPW % Z::RT;
   const bool own = tr < Z::RT;          // (r <= 32: the other wavefronts own no tile)
   const int k = lane >> 4, c16 = lane & 15;
@@ -113,74 +113,91 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
 #pragma unroll
   for (int j = 0; j < NB; ++j)
     bv[j] = reinterpret_cast<const float4*>(Bm)[min(t + kInvThreads * j, NB4 - 1)];
-  double xv = 0.0;
-  if (t < kD)
-    xv = isq ? a.q[head * kD + t]
-             : kv_load<BF16>(static_cast<const char*>(a.k_new) + head * ROWB, t);
-  f64x4 d[Z::TPW];
+  // (q and k both, of which one is wanted: a load inside a branch is waited for before the next is issued)
+  const float q_t = a.q[(isq ? head : 0) * kD + (t & (kD - 1))];
+  const float k_t = kv_load<BF16>(static_cast<const char*>(a.k_new) + (size_t)bkv * ROWB, t & (kD - 1));
+  // The chunk partials are on their way while B B^T is made: of the matrix, of the first SB chunks; of c,
+  // row t / 8 and every eighth chunk, of the first 16.  (A KV head reads a query head's and drops them.)
+  // Issued earlier, beside the loads of B, they make those wait: at r = 64 all compute units together read
+  // 30 MB.  The whole call so, with the load of q or k in no branch, 77.5 -> 76.5 us there, 26.3 -> 25.9 at
+  // 32 + 8 heads, r = 32, k = 2048.
+  constexpr int SB = 16 / Z::TPW;
+  float x[SB][Z::TPW][4];
+  auto fetch = [&](int s0) {
 #pragma unroll
-  for (int u = 0; u < Z::TPW; ++u) d[u] = f64x4{0.0, 0.0, 0.0, 0.0};
-  if (isq && own) {
-    constexpr int SB = 16 / Z::TPW;  // chunks whose loads are in flight together
-    for (int s0 = 0; s0 < a.nchunk; s0 += SB) {
-      float x[SB][Z::TPW][4];
+    for (int sc = 0; sc < SB; ++sc)
 #pragma unroll
-      for (int sc = 0; sc < SB; ++sc)
+      for (int u = 0; u < Z::TPW; ++u)
 #pragma unroll
-        for (int u = 0; u < Z::TPW; ++u)
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            x[sc][u][v] = part[(size_t)min(s0 + sc, a.nchunk - 1) * (kEntries + R) +
-                               (16 * tr + 4 * v + k) * R + 16 * (tc0 + u) + c16];
-#pragma unroll
-      for (int sc = 0; sc < SB; ++sc)
-#pragma unroll
-        for (int u = 0; u < Z::TPW; ++u)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) d[u][v] += s0 + sc < a.nchunk ? (double)x[sc][u][v] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < Z::TPW; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) d[u][v] *= (double)a.lam2;
-  }
-  if (t < kD) xs[t] = xv;
+        for (int v = 0; v < 4; ++v)
+          x[sc][u][v] = part[(size_t)min(s0 + sc, a.nchunk - 1) * (kEntries + R) +
+                             (16 * min(tr, Z::RT - 1) + 4 * v + k) * R + 16 * (tc0 + u) + c16];
+  };
+  const int row = t >> 3, part8 = t & 7;
+  auto g_at = [&](int s) {
+    return part[(size_t)min(s, a.nchunk - 1) * (kEntries + R) + kEntries + min(row, R - 1)];
+  };
+  if (t < kD) xs[t] = isq ? q_t : k_t;
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
     const int e = 4 * (t + kInvThreads * j);
     if (e < R * kD) {
-      double* x = X + e / kD * kLdb + e % kD;
-      x[0] = bv[j].x; x[1] = bv[j].y; x[2] = bv[j].z; x[3] = bv[j].w;
+      double* b = X + e / kD * kLdb + e % kD;
+      b[0] = bv[j].x; b[1] = bv[j].y; b[2] = bv[j].z; b[3] = bv[j].w;
     }
   }
   lds_barrier();
+  const float g0 = g_at(part8), g1 = g_at(part8 + 8);
+  fetch(0);
+  __builtin_amdgcn_sched_barrier(0);
+  // B B^T
+  f64x4 d[Z::TPW];
+#pragma unroll
+  for (int u = 0; u < Z::TPW; ++u) {
+    d[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+    const double* xa = X + (16 * tr + c16) * kLdb + k;
+    const double* xb = X + (16 * (tc0 + u) + c16) * kLdb + k;
+    if (own) {
+#pragma unroll 8
+      for (int s = 0; s < kD; s += 4) d[u] = mfma_f64(xa[s], xb[s], d[u]);
+    }
+  }
   // c (or nb): 8 lanes a row
   double* const out = a.inv + m * (kEntries + R);
+  const double lam2 = isq ? (double)a.lam2 : 0.0;
   {
-    const int row = t >> 3, part8 = t & 7;
     double c = 0.0;
     if (row < R) {
-      const double* x = X + row * kLdb + part8;
+      const double* b = X + row * kLdb + part8;
 #pragma unroll
-      for (int j = 0; j < kD; j += 8) c = __builtin_fma(x[j], xs[j + part8], c);
-      if (isq)
-        for (int s = part8; s < a.nchunk; s += 8)
-          c = __builtin_fma((double)a.lam2, (double)part[(size_t)s * (kEntries + R) + kEntries + row], c);
+      for (int j = 0; j < kD; j += 8) c = __builtin_fma(b[j], xs[j + part8], c);
+    }
+    if (isq) {
+      if (part8 < a.nchunk) c = __builtin_fma(lam2, (double)g0, c);
+      if (part8 + 8 < a.nchunk) c = __builtin_fma(lam2, (double)g1, c);
+      for (int s = part8 + 16; s < a.nchunk; s += 8) c = __builtin_fma(lam2, (double)g_at(s), c);
     }
     c += dpp_f64<0xB1>(c);   // quad_perm [1,0,3,2]
     c += dpp_f64<0x4E>(c);   // quad_perm [2,3,0,1]
     c += dpp_f64<0x141>(c);  // row_half_mirror
     if (row < R && part8 == 0) out[kEntries + row] = c;
   }
-  // += B B^T
-  if (own) {
+  // += lambda_d2 A_Om^T A_Om, in chunk order
+  if (isq && own) {
+    f64x4 sum[Z::TPW] = {};
+    for (int s0 = 0; s0 < a.nchunk; s0 += SB) {
+      if (s0 > 0) fetch(s0);
 #pragma unroll
-    for (int u = 0; u < Z::TPW; ++u) {
-      const double* xa = X + (16 * tr + c16) * kLdb + k;
-      const double* xb = X + (16 * (tc0 + u) + c16) * kLdb + k;
-#pragma unroll 8
-      for (int s = 0; s < kD; s += 4) d[u] = mfma_f64(xa[s], xb[s], d[u]);
+      for (int sc = 0; sc < SB; ++sc)
+#pragma unroll
+        for (int u = 0; u < Z::TPW; ++u)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sum[u][v] += s0 + sc < a.nchunk ? (double)x[sc][u][v] : 0.0;
     }
+#pragma unroll
+    for (int u = 0; u < Z::TPW; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) d[u][v] = __builtin_fma(lam2, sum[u][v], d[u][v]);
   }
   lds_barrier();  // X has been read: the exchanged tiles take its place
   sweep_tiles<Z::RT, Z::RT, Z::TPW, 1, true>(d, tr, tc0, X, lane);
@@ -227,8 +244,15 @@ struct RoundShape {
   static constexpr int LDV = R + 2;  // LDS row stride of the exchanged vectors: 8 rows, 8 bank groups
   // q_hat (padded to a tile); q_hat N^-1, u (padded); a vector per wavefront; parts of z
   static constexpr int kVectors = 16 + 16 + kWaves + kWaves;
-  static constexpr size_t lds_bytes =
-      ((size_t)R * R + kVectors * LDV + 128 + kAcross * kD + 3 * kMaxG + 1) * sizeof(double);
+  // The first matrix of the gradient steps waits in LDS at r = 64, where P^-1 takes half of the registers:
+  // kept in others, each of its loads was waited for and spilled (with kAside below the kernel takes 23.6 us
+  // instead of 25.7 at 8 x (28 + 4) heads, the call 73.4 instead of 76.5).
+  static constexpr bool kStash = R > 32;
+  // and so do kAside of the 32 elements of P^-1 that a lane holds
+  static constexpr int kAside = R > 32 ? 6 : 0;
+  static constexpr size_t doubles =
+      (size_t)R * R + kVectors * LDV + 128 + kAcross * kD + 3 * kMaxG + 1 + kAside * kThreads;
+  static constexpr size_t lds_bytes = doubles * sizeof(double) + (kStash ? (size_t)R * kD * sizeof(float) : 0);
 };
 
 template <int R, bool BF16>
@@ -248,6 +272,8 @@ __global__ __launch_bounds__(RoundShape<R>::kThreads) void factor_rounds_kernel(
   double* const s_s = part_s + Z::kAcross * kD; // [8]  lambda_d1 s
   double* const qk_s = s_s + kMaxG;             // [8]  lambda_d1 q.k
   double* const inv_norm_s = qk_s + kMaxG;      // [9]  1 / |x_hat|^2 of the group's q_hat, of k_hat
+  double* const aside = inv_norm_s + kMaxG + 1 + threadIdx.x;                         // [kAside][threads]
+  float* const stash = reinterpret_cast<float*>(rnd_lds + Z::doubles) + threadIdx.x;  // [kRows][threads]
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int g = w % kMaxG, h = w / kMaxG;  // head, and which rows of P^-1
   const int G = a.Hq / a.Hkv;
@@ -270,15 +296,25 @@ __global__ __launch_bounds__(RoundShape<R>::kThreads) void factor_rounds_kernel(
            sub * Z::kRows * kD + col;
   };
 
-  for (int e = t; e < kEntries / 2; e += kRoundThreads)
-    reinterpret_cast<double2*>(n_s)[e] = reinterpret_cast<const double2*>(inv_k)[e];
+  float bv[Z::kRows];
+#pragma unroll
+  for (int i = 0; i < Z::kRows; ++i) bv[i] = matrix(part)[i * kD];
+  constexpr int kN = kEntries / 2 / kRoundThreads;
+  static_assert(kN * kRoundThreads * 2 == kEntries, "whole pieces");
+  double2 nv[kN];
+#pragma unroll
+  for (int j = 0; j < kN; ++j) nv[j] = reinterpret_cast<const double2*>(inv_k)[t + j * kRoundThreads];
   double pinv[32];
 #pragma unroll
   for (int c = 0; c < 32; ++c) pinv[c] = inv_q[(32 * h + c) * R + li];
   const double cvec = inv_q[kEntries + li], nb = inv_k[kEntries + li];
-  float bv[Z::kRows];
 #pragma unroll
-  for (int i = 0; i < Z::kRows; ++i) bv[i] = matrix(part)[i * kD];
+  for (int i = 0; i < Z::kRows; ++i)
+    if (Z::kStash) stash[i * kRoundThreads] = bv[i];
+#pragma unroll
+  for (int j = 0; j < kN; ++j) reinterpret_cast<double2*>(n_s)[t + j * kRoundThreads] = nv[j];
+#pragma unroll
+  for (int c = 0; c < Z::kAside; ++c) aside[c * kRoundThreads] = pinv[c];
   for (int e = t; e < 32 * LDV; e += kRoundThreads) qh_s[e] = 0.0;  // and wv_s
   const double qk = wave_sum_f64((double)qp[lane] * kv_load<BF16>(kp, lane) +
                                  (double)qp[lane + 64] * kv_load<BF16>(kp, lane + 64));
@@ -297,8 +333,8 @@ __global__ __launch_bounds__(RoundShape<R>::kThreads) void factor_rounds_kernel(
 #pragma unroll
     for (int c = 0; c < 32; c += 2) {
       const double2 v = *reinterpret_cast<const double2*>(vec + 32 * h + c);
-      s0 = __builtin_fma(pinv[c], v.x, s0);
-      s1 = __builtin_fma(pinv[c + 1], v.y, s1);
+      s0 = __builtin_fma(c < Z::kAside ? aside[c * kRoundThreads] : pinv[c], v.x, s0);
+      s1 = __builtin_fma(c < Z::kAside ? aside[(c + 1) * kRoundThreads] : pinv[c + 1], v.y, s1);
     }
     s0 += s1;
     if (Z::kPerHead > 1) {
@@ -388,9 +424,9 @@ __global__ __launch_bounds__(RoundShape<R>::kThreads) void factor_rounds_kernel(
   for (int job = part; job <= G; job += a.parts) {
     const bool isq = job < G;
     float* Bm = matrix(job);
-    if (job != part) {
+    if (job != part || Z::kStash) {
 #pragma unroll
-      for (int i = 0; i < Z::kRows; ++i) bv[i] = Bm[i * kD];
+      for (int i = 0; i < Z::kRows; ++i) bv[i] = job != part ? Bm[i * kD] : stash[i * kRoundThreads];
     }
     const double* xh = (isq ? qh_s + job * LDV : vec_s) + sub * Z::kRows;
     double s0 = 0.0, s1 = 0.0;
