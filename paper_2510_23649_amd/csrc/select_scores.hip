@@ -15,10 +15,11 @@
 //     (cut_of_entries), one prefix count for their places.
 // A head with fewer than k candidates or more than the list holds (a sample that misleads, massive ties)
 // goes through exact_select_from_scores, which reads the scores as often as it needs.
-// At 32 heads, l = 50001, k = 1000 the kernel takes 14.0 us, 20.0 with two passes over the scores in batches of
+// At 32 heads, l = 50001, k = 1000 the kernel takes 10.9 us, 20.0 with two passes over the scores in batches of
 // eight loads and a three-level radix select over fixed key bits (select_resolve.hip, which still takes
 // longer contexts: more than 64 scores a thread would not stay in registers); the chain of stand-alone calls
-// 81.5 instead of 87.5.
+// 77.7 instead of 87.2.  Cycles at 2.3 GHz: loads 4500, sample 4600, scan 1200, bitmap 5500, list and read-back
+// 2300, cut 5500, places 1300.
 #include "lrqk_device.h"
 #include "lrqk_internal.h"
 #include "select_common.h"
@@ -59,12 +60,18 @@ __global__ __launch_bounds__(kT) void select_scores_kernel(const float* __restri
   // (One in eight: of every other thread's four scores one, another one in the next 4096 positions.
   // 16384 and k >= 512 leave the estimate five standard deviations of margin.)
   const bool sampled = n >= 16384 && k >= 512;
+  auto count = [&](float v) { atomicAdd(&hist[order_key(v) >> kBinShift], 1u); };
+  if (sampled) {
 #pragma unroll
-  for (int j = 0; j < NV; ++j)
+    for (int j = 0; j < NV; ++j)
+      if (((t ^ j) & 1) == 0 && ((j + 1) * kIter <= n || j * kIter + 4 * t + (j & 3) < n)) count(raw[j].v[j & 3]);
+  } else {
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-      if (j * kIter + 4 * t + c < n && (!sampled || (c == (j & 3) && ((t ^ j) & 1) == 0)))
-        atomicAdd(&hist[order_key(raw[j].v[c]) >> kBinShift], 1u);
+    for (int j = 0; j < NV; ++j)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if ((j + 1) * kIter <= n || j * kIter + 4 * t + c < n) count(raw[j].v[c]);
+  }
   lds_barrier();
   {
     const uint32_t ks = (uint32_t)(k + 7) / 8;
@@ -85,15 +92,26 @@ __global__ __launch_bounds__(kT) void select_scores_kernel(const float* __restri
   const uint32_t b_lo = res[0];
   // ---- 2. the candidates, in position order -----------------------------------------------------------
   reinterpret_cast<uint4*>(hist)[t] = make_uint4(0u, 0u, 0u, 0u);
+  // (what takes time here are the instructions for every score; where the bin's lower edge is a positive number
+  // its bits compare with a score's as signed integers as their keys do, and no key is needed: this phase
+  // 10300 -> 5500 cycles at n = 49941)
+  auto mark = [&](auto at_or_above) {
 #pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    const int e = j * kIter + 4 * t;
-    uint32_t nib = 0;
+    for (int j = 0; j < NV; ++j) {
+      const int e = j * kIter + 4 * t;
+      uint32_t nib = 0;
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-      nib |= e + c < n && (order_key(raw[j].v[c]) >> kBinShift) >= b_lo ? 1u << c : 0u;
-    const uint32_t word = or_reduce8(nib << (4 * (lane & 7)));
-    if ((lane & 7) == 0) bitmap[e >> 5] = word;
+      for (int c = 0; c < 4; ++c) nib |= at_or_above(raw[j].v[c]) ? 1u << c : 0u;
+      if ((j + 1) * kIter > n) nib &= (1u << min(max(n - e, 0), 4)) - 1u;  // (scores that exist)
+      const uint32_t word = or_reduce8(nib << (4 * (lane & 7)));
+      if ((lane & 7) == 0) bitmap[e >> 5] = word;
+    }
+  };
+  if (__builtin_expect(b_lo > 0x800u, 1)) {
+    const int edge = (int)((b_lo << kBinShift) & 0x7fffffffu);
+    mark([&](float v) { return __float_as_int(v) >= edge; });
+  } else {
+    mark([&](float v) { return (order_key(v) >> kBinShift) >= b_lo; });
   }
   lds_barrier();
   constexpr int kWords = NV * kIter / 32, kWpt = (kWords + kT - 1) / kT;
