@@ -9,7 +9,7 @@
 //     touched once per step, so the loads are non-temporal;
 //   * the tile goes through LDS (row stride r+4 floats, so that 16-byte row
 //     reads by neighbouring lanes fall on different banks) to turn "lane =
-//     16-byte chunk" into "lane = row";
+//     16-byte chunk" into "lane = row", every wavefront its own 64 rows;
 //   * each lane then owns one row and runs, for each of the G query heads that
 //     share the KV head, one fp32 fused-multiply-add chain over j = 0..r-1.
 //     A_K is read once for the whole group; q_hat is wave-uniform;
@@ -54,10 +54,10 @@ __global__ __launch_bounds__(kTileRows) void proxy_scores_kernel(
     const float* __restrict__ thr_norm, uint32_t* __restrict__ thr_out,
     unsigned long long* __restrict__ bitmap, float* __restrict__ cand_scores, int words64) {
   // The tile goes through LDS in column phases of CH floats; the fma chain simply continues
-  // from one phase to the next, in the same order.  Every supported rank takes one phase: at
-  // r = 64 two phases of 32 columns (half the LDS, twice the resident workgroups, one more pair
-  // of barriers) measured 2.5 % slower, four phases of 16 columns 50 % slower.
-  constexpr int CH = R;                // columns per phase
+  // from one phase to the next, in the same order.  One phase but at r = 64 with eight heads, whose
+  // products take so long that twice the resident workgroups (half the LDS) pay: 21.2 -> 19.4 us at 2 KV heads,
+  // l = 100001; with four heads 43.5 -> 47.2 at 8 KV heads, l = 131072, with seven no difference.
+  constexpr int CH = R > 32 && G > 7 ? 32 : R;  // columns per phase
   constexpr int NPH = R / CH;          // phases
   constexpr int V4 = CH / 4;           // 16-byte chunks per row and phase
   constexpr int ROW4 = V4 + 1;         // padded LDS row stride in 16-byte units
@@ -81,15 +81,19 @@ __global__ __launch_bounds__(kTileRows) void proxy_scores_kernel(
   const int rows_valid = min(kTileRows, l - row0);
 
   const size_t bh0 = (size_t)b * Hq + (size_t)kv * G;  // first head of the group
-  // all phases' loads are issued up front: chunk idx of phase p is row idx / V4,
-  // 16-byte column p * V4 + idx % V4 (8 lanes read 128 contiguous bytes of a row)
+  // all phases' loads are issued up front: chunk idx of phase p is row idx / V4 of the wavefront's 64,
+  // 16-byte column p * V4 + idx % V4 (8 lanes read 128 contiguous bytes of a row).  A wavefront loads the
+  // rows that it will need, so that nothing waits for another one's (with the tile's rows dealt out over
+  // the workgroup and a barrier behind the stores: 7.55 -> 7.40 us at 8 KV heads, l = 32768, r = 32,
+  // 44.7 -> 43.6 at l = 131072, r = 64, 24.4 -> 23.2 for all scores at 8 x 7 heads, l = 50021, r = 64).
+  const int lane = t & 63, wrow0 = t & ~63;
   float4 pre[NPH][V4];
 #pragma unroll
   for (int p = 0; p < NPH; ++p)
 #pragma unroll
     for (int i = 0; i < V4; ++i) {
-      const int idx = i * kTileRows + t;
-      const int rr = idx / V4, cc = idx % V4;
+      const int idx = i * 64 + lane;
+      const int rr = wrow0 + idx / V4, cc = idx % V4;
       pre[p][i] = rr < rows_valid ? load_streaming(src + (size_t)rr * (R / 4) + p * V4 + cc)
                                   : make_float4(0.f, 0.f, 0.f, 0.f);
     }
@@ -101,9 +105,9 @@ __global__ __launch_bounds__(kTileRows) void proxy_scores_kernel(
   // are summed with no memory instruction of their own while the tile's loads are in flight --
   // the heads dealt out over the four wavefronts, which keeps this off the workgroup's
   // critical path -- and the keys are handed to everyone through LDS (published by the
-  // barrier that follows the tile store).
+  // barrier that follows).
   if (FILTER) {
-    const int wv = t >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       if ((g & 3) != wv) continue;  // wave-uniform
@@ -121,18 +125,19 @@ __global__ __launch_bounds__(kTileRows) void proxy_scores_kernel(
     }
   }
 
+  if (FILTER) dev::lds_barrier();  // the threshold keys
   float acc[G];
 #pragma unroll
   for (int g = 0; g < G; ++g) acc[g] = 0.0f;
 #pragma unroll
   for (int p = 0; p < NPH; ++p) {
-    if (p > 0) __syncthreads();  // the previous phase has been consumed
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int i = 0; i < V4; ++i) {
-      const int idx = i * kTileRows + t;
-      tile[(idx / V4) * ROW4 + (idx % V4)] = pre[p][i];
+      const int idx = i * 64 + lane;
+      tile[(wrow0 + idx / V4) * ROW4 + (idx % V4)] = pre[p][i];
     }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int c = 0; c < V4; ++c) {
       const float4 a = tile[t * ROW4 + c];
@@ -154,7 +159,6 @@ __global__ __launch_bounds__(kTileRows) void proxy_scores_kernel(
     }
   } else {
     const int wrow = row0 + (t & ~63);  // first row of this wavefront
-    const int lane = t & 63;
     // The 64 rows of the tile that this wavefront owns are read by no other wavefront, so
     // their LDS space can stage the packed candidate scores without a workgroup barrier.
     float* stage = reinterpret_cast<float*>(&tile[(t & ~63) * ROW4]);
@@ -171,9 +175,12 @@ __global__ __launch_bounds__(kTileRows) void proxy_scores_kernel(
     const int my_head = lane >> 3;       // head of this lane in the two stores below
     unsigned long long mask_of_my_head = 0ull, mask_of_lane_head = 0ull;
     bool more = false;  // uniform
+    uint32_t thr_keys[G];  // (all at once: a read behind another head's staged scores would wait for them)
+#pragma unroll
+    for (int g = 0; g < G; ++g) thr_keys[g] = *thr_slot(g);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const uint32_t thr_g = *thr_slot(g);
+      const uint32_t thr_g = thr_keys[g];
       if (blockIdx.x == 0 && t == 0) thr_out[bh0 + g] = thr_g;
       const bool in = row < n && dev::order_key(acc[g]) >= thr_g;
       const unsigned long long mask = __ballot(in);
