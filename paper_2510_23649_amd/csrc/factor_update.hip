@@ -21,7 +21,8 @@
 // latency: the loads at the start of each launch (2 us; 5 to 9 us at the second shape, where every
 // compute unit reads 130 and 265 KB), the eliminations (3.5 and 9 us) and the rounds (2 and 5 us each).
 //
-// Sums over rows are fp32 (App. B.1 runs these updates in fp32), the rest fp64.
+// Sums over rows are fp32 (App. B.1 runs these updates in fp32; at r = 64 made of products of the bf16 terms
+// that add up to the fp32 numbers), the rest fp64.
 #include <algorithm>
 
 #include "lrqk_alg64.h"

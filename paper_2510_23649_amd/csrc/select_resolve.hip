@@ -11,7 +11,7 @@
 //      In the fused step it comes from the proxy-score pass (one 64-bit ballot per 64
 //      positions, with the candidates' scores packed 8 per 64-position group beside it)
 //      and is copied into LDS.  Working from a materialised score array (the stand-alone
-//      entry point) the kernel builds it itself: a histogram of the top 12 key bits over a
+//      entry point beyond 65536 positions; select_scores.hip up to there) the kernel builds it itself: a histogram of the top 12 key bits over a
 //      1-in-8 sample of the positions gives a bin at or below the bin of the k-th largest
 //      score, with a safety margin, and one pass over the scores marks every position at
 //      or above that bin (4 positions per lane, 8 lanes OR-ed into one word: no atomics);

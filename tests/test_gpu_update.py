@@ -1,7 +1,7 @@
 """GPU parity of the decode-time factor update (lrqk_factor_update) against the CPU oracle
 (oracle/lrqk_update_oracle.py), through the C ABI.
 
-The Gram sums over the k + w rows of Omega are fp32; the r x r systems are fp32 Cholesky solves at
+The Gram sums over the k + w rows of Omega are fp32 (r = 64: of products of three bf16 terms a number); the r x r systems are fp32 Cholesky solves at
 r <= 16 and fp64 inverses (other kernels, hence most tests at both) from r = 32 on; the oracle is
 float64.  Tolerance: the forward error of a backward-stable fp32
 solve is about r * 2^-24 * cond(M) relative to the solution's norm (that of fp32 sums alone is
