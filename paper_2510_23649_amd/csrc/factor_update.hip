@@ -250,7 +250,7 @@ struct RoundShape {
   // instead of 25.7 at 8 x (28 + 4) heads, the call 73.4 instead of 76.5).
   static constexpr bool kStash = R > 32;
   // and so do kAside of the 32 elements of P^-1 that a lane holds
-  static constexpr int kAside = R > 32 ? 6 : 0;
+  static constexpr int kAside = R > 32 ? 4 : 0;
   static constexpr size_t doubles =
       (size_t)R * R + kVectors * LDV + 128 + kAcross * kD + 3 * kMaxG + 1 + kAside * kThreads;
   static constexpr size_t lds_bytes = doubles * sizeof(double) + (kStash ? (size_t)R * kD * sizeof(float) : 0);
@@ -328,8 +328,10 @@ __global__ __launch_bounds__(RoundShape<R>::kThreads) void factor_rounds_kernel(
     if (row) vec[lane] = x;
     __builtin_amdgcn_wave_barrier();
   };
-  auto times_pinv = [&](double x) {  // (a barrier at r = 64)
-    put(x);
+  auto times_pinv = [&](double x, int ln) {  // (a barrier at r = 64); ln: the lane
+    __builtin_amdgcn_wave_barrier();
+    if (row) vec[ln] = x;
+    __builtin_amdgcn_wave_barrier();
     double s0 = 0.0, s1 = 0.0;
 #pragma unroll
     for (int c = 0; c < 32; c += 2) {
@@ -339,13 +341,13 @@ __global__ __launch_bounds__(RoundShape<R>::kThreads) void factor_rounds_kernel(
     }
     s0 += s1;
     if (Z::kPerHead > 1) {
-      if (row) z_s[w * LDV + lane] = s0;
+      if (row) z_s[w * LDV + ln] = s0;
       lds_barrier();
-      s0 = z_s[g * LDV + li] + z_s[(g + kMaxG) * LDV + li];
+      s0 = z_s[g * LDV + ln] + z_s[(g + kMaxG) * LDV + ln];
     }
     return row ? s0 : 0.0;
   };
-  const double y0 = times_pinv(cvec);
+  const double y0 = times_pinv(cvec, lane);
   __syncthreads();  // n_s, qk_s; qh_s and wv_s are zero
   // k0 = nb N^-1, also the initial guess (lambda_d1 = 0): every wavefront its share of the sum
   {
@@ -363,15 +365,20 @@ __global__ __launch_bounds__(RoundShape<R>::kThreads) void factor_rounds_kernel(
   for (int ww = 0; ww < Z::kWaves; ++ww) k0 += vec_s[ww * LDV + li];
   if (!row) k0 = 0.0;
   lds_barrier();
-  const int c16 = lane & 15, k4 = lane >> 4;
   double k_hat = k0, q_hat = 0.0;
 #pragma unroll 1
   for (int it = 0; it < a.n_iter; ++it) {
-    const double z = times_pinv(k_hat);
+    // r = 64: addresses are made anew in every round; kept across them they were spilled, as P^-1 was for
+    // their sake (24 -> 20.5 us for the kernel at 8 x (28 + 4) heads, 73.4 -> 69.8 for the call).  At r = 32
+    // there are registers for them (25.8 us for the call at 32 + 8 heads, 26.0 without them).
+    int ln = lane;
+    if (R > 32) asm volatile("" : "+v"(ln));
+    const int c16 = ln & 15, k4 = ln >> 4, li = row ? ln : 0;
+    const double z = times_pinv(k_hat, ln);
     const double v = __builtin_fma(lam1 * qk, z, y0);
     const double kv_ = wave_sum_f64(k_hat * v), kz = wave_sum_f64(k_hat * z);
     q_hat = __builtin_fma(-z, lam1 * kv_ / __builtin_fma(lam1, kz, 1.0), v);
-    if (act && row && h == 0) qh_s[g * LDV + lane] = q_hat;
+    if (act && row && h == 0) qh_s[g * LDV + ln] = q_hat;
     lds_barrier();
     const double* qa = qh_s + c16 * LDV + k4;
     if (w < R / 16) {  // W, 16 columns a wavefront
@@ -387,7 +394,7 @@ __global__ __launch_bounds__(RoundShape<R>::kThreads) void factor_rounds_kernel(
 #pragma unroll
       for (int gg = 0; gg < kMaxG; ++gg) u = __builtin_fma(qk_s[gg], wv_s[gg * LDV + li], u);
       __builtin_amdgcn_wave_barrier();
-      if (row) wv_s[8 * LDV + lane] = u;
+      if (row) wv_s[8 * LDV + ln] = u;
       __builtin_amdgcn_wave_barrier();
       // element (a, b) is q_hat_a . w_b, and (a, 8) is q_hat_a . u
       const double* wb = wv_s + c16 * LDV + k4;
@@ -397,8 +404,8 @@ __global__ __launch_bounds__(RoundShape<R>::kThreads) void factor_rounds_kernel(
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (c16 != 8) d[e] = __builtin_fma(lam1, d[e], 4 * e + k4 == c16 ? 1.0 : 0.0);
-      pivot_step(d, 0, piv_s, lane);
-      if (G > 4) pivot_step(d, 1, piv_s, lane);
+      pivot_step(d, 0, piv_s, ln);
+      if (G > 4) pivot_step(d, 1, piv_s, ln);
       if (c16 == 8) {
         s_s[k4] = lam1 * d[0];
         s_s[4 + k4] = G > 4 ? lam1 * d[1] : 0.0;
