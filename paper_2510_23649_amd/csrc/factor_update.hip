@@ -16,10 +16,10 @@
 //  3. factor_rounds_kernel: the n_iter rounds and the line-search gradient steps on B_Q and B_K in
 //     place, workgroups per (batch, KV head).
 // Times in us at k = 2048, w = 64, 32 + 8 heads, r = 32: 8.6 + 9.8 + 9.6; at 8 x (28 + 4) heads, k = 1024, r = 64:
-// 32 + 22 + 24.  (Factorising in fp32 with a row per lane, P once and the k_hat system in every
+// 32 + 22 + 20.  (Factorising in fp32 with a row per lane, P once and the k_hat system in every
 // round, all in one wavefront per head, launches 2 and 3 took 30 and 114 us.)  What is left is
 // latency: the loads at the start of each launch (2 us; 5 to 9 us at the second shape, where every
-// compute unit reads 130 and 265 KB), the eliminations (3.5 and 9 us) and the rounds (2 and 5 us each).
+// compute unit reads 130 and 265 KB), the eliminations (3.5 and 9 us) and the rounds (2 and 4 us each).
 //
 // Sums over rows are fp32 (App. B.1 runs these updates in fp32; at r = 64 made of products of the bf16 terms
 // that add up to the fp32 numbers), the rest fp64.
@@ -246,7 +246,7 @@ struct RoundShape {
   // q_hat (padded to a tile); q_hat N^-1, u (padded); a vector per wavefront; parts of z
   static constexpr int kVectors = 16 + 16 + kWaves + kWaves;
   // The first matrix of the gradient steps waits in LDS at r = 64, where P^-1 takes half of the registers:
-  // kept in others, each of its loads was waited for and spilled (with kAside below the kernel takes 23.6 us
+  // kept in others, each of its loads was waited for and spilled (so, with kAside, the kernel took 23.6 us
   // instead of 25.7 at 8 x (28 + 4) heads, the call 73.4 instead of 76.5).
   static constexpr bool kStash = R > 32;
   // and so do kAside of the 32 elements of P^-1 that a lane holds
