@@ -299,6 +299,7 @@ __device__ __forceinline__ void gram_store(GramLds<R>& s, GramAcc<R>& acc, float
     float* const turned = s.a;
     const int c = lane & 31;
     if (wave == 1) {
+      __builtin_amdgcn_wave_barrier();  // other lanes of the wavefront have read what is overwritten
 #pragma unroll
       for (int v = 0; v < 16; ++v) turned[c * 32 + (dev::mfma_row(v, lane) ^ c)] = acc.s[1][v];
     }

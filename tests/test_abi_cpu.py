@@ -3,6 +3,7 @@ header declares, and rejects bad arguments before touching a device.  No GPU."""
 import ctypes as C
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -183,3 +184,50 @@ def test_prefill_workspace_grows_with_the_shape(lib, r):
     for l in (100, 5000, 131072):
         sizes = [need(B, l) for B in (1, 2, 3, 8, 32, 40)]
         assert sizes == sorted(sizes)
+
+
+def device_ir(tmp_path, body):
+    """LLVM IR of a device source of this test, compiled with the library's flags and headers."""
+    from paper_2510_23649_amd import build as B
+    src, out = tmp_path / "t.hip", tmp_path / "t.ll"
+    src.write_text(body)
+    cmd = [B.HIPCC, *B.FLAGS, "--offload-device-only", "-S", "-emit-llvm", str(src), "-o", str(out)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return out.read_text()
+
+
+def kernel_body(ir, name):
+    return re.search(r"^define [^\n]*@%s\(.*?^}" % name, ir, re.S | re.M).group(0)
+
+
+def test_wavefronts_own_exchanges_through_lds_are_ordered(tmp_path):
+    """Where the lanes of one wavefront exchange data through LDS with no workgroup barrier between, a wave barrier
+    keeps the accesses in program order (a wavefront's LDS operations execute in the order in which they are
+    issued): the compiler takes it to read and write memory.  The rank-64 sums of the factor update have one where
+    a block is overwritten that other lanes have read."""
+    ir = device_ir(tmp_path, """
+#include "update_gram.h"
+using namespace lrqk;
+extern "C" __global__ void exchange(float* o) {
+  __shared__ float a[64];
+  const int t = threadIdx.x;
+  a[t] = o[t];
+  __builtin_amdgcn_wave_barrier();
+  o[t] = a[t];
+}
+extern "C" __global__ __launch_bounds__(kGramThreads) void store(const GramAcc<64>* in, float* out) {
+  __shared__ GramLds<64> s;
+  GramAcc<64> acc = in[threadIdx.x];
+  gram_store<64>(s, acc, 0.0f, out, threadIdx.x);
+}
+""")
+    group = re.search(r"declare void @llvm\.amdgcn\.wave\.barrier\(\) (#\d+)", ir).group(1)
+    assert "memory(" not in re.search(r"^attributes %s = (.*)$" % group, ir, re.M).group(1)
+    load, store = r"load float, ptr addrspace\(3\)", r"store float [^\n]*, ptr addrspace\(3\)"
+    wave, workgroup = r"call void @llvm\.amdgcn\.wave\.barrier", r"call void @llvm\.amdgcn\.s\.barrier"
+    # the load after the barrier is not replaced by what the lane itself has stored
+    assert re.search(f"{store}.*{wave}.*{load}", kernel_body(ir, "exchange"), re.S)
+    stretches = re.split(workgroup, kernel_body(ir, "store"))  # between workgroup barriers
+    mixed = [x for x in stretches if re.search(load, x) and re.search(store, x)]
+    assert any(re.search(f"{load}.*{wave}.*{store}", x, re.S) for x in mixed)
