@@ -65,6 +65,10 @@ def _solve_right(m: np.ndarray, M: np.ndarray) -> np.ndarray:
     return np.linalg.solve(M.T, m)
 
 
+def _gram(A_om: np.ndarray) -> np.ndarray:
+    return A_om.T @ A_om                        # r x r
+
+
 def _line_search_step(x_hat: np.ndarray, Bm: np.ndarray, x: np.ndarray):
     """One gradient step on 1/2 |x_hat B - x|^2 with the optimal step length (App. A.2)."""
     resid = x_hat @ Bm - x                      # 1 x d
@@ -112,7 +116,7 @@ def factor_update(q, k_new, B_Q, B_K, A_K, K_store, omega, lam1: float, lam2: fl
                 K_om = _rows_as_f64(K_store[b, kv, pos, :])          # n_omega x d
                 per_head[h] = dict(BQ=BQ, qt=qt, qk=float(qt @ kt), qBQt=qt @ BQ.T,
                                    BQBQt=BQ @ BQ.T, qKtA=(qt @ K_om.T) @ A_om,
-                                   AtA=A_om.T @ A_om, q_hat=None)
+                                   AtA=_gram(A_om), q_hat=None)
             for _ in range(n_iter):
                 for h in heads:
                     t = per_head[h]

@@ -1,9 +1,9 @@
 """GPU parity of the decode-time factor update (lrqk_factor_update) against the CPU oracle
 (oracle/lrqk_update_oracle.py), through the C ABI.
 
-The Gram sums over the k + w rows of Omega are fp32 (r = 64: of products of three bf16 terms a number); the r x r systems are fp32 Cholesky solves at
-r <= 16 and fp64 inverses (other kernels, hence most tests at both) from r = 32 on; the oracle is
-float64.  Tolerance: the forward error of a backward-stable fp32
+The Gram sums over the k + w rows of Omega are fp32 (r = 64: of products of three bf16 terms a number);
+the r x r systems are fp32 Cholesky solves at r <= 16 and fp64 inverses (other kernels, hence most tests
+at both) from r = 32 on; the oracle is float64.  Tolerance: the forward error of a backward-stable fp32
 solve is about r * 2^-24 * cond(M) relative to the solution's norm (that of fp32 sums alone is
 smaller); the synthetic workloads
 have cond(M) of a few tens (A_Om^T A_Om dominates M, and its spectrum is that of k + w
@@ -51,7 +51,30 @@ def factors_for(cfg, data, seed, perturb=0.05):
     return B_Q.contiguous(), B_K.contiguous(), k_new.contiguous()
 
 
-def run_update_case(cfg, lam1=1.0, lam2=1.0, n_iter=2, warm_steps=2, seed=7, drop=0):
+# Rank 64, whose systems are solved in fp64: the results are rounded to fp32 (at most 2^-24 of the largest entry)
+# and the sums carry the rounding of their fp32 additions, up to 2^-24 of a sum each (18 matrix instructions and
+# three more additions a chunk; the chunks' sums are added in fp64), amplified by the systems' condition.  Signs
+# differ, so that sums come out a small part of 2^-24 off: a third of 2^-24 * cond(M) is 2 to 8 times what is
+# measured, and less than any product of terms that is left out costs (test_update_oracle_pins.py).
+RANK64_CASES = [(1, 0, "bf16"), (16, 1, "bf16"), (143, 1, "bf16"), (144, 1, "f32"), (600, 37, "bf16"),
+                (1100, 52, "f32")]     # k, w, rows
+
+
+def rank64_cfg(k, w, kvd):
+    return upd_cfg(B=1, Hq=6, Hkv=2, r=64, k=k, w=w, C=2 * k, n_heavy=min(32, k), kv_dtype=kvd)
+
+
+def rank64_limit(A_K, B_Q, omega):
+    """Allowed distance from the oracle, of an array's largest entry; lambda_d2 = 1."""
+    G = B_Q.shape[1] // A_K.shape[1]
+    cond = 0.0
+    for b, h in np.ndindex(B_Q.shape[:2]):
+        Bq, A = B_Q[b, h].astype(np.float64), A_K[b, h // G, omega[b, h]].astype(np.float64)
+        cond = max(cond, np.linalg.cond(Bq @ Bq.T + A.T @ A))
+    return 2.0 ** -24 * (1.0 + cond / 3.0)
+
+
+def run_update_case(cfg, lam1=1.0, lam2=1.0, n_iter=2, warm_steps=2, seed=7, drop=0, limit=None):
     data = make_layer(cfg)
     dl = DeviceLayer(cfg, data)
     plan = L.Plan(dl.shape)
@@ -91,18 +114,16 @@ def run_update_case(cfg, lam1=1.0, lam2=1.0, n_iter=2, warm_steps=2, seed=7, dro
     torch.cuda.synchronize()
     got = dict(q_hat=q_hat_d.cpu().numpy(), k_hat=k_hat_d.cpu().numpy(),
                B_Q=dBQ.cpu().numpy(), B_K=dBK.cpu().numpy())
-    worst = 0.0
+    allowed = limit(dl.np["A_K"], as_numpy(B_Q), omega) if limit else REL_TOL
     for name, arr in got.items():
         assert np.all(np.isfinite(arr)), name
         rel = np.abs(arr - ref[name]).max() / np.abs(ref[name]).max()
-        say(f"   {name}: max rel err {rel:.2e}")
-        worst = max(worst, rel)
-        assert rel <= REL_TOL, f"{name}: {rel}"
+        say(f"   {name}: max rel err {rel:.2e} ({allowed:.1e} allowed)")
+        assert rel <= allowed, f"{name}: {rel}"
     # the step must really have moved B (the comparison above is not vacuous)
     assert np.abs(got["B_Q"] - as_numpy(B_Q)).max() > 1e-3
     assert np.abs(got["B_K"] - as_numpy(B_K)).max() > 1e-3
     plan.close()
-    return worst
 
 
 @pytest.mark.parametrize("r", [8, 16, 32, 64])
@@ -153,16 +174,11 @@ def test_factor_update_no_lite_window(r):
     run_update_case(upd_cfg(B=1, Hq=2, Hkv=1, r=r, w=0))
 
 
-@pytest.mark.parametrize("k,w,kvd", [(1, 0, "bf16"), (16, 1, "bf16"), (143, 1, "bf16"), (144, 1, "f32"),
-                                     (600, 37, "bf16"), (1100, 52, "f32")])
+@pytest.mark.parametrize("k,w,kvd", RANK64_CASES)
 def test_factor_update_row_counts_at_rank_64(k, w, kvd):
-    """Edges of the steps of 16 rows and chunks of 144, from one row on.  Sums of products of bf16 terms,
-    complete down to 2^-24 of a product: at most 54 fp32 additions a chunk, each half a unit in the last place of
-    a sum that grows with them (54 * 2^-25 / 2 = 8e-7), times the systems' condition of about 10 (with more rows
-    than the rank; REL_TOL alone otherwise)."""
+    """Edges of the steps of 16 rows and chunks of 144, from one row on."""
     say(f"factor update r=64, k={k} w={w}, {kvd} rows")
-    worst = run_update_case(upd_cfg(B=1, Hq=6, Hkv=2, r=64, k=k, w=w, C=2 * k, n_heavy=min(32, k), kv_dtype=kvd))
-    assert k + w < 2 * 64 or worst <= 8e-6
+    run_update_case(rank64_cfg(k, w, kvd), limit=rank64_limit)
 
 
 def test_factor_update_at_the_headline_shape():

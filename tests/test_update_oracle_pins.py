@@ -10,7 +10,9 @@ import numpy as np
 import pytest
 from scipy import optimize
 
-from oracle import lrqk_update_oracle as upd
+import test_gpu_update as gpu
+from gen import QueryStream, as_numpy, make_layer
+from oracle import lrqk_oracle as orc, lrqk_update_oracle as upd
 from helpers import f32_to_bf16_bits, bf16_to_f64
 
 
@@ -316,3 +318,50 @@ def test_append_writes_row_l_only():
     assert np.array_equal(K[:, :, keep], K0[:, :, keep]) and np.array_equal(V[:, :, keep], V0[:, :, keep])
     assert np.array_equal(A_K[:, :, l], k_hat.astype(np.float32))
     assert np.array_equal(K[:, :, l], k_new) and np.array_equal(V[:, :, l], v_new)
+
+
+# ------------------------------------------------------------ the limit of the rank-64 GPU tests
+
+def bf16_terms(x):
+    """Three bf16 numbers (as float64) that add up to each fp32 number."""
+    x, out = x.astype(np.float32), []
+    for _ in range(3):
+        t = bf16_to_f64(f32_to_bf16_bits(x)).astype(np.float32)
+        out.append(t.astype(np.float64))
+        x = x - t
+    assert not x.any()
+    return out
+
+
+@pytest.mark.parametrize("k,w,kvd", gpu.RANK64_CASES)
+def test_limit_at_rank_64_rejects_a_missing_product_of_terms(k, w, kvd, monkeypatch):
+    """At r = 64 the sums over Omega are made of the six products of bf16 terms down to 2^-16 of the leading one.
+    On the data of the GPU tests: all six stay within a fifth of their limit, without any one of them (in the upper
+    half, which the elimination reads, and its mirror) the update is outside."""
+    cfg = gpu.rank64_cfg(k, w, kvd)
+    data = make_layer(cfg)
+    queries = QueryStream(data)
+    A_K = as_numpy(data.A_K)
+    queries.next()
+    _, q_hat = queries.next()                       # the step that leaves the selection
+    _, s32 = orc.proxy_scores(A_K, as_numpy(q_hat))
+    omega = upd.omega_positions(orc.select_topk(s32, cfg.k, cfg.w), cfg.l, cfg.w)
+    q, _ = queries.next()
+    B_Q, B_K, k_new = gpu.factors_for(cfg, data, 7)
+    args = (as_numpy(q), as_numpy(k_new), as_numpy(B_Q), as_numpy(B_K), A_K, as_numpy(data.K), omega, 1.0, 1.0)
+    ref = upd.factor_update(*args)
+
+    def distance(products):
+        def gram(A_om):
+            t = bf16_terms(A_om)
+            S = sum(t[i].T @ t[j] for i, j in products)
+            return np.triu(S) + np.triu(S, 1).T
+        monkeypatch.setattr(upd, "_gram", gram)
+        got = upd.factor_update(*args)
+        return max(np.abs(got[n] - ref[n]).max() / np.abs(ref[n]).max() for n in ("q_hat", "k_hat", "B_Q", "B_K"))
+
+    six = [(2, 0), (0, 2), (1, 1), (1, 0), (0, 1), (0, 0)]
+    limit = gpu.rank64_limit(A_K, as_numpy(B_Q), omega)
+    assert distance(six) <= limit / 5
+    for left_out in six:
+        assert distance([p for p in six if p != left_out]) > 1.5 * limit, left_out
