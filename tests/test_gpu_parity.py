@@ -39,7 +39,8 @@ def say(msg):
 @pytest.mark.parametrize("r,G,l,B,Hkv", [
     (32, 4, 4096, 1, 8), (32, 4, 5000, 2, 2), (16, 4, 1031, 1, 2), (64, 4, 2049, 1, 2),
     (32, 7, 3001, 2, 1), (32, 1, 777, 1, 3), (32, 2, 255, 1, 2), (32, 8, 512, 1, 1),
-    (16, 7, 300, 1, 1), (64, 1, 1000, 1, 1),
+    (16, 7, 300, 1, 1), (64, 1, 1000, 1, 1), (64, 7, 1023, 1, 2),
+    (64, 8, 2051, 2, 2),           # the tile in two halves of its columns
     (4, 4, 1000, 1, 2), (8, 3, 1500, 2, 2), (48, 5, 999, 1, 2), (128, 8, 700, 1, 1), (100, 6, 130, 1, 1),
 ])
 def test_proxy_scores_bit_exact(r, G, l, B, Hkv):
@@ -462,6 +463,9 @@ def test_group_fetch_alone_fills_the_same_caches_as_the_oracle():
     dict(B=1, Hq=2, Hkv=1, l=12000, r=32, k=1400, w=64, C=2048),    # about 10 candidates per group
     dict(B=1, Hq=2, Hkv=1, l=12000, r=16, k=1400, w=64, C=2048),    # ... their scores computed again, short rows
     dict(B=1, Hq=2, Hkv=1, l=6001, r=64, k=900, w=7, C=1000),       # ... and long ones
+    dict(B=2, Hq=16, Hkv=2, l=6001, r=64, k=100, w=7, C=150),       # G = 8 at rank 64: the tile in two halves
+    dict(B=1, Hq=16, Hkv=2, l=6001, r=64, k=700, w=7, C=900),       # ... with 16 packed scores per group
+    dict(B=1, Hq=7, Hkv=1, l=3333, r=64, k=100, w=5, C=150),        # G = 7 at rank 64
     dict(B=2, Hq=4, Hkv=4, l=70, r=16, k=20, w=3, C=25),            # a context of two 64-position groups
     dict(B=1, Hq=8, Hkv=2, l=64, r=32, k=64, w=0, C=64),            # one group, everything selected, no lite rows
 ])
