@@ -100,23 +100,62 @@ def test_select_topk_ties_zeros_and_massive_duplicates():
     assert np.array_equal(got[0, 1], np.arange(k))
 
 
-def test_select_topk_sampled_estimate_is_verified_not_trusted():
-    say("select_topk, long heads: inputs built to mislead the 1-in-8 sample, and heavy ties")
-    rng = np.random.default_rng(9)
-    l, w, k = 150000, 64, 2048
-    e = np.arange(l)
-    sampled = ((e // 4096) & 7) == (((e % 4096) // 256) & 7)     # positions the first pass looks at
-    s = np.empty((1, 8, l), np.float32)
+def sampled_positions(n, k):
+    """Which of the n scores of a head a one-launch selection counts to estimate the key of the k-th largest, and
+    the rank among those that the estimate is taken at."""
+    e = np.arange(n)
+    if n < 16384 or k < 512:
+        return np.ones(n, bool), k
+    if n <= 65536:   # select_scores.hip
+        sampled = (e % 4 == (e // 4096) % 4) & ((e % 4096 // 4 + e // 4096) % 2 == 0)
+    else:            # select_resolve.hip
+        sampled = (e % 32 < 4) & (e < n // 32 * 32)
+    ks = (k + 7) // 8
+    return sampled, ks + ks * 3 // 8 + 16
+
+
+def estimate_of(row, n, k):
+    """Where that estimate leads for a head: "list" (the candidates, positions in its bin of 2^20 keys or above, are
+    listed), "few" (fewer than k), "many" (more than the list holds)."""
+    u = row[:n].astype(np.float32).view(np.uint32).copy()
+    u[u == 0x80000000] = 0
+    bins = np.where(u >> 31, ~u, u | np.uint32(0x80000000)) >> 20
+    sampled, rank = sampled_positions(n, k)
+    at_or_above = np.cumsum(np.bincount(bins[sampled], minlength=4096)[::-1])[::-1]
+    enough = np.nonzero(at_or_above >= rank)[0]
+    m = int((bins >= (enough[-1] if len(enough) else 0)).sum())
+    cap = 8192 if n <= 65536 else min(8192, max(4096, 2 * k + 2048))
+    return "few" if m < k else "many" if m > cap else "list"
+
+
+def misleading_rows(l, w, k, rng):
+    """Scores [1,10,l] of heads built to mislead the estimate, and where each has to lead it."""
+    n = l - w
     base = (rng.standard_normal(l) * 11.3).astype(np.float32)
-    s[0, 0] = np.where(sampled, -1.0, base)                      # sample sees one value only
-    s[0, 1] = np.where(sampled, base + 200.0, base)              # sample far above the rest
-    s[0, 2] = np.where(sampled, base - 200.0, base)              # sample far below the rest
-    s[0, 3] = 7.5                                                # every score equal
-    s[0, 4] = np.round(base)                                     # heavy ties around the threshold
-    s[0, 5] = np.where(rng.random(l) < 0.01, 1e3, -1e3)          # 1500 large, rest equal: k cuts the ties
-    s[0, 6] = base
-    s[0, 6, :3000] = 1e4                                         # more than k at the top, all tied
-    s[0, 7] = -np.abs(base) - 1.0
+    sampled = np.zeros(l, bool)
+    sampled[:n], rank = sampled_positions(n, k)
+    few = base.copy()
+    few[rng.choice(np.nonzero(sampled)[0], rank, replace=False)] += 200.0   # as many as the estimate looks for
+    tied = np.where(rng.random(l) < 0.01, 1e3, -1e3)                        # k > those: cuts the ties
+    tied[np.nonzero(tied[:n] > 0)[0][k // 2:]] = -1e3
+    top = base.copy()
+    top[:k + 100] = 1e4                                                     # the cut falls into ties of the top
+    rows = [(base, "list"), (few, "few"), (np.where(sampled, base - 200.0, base), "many"),
+            (np.where(sampled, -1.0, base), "many"),                        # the sample sees one value only
+            (np.full(l, 7.5), "many"), (tied, "many"), (np.round(base), "list"), (top, "list"),
+            (-np.abs(base) - 1.0, "list"), (np.where(sampled, base + 200.0, base), None)]
+    s = np.stack([r for r, _ in rows]).astype(np.float32)
+    for row, (_, want) in zip(s, rows):
+        assert want is None or estimate_of(row, n, k) == want
+    s[:, n:] = 1e6             # the lite window must never be listed
+    return s[None]
+
+
+@pytest.mark.parametrize("l,w,k", [(16384, 0, 512), (16389, 5, 700), (50001, 60, 1000), (65536, 0, 513),
+                                   (65537, 0, 513), (70001, 60, 1000), (150000, 64, 2048)])
+def test_select_topk_sampled_estimate_is_verified_not_trusted(l, w, k):
+    say(f"select_topk l={l} w={w} k={k}: inputs built to mislead the 1-in-8 sample, and heavy ties")
+    s = misleading_rows(l, w, k, np.random.default_rng(9))
     got = run_select(s, k, w)
     assert np.array_equal(got, orc.select_topk(s, k, w))
 
@@ -124,11 +163,11 @@ def test_select_topk_sampled_estimate_is_verified_not_trusted():
 @pytest.mark.parametrize("l,w,k", [(16383, 0, 512), (16389, 5, 512), (16384, 0, 511),
                                    (50001, 60, 1000), (4099, 3, 64), (3, 0, 2)])
 def test_select_topk_around_the_sampling_limit(l, w, k):
-    say(f"select_topk l={l} w={w} k={k}: odd row lengths, inputs built to mislead the 1-in-8 sample")
+    say(f"select_topk l={l} w={w} k={k}: odd row lengths, with and without a sample")
     rng = np.random.default_rng(l)
-    sampled = np.arange(l) % 32 < 4
+    first = np.arange(l) % 32 < 4
     base = (rng.standard_normal(l) * 11.3).astype(np.float32)
-    s = np.stack([base, np.where(sampled, base - 200.0, base), np.where(sampled, base + 200.0, base),
+    s = np.stack([base, np.where(first, base - 200.0, base), np.where(first, base + 200.0, base),
                   np.where(np.arange(l) < 2 * k, base + 50.0, base), np.round(base)])[None]
     got = run_select(s.astype(np.float32), k, w)
     assert np.array_equal(got, orc.select_topk(s.astype(np.float32), k, w))
