@@ -15,8 +15,10 @@
 //     of these two), a workgroup per matrix.
 //  3. factor_rounds_kernel: the n_iter rounds and the line-search gradient steps on B_Q and B_K in
 //     place, workgroups per (batch, KV head).
-// Times in us at k = 2048, w = 64, 32 + 8 heads, r = 32: 8.6 + 9.8 + 9.6; at 8 x (28 + 4) heads, k = 1024, r = 64:
-// 32 + 22 + 20.  (Factorising in fp32 with a row per lane, P once and the k_hat system in every
+// Times in us at k = 2048, w = 64, 32 + 8 heads, r = 32: 10.5 + 9.2 + 9.5; at 8 x (28 + 4) heads, k = 1024, r = 64:
+// 37 + 22 + 19.5 (launches on four sets of inputs in turn; on one set, whose rows the caches then hold, launch 1
+// takes 8.6 and 32, and the calls that the comments below give times of 25.8 and 69.8 instead of 27.9 and 77).
+// (Factorising in fp32 with a row per lane, P once and the k_hat system in every
 // round, all in one wavefront per head, launches 2 and 3 took 30 and 114 us.)  What is left is
 // latency: the loads at the start of each launch (2 us; 5 to 9 us at the second shape, where every
 // compute unit reads 130 and 265 KB), the eliminations (3.5 and 9 us) and the rounds (2 and 4 us each).
@@ -36,8 +38,8 @@ namespace {
 using namespace alg64;
 using dev::place;
 
-// (r = 64: as many workgroups on a compute unit as its LDS holds, 79.6 -> 77.6 us for the call at
-// 8 x (28 + 4) heads, bf16 rows; left alone the registers allow one fewer)
+// (r = 64, bf16 rows: as many workgroups on a compute unit as its LDS holds, four, 79.6 -> 77.6 us for the call at
+// 8 x (28 + 4) heads; left alone the registers allow one fewer.  fp32 rows keep twice as many in flight: three)
 template <int R, bool BF16>
 __global__ __launch_bounds__(kGramThreads, R > 32 ? BF16 ? 4 : 3 : 1) void factor_gram_kernel(GramRows a,
                                                                                            int BHkv,
@@ -183,7 +185,9 @@ __global__ __launch_bounds__(kInvThreads) void factor_inverse_kernel(SolveArgs a
     c += dpp_f64<0x141>(c);  // row_half_mirror
     if (row < R && part8 == 0) out[kEntries + row] = c;
   }
-  // += lambda_d2 A_Om^T A_Om, in chunk order
+  // += lambda_d2 A_Om^T A_Om, in chunk order.  (At r = 64 an entry of the sums and its mirror image may differ in
+  // their last bits, and the elimination takes pivot columns from pivot rows: with such sums of condition 10 to 1e6
+  // emulated on the CPU the solutions are as far off as with the upper half mirrored, to three digits.)
   if (isq && own) {
     f64x4 sum[Z::TPW] = {};
     for (int s0 = 0; s0 < a.nchunk; s0 += SB) {

@@ -191,7 +191,8 @@ __device__ __forceinline__ uint32_t pack_bf16(float x0, float x1) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
 }
 // x0, x1 as three bf16 pairs (packed in dwords) that add up to them, the first of them the multiples
-// of a grid (`grid`: 1.5 x 2^23 times its unit; see prefill_reduce_kernel) that are nearest to them.  Without a grid the sum is exact.
+// of a grid (`grid`: 1.5 x 2^23 times its unit; see prefill_reduce_kernel) that are nearest to them.
+// Without a grid the sum is exact.
 __device__ __forceinline__ void split3(float x0, float x1, uint32_t (&s)[3], float grid = 0.0f) {
 #pragma unroll
   for (int i = 0; i < 3; ++i) {

@@ -83,9 +83,12 @@ __global__ __launch_bounds__(kTileRows) void proxy_scores_kernel(
   const size_t bh0 = (size_t)b * Hq + (size_t)kv * G;  // first head of the group
   // all phases' loads are issued up front: chunk idx of phase p is row idx / V4 of the wavefront's 64,
   // 16-byte column p * V4 + idx % V4 (8 lanes read 128 contiguous bytes of a row).  A wavefront loads the
-  // rows that it will need, so that nothing waits for another one's (with the tile's rows dealt out over
-  // the workgroup and a barrier behind the stores: 7.55 -> 7.40 us at 8 KV heads, l = 32768, r = 32,
-  // 44.7 -> 43.6 at l = 131072, r = 64, 24.4 -> 23.2 for all scores at 8 x 7 heads, l = 50021, r = 64).
+  // rows that it will need, so that nothing waits for another one's.  Against the tile's rows dealt out over
+  // the workgroup and a barrier behind the stores, four heads a group: 7.47 -> 7.24 us at 8 KV heads, l = 32768,
+  // r = 32, 22.4 -> 22.2 at l = 131072, 44.1 -> 43.1 at l = 131072, r = 64, 24.4 -> 23.1 for all scores at 8 x 7
+  // heads, l = 50021, r = 64.  Where all workgroups are resident at once, two a compute unit, r = 64 loses
+  // 0.15 us (8.06 -> 8.19 at 8 KV heads, l = 16384; one head a group 6.80 -> 6.96): wavefronts that begin at
+  // other rows of theirs get that back and cost 1 to 3 % at longer contexts.
   const int lane = t & 63, wrow0 = t & ~63;
   float4 pre[NPH][V4];
 #pragma unroll
@@ -131,7 +134,7 @@ __global__ __launch_bounds__(kTileRows) void proxy_scores_kernel(
   for (int g = 0; g < G; ++g) acc[g] = 0.0f;
 #pragma unroll
   for (int p = 0; p < NPH; ++p) {
-    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_wave_barrier();  // (a wavefront's LDS operations stay in the order given here)
 #pragma unroll
     for (int i = 0; i < V4; ++i) {
       const int idx = i * 64 + lane;

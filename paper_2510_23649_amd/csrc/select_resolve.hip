@@ -11,10 +11,12 @@
 //      In the fused step it comes from the proxy-score pass (one 64-bit ballot per 64
 //      positions, with the candidates' scores packed 8 per 64-position group beside it)
 //      and is copied into LDS.  Working from a materialised score array (the stand-alone
-//      entry point beyond 65536 positions; select_scores.hip up to there) the kernel builds it itself: a histogram of the top 12 key bits over a
-//      1-in-8 sample of the positions gives a bin at or below the bin of the k-th largest
-//      score, with a safety margin, and one pass over the scores marks every position at
-//      or above that bin (4 positions per lane, 8 lanes OR-ed into one word: no atomics);
+//      entry point beyond 65536 positions, select_scores.hip up to there; fused steps of any
+//      length whose rank or group size has no filtered pass) the kernel builds it itself: a
+//      histogram of the top 12 key bits over a 1-in-8 sample of the positions gives a bin at
+//      or below the bin of the k-th largest score, with a safety margin, and one pass over the
+//      scores marks every position at or above that bin (4 positions per lane, 8 lanes OR-ed
+//      into one word: no atomics);
 //   2. a prefix count over the bitmap turns it into an ascending list of m candidate
 //      positions; if k <= m <= capacity the estimate was good (this is checked, not
 //      assumed).  The candidates' keys are taken from the packed scores (a group with more
@@ -129,8 +131,9 @@ __global__ __launch_bounds__(kT) void select_resolve_kernel(
   } else {
   // ---- 1. sampled histogram -> b_lo ------------------------------------------------------
   // Long contexts are sampled, the first 4 positions of every 32 (evenly, however the large
-  // scores are clustered): 16384 and k >= 512 leave the estimate five standard deviations of
-  // margin, and a pass over all positions costs 5 us more at l = 50000.
+  // scores are clustered): k >= 512 leaves the estimate five standard deviations of margin.  A
+  // histogram of all positions costs 6 us more at l = 65537 and 70001, 10 at 131072 (stand-alone,
+  // 32 heads: 27.6, 28.0 and 35.6 us at k = 511; 21.3, 21.8 and 25.9 at k = 512).
   const int stride = (n >= 16384 && k >= 512) ? kSampleStride : 1;
   for (int i = t; i < kBins; i += kT) hist[i] = 0u;
   __syncthreads();

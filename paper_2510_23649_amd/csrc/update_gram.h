@@ -81,8 +81,10 @@ __device__ __forceinline__ float dot_piece(const RowPiece<BF16>& p, const float 
 // and the six products of terms down to 2^-16 of the leading one (what is left out is 2^-24 of a product
 // and smaller, as the rounding of an fp32 sum), the small ones first; a wavefront sums every fourth 16 rows.
 // 18 MFMAs of 32 cycles for 16 rows instead of 32 of 64 cycles in fp32, and fewer roundings: at 8 x (28 + 4)
-// heads, k = 1024 the kernel takes 31 us instead of 38 (24 would be its bytes), and the update's results are
-// 1.1e-7 instead of 1.7e-7 from those in 64 bits.
+// heads, k = 1024 the kernel takes 31 us instead of 38 (24 would be its bytes; calls back to back on the same
+// inputs, 37 on four sets of inputs in turn), and the update's results are 1.2e-7 instead of 1.7e-7 from those in
+// 64 bits.  (Of an entry of a diagonal block and its mirror image two products swap places, so that the two may
+// differ in their last bits.)
 // g: thread t sums column t % r over every (256 / r)-th row.
 using dev::bf16x8;
 using dev::f32x16;
